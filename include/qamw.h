@@ -209,6 +209,22 @@ typedef struct qamw_encode_item {
 int qamw_encode_batch(const qamw_encode_item *items, int n_items, int dtype, const float *codebook, int bits,
                       int hadamard_block, void *stream);
 
+/* qamw_encode / qamw_encode_batch with device scratch: the same bytes and norms, several times sooner.  With
+ * qamw_encode_workspace_bytes() bytes (128 KB at 11 bits; 0 = scratch is of no use at these bits) the call first makes, on
+ * the device, a table of the codewords that can be nearest to a point of each cell of a grid -- from this call's codebook,
+ * every time -- and then searches only those.  workspace: device, 16-byte aligned, owned by the caller until the call's
+ * work on the stream has finished, contents unspecified afterwards; calls that overlap need one each.  NULL or too small,
+ * or a shape outside the fast kernels' range: as qamw_encode / qamw_encode_batch.  (The counting qamw_encode_stats always
+ * searches the whole codebook.)
+ * Errors: as qamw_encode / qamw_encode_batch; a misaligned workspace, bits outside [1,12], NULL bytes_out -> INVALID_ARG. */
+int qamw_encode_workspace_bytes(int bits, size_t *bytes_out);
+int qamw_encode_ws(const void *W, int dtype, int d_out, int d_in, int64_t ldw, const float *chan_scale,
+                   const int8_t *signs, const float *pair_sigma, const float *codebook, int bits,
+                   int hadamard_block, void *workspace, size_t workspace_bytes, uint8_t *packed_out,
+                   float *row_norms_out, void *stream);
+int qamw_encode_batch_ws(const qamw_encode_item *items, int n_items, int dtype, const float *codebook, int bits,
+                         int hadamard_block, void *workspace, size_t workspace_bytes, void *stream);
+
 /* Codebook training on the device (Sec. 3.5; a codebook fitted to a checkpoint's own pairs is the follow-up
  * named in the paper's discussion).
  *

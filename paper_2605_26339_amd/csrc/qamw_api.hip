@@ -257,8 +257,8 @@ int qamw_encode_stats(const void *W, int dtype, int d_out, int d_in, int64_t ldw
                        row_norms_out, full_scans, stream);
 }
 
-int qamw_encode_batch(const qamw_encode_item *items, int n_items, int dtype, const float *codebook, int bits,
-                      int hadamard_block, void *stream) {
+static int encode_batch_impl(const qamw_encode_item *items, int n_items, int dtype, const float *codebook, int bits,
+                             int hadamard_block, void *workspace, size_t workspace_bytes, void *stream) {
     static_assert(QAMW_MAX_BATCH == qamw::QAMW_ENCODE_MAX_BATCH, "batch limits differ");
     if (!items || !codebook || n_items < 1 || n_items > QAMW_MAX_BATCH) return QAMW_ERR_INVALID_ARG;
     if (dtype != QAMW_DTYPE_F32 && dtype != QAMW_DTYPE_BF16) return QAMW_ERR_INVALID_ARG;
@@ -274,10 +274,14 @@ int qamw_encode_batch(const qamw_encode_item *items, int n_items, int dtype, con
         qamw::Problem pi = make_problem(q.d_out, q.d_in, nullptr, nullptr, nullptr, codebook, bits, hadamard_block, stream);
         fused = fused && qamw::fused_norms_supported(pi);
     }
-    if (g_kernel_path.load() == 0 && fused) {
+    if (workspace && (reinterpret_cast<uintptr_t>(workspace) & 15)) return QAMW_ERR_INVALID_ARG;
+    if (g_kernel_path.load() == 0) {
         qamw::Problem shared = make_problem(items[0].d_out, items[0].d_in, nullptr, nullptr, nullptr, codebook, bits,
                                             hadamard_block, stream);
-        hipError_t e = qamw::launch_encode_batch_mfma(its, n_items, dtype, shared, false);
+        hipError_t e = hipErrorNotSupported;
+        if (workspace && qamw::encode_cells_bytes(bits) && workspace_bytes >= qamw::encode_cells_bytes(bits))
+            e = qamw::launch_encode_cells(its, n_items, dtype, shared, workspace);
+        if (e == hipErrorNotSupported && fused) e = qamw::launch_encode_batch_mfma(its, n_items, dtype, shared, false);
         if (e == hipSuccess) return QAMW_OK;
         if (e != hipErrorNotSupported) return QAMW_ERR_DEVICE;
     }
@@ -288,6 +292,29 @@ int qamw_encode_batch(const qamw_encode_item *items, int n_items, int dtype, con
         if (rc != QAMW_OK) return rc;
     }
     return QAMW_OK;
+}
+
+int qamw_encode_batch(const qamw_encode_item *items, int n_items, int dtype, const float *codebook, int bits,
+                      int hadamard_block, void *stream) {
+    return encode_batch_impl(items, n_items, dtype, codebook, bits, hadamard_block, nullptr, 0, stream);
+}
+
+int qamw_encode_workspace_bytes(int bits, size_t *bytes_out) {
+    if (!bytes_out || bits < 1 || bits > QAMW_MAX_BITS) return QAMW_ERR_INVALID_ARG;
+    *bytes_out = qamw::encode_cells_bytes(bits);
+    return QAMW_OK;
+}
+
+int qamw_encode_batch_ws(const qamw_encode_item *items, int n_items, int dtype, const float *codebook, int bits,
+                         int hadamard_block, void *workspace, size_t workspace_bytes, void *stream) {
+    return encode_batch_impl(items, n_items, dtype, codebook, bits, hadamard_block, workspace, workspace_bytes, stream);
+}
+
+int qamw_encode_ws(const void *W, int dtype, int d_out, int d_in, int64_t ldw, const float *chan_scale,
+                   const int8_t *signs, const float *pair_sigma, const float *codebook, int bits, int hadamard_block,
+                   void *workspace, size_t workspace_bytes, uint8_t *packed_out, float *row_norms_out, void *stream) {
+    const qamw_encode_item it{W, ldw, chan_scale, signs, pair_sigma, packed_out, row_norms_out, d_out, d_in};
+    return encode_batch_impl(&it, 1, dtype, codebook, bits, hadamard_block, workspace, workspace_bytes, stream);
 }
 
 int qamw_normalised_pairs(const void *W, int dtype, int d_out, int d_in, int64_t ldw, const float *chan_scale,

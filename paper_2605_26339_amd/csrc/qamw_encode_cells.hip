@@ -1,0 +1,579 @@
+// QAM-W encoder with a cell table made on the device (Sec. 3.1 / Sec. 3.5; the index is the one the search over the
+// whole codebook returns, lowest index on ties).
+//
+// k_cells_prepare cuts the square [-4, 4)^2 -- where 99.99 % of the normalised pairs lie -- into G x G cells and lists,
+// per cell, every codeword that can be nearest to a point of the cell; the same launch computes the row norms.
+// k_encode_cells keeps the codebook and the whole table in LDS and decides a pair by the exact fp32 squared distances to
+// its cell's candidates, at most five.  A pair outside the table, or in a cell that lists more, is decided by the exact
+// scan of the whole codebook (64 lanes x K/64 codewords).
+//
+// Which codewords a cell lists.  For two codewords a and c the difference |x - c|^2 - |x - a|^2 is linear in x, so on a
+// box of half-width w around m it is at least |m - c|^2 - |m - a|^2 - 2 w (|c.x - a.x| + |c.y - a.y|).  c is left out
+// when that exceeds a margin: then a is nearer at every point of the box, also after the roundings of the fp32 distances
+// (relative error below 2.4e-7 each; the margin is 4e-6 of the two squared distances and 1e-5 w^2).  As `a` serve the
+// codewords nearest and second nearest to m: for a Lloyd codebook of the Gaussian that leaves the same lists as testing
+// all pairs (2^11 points, G = 128: 3.1 candidates on average over the pairs, never more than 5).  The lists are found
+// top down -- 8 x 8 cells, 4 x 4 cells, single cells -- and each level searches only its parent's list.
+//
+// What bounds k_encode_cells: vector-ALU issue, with the LDS gathers (one record and five codewords per pair) close
+// behind.  Hence one workgroup of 16 waves per CU that stages its 144 KB once and walks the rows; a wave keeps to one
+// 1024-column slab of a matrix, so the slab's scales, signs and pair gains are loaded, divided and combined once per
+// wave instead of once per row.
+#include <atomic>
+#include <cmath>
+
+#include "qamw_front.hpp"
+
+namespace qamw {
+
+constexpr float CELLS_HALF = 4.0f;                             // the table covers [-4, 4)^2 less a border of one cell
+constexpr int CELLS_LIST = 5;                                  // candidates of a record
+constexpr uint32_t CELLS_SCAN = 0x80000000u;                   // in the record's upper word: decided by the whole codebook
+constexpr uint32_t CELLS_MORE = 1u;                            // in its lower word: more than three candidates
+
+constexpr int CELLS_MIN_ITEMS = 1024;                          // (row, slab) items of a launch from which small codebooks use the table
+
+// Cells per side.  Four cells per codeword spacing at the centre of a Lloyd codebook keep the lists within a record;
+// the LDS holds 128 x 128 records beside 2048 codewords.
+constexpr int cells_side(int bits) { return bits >= 11 ? 128 : bits == 10 ? 96 : 64; }
+
+struct CellsMat {
+    const void *W;
+    int64_t ldw;
+    const float *chan_scale;
+    const int8_t *signs;
+    const float *pair_sigma;
+    float *norms;
+    uint8_t *packed;
+    int64_t row_bytes;
+    int d_in, d_out, n_slabs;
+    float g_default;
+};
+struct CellsBatch {
+    CellsMat m[QAMW_ENCODE_MAX_BATCH];
+    int norm_begin[QAMW_ENCODE_MAX_BATCH + 1];   // k_cells_prepare: first norm workgroup of each matrix
+    int n, bits, K;
+    float inv_sqrt_block;
+    const float *codebook;
+    uint2 *table;                                // G x G records
+};
+
+// ------------------------------------------------------------------------------------------------ the table
+constexpr int CP_THREADS = 256;
+constexpr int CP_WAVES = CP_THREADS / WAVE;
+constexpr int CP_REGION_LIST = 512;                            // candidates of 8 x 8 cells (200 at most for 2^11 Lloyd points)
+constexpr int CP_BLOCK_LIST = 128;                             // candidates of 4 x 4 cells (55)
+constexpr int CP_PER_THREAD = 2048 / CP_THREADS;
+
+// Is codeword c farther than codeword a at every point of the box of half-width w around m?  dc2, da2: their squared
+// distances from m.
+__device__ __forceinline__ bool cells_dominated(float2 c, float dc2, float2 a, float da2, float w) {
+    const float reach = 2.00002f * w * (fabsf(c.x - a.x) + fabsf(c.y - a.y));
+    return dc2 - da2 > reach + 4e-6f * (dc2 + da2) + 1e-5f * w * w;
+}
+__device__ __forceinline__ float cells_dist2(float mx, float my, float2 c) {
+    const float ex = mx - c.x, ey = my - c.y;
+    return ex * ex + ey * ey;
+}
+
+// Candidate lists of 8 x 8 cells by one workgroup; wave w takes their w-th quarter of 4 x 4 cells.
+template <int G>
+__device__ __forceinline__ void cells_build_region(const CellsBatch &bt, int region) {
+    __shared__ float2 reg_c[CP_REGION_LIST];
+    __shared__ uint16_t reg_i[CP_REGION_LIST];
+    __shared__ float2 blk_c[CP_WAVES][CP_BLOCK_LIST];
+    __shared__ uint16_t blk_i[CP_WAVES][CP_BLOCK_LIST];
+    __shared__ uint16_t rec_i[CP_WAVES][16][8];
+    __shared__ float red_d[CP_WAVES];
+    __shared__ float2 red_c[CP_WAVES];
+    __shared__ int red_n[CP_WAVES];
+    constexpr float h = 2.0f * CELLS_HALF / G;
+    constexpr float slack = CELLS_HALF / 524288.0f;            // the fp32 roundings of the centres and of the cell lookup
+    const int lane = threadIdx.x & (WAVE - 1), wid = threadIdx.x >> 6;
+    const int K = bt.K;
+    const float2 *cbk = reinterpret_cast<const float2 *>(bt.codebook);
+    const int x0 = (region % (G / 8)) * 8, y0 = (region / (G / 8)) * 8;
+
+    // ---- 8 x 8 cells: every thread holds a run of consecutive codewords
+    const int per = (K + CP_THREADS - 1) / CP_THREADS, first = (int)threadIdx.x * per;
+    float2 c[CP_PER_THREAD];
+    float d2[CP_PER_THREAD];
+    float mx = ((float)x0 + 3.5f - 0.5f * G) * h, my = ((float)y0 + 3.5f - 0.5f * G) * h, w = 4.0f * h + slack;
+    float nd = 3.0e38f;
+    float2 nc = make_float2(0.0f, 0.0f);
+#pragma unroll
+    for (int j = 0; j < CP_PER_THREAD; ++j) {
+        const bool have = j < per && first + j < K;
+        c[j] = cbk[have ? first + j : 0];
+        d2[j] = cells_dist2(mx, my, c[j]);
+        if (d2[j] < nd) {
+            nd = d2[j];
+            nc = c[j];
+        }
+    }
+#pragma unroll
+    for (int s = 1; s < WAVE; s <<= 1) {
+        const float od = __shfl_xor(nd, s, WAVE), ox = __shfl_xor(nc.x, s, WAVE), oy = __shfl_xor(nc.y, s, WAVE);
+        if (od < nd) {
+            nd = od;
+            nc = make_float2(ox, oy);
+        }
+    }
+    if (lane == 0) {
+        red_d[wid] = nd;
+        red_c[wid] = nc;
+    }
+    __syncthreads();
+    nd = red_d[0];
+    nc = red_c[0];
+#pragma unroll
+    for (int q = 1; q < CP_WAVES; ++q) {
+        if (red_d[q] < nd) {
+            nd = red_d[q];
+            nc = red_c[q];
+        }
+    }
+    unsigned keep = 0;
+#pragma unroll
+    for (int j = 0; j < CP_PER_THREAD; ++j)
+        if (j < per && first + j < K && !cells_dominated(c[j], d2[j], nc, nd, w)) keep |= 1u << j;
+    int below = __popc(keep);                                   // inclusive sum over the lanes up to this one
+#pragma unroll
+    for (int s = 1; s < WAVE; s <<= 1) {
+        const int o = __shfl_up(below, s, WAVE);
+        if (lane >= s) below += o;
+    }
+    if (lane == WAVE - 1) red_n[wid] = below;
+    __syncthreads();
+    int at = below - __popc(keep), n_reg = 0;
+#pragma unroll
+    for (int q = 0; q < CP_WAVES; ++q) {
+        if (q < wid) at += red_n[q];
+        n_reg += red_n[q];
+    }
+#pragma unroll
+    for (int j = 0; j < CP_PER_THREAD; ++j) {
+        if ((keep >> j) & 1u) {
+            if (at < CP_REGION_LIST) {
+                reg_c[at] = c[j];
+                reg_i[at] = (uint16_t)(first + j);
+            }
+            ++at;
+        }
+    }
+    __syncthreads();
+    bool too_long = n_reg > CP_REGION_LIST;
+    if (too_long) n_reg = 0;
+
+    // ---- 4 x 4 cells: the wave's lanes share the region's candidates
+    const int bx = x0 + 4 * (wid & 1), by = y0 + 4 * (wid >> 1);
+    mx = ((float)bx + 1.5f - 0.5f * G) * h;
+    my = ((float)by + 1.5f - 0.5f * G) * h;
+    w = 2.0f * h + slack;
+    nd = 3.0e38f;
+    for (int e = lane; e < n_reg; e += WAVE) {
+        const float2 ce = reg_c[e];
+        const float d = cells_dist2(mx, my, ce);
+        if (d < nd) {
+            nd = d;
+            nc = ce;
+        }
+    }
+#pragma unroll
+    for (int s = 1; s < WAVE; s <<= 1) {
+        const float od = __shfl_xor(nd, s, WAVE), ox = __shfl_xor(nc.x, s, WAVE), oy = __shfl_xor(nc.y, s, WAVE);
+        if (od < nd) {
+            nd = od;
+            nc = make_float2(ox, oy);
+        }
+    }
+    int n_blk = 0;
+    for (int e0 = 0; e0 < n_reg; e0 += WAVE) {
+        const int e = e0 + lane;
+        const float2 ce = reg_c[e < n_reg ? e : 0];
+        const bool k = e < n_reg && !cells_dominated(ce, cells_dist2(mx, my, ce), nc, nd, w);
+        const unsigned long long mask = __ballot(k);
+        const int pos = n_blk + __popcll(mask & ((1ull << lane) - 1ull));
+        if (k && pos < CP_BLOCK_LIST) {
+            blk_c[wid][pos] = ce;
+            blk_i[wid][pos] = reg_i[e];
+        }
+        n_blk += __popcll(mask);
+    }
+    too_long = too_long || n_blk > CP_BLOCK_LIST;
+    if (too_long) n_blk = 0;
+    __syncthreads();
+
+    // ---- single cells: four lanes per cell, each a quarter of the block's candidates
+    const int cell = lane >> 2, part = lane & 3;
+    const int ix = bx + (cell & 3), iy = by + (cell >> 2);
+    mx = ((float)ix - 0.5f * G) * h;
+    my = ((float)iy - 0.5f * G) * h;
+    w = 0.5f * h + slack;
+    const int quarter = (n_blk + 3) >> 2, e_begin = part * quarter, e_end = min(n_blk, e_begin + quarter);
+    float da = 3.0e38f, db = 3.0e38f;                           // nearest and second nearest
+    float2 ca = make_float2(0.0f, 0.0f), cb = ca;
+    for (int e = e_begin; e < e_end; ++e) {
+        const float2 ce = blk_c[wid][e];
+        const float d = cells_dist2(mx, my, ce);
+        if (d < da) {
+            db = da;
+            cb = ca;
+            da = d;
+            ca = ce;
+        } else if (d < db) {
+            db = d;
+            cb = ce;
+        }
+    }
+#pragma unroll
+    for (int s = 1; s <= 2; s <<= 1) {
+        const float oda = __shfl_xor(da, s, WAVE), odb = __shfl_xor(db, s, WAVE);
+        const float2 oca = make_float2(__shfl_xor(ca.x, s, WAVE), __shfl_xor(ca.y, s, WAVE));
+        const float2 ocb = make_float2(__shfl_xor(cb.x, s, WAVE), __shfl_xor(cb.y, s, WAVE));
+        // each side's two, sorted: the first is the smaller head, the second the smaller of the other head and its own second
+        const bool swap = oda < da;
+        const float hd = swap ? da : oda, td = swap ? odb : db;
+        const float2 hc = swap ? ca : oca, tc = swap ? ocb : cb;
+        if (swap) {
+            da = oda;
+            ca = oca;
+        }
+        const bool head = hd < td;
+        db = head ? hd : td;
+        cb = head ? hc : tc;
+    }
+    unsigned kept = 0;                                          // bit e - e_begin (a quarter is at most 32 candidates)
+    for (int e = e_begin; e < e_end; ++e) {
+        const float2 ce = blk_c[wid][e];
+        const float d = cells_dist2(mx, my, ce);
+        const bool out = cells_dominated(ce, d, ca, da, w) || (db < 3.0e38f && cells_dominated(ce, d, cb, db, w));
+        if (!out) kept |= 1u << (e - e_begin);
+    }
+    const int mine = __popc(kept);
+    int before = 0, total = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int o = __shfl(mine, (lane & ~3) | q, WAVE);
+        if (q < part) before += o;
+        total += o;
+    }
+    while (kept) {
+        const int e = e_begin + __ffs((int)kept) - 1;
+        kept &= kept - 1u;
+        if (before < CELLS_LIST) rec_i[wid][cell][before] = blk_i[wid][e];
+        ++before;
+    }
+    __syncthreads();
+    if (part == 0) {
+        uint2 r = make_uint2(0u, CELLS_SCAN);
+        // the border belongs to everything outside the square: the lookup clamps to it
+        const bool inside = ix > 0 && ix < G - 1 && iy > 0 && iy < G - 1;
+        if (inside && total >= 1 && total <= CELLS_LIST) {
+            unsigned i5[CELLS_LIST];
+#pragma unroll
+            for (int q = 0; q < CELLS_LIST; ++q) i5[q] = rec_i[wid][cell][q < total ? q : 0];
+            // ascending; bits 3, 15, 27, 39, 51 onwards, padded with the first
+            r.x = (i5[0] << 3) | (i5[1] << 15) | (i5[2] << 27) | (total > 3 ? CELLS_MORE : 0u);
+            r.y = (i5[2] >> 5) | (i5[3] << 7) | (i5[4] << 19);
+        }
+        bt.table[iy * G + ix] = r;
+    }
+}
+
+// Workgroups 0 .. (G/8)^2 - 1 make the table; the rest compute the row norms, one wave per row.
+template <int DTYPE, int G>
+__global__ __launch_bounds__(CP_THREADS) void k_cells_prepare(CellsBatch bt) {
+    constexpr int REGIONS = (G / 8) * (G / 8);
+    if (blockIdx.x < REGIONS) {
+        cells_build_region<G>(bt, (int)blockIdx.x);
+        return;
+    }
+    const int b = (int)blockIdx.x - REGIONS;
+    int mi = 0;
+    while (mi + 1 < bt.n && b >= bt.norm_begin[mi + 1]) ++mi;
+    const CellsMat &M = bt.m[mi];
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int row = __builtin_amdgcn_readfirstlane((b - bt.norm_begin[mi]) * CP_WAVES + (int)(threadIdx.x >> 6));
+    if (row >= M.d_out) return;
+    const double s2 = wave_row_sum_of_squares<DTYPE>(M.W, row, M.ldw, M.d_in, M.chan_scale, lane);
+    if (lane == 0) M.norms[row] = (float)sqrt(s2);
+}
+
+// ------------------------------------------------------------------------------------------------ the encoder
+constexpr int cells_threads(int G) { return G == 128 ? 1024 : 512; }
+constexpr int cells_codewords(int G) { return G == 128 ? 2048 : G == 96 ? 1024 : 512; }
+constexpr size_t cells_lds_bytes(int G) { return (size_t)cells_codewords(G) * 8 + (size_t)G * G * 8; }
+
+template <int DTYPE, int B, int G>
+__global__ __launch_bounds__(cells_threads(G)) void k_encode_cells(CellsBatch bt) {
+    constexpr int THREADS = cells_threads(G), WAVES = THREADS / WAVE;
+    extern __shared__ __align__(16) float2 cells_lds[];        // codebook, then the table
+    const float2 *cb = cells_lds;
+    char *table = reinterpret_cast<char *>(cells_lds + cells_codewords(G));
+    const int K = bt.K, bits = bt.bits;
+    {
+        const float2 *cbk = reinterpret_cast<const float2 *>(bt.codebook);
+        for (int i = threadIdx.x; i < K; i += THREADS) cells_lds[i] = cbk[i];
+        const uint4 *src = reinterpret_cast<const uint4 *>(bt.table);
+        uint4 *dst = reinterpret_cast<uint4 *>(table);
+#pragma unroll 8
+        for (int i = threadIdx.x; i < G * G / 2; i += THREADS) dst[i] = src[i];
+    }
+    __syncthreads();
+
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const LaneSigns<B> ls(lane);
+    const int pos = slab_pos(lane);
+    constexpr float inv_h = G / (2.0f * CELLS_HALF);
+    constexpr float magic = 8388608.0f;                        // 2^23: adding it rounds to an integer, left in the low bits
+    const float unit = ls.parity * bt.inv_sqrt_block;
+
+    // The waves of the launch take the (row, slab) items of a matrix in turn, `step` at a time, a multiple of the slab
+    // count: a wave stays on its slab.  The next matrix begins with the wave after the last one that got an item.
+    const int n_waves = (int)gridDim.x * WAVES;
+    const int gw = (int)blockIdx.x * WAVES + wid;
+    int turn = 0;
+#pragma unroll 1
+    for (int mi = 0; mi < bt.n; ++mi) {
+        const CellsMat &M = bt.m[mi];
+        const int n_slabs = M.n_slabs, n_items = M.d_out * n_slabs;
+        const int rows_step = n_waves / n_slabs, step = rows_step * n_slabs;
+        int local = gw - turn;
+        if (local < 0) local += n_waves;
+        turn += n_items % step;
+        if (turn >= n_waves) turn -= n_waves;
+        if (local >= step || local >= n_items) continue;
+        int row = local / n_slabs;
+        const int slab = local - row * n_slabs;
+        const int col0 = slab * 1024 + 16 * pos;
+        const bool active = col0 < M.d_in;
+        const int c = active ? col0 : 0;
+        const void *__restrict__ W = M.W;
+        const int64_t ldw = M.ldw;
+        const float *__restrict__ norms = M.norms;
+        const int d_out = M.d_out;
+
+        // the slab's constants: scale x sign per column, gain per pair
+        float sc[16], g[8];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) sc[e] = 1.0f;
+        if (M.chan_scale) {
+            const float4 *s4 = reinterpret_cast<const float4 *>(M.chan_scale + c);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const float4 v = s4[t];
+                sc[4 * t] = v.x; sc[4 * t + 1] = v.y; sc[4 * t + 2] = v.z; sc[4 * t + 3] = v.w;
+            }
+        }
+        if (M.signs) {
+            const uint4 sg = *reinterpret_cast<const uint4 *>(M.signs + c);
+            const uint32_t wds[4] = {sg.x, sg.y, sg.z, sg.w};
+#pragma unroll
+            for (int e = 0; e < 16; ++e)                        // int8 -1: sign bit of the byte
+                sc[e] = __uint_as_float(__float_as_uint(sc[e]) ^ (((wds[e >> 2] >> (8 * (e & 3) + 7)) & 1u) << 31));
+        }
+        {
+            Problem p;
+            p.pair_sigma = M.pair_sigma;
+            p.g_default = M.g_default;
+            load_pair_gains(g, p, c);
+        }
+
+        RawRow<DTYPE> next;
+        load_raw_row<DTYPE>(next, W, (int64_t)row * ldw, c);
+        float norm_next = norms[row];
+        for (; row < d_out; row += rows_step) {
+            const RawRow<DTYPE> raw = next;
+            const float norm = norm_next;
+            if (row + rows_step < d_out) {                      // the wave's next row is on its way while this one is searched
+                load_raw_row<DTYPE>(next, W, (int64_t)(row + rows_step) * ldw, c);
+                norm_next = norms[row + rows_step];
+            }
+
+            // ---------------- front half (rotated_unit_row with the sign folded into the scale: exact)
+            float x[16];
+            widen_raw_row<DTYPE>(x, raw);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) x[e] = x[e] * sc[e];
+            divide_by_norm(x, norm);
+            fwht_wave<B>(x, ls);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) x[e] = (x[e] * unit) * g[e >> 1];
+
+            // ---------------- the cells' records
+            uint2 rec[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const float vx = fminf(fmaxf(__builtin_fmaf(x[2 * k], inv_h, magic + G / 2), magic), magic + (G - 1));
+                const float vy = fminf(fmaxf(__builtin_fmaf(x[2 * k + 1], inv_h, magic + G / 2), magic), magic + (G - 1));
+                const unsigned at = (__float_as_uint(vy) & 0xffffu) * (G * 8) + (__float_as_uint(vx) & 0xffffu) * 8;
+                rec[k] = *reinterpret_cast<const uint2 *>(table + at);
+            }
+            unsigned idx[8];
+            unsigned scan = 0;                                  // bit k: pair k needs the whole codebook
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const float x0 = x[2 * k], x1 = x[2 * k + 1];
+                const unsigned lo = rec[k].x, hi = rec[k].y;
+                scan |= (hi >> 31) << k;
+                // byte offsets of the candidates in the codebook
+                const unsigned o0 = lo & 0x7ff8u, o1 = (lo >> 12) & 0x7ff8u, o2 = __builtin_amdgcn_alignbit(hi, lo, 24) & 0x7ff8u;
+                auto dist = [&](unsigned o) {
+                    return exact_dist2(x0, x1, *reinterpret_cast<const float2 *>(reinterpret_cast<const char *>(cb) + o));
+                };
+                const float d0 = dist(o0), d1 = dist(o1), d2 = dist(o2);
+                float m = fminf(fminf(d0, d1), d2);
+                unsigned o = o2;
+                if (G == 128 || __ballot(lo & CELLS_MORE)) {    // in the smaller tables most waves hold three candidates at most
+                    const unsigned o3 = (hi >> 4) & 0x7ff8u, o4 = (hi >> 16) & 0x7ff8u;
+                    const float d3 = dist(o3), d4 = dist(o4);
+                    m = fminf(fminf(m, d3), d4);
+                    o = (d3 == m) ? o3 : o4;
+                    o = (d2 == m) ? o2 : o;
+                }
+                o = (d1 == m) ? o1 : o;                         // the lowest index among equals: the candidates ascend
+                o = (d0 == m) ? o0 : o;
+                idx[k] = o >> 3;
+            }
+
+            // ---------------- the exact scan for the rest: the whole wave works on one pair at a time
+            if (!active) scan = 0;
+            if (__ballot(scan != 0)) {
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    unsigned long long mask = __ballot((scan >> k) & 1u);
+                    while (mask) {
+                        const int src = __ffsll((long long)mask) - 1;
+                        mask &= mask - 1;
+                        const float x0 = __shfl(x[2 * k], src, WAVE), x1 = __shfl(x[2 * k + 1], src, WAVE);
+                        const int bi = wave_exact_scan(x0, x1, cb, K, lane);
+                        if (lane == src) idx[k] = (unsigned)bi;
+                    }
+                }
+            }
+
+            if (active) store_fields(M.packed + (int64_t)row * M.row_bytes, M.row_bytes, M.d_in, c, idx, bits);
+        }
+    }
+}
+
+// More than the default 64 KB of LDS per workgroup has to be asked for: a host-side setting per kernel and device, made
+// once per kernel instantiation and device (the devices' bits of `done`).
+template <int DTYPE, int B, int G> static bool cells_allow_large_lds(int dev) {
+    static std::atomic<uint64_t> done{0};
+    if (dev < 0 || dev >= 64) return false;
+    if (done.load(std::memory_order_acquire) & (1ull << dev)) return true;
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_encode_cells<DTYPE, B, G>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)cells_lds_bytes(G));
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    done.fetch_or(1ull << dev, std::memory_order_release);
+    return true;
+}
+
+template <int DTYPE, int B, int G>
+static hipError_t launch_cells_dbg(CellsBatch &bt, hipStream_t stream) {
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        cus < 1) {
+        (void)hipGetLastError();
+        return hipErrorNotSupported;
+    }
+    if (cells_lds_bytes(G) > 64 * 1024 && !cells_allow_large_lds<DTYPE, B, G>(dev)) return hipErrorNotSupported;
+    constexpr int WAVES = cells_threads(G) / WAVE;
+    int64_t items = 0;
+    int norm_blocks = 0, most_slabs = 1;
+    for (int i = 0; i < bt.n; ++i) {
+        const CellsMat &M = bt.m[i];
+        items += (int64_t)M.d_out * M.n_slabs;
+        bt.norm_begin[i] = norm_blocks;
+        norm_blocks += (M.d_out + CP_WAVES - 1) / CP_WAVES;
+        if (M.n_slabs > most_slabs) most_slabs = M.n_slabs;
+    }
+    for (int i = bt.n; i <= QAMW_ENCODE_MAX_BATCH; ++i) bt.norm_begin[i] = norm_blocks;
+    const int per_cu = G == 128 ? 1 : 2;          // workgroups that fit a CU's LDS and registers
+    int64_t blocks = (items + WAVES - 1) / WAVES;
+    if (blocks > (int64_t)cus * per_cu) blocks = (int64_t)cus * per_cu;
+    if (blocks * WAVES < most_slabs) return hipErrorNotSupported;   // every wave keeps to one slab: at least a row's worth of waves
+    const unsigned prep = (unsigned)((G / 8) * (G / 8) + norm_blocks);
+    hipLaunchKernelGGL((k_cells_prepare<DTYPE, G>), dim3(prep), dim3(CP_THREADS), 0, stream, bt);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_encode_cells<DTYPE, B, G>), dim3((unsigned)blocks), dim3(cells_threads(G)), cells_lds_bytes(G), stream, bt);
+    return hipGetLastError();
+}
+
+template <int DTYPE, int B>
+static hipError_t launch_cells_db(CellsBatch &bt, hipStream_t stream) {
+    switch (cells_side(bt.bits)) {
+        case 128: return launch_cells_dbg<DTYPE, B, 128>(bt, stream);
+        case 96: return launch_cells_dbg<DTYPE, B, 96>(bt, stream);
+        default: return launch_cells_dbg<DTYPE, B, 64>(bt, stream);
+    }
+}
+
+template <int DTYPE>
+static hipError_t launch_cells_d(CellsBatch &bt, int block, hipStream_t stream) {
+    switch (block) {
+        case 64: return launch_cells_db<DTYPE, 64>(bt, stream);
+        case 128: return launch_cells_db<DTYPE, 128>(bt, stream);
+        case 256: return launch_cells_db<DTYPE, 256>(bt, stream);
+        case 512: return launch_cells_db<DTYPE, 512>(bt, stream);
+        case 1024: return launch_cells_db<DTYPE, 1024>(bt, stream);
+        default: return hipErrorNotSupported;
+    }
+}
+
+size_t encode_cells_bytes(int bits) { return bits <= 11 ? (size_t)cells_side(bits) * cells_side(bits) * sizeof(uint2) : 0; }
+
+// n <= QAMW_ENCODE_MAX_BATCH matrices that share codebook, bits, block and element type; table: encode_cells_bytes(bits)
+// bytes of device scratch, 16-byte aligned.  Returns hipErrorNotSupported (nothing launched) when any item is outside the
+// kernel's range.
+hipError_t launch_encode_cells(const EncodeItem *items, int n, int dtype, const Problem &p, void *table) {
+    if (n < 1 || n > QAMW_ENCODE_MAX_BATCH || p.bits > 11 || !table || (reinterpret_cast<uintptr_t>(table) & 15) ||
+        (reinterpret_cast<uintptr_t>(p.codebook) & 7))
+        return hipErrorNotSupported;
+    const int unit = p.block > 16 ? p.block : 16;
+    CellsBatch bt;
+    int64_t items_total = 0;
+    for (int i = 0; i < n; ++i) {
+        Problem q = p;
+        q.chan_scale = items[i].chan_scale;
+        q.signs = items[i].signs;
+        q.pair_sigma = items[i].pair_sigma;
+        if (p.block < 64 || items[i].d_in % unit || !front_alignment_ok(items[i].W, dtype, items[i].ldw, q)) return hipErrorNotSupported;
+        CellsMat &M = bt.m[i];
+        M.W = items[i].W;
+        M.ldw = items[i].ldw;
+        M.chan_scale = items[i].chan_scale;
+        M.signs = items[i].signs;
+        M.pair_sigma = items[i].pair_sigma;
+        M.norms = items[i].norms;
+        M.packed = items[i].packed;
+        M.row_bytes = (((int64_t)(items[i].d_in / 2) * p.bits + 31) / 32) * 4;
+        M.d_in = items[i].d_in;
+        M.d_out = items[i].d_out;
+        M.n_slabs = (items[i].d_in + 1023) / 1024;
+        M.g_default = (float)std::sqrt((double)items[i].d_in);
+        if ((int64_t)M.d_out * M.n_slabs > 0x3fffffff) return hipErrorNotSupported;
+        items_total += (int64_t)M.d_out * M.n_slabs;
+    }
+    // Two launches of 12 us at the least: codebooks of up to 32 points are searched whole sooner in small matrices (32
+    // points, bf16: 256 x 2048, 512 items, 11.4 us against 12.7; 1024 x 2048, 2048 items, 14.2 against 12.8).  With 64
+    // points and more the table wins from the smallest matrix on (48 x 512: 17.7 against 11.6; 2048 points: 89 against 23).
+    if (p.bits < 6 && items_total < CELLS_MIN_ITEMS) return hipErrorNotSupported;
+    for (int i = n; i < QAMW_ENCODE_MAX_BATCH; ++i) bt.m[i] = bt.m[0];
+    bt.n = n;
+    bt.bits = p.bits;
+    bt.K = p.K;
+    bt.inv_sqrt_block = p.inv_sqrt_block;
+    bt.codebook = p.codebook;
+    bt.table = static_cast<uint2 *>(table);
+    return dtype == 0 ? launch_cells_d<0>(bt, p.block, p.stream) : launch_cells_d<1>(bt, p.block, p.stream);
+}
+
+}  // namespace qamw

@@ -34,29 +34,22 @@ __device__ __forceinline__ void load_raw_row(RawRow<DTYPE> &raw, const void *__r
     }
 }
 
-// c: first of the lane's 16 columns (multiple of 16, < d_in); r: the row's norm.
-// Requires 16-byte aligned rows and side arrays (checked on the host).
-template <int DTYPE, int B>
-__device__ __forceinline__ void rotated_unit_row_from(float (&y)[16], const RawRow<DTYPE> &raw, int c, float r, const Problem &p,
-                                                      const LaneSigns<B> &ls) {
+// The 16 weights as fp32 (bf16 is the upper half of an fp32).
+template <int DTYPE> __device__ __forceinline__ void widen_raw_row(float (&y)[16], const RawRow<DTYPE> &raw) {
     if (DTYPE == 0) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) y[e] = __uint_as_float(raw.w[e]);
     } else {
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {                           // bf16 is the upper half of an fp32
+        for (int q = 0; q < 8; ++q) {
             y[2 * q] = __uint_as_float(raw.w[q] << 16);
             y[2 * q + 1] = __uint_as_float(raw.w[q] & 0xFFFF0000u);
         }
     }
-    if (p.chan_scale) {
-        const float4 *s4 = reinterpret_cast<const float4 *>(p.chan_scale + c);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            float4 v = s4[t];
-            y[4 * t] *= v.x; y[4 * t + 1] *= v.y; y[4 * t + 2] *= v.z; y[4 * t + 3] *= v.w;
-        }
-    }
+}
+
+// The scaled weights divided by the row's norm; a zero norm gives zeros.
+__device__ __forceinline__ void divide_by_norm(float (&y)[16], float r) {
     // u = ws / r, the correctly rounded quotient.  With q = fl(1/r) correctly rounded, q0 = fl(ws q) and the exact
     // remainder rem = ws - q0 r (one fused multiply-add), fl(q0 + rem q) IS the correctly rounded ws / r (Markstein's
     // division theorem) as long as nothing under- or overflows on the way: r within 2^+-60 and every |ws| at least
@@ -82,6 +75,23 @@ __device__ __forceinline__ void rotated_unit_row_from(float (&y)[16], const RawR
 #pragma unroll
         for (int e = 0; e < 16; ++e) y[e] = 0.0f;
     }
+}
+
+// c: first of the lane's 16 columns (multiple of 16, < d_in); r: the row's norm.
+// Requires 16-byte aligned rows and side arrays (checked on the host).
+template <int DTYPE, int B>
+__device__ __forceinline__ void rotated_unit_row_from(float (&y)[16], const RawRow<DTYPE> &raw, int c, float r, const Problem &p,
+                                                      const LaneSigns<B> &ls) {
+    widen_raw_row<DTYPE>(y, raw);
+    if (p.chan_scale) {
+        const float4 *s4 = reinterpret_cast<const float4 *>(p.chan_scale + c);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            float4 v = s4[t];
+            y[4 * t] *= v.x; y[4 * t + 1] *= v.y; y[4 * t + 2] *= v.z; y[4 * t + 3] *= v.w;
+        }
+    }
+    divide_by_norm(y, r);
     if (p.signs) {
         const uint4 sg = *reinterpret_cast<const uint4 *>(p.signs + c);
         const uint32_t wds[4] = {sg.x, sg.y, sg.z, sg.w};
@@ -189,6 +199,54 @@ __device__ __forceinline__ float row_norm_from_slab_sums(const double *part, int
     return (float)sqrt(s2);
 }
 
+// Sum of squares of a row's scaled weights, by one wave: 16-byte loads, squares exact in fp64, the lane-strided sums
+// combined with the fixed butterfly of wave_sum().  The same in every lane.
+template <int DTYPE>
+__device__ __forceinline__ double wave_row_sum_of_squares(const void *__restrict__ W, int row, int64_t ldw, int d_in,
+                                                          const float *__restrict__ s, int lane) {
+    constexpr int V = DTYPE == 0 ? 4 : 8;                       // elements per 16-byte load
+    constexpr int U = 4;                                        // loads requested together: a wave alone on its row has
+                                                                // nothing else to hide the memory round trip behind
+    const char *base = reinterpret_cast<const char *>(W) + (int64_t)row * ldw * (DTYPE == 0 ? 4 : 2);
+    double acc = 0.0;
+    for (int j0 = lane * V; j0 < d_in; j0 += U * WAVE * V) {
+        uint4 raw[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = j0 + u * WAVE * V;
+            raw[u] = make_uint4(0, 0, 0, 0);
+            if (j < d_in) raw[u] = *reinterpret_cast<const uint4 *>(base + (int64_t)j * (DTYPE == 0 ? 4 : 2));
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = j0 + u * WAVE * V;
+            if (j >= d_in) break;
+            float w[V];
+            const uint32_t q4[4] = {raw[u].x, raw[u].y, raw[u].z, raw[u].w};
+            if (DTYPE == 0) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) w[q] = __uint_as_float(q4[q]);
+            } else {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    w[2 * q] = __uint_as_float(q4[q] << 16);
+                    w[2 * q + 1] = __uint_as_float(q4[q] & 0xFFFF0000u);
+                }
+            }
+            if (s) {
+#pragma unroll
+                for (int t = 0; t < V; t += 4) {
+                    float4 sv = *reinterpret_cast<const float4 *>(s + j + t);
+                    w[t] *= sv.x; w[t + 1] *= sv.y; w[t + 2] *= sv.z; w[t + 3] *= sv.w;
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < V; ++t) acc += (double)w[t] * (double)w[t];
+        }
+    }
+    return wave_sum(acc);
+}
+
 // Exact squared distance as every encoder decides with it: fma(e1, e1, e0 * e0), e = x - c.
 __device__ __forceinline__ float exact_dist2(float x0, float x1, float2 c) {
     const float e0 = x0 - c.x, e1 = x1 - c.y;
@@ -251,6 +309,62 @@ __device__ __forceinline__ void store_packed_fields(uint8_t *__restrict__ packed
         uint8_t *rowp = packed + (int64_t)row * p.row_bytes;
         for (int64_t t = used; t < p.row_bytes; ++t) rowp[t] = 0;
     }
+}
+
+// The same with the bit count known to the compiler: the fields are shifted into dwords and stored as one or two unaligned
+// dword groups and the one to three bytes that remain.
+template <int BITS> __device__ __forceinline__ void store_fields_n(uint8_t *dst, const unsigned (&idx)[8]) {
+    typedef uint32_t u32_a1_t __attribute__((aligned(1)));
+    typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+    typedef u32x2_t u32x2_a1_t __attribute__((aligned(1)));
+    typedef uint16_t u16_a1_t __attribute__((aligned(1)));
+    uint32_t w[(8 * BITS + 31) / 32 + 1];
+#pragma unroll
+    for (int q = 0; q < (8 * BITS + 31) / 32 + 1; ++q) w[q] = 0u;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const int bit = k * BITS, word = bit >> 5, off = bit & 31;
+        w[word] |= idx[k] << off;
+        if (off + BITS > 32) w[word + 1] |= idx[k] >> (32 - off);
+    }
+    int at = 0;
+    if (BITS >= 8) {
+        *reinterpret_cast<u32x2_a1_t *>(dst) = u32x2_t{w[0], w[1]};
+        at = 8;
+    } else if (BITS >= 4) {
+        *reinterpret_cast<u32_a1_t *>(dst) = w[0];
+        at = 4;
+    }
+    if (BITS - at >= 4) {
+        *reinterpret_cast<u32_a1_t *>(dst + at) = w[at / 4];
+        at += 4;
+    }
+    if (BITS - at >= 2) {
+        *reinterpret_cast<u16_a1_t *>(dst + at) = (uint16_t)w[at / 4];
+        if (BITS - at == 3) dst[at + 2] = (uint8_t)(w[at / 4] >> 16);
+    } else if (BITS - at == 1) {
+        dst[at] = (uint8_t)w[at / 4];
+    }
+}
+// row: the row's packed bytes; c: first of the lane's 16 columns.
+__device__ __forceinline__ void store_fields(uint8_t *row, int64_t row_bytes, int d_in, int c, const unsigned (&idx)[8], int bits) {
+    uint8_t *dst = row + (int64_t)(c >> 4) * bits;
+    switch (bits) {
+        case 1: store_fields_n<1>(dst, idx); break;
+        case 2: store_fields_n<2>(dst, idx); break;
+        case 3: store_fields_n<3>(dst, idx); break;
+        case 4: store_fields_n<4>(dst, idx); break;
+        case 5: store_fields_n<5>(dst, idx); break;
+        case 6: store_fields_n<6>(dst, idx); break;
+        case 7: store_fields_n<7>(dst, idx); break;
+        case 8: store_fields_n<8>(dst, idx); break;
+        case 9: store_fields_n<9>(dst, idx); break;
+        case 10: store_fields_n<10>(dst, idx); break;
+        case 11: store_fields_n<11>(dst, idx); break;
+        default: store_fields_n<12>(dst, idx); break;
+    }
+    if (c + 16 == d_in)                                         // the lane with the row's last columns zeroes the padding
+        for (int64_t t = (int64_t)(d_in >> 4) * bits; t < row_bytes; ++t) row[t] = 0;
 }
 
 // Host-side check of what the vector loads above assume.

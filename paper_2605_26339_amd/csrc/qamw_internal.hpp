@@ -124,6 +124,9 @@ struct EncodeItem {
     uint8_t *packed;
     int d_out, d_in;
 };
+// The encoder with a cell table made on the device: table is encode_cells_bytes(bits) bytes of scratch (0: no such encoder).
+size_t encode_cells_bytes(int bits);
+hipError_t launch_encode_cells(const EncodeItem *items, int n, int dtype, const Problem &p, void *table);
 hipError_t launch_encode_batch_mfma(const EncodeItem *items, int n, int dtype, const Problem &p, bool norms_ready);
 
 }  // namespace qamw

@@ -23,6 +23,7 @@ EXPORTS = [
     "qamw_matmul_workspace_bytes", "qamw_matmul", "qamw_matmul_batch", "qamw_encode_stats",
     "qamw_normalised_pairs", "qamw_lloyd_workspace_bytes", "qamw_lloyd_device",
     "qamw_search_grid_size", "qamw_search_grid_build", "qamw_encode_pruned", "qamw_calibrate_sigma_static", "qamw_decode_traffic_probe", "qamw_encode_batch", "qamw_calibrate_sigma_batch",
+    "qamw_encode_workspace_bytes", "qamw_encode_ws", "qamw_encode_batch_ws",
 ]
 
 
@@ -95,6 +96,9 @@ def lib() -> C.CDLL:
         L.qamw_decode_batch.argtypes = [C.POINTER(DecodeItem), i32, vp, i32, i32, vp]
         L.qamw_decode_traffic_probe.argtypes = [C.POINTER(DecodeItem), i32, vp, i32, i32, vp]
         L.qamw_encode_batch.argtypes = [C.POINTER(EncodeItem), i32, i32, vp, i32, i32, vp]
+        L.qamw_encode_workspace_bytes.argtypes = [i32, C.POINTER(C.c_size_t)]
+        L.qamw_encode_ws.argtypes = [vp, i32, i32, i32, i64, vp, vp, vp, vp, i32, i32, vp, C.c_size_t, vp, vp, vp]
+        L.qamw_encode_batch_ws.argtypes = [C.POINTER(EncodeItem), i32, i32, vp, i32, i32, vp, C.c_size_t, vp]
         L.qamw_calibrate_sigma_batch.argtypes = [C.POINTER(CalibrateItem), i32, i32, i32, i32, vp, C.c_size_t, vp]
         L.qamw_set_kernel_path.argtypes = [i32]
         L.qamw_matmul_workspace_bytes.argtypes = [i32, i32, i32, C.POINTER(C.c_size_t)]
@@ -279,6 +283,28 @@ def calibrate_sigma_static(W, block: int, out, chan_scale=None, signs=None, max_
     return out
 
 
+def encode_workspace_bytes(bits: int) -> int:
+    out = C.c_size_t()
+    _check(lib().qamw_encode_workspace_bytes(bits, C.byref(out)), "qamw_encode_workspace_bytes")
+    return int(out.value)
+
+
+def _scratch(nbytes: int, device, stream):
+    """Device scratch for one call.  Its memory goes back to torch's allocator when the caller drops it, which is safe
+    on the stream it was allocated on; on another stream the allocator is told to wait for that stream's work."""
+    import torch
+
+    ws = torch.empty(nbytes, dtype=torch.uint8, device=device)
+    if stream is not None and stream != torch.cuda.current_stream(device):
+        ws.record_stream(stream)
+    return ws
+
+
+def _encode_scratch(bits: int, device, stream):
+    n = encode_workspace_bytes(bits) if 1 <= bits <= 12 else 0
+    return (_scratch(n, device, stream), n) if n else (None, 0)
+
+
 def encode(W, codebook, bits: int, block: int, chan_scale=None, signs=None, pair_sigma=None, out=None, stream=None,
            full_scans=None):
     """Encode W (torch CUDA tensor, fp32 or bf16, row-major, stride(1) == 1).
@@ -302,9 +328,10 @@ def encode(W, codebook, bits: int, block: int, chan_scale=None, signs=None, pair
                                        _ptr(pair_sigma), _ptr(codebook), bits, block, _ptr(packed), _ptr(norms),
                                        _ptr(full_scans), _stream(stream)), "qamw_encode_stats")
         return packed, norms
-    _check(lib().qamw_encode(_ptr(W), _dtype_code(W), d_out, d_in, W.stride(0), _ptr(chan_scale), _ptr(signs),
-                             _ptr(pair_sigma), _ptr(codebook), bits, block, _ptr(packed), _ptr(norms),
-                             _stream(stream)), "qamw_encode")
+    ws, n = _encode_scratch(bits, W.device, stream)
+    _check(lib().qamw_encode_ws(_ptr(W), _dtype_code(W), d_out, d_in, W.stride(0), _ptr(chan_scale), _ptr(signs),
+                                _ptr(pair_sigma), _ptr(codebook), bits, block, _ptr(ws), n, _ptr(packed), _ptr(norms),
+                                _stream(stream)), "qamw_encode_ws")
     return packed, norms
 
 
@@ -499,7 +526,9 @@ def make_encode_items(entries):
 def encode_batch(items, codebook, bits: int, block: int, stream=None):
     """Encode up to MAX_BATCH matrices (an EncodeItem array from make_encode_items) in one launch."""
     arr, _keep, code = items
-    _check(lib().qamw_encode_batch(arr, len(arr), code, _ptr(codebook), bits, block, _stream(stream)), "qamw_encode_batch")
+    ws, n = _encode_scratch(bits, codebook.device, stream)
+    _check(lib().qamw_encode_batch_ws(arr, len(arr), code, _ptr(codebook), bits, block, _ptr(ws), n, _stream(stream)),
+           "qamw_encode_batch_ws")
 
 
 def make_calibrate_items(entries, max_rows: int = 1024):
