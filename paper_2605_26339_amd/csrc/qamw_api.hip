@@ -462,7 +462,8 @@ static int matmul_batch_impl(const qamw_matmul_item *items, int n_items, int x_d
     if (!items || !codebook || !workspace || n_items < 1 || n_items > QAMW_MATMUL_MAX_BATCH) return QAMW_ERR_INVALID_ARG;
     if (x_dtype != QAMW_DTYPE_F32 && x_dtype != QAMW_DTYPE_BF16) return QAMW_ERR_INVALID_ARG;
     if (m < 1 || m > QAMW_MATMUL_MAX_ROWS) return QAMW_ERR_INVALID_ARG;
-    const int tile = matmul_tile_rows(m);
+    int tile = matmul_tile_rows(m);
+    size_t per_row = 0;
     qamw::MatmulItem its[QAMW_MATMUL_MAX_BATCH];
     size_t need = 0;
     bool supported = true;
@@ -475,10 +476,18 @@ static int matmul_batch_impl(const qamw_matmul_item *items, int n_items, int x_d
         qamw::Problem pi = make_problem(q.d_out, q.d_in, nullptr, nullptr, nullptr, codebook, bits, hadamard_block, stream);
         if (!qamw::matmul_supported(pi, tile) || (reinterpret_cast<uintptr_t>(q.packed) & 3)) supported = false;
         need += qamw::matmul_workspace_bytes(q.d_in, q.d_out, tile);
+        per_row += (size_t)q.d_in * sizeof(uint16_t);
         its[i] = qamw::MatmulItem{q.X, q.ldx, q.packed, q.row_norms, q.chan_scale, q.signs, q.pair_sigma, q.Y, q.ldy, q.d_out, q.d_in};
     }
     if (workspace_bytes < need || (reinterpret_cast<uintptr_t>(workspace) & 15)) return QAMW_ERR_INVALID_ARG;
     if (!supported) return QAMW_ERR_UNSUPPORTED;
+    // A workspace that holds more than one tile's rotated rows (32 at a time): as many rows per launch as fit, in tiles of
+    // equal size, if that makes them enough for the kernel for many rows.
+    if (m > QAMW_MATMUL_TILE_ROWS) {
+        const size_t fit = workspace_bytes / per_row / 32 * 32;
+        const int most = fit < (size_t)m ? (int)fit : m, tiles = most > 0 ? (m + most - 1) / most : m;
+        if (qamw::matmul_wide((m + tiles - 1) / tiles)) tile = (m + tiles - 1) / tiles;
+    }
     qamw::Problem p = make_problem(items[0].d_out, items[0].d_in, nullptr, nullptr, nullptr, codebook, bits, hadamard_block, stream);
     const size_t x_elem = x_dtype == QAMW_DTYPE_F32 ? sizeof(float) : sizeof(uint16_t);
     // one launch pair per tile of activation rows; the tiles follow one another on the stream and share the workspace

@@ -81,6 +81,7 @@ bool polar_encode_launchable(const void *W, int dtype, int64_t ldw, const Proble
 hipError_t launch_encode_polar(const void *W, int dtype, int64_t ldw, const Problem &p, const float *levels, int bits_a,
                                int bits_p, float *norms, bool norms_ready, uint8_t *packed);
 bool matmul_supported(const Problem &p, int m);
+bool matmul_wide(int m);                 // a launch of m activation rows goes to the kernel for many rows
 size_t matmul_workspace_bytes(int d_in, int d_out, int m);
 constexpr int QAMW_MATMUL_MAX_BATCH = 16;
 struct MatmulItem {

@@ -24,6 +24,7 @@
 // (slab, row group) steps (about 4): a product alone in a launch -- as a forward pass issues most of them --
 // takes as long as one wave's chain of dependent loads.
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 
 #include "qamw_common.hpp"
@@ -54,6 +55,7 @@ typedef uint32_t gv_u32x2_t __attribute__((ext_vector_type(2)));
 typedef float gv_f32x2_t __attribute__((ext_vector_type(2)));
 typedef __bf16 gv_bf16x2_t __attribute__((ext_vector_type(2)));
 typedef __bf16 gv_bf16x8_t __attribute__((ext_vector_type(8)));
+typedef float gv_f32x4_t __attribute__((ext_vector_type(4)));
 typedef float gv_f32x16_t __attribute__((ext_vector_type(16)));
 
 // One product of a batch, as the kernels see it.  Z and partial point into the caller's workspace.
@@ -679,13 +681,276 @@ void k_qgemm(GemvBatch bt) {
     }
 }
 
+// ---------------------------------------------------------------------------------------------------------
+// More than 64 activation rows: the same product in tiles of 128 weight rows x 128 TT activation rows, 8 waves (2 x 4) of
+// 64 x 32 TT each.
+//   A stage is 4 matrix instructions of depth (64 of the 256 columns of a chunk).  The weights' side of a stage is unpacked
+// once per workgroup: a lane takes 8 pairs of one (row, half), gathers their bf16 codewords and leaves them in LDS in the
+// order the A operand is read; the activations go from memory straight into LDS (k_rotate_x wrote them in B's order).
+// While stage s is multiplied the weights of stage s + 1 are unpacked (two buffers) and the
+// activations of stage s + 2 requested (three: an L2 round trip is longer than a stage); one barrier per stage.
+//   What bounds it: the LDS pipe -- per stage of a 128 x 256 tile 128 KB of operand reads, 8 K codeword gathers and 48 KB
+// of writes against 1024 cycles of matrix instructions per SIMD -- so an unpacked operand has to serve many activation
+// rows; the kernel for up to 64 rows unpacks the matrix again for every launch.
+//   Summation order: exactly that of k_qgemm -- the chunks w, w + 8, ... summed in an accumulator of their own for
+// w = 0 .. 7, those eight then added in order -- so a row of Y has the same bits whatever m is and whichever of the two
+// kernels computes it; that is why the kernel keeps two accumulators.
+constexpr int GW_ROWS = 128;               // weight rows of a workgroup
+constexpr int GW_WAVES = 8, GW_THREADS = GW_WAVES * WAVE;
+constexpr int GW_MIN_M = 192;              // more activation rows than this
+constexpr int GW_CUS = 256;                // one workgroup per CU at a time
+constexpr int GW_STAGE = 4;                // matrix instructions of depth per stage
+
+constexpr int gw_ahead(int tt) { return tt == 2 ? 2 : 4; }      // 136 and 120 KB of LDS
+
+// LDS by byte address: the kernel has no static LDS, so the dynamic block begins at 0 and constant parts of an address go
+// into the instruction's offset.
+template <typename T> __device__ __forceinline__ T gw_lds_read(uint32_t at) {
+    return *reinterpret_cast<const __attribute__((address_space(3))) T *>(at);
+}
+template <typename T> __device__ __forceinline__ void gw_lds_write(uint32_t at, T v) {
+    *reinterpret_cast<__attribute__((address_space(3))) T *>(at) = v;
+}
+
+template <int BITS, int TT>
+__global__ __launch_bounds__(GW_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void k_qgemm_wide(GemvBatch bt) {
+    constexpr int AHEAD = gw_ahead(TT);                         // stages the activations are requested ahead
+    constexpr int TILES = 4 * TT;                               // 32-row tiles of activation rows
+    constexpr int KC = 1 << BITS;
+    constexpr uint32_t A_BYTES = 4 * GW_STAGE * 1024, Z_BYTES = TILES * GW_STAGE * 1024;
+    constexpr uint32_t A_AT = KC * 4;                           // after the K codewords, (bf16 c0) | (bf16 c1) << 16:
+                                                                // 2 buffers [4 tiles of 32 rows][4 instructions][64 lanes] x 16 bytes
+    constexpr uint32_t Z_AT = A_AT + 2 * A_BYTES;               // AHEAD + 1 buffers [TILES][2 halves][4 instructions][32 rows] x 16 bytes
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r = lane & 31, h = lane >> 5;
+    const int wn = wid & 1, wm = wid >> 1;
+
+    const int grp = blockIdx.x;
+    const int mi = gv_find(bt.grp_begin, bt.n, grp);
+    const GemvMat &M = bt.mat[mi];
+    const int m = bt.m, d_out = M.d_out, last_row = d_out - 1;
+    const int tok_tiles = (m + 31) >> 5, m_tiles = (tok_tiles + TILES - 1) / TILES;
+    // Workgroup b runs on XCD b mod 8: the activation tiles of one weight tile follow one another on the same XCD, so the
+    // packed rows come from its L2 after the first.
+    const int local = grp - bt.grp_begin[mi], n_tiles = (d_out + GW_ROWS - 1) / GW_ROWS;
+    int nt, mt;
+    {
+        const int whole = n_tiles / 8 * 8 * m_tiles;            // the last n_tiles mod 8 weight tiles in plain order
+        if (local < whole) {
+            const int x = local & 7, q = local >> 3;
+            nt = x + 8 * (q / m_tiles);
+            mt = q - q / m_tiles * m_tiles;
+        } else {
+            const int q = local - whole;
+            nt = n_tiles / 8 * 8 + q / m_tiles;
+            mt = q - q / m_tiles * m_tiles;
+        }
+    }
+    const int row0 = nt * GW_ROWS, tile0 = mt * TILES;
+    const int n_chunks = M.d_in / GM_CHUNK;
+
+    {   // stage the codebook, rounded to bf16
+        const float2 *cbk = reinterpret_cast<const float2 *>(bt.codebook);
+        for (int i = threadIdx.x; i < KC; i += GW_THREADS) {
+            const float2 c = cbk[i];
+            const gv_f32x2_t v = {c.x, c.y};
+            gw_lds_write<uint32_t>(4 * i, __builtin_bit_cast(uint32_t, __builtin_convertvector(v, gv_bf16x2_t)));
+        }
+    }
+
+    // Stage q of a chunk: waves w and w + 4 unpack the w-th 32 rows; this wave's part is 8 pairs, BITS bytes from byte
+    // (2 q + part) BITS of the lane's half of the row.  A lane holds the dwords that cover them (moved back where they would
+    // reach past the half, i.e. possibly past the matrix), four stages ahead.
+    constexpr int PIECE = (BITS + 3) / 4 + (BITS % 4 ? (BITS % 4 > 1 ? 1 : 0) : 0);
+    static_assert(PIECE == (BITS == 11 ? 4 : BITS == 7 ? 3 : 2), "dwords that cover a piece at any byte offset");
+    const int part = wid >> 2;
+    const uint8_t *src_row = M.packed + (int64_t)min(row0 + 32 * (wid & 3) + r, last_row) * M.row_bytes + h * (8 * BITS);
+    uint32_t pc[4][PIECE];
+    auto load_piece = [&](int ch, int q, uint32_t (&w)[PIECE]) {
+        typedef uint32_t u32xp_t __attribute__((ext_vector_type(PIECE)));
+        typedef u32xp_t u32xp_a4_t __attribute__((aligned(4)));
+        const int at = min(((2 * q + part) * BITS) & ~3, 8 * BITS - 4 * PIECE);
+        const u32xp_t v = *reinterpret_cast<const u32xp_a4_t *>(src_row + (int64_t)ch * (16 * BITS) + at);
+#pragma unroll
+        for (int i = 0; i < PIECE; ++i) w[i] = v[i];
+    };
+    // the piece's 8 fields from bit 0 on
+    auto align_piece = [&](const uint32_t (&w)[PIECE], int q, uint32_t (&f)[3]) {
+        const bool back = q == 3 && part == 1 && BITS != 8;     // the one piece whose dwords were moved back, by 4 bytes
+        const uint32_t sh = (((2 * q + part) * BITS) & 3) * 8;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            auto dw = [&](int k) { return k < PIECE ? w[k] : 0u; };
+            const uint32_t lo = back ? dw(i + 1) : dw(i), hi = back ? dw(i + 2) : dw(i + 1);
+            f[i] = BITS == 8 ? lo : __builtin_amdgcn_alignbit(hi, lo, sh);
+        }
+    };
+    // activations of stage q of a chunk: 1 KB pieces (two instructions of one half of one tile), 2 TT per wave
+    const int my_tile = wid * TT / 2;
+    const char *zsrc = reinterpret_cast<const char *>(M.Z) + (int64_t)min(tile0 + my_tile, tok_tiles - 1) * n_chunks * 16384 +
+                       (TT == 1 ? (wid & 1) * 8192 : 0);        // tiles past the end repeat the last (not stored)
+    auto request_z = [&](int ch, int q, uint32_t buf) {            // buf: byte offset of the buffer
+#pragma unroll
+        for (int u = 0; u < 2 * TT; ++u) {
+            const char *src = zsrc + (int64_t)ch * 16384 + (u >> 1) * 8192 + q * 2048 + (u & 1) * 1024;
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + lane * 16),
+                                             reinterpret_cast<__attribute__((address_space(3))) void *>(Z_AT + buf + (wid * 2 * TT + u) * 1024u), 16, 0, 0);
+        }
+    };
+    const uint32_t a_write = A_AT + (uint32_t)((wid & 3) * GW_STAGE + 2 * part) * 1024 + lane * 16;
+    const uint32_t a_read = A_AT + (uint32_t)(2 * wn) * (GW_STAGE * 1024) + lane * 16;
+    const uint32_t z_read = Z_AT + (uint32_t)(wm * TT) * 4096 + h * 2048 + r * 16;
+    // four codewords of an instruction
+    auto gather = [&](const uint32_t (&f)[3], int j) {
+        gv_u32x4_t a;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int bit = (4 * j + i) * BITS, word = bit >> 5, off = bit & 31;
+            const uint32_t v = (off + BITS <= 32) ? (f[word] >> off) : __builtin_amdgcn_alignbit(f[word + 1], f[word], off);
+            a[i] = gw_lds_read<uint32_t>((v & (KC - 1u)) << 2);
+        }
+        return a;
+    };
+
+    gv_f32x16_t acc[2][TT], total[2][TT];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int t = 0; t < TT; ++t)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[a][t][i] = total[a][t][i] = 0.0f;
+
+#pragma unroll
+    for (int q = 0; q < 4; ++q) load_piece(0, q, pc[q]);
+#pragma unroll
+    for (int q = 0; q < (AHEAD < 4 ? AHEAD : 4); ++q) request_z(0, q, q * Z_BYTES);
+    __syncthreads();                                            // the codebook is staged
+    {
+        uint32_t f[3];
+        align_piece(pc[0], 0, f);
+        gw_lds_write(a_write, gather(f, 0));
+        gw_lds_write(a_write + 1024, gather(f, 1));
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);                        // vmcnt(0): the wave's activations have landed
+    __syncthreads();
+    int ch = 0, seg = 0;
+    uint32_t z_now = 0, z_ask = AHEAD * Z_BYTES;                // the activations' buffers: this stage's, the one being filled
+#pragma unroll 1
+    while (true) {
+        // the chunk after this one: the next of the segment (+ 8), or the first of the next segment
+        int next = ch + GM_WAVES, next_seg = seg;
+        if (next >= n_chunks) {
+            next_seg = seg + 1;
+            next = next_seg;
+        }
+        const bool more = next_seg < GM_WAVES && next < n_chunks;
+        const int load_ch = more ? next : ch;                   // past the end: the same chunk again (unused)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int cur = q & 1, nxt = cur ^ 1;
+            request_z(q + AHEAD < 4 ? ch : load_ch, (q + AHEAD) & 3, z_ask);
+            // the piece of stage q has been used: the next chunk's takes its place.  The one load stays between here and
+            // the wait below: its count relies on it.
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+            load_piece(load_ch, q, pc[q]);
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+            gv_bf16x8_t av[2][2], bv[2][TT];
+            const uint32_t zr = z_read + z_now;
+            auto operands = [&](int j) {
+#pragma unroll
+                for (int a = 0; a < 2; ++a) av[j & 1][a] = gw_lds_read<gv_bf16x8_t>(a_read + cur * A_BYTES + (a * GW_STAGE + j) * 1024);
+#pragma unroll
+                for (int t = 0; t < TT; ++t) bv[j & 1][t] = gw_lds_read<gv_bf16x8_t>(zr + t * 4096 + j * 512);
+            };
+            operands(0);
+            uint32_t f[3];
+            align_piece(pc[(q + 1) & 3], (q + 1) & 3, f);
+            gv_u32x4_t cw[2];
+#pragma unroll
+            for (int j = 0; j < GW_STAGE; ++j) {
+                if (j < 2) cw[j] = gather(f, j);
+                if (j + 1 < GW_STAGE) operands(j + 1);
+                __builtin_amdgcn_sched_barrier(0);              // the reads go out before the products they are to hide behind
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+#pragma unroll
+                    for (int t = 0; t < TT; ++t)
+                        acc[a][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[j & 1][a], bv[j & 1][t], acc[a][t], 0, 0, 0);
+                if (j >= 1 && j < 3) gw_lds_write(a_write + nxt * A_BYTES + (j - 1) * 1024, cw[j - 1]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            // The next stage's activations have landed.  What was requested since may be under way: a piece, then AHEAD - 1
+            // times the 2 TT loads of a stage and a piece.
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(1 + (AHEAD - 1) * (2 * TT + 1)) : "memory");
+            __builtin_amdgcn_sched_barrier(0);
+            z_now = z_now == AHEAD * Z_BYTES ? 0 : z_now + Z_BYTES;
+            z_ask = z_ask == AHEAD * Z_BYTES ? 0 : z_ask + Z_BYTES;
+        }
+        if (next_seg != seg) {
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int t = 0; t < TT; ++t) {
+                    total[a][t] = seg == 0 ? acc[a][t] : total[a][t] + acc[a][t];
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) acc[a][t][i] = 0.0f;
+                }
+        }
+        if (!more) break;
+        ch = next;
+        seg = next_seg;
+    }
+
+    // The norms first, all of them, then four consecutive weight rows per store: a load between two stores would wait for
+    // the first to reach memory.
+    float nr[2][16];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) nr[a][i] = M.norms[min(row0 + 32 * (2 * wn + a) + 8 * (i >> 2) + 4 * h + (i & 3), last_row)];
+    typedef gv_f32x4_t f32x4_a4_t __attribute__((aligned(4)));
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+#pragma unroll
+        for (int t = 0; t < TT; ++t) {
+            const int tok = 32 * (tile0 + wm * TT + t) + r;     // the accumulator's column is the activation row
+            if (tok >= m) continue;
+            float *dst = M.Y + (int64_t)tok * M.ldy;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {                       // accumulators 4 g .. 4 g + 3 of half h
+                const int row = row0 + 32 * (2 * wn + a) + 8 * g + 4 * h;
+                gv_f32x4_t y;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) y[i] = nr[a][4 * g + i] * total[a][t][4 * g + i];
+                if (row + 3 <= last_row) {
+                    *reinterpret_cast<f32x4_a4_t *>(dst + row) = y;
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 3; ++i)
+                        if (row + i <= last_row) dst[row + i] = y[i];
+                }
+            }
+        }
+    }
+}
+
 bool matmul_supported(const Problem &p, int m) {
     const int unit = p.block > 16 ? p.block : 16;
     if (p.d_in % unit || p.block < 64) return false;
     if (p.bits != 7 && p.bits != 8 && p.bits != 11) return false;
-    if (m > GV_MAX_M) return m <= GM_MAX_M && p.d_in % GM_CHUNK == 0;      // the matrix-core kernel walks 256-column chunks
+    if (m > GV_MAX_M) return p.d_in % GM_CHUNK == 0;               // the matrix-core kernels walk 256-column chunks
     return m >= 1;
 }
+
+// Whether a tile of m activation rows is better taken whole, by the wide kernel.  Up to three tiles of 64 the smaller kernel, once per tile, is
+// sooner done: a wide workgroup walks all columns, 0.8 us per 64 of them, whatever the number of rows (4096 x 4096: 54 us
+// in three tiles, 70 in four, 63-65 wide; 1024 x 2048: 39, 51, 39; 4096 x 11008: 108, 142, 142; 11008 x 4096, the other way
+// round from three tiles on: 78, 103, 65).
+bool matmul_wide(int m) { return m > GW_MIN_M; }
 
 size_t matmul_workspace_bytes(int d_in, int d_out, int m) {
     (void)d_out;
@@ -751,6 +1016,28 @@ static hipError_t launch_qgemm(const GemvBatch &bt, hipStream_t stream) {
     return hipGetLastError();
 }
 
+template <int BITS, int TT>
+static hipError_t launch_qgemm_wide_t(const GemvBatch &bt, hipStream_t stream) {
+    constexpr size_t lds = ((size_t)4 << BITS) + (2 * 4 + (gw_ahead(TT) + 1) * 4 * TT) * GW_STAGE * 1024;
+    if (lds > 64 * 1024) {
+        static std::atomic<uint64_t> done{0};                   // the devices on which the larger LDS was asked for
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorNotSupported;
+        if (!(done.load(std::memory_order_acquire) & (1ull << dev))) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_qgemm_wide<BITS, TT>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            if (e != hipSuccess) return e;
+            done.fetch_or(1ull << dev, std::memory_order_release);
+        }
+    }
+    hipLaunchKernelGGL((k_qgemm_wide<BITS, TT>), dim3((unsigned)bt.grp_begin[bt.n]), dim3(GW_THREADS), lds, stream, bt);
+    return hipGetLastError();
+}
+template <int BITS>
+static hipError_t launch_qgemm_wide(const GemvBatch &bt, int tt, hipStream_t stream) {
+    return tt == 2 ? launch_qgemm_wide_t<BITS, 2>(bt, stream) : launch_qgemm_wide_t<BITS, 1>(bt, stream);
+}
+
 // Y_i = X_i W_i^T for n <= QAMW_MATMUL_MAX_BATCH matrices that share codebook, bits, block, m and the element type
 // of X.  workspace: the sum of matmul_workspace_bytes() over the items, 16-byte aligned.
 // Returns hipErrorNotSupported (nothing launched) outside the supported shapes.  variant: 0, or 1 / 2 to force the
@@ -773,6 +1060,14 @@ hipError_t launch_matmul_batch(const MatmulItem *items, int n, int xdtype, int m
     int64_t tiles32 = 0;
     for (int i = 0; i < n; ++i) tiles32 += (items[i].d_out + GM_ROWS - 1) / GM_ROWS;
     bt.gm_rows = tiles32 <= GM_HALF_TILE_MAX_WGS ? GM_ROWS / 2 : GM_ROWS;
+    // More than 64 activation rows: tiles of 256 of them where those make enough workgroups for the chip, else of 128.
+    const bool wide = m > GM_MAX_M;
+    auto wide_groups = [&](const MatmulItem &it, int tt) {
+        return (int64_t)((it.d_out + GW_ROWS - 1) / GW_ROWS) * ((m + 128 * tt - 1) / (128 * tt));
+    };
+    int64_t groups256 = 0;
+    for (int i = 0; i < n; ++i) groups256 += wide_groups(items[i], 2);
+    const int tt = groups256 >= GW_CUS ? 2 : 1;
     for (int i = 0; i < n; ++i) {
         const MatmulItem &it = items[order[i]];
         Problem q = p;
@@ -811,7 +1106,7 @@ hipError_t launch_matmul_batch(const MatmulItem *items, int n, int xdtype, int m
         bt.rot_begin[i] = (int)rot;
         bt.grp_begin[i] = (int)groups;
         rot += (int64_t)(m > GV_MAX_M ? (m + 31) / 32 * 32 : m) * M.n_slabs;
-        groups += (M.d_out + M.rows_per_wg - 1) / M.rows_per_wg;
+        groups += wide ? wide_groups(it, tt) : (M.d_out + M.rows_per_wg - 1) / M.rows_per_wg;
         if (groups > 0x3fffffff || rot > 0x3fffffff) return hipErrorNotSupported;
     }
     for (int i = n; i <= QAMW_MATMUL_MAX_BATCH; ++i) {
@@ -833,6 +1128,33 @@ hipError_t launch_matmul_batch(const MatmulItem *items, int n, int xdtype, int m
     hipError_t e = hipSuccess;
     if (!self_rotate) e = xdtype == 0 ? launch_rotate<0>(bt, p.block, p.stream) : launch_rotate<1>(bt, p.block, p.stream);
     if (e != hipSuccess) return e;
+    if (wide) {
+        auto launch_wide = [&](const GemvBatch &b, int t) {
+            if (p.bits == 11) return launch_qgemm_wide<11>(b, t, p.stream);
+            if (p.bits == 8) return launch_qgemm_wide<8>(b, t, p.stream);
+            return launch_qgemm_wide<7>(b, t, p.stream);
+        };
+        // One product whose 256-row tiles leave most of the chip idle in the last round: the weight rows of that round go
+        // into a launch of 128-row tiles, if those are at most a round (11008 x 4096, 1000 rows, 344 tiles: 172 -> 160 us).
+        const int m_tiles = (m + 255) / 256, n_tiles = (items[0].d_out + GW_ROWS - 1) / GW_ROWS;
+        const int first = (int)(groups256 / GW_CUS * GW_CUS) / m_tiles, rest = (n_tiles - first) * ((m + 127) / 128);
+        if (n == 1 && tt == 2 && first < n_tiles && rest <= GW_CUS) {
+            GemvBatch b2 = bt;
+            GemvMat &M = bt.mat[0], &M2 = b2.mat[0];
+            M.d_out = first * GW_ROWS;
+            M2.d_out -= M.d_out;
+            M2.packed += (int64_t)M.d_out * M.row_bytes;
+            M2.norms += M.d_out;
+            M2.Y += M.d_out;
+            for (int i = 1; i <= QAMW_MATMUL_MAX_BATCH; ++i) {
+                bt.grp_begin[i] = first * m_tiles;
+                b2.grp_begin[i] = rest;
+            }
+            e = launch_wide(bt, 2);
+            return e != hipSuccess ? e : launch_wide(b2, 1);
+        }
+        return launch_wide(bt, tt);
+    }
     if (m > GV_MAX_M) {
         if (p.bits == 11) return launch_qgemm<11>(bt, p.stream);
         if (p.bits == 8) return launch_qgemm<8>(bt, p.stream);

@@ -429,11 +429,17 @@ def matmul_workspace_bytes(d_in: int, d_out: int, m: int) -> int:
     return int(out.value)
 
 
+def _matmul_scratch_bytes(d_in: int, d_out: int, m: int) -> int:
+    """What a product asks for: beyond one tile of rows, room for all of them (the least is matmul_workspace_bytes())."""
+    least = matmul_workspace_bytes(d_in, d_out, m)
+    return max(least, (m + 31) // 32 * 32 * d_in * 2) if m > MATMUL_TILE_ROWS else least
+
+
 def matmul(X, packed, row_norms, codebook, bits: int, block: int, chan_scale=None, signs=None, pair_sigma=None,
            workspace=None, out=None, stream=None):
     """Y = X W^T (fp32 [m][d_out]) for m <= 4096 rows of X (fp32 or bf16 [m][d_in]) against the packed matrix.
-    Up to 8 rows: fp32 arithmetic throughout; more: bf16 operands on the matrix cores, fp32 accumulation, in tiles of at
-    most 64 activation rows."""
+    Up to 8 rows: fp32 arithmetic throughout; more: bf16 operands on the matrix cores, fp32 accumulation.  Beyond 64 rows a
+    workspace of at least matmul_workspace_bytes() serves; one that holds all the rotated rows is faster."""
     import torch
 
     _require_cuda(X, packed, row_norms, codebook, chan_scale, signs, pair_sigma)
@@ -442,7 +448,7 @@ def matmul(X, packed, row_norms, codebook, bits: int, block: int, chan_scale=Non
     m, d_in = X.shape
     d_out = row_norms.shape[0]
     if workspace is None:
-        workspace = torch.empty(matmul_workspace_bytes(d_in, d_out, m), dtype=torch.uint8, device=X.device)
+        workspace = _scratch(_matmul_scratch_bytes(d_in, d_out, m), X.device, stream)
     if out is None:
         out = torch.empty((m, d_out), dtype=torch.float32, device=X.device)
     _check(lib().qamw_matmul(_ptr(X), _dtype_code(X), m, X.stride(0), _ptr(packed), _ptr(row_norms), d_out, d_in,
@@ -469,7 +475,7 @@ def make_matmul_items(entries):
         arr[i] = MatmulItem(X.data_ptr(), X.stride(0), packed.data_ptr(), norms.data_ptr(), None if s is None else s.data_ptr(),
                             None if sg is None else sg.data_ptr(), None if sigma is None else sigma.data_ptr(), Y.data_ptr(),
                             Y.stride(0), d_out, d_in)
-        need += matmul_workspace_bytes(d_in, d_out, m)
+        need += _matmul_scratch_bytes(d_in, d_out, m)
     return arr, list(entries), m, code, need
 
 
