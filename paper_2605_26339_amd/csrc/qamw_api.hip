@@ -344,10 +344,10 @@ int qamw_lloyd_device(const float *samples, uint64_t n_samples, int bits, float 
         return QAMW_ERR_INVALID_ARG;
     const int K = 1 << bits;
     if (n_samples < (uint64_t)K || n_samples > (1ull << 24)) return QAMW_ERR_INVALID_ARG;
-    if (workspace_bytes < qamw::lloyd_workspace_bytes(K) || (reinterpret_cast<uintptr_t>(workspace) & 15) ||
+    if (workspace_bytes < qamw::lloyd_least_workspace_bytes(K) || (reinterpret_cast<uintptr_t>(workspace) & 15) ||
         (reinterpret_cast<uintptr_t>(samples) & 7) || (reinterpret_cast<uintptr_t>(codebook) & 7))
         return QAMW_ERR_INVALID_ARG;
-    hipError_t e = qamw::run_lloyd(samples, (long long)n_samples, K, codebook, max_iters, tol, workspace, mse_out, iters_out,
+    hipError_t e = qamw::run_lloyd(samples, (long long)n_samples, K, codebook, max_iters, tol, workspace, workspace_bytes, mse_out, iters_out,
                                    (hipStream_t)stream);
     return e == hipSuccess ? QAMW_OK : QAMW_ERR_DEVICE;
 }

@@ -96,9 +96,10 @@ struct MatmulItem {
     int d_out, d_in;
 };
 hipError_t launch_matmul_batch(const MatmulItem *items, int n, int xdtype, int m, const Problem &p, void *workspace, int variant);
-size_t lloyd_workspace_bytes(int K);
+size_t lloyd_workspace_bytes(int K);          // with room for the cell table and the workgroups' sums
+size_t lloyd_least_workspace_bytes(int K);    // what the search over all points needs
 hipError_t run_lloyd(const float *samples, long long n, int K, float *codebook, int max_iters, double tol, void *workspace,
-                     double *mse_out, int *iters_out, hipStream_t stream);
+                     size_t workspace_bytes, double *mse_out, int *iters_out, hipStream_t stream);
 bool pairs_launchable(const void *W, int dtype, int64_t ldw, const Problem &p, const float *pairs);
 hipError_t launch_pairs(const void *W, int dtype, int64_t ldw, const Problem &p, float *norms, bool norms_ready, float *pairs);
 // The pruned-search table in device memory (layout: qamw_search_grid_build) and its grid size, which follows from bits.

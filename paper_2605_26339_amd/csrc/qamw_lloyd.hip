@@ -8,9 +8,12 @@
 // codebook (lowest index on ties), sums of each cell accumulated in 64-bit fixed point (2^-30), so the
 // result does not depend on the order the atomics land in.
 // k_lloyd_update: every point to the mean of its cell (an empty cell keeps its point).
+// k_cells_lloyd_*: the same iteration for 64 to 2048 points with a cell table (qamw_cells.hpp) made from every iteration's
+// points, the sums of a workgroup in LDS, and the stopping rule on the device, so the host launches ahead.
+#include <atomic>
 #include <cmath>
 
-#include "qamw_front.hpp"
+#include "qamw_cells.hpp"
 
 namespace qamw {
 
@@ -120,7 +123,244 @@ __global__ __launch_bounds__(LL_THREADS) void k_lloyd_init(int K, LloydAcc acc, 
     }
 }
 
-size_t lloyd_workspace_bytes(int K) { return (size_t)K * (2 * sizeof(double) + 3 * sizeof(long long)) + 64; }
+// ------------------------------------------------------------------------------------------------ with a cell table
+// Per iteration t, points in buffer t mod 2: k_cells_lloyd_table makes the table, k_cells_lloyd_assign assigns every sample
+// and leaves each workgroup's sums, k_cells_lloyd_move adds them up, decides whether to stop and writes the next points to
+// the other buffer.  Once it has stopped, the kernels of later iterations return at once.
+//   What bounds it: the assignment reads 8 bytes per sample and does some 50 instructions per wave of them; at 2^20 samples
+// the three launches, each a few us of staging and latency, are most of an iteration (2048 points: 401 us a pass for the
+// distances to all of them before).
+struct LloydState {
+    double D;
+    int stopped_at;                       // the last iteration, LC_RUNNING before it is known
+};
+constexpr int LC_RUNNING = 0x7fffffff;
+constexpr int LC_THREADS = 1024;
+constexpr int LC_POINTS = 16;                                  // points per workgroup of k_cells_lloyd_move
+constexpr int LC_MAX_BLOCKS = 256;                             // one workgroup per CU: a workgroup's sums are 20 bytes per point in LDS and in the workspace
+constexpr int LC_AHEAD = 16;                                   // iterations launched before the host looks whether it has stopped
+constexpr int lc_side(int K) { return K == 2048 ? 112 : K == 1024 ? 96 : 64; }   // beside the sums 128 x 128 records do not fit the LDS
+
+struct LloydCells {
+    double *cb64[2];
+    float *cb32[2];
+    uint2 *table;
+    long long *psx, *psy;                                      // [workgroups][K]
+    unsigned *pcnt;
+    unsigned long long *perr;                                  // [workgroups]
+    LloydState *state;
+};
+static size_t lloyd_cells_bytes(int K) {
+    const size_t G = lc_side(K);
+    return (size_t)K * 2 * (16 + 8) + G * G * 8 + (size_t)LC_MAX_BLOCKS * ((size_t)K * 20 + 8) + 64;
+}
+static LloydCells lloyd_cells_layout(void *workspace, int K) {
+    LloydCells a;
+    char *p = static_cast<char *>(workspace);
+    auto take = [&](size_t bytes) {
+        char *at = p;
+        p += bytes;
+        return at;
+    };
+    for (int i = 0; i < 2; ++i) a.cb64[i] = reinterpret_cast<double *>(take((size_t)K * 16));
+    for (int i = 0; i < 2; ++i) a.cb32[i] = reinterpret_cast<float *>(take((size_t)K * 8));
+    a.table = reinterpret_cast<uint2 *>(take((size_t)lc_side(K) * lc_side(K) * 8));
+    a.psx = reinterpret_cast<long long *>(take((size_t)LC_MAX_BLOCKS * K * 8));
+    a.psy = reinterpret_cast<long long *>(take((size_t)LC_MAX_BLOCKS * K * 8));
+    a.perr = reinterpret_cast<unsigned long long *>(take((size_t)LC_MAX_BLOCKS * 8));
+    a.state = reinterpret_cast<LloydState *>(take(64));
+    a.pcnt = reinterpret_cast<unsigned *>(take((size_t)LC_MAX_BLOCKS * K * 4));
+    return a;
+}
+
+__global__ __launch_bounds__(LL_THREADS) void k_cells_lloyd_init(int K, LloydCells a, const float *codebook) {
+    const int i = blockIdx.x * LL_THREADS + threadIdx.x;
+    if (i < 2 * K) {
+        a.cb64[0][i] = (double)codebook[i];
+        a.cb32[0][i] = codebook[i];
+    }
+    if (i == 0) *a.state = LloydState{0.0, LC_RUNNING};
+}
+
+template <int G> __global__ __launch_bounds__(CP_THREADS) void k_cells_lloyd_table(int K, LloydCells a, int t) {
+    if (a.state->stopped_at < t) return;
+    cells_build_region<G>(a.cb32[t & 1], K, a.table, (int)blockIdx.x);
+}
+
+template <int G>
+__global__ __launch_bounds__(LC_THREADS) void k_cells_lloyd_assign(const float2 *__restrict__ samples, long long n, int K, LloydCells a, int t) {
+    extern __shared__ __align__(16) float2 lc_lds[];           // points, table, then the sums: x, y (64 bits), count (32)
+    if (a.state->stopped_at < t) return;
+    char *table = reinterpret_cast<char *>(lc_lds + K);
+    unsigned long long *sx = reinterpret_cast<unsigned long long *>(table + G * G * 8), *sy = sx + K;
+    unsigned *cnt = reinterpret_cast<unsigned *>(sy + K);
+    __shared__ unsigned long long err_sum;
+    const float2 *cbk = reinterpret_cast<const float2 *>(a.cb32[t & 1]);
+    for (int i = threadIdx.x; i < K; i += LC_THREADS) {
+        lc_lds[i] = cbk[i];
+        sx[i] = 0;
+        sy[i] = 0;
+        cnt[i] = 0;
+    }
+    if (threadIdx.x == 0) err_sum = 0;
+    const uint4 *src = reinterpret_cast<const uint4 *>(a.table);
+    uint4 *dst = reinterpret_cast<uint4 *>(table);
+#pragma unroll 8
+    for (int i = threadIdx.x; i < G * G / 2; i += LC_THREADS) dst[i] = src[i];
+    __syncthreads();
+
+    const int lane = threadIdx.x & (WAVE - 1);
+    const long long stride = (long long)gridDim.x * LC_THREADS;
+    double err = 0.0;
+    long long i = (long long)blockIdx.x * LC_THREADS + threadIdx.x;
+    float2 next = i < n ? samples[i] : make_float2(0.0f, 0.0f);
+    for (; i - lane < n; i += stride) {                         // the wave's lanes stay together
+        const bool active = i < n;
+        const float2 x = next;
+        if (i + stride < n) next = samples[i + stride];
+        const uint2 rec = cells_record<G>(table, x.x, x.y);
+        float d;
+        int bi = (int)(cells_nearest<(G > 64)>(rec, x.x, x.y, lc_lds, d) >> 3);
+        unsigned long long mask = __ballot(active && cells_scan(rec));
+        while (mask) {                                          // outside the table, or too many candidates: the whole codebook
+            const int at = __ffsll((long long)mask) - 1;
+            mask &= mask - 1;
+            const float x0 = __shfl(x.x, at, WAVE), x1 = __shfl(x.y, at, WAVE);
+            const int found = wave_exact_scan(x0, x1, lc_lds, K, lane);
+            if (lane == at) {
+                bi = found;
+                d = fminf(exact_dist2(x0, x1, lc_lds[found]), 3.0e38f);
+            }
+        }
+        if (active) {
+            const float cx = fminf(fmaxf(x.x, -LL_CLAMP), LL_CLAMP), cy = fminf(fmaxf(x.y, -LL_CLAMP), LL_CLAMP);
+            atomicAdd(sx + bi, (unsigned long long)__double2ll_rn((double)cx * LL_SCALE));
+            atomicAdd(sy + bi, (unsigned long long)__double2ll_rn((double)cy * LL_SCALE));
+            atomicAdd(cnt + bi, 1u);
+            err += (double)fminf(d, 2.0f * LL_CLAMP * LL_CLAMP);
+        }
+    }
+#pragma unroll
+    for (int s = 1; s < WAVE; s <<= 1) err += __shfl_xor(err, s, WAVE);
+    if (lane == 0) atomicAdd(&err_sum, (unsigned long long)__double2ll_rn(err * LL_SCALE));
+    __syncthreads();
+    const size_t base = (size_t)blockIdx.x * K;
+    for (int k = threadIdx.x; k < K; k += LC_THREADS) {
+        a.psx[base + k] = (long long)sx[k];
+        a.psy[base + k] = (long long)sy[k];
+        a.pcnt[base + k] = cnt[k];
+    }
+    if (threadIdx.x == 0) a.perr[blockIdx.x] = err_sum;
+}
+
+// LC_POINTS points per workgroup, 1024 / LC_POINTS threads per point share the workgroups' sums (integers: any order gives
+// the same).  stopped_at becomes t in iteration t's own launch, so `< t` means the same to all its workgroups.
+__global__ __launch_bounds__(LC_THREADS) void k_cells_lloyd_move(long long n, int K, LloydCells a, int t, int n_blocks, int max_iters, double tol) {
+    constexpr int P = LC_POINTS, Q = LC_THREADS / P;
+    __shared__ long long red[2][Q][P + 1];
+    __shared__ unsigned red_n[Q][P + 1];
+    __shared__ unsigned long long err;
+    if (a.state->stopped_at < t) return;
+    const int p = threadIdx.x % P, q = threadIdx.x / P, k = blockIdx.x * P + p;
+    if (threadIdx.x == 0) err = 0;
+    long long sx = 0, sy = 0;
+    unsigned c = 0;
+#pragma unroll 4
+    for (int b = q; b < n_blocks; b += Q) {
+        sx += a.psx[(size_t)b * K + k];
+        sy += a.psy[(size_t)b * K + k];
+        c += a.pcnt[(size_t)b * K + k];
+    }
+    red[0][q][p] = sx;
+    red[1][q][p] = sy;
+    red_n[q][p] = c;
+    __syncthreads();
+    if (blockIdx.x == 0 && (int)threadIdx.x < n_blocks) atomicAdd(&err, a.perr[threadIdx.x]);
+    if (q == 0) {
+#pragma unroll 16
+        for (int r = 1; r < Q; ++r) {
+            sx += red[0][r][p];
+            sy += red[1][r][p];
+            c += red_n[r][p];
+        }
+        double px = a.cb64[t & 1][2 * k], py = a.cb64[t & 1][2 * k + 1];
+        if (c > 0) {
+            px = (double)sx / LL_SCALE / (double)c;
+            py = (double)sy / LL_SCALE / (double)c;
+        }
+        const int o = (t + 1) & 1;
+        a.cb64[o][2 * k] = px;
+        a.cb64[o][2 * k + 1] = py;
+        a.cb32[o][2 * k] = (float)px;
+        a.cb32[o][2 * k + 1] = (float)py;
+    }
+    __syncthreads();
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        const double prev = a.state->D, D = (double)err / LL_SCALE / (double)n;
+        a.state->D = D;
+        if ((t > 0 && fabs(prev - D) < tol * prev) || t + 1 >= max_iters) a.state->stopped_at = t;
+    }
+}
+
+// the points of the last assignment
+__global__ __launch_bounds__(LL_THREADS) void k_cells_lloyd_finish(int K, LloydCells a, float *codebook) {
+    const int i = blockIdx.x * LL_THREADS + threadIdx.x;
+    if (i < 2 * K) codebook[i] = a.cb32[a.state->stopped_at & 1][i];
+}
+
+template <int G>
+static hipError_t run_lloyd_cells(const float *samples, long long n, int K, float *codebook, int max_iters, double tol,
+                                  void *workspace, double *mse_out, int *iters_out, hipStream_t stream) {
+    const LloydCells a = lloyd_cells_layout(workspace, K);
+    const size_t lds = (size_t)K * 28 + (size_t)G * G * 8;
+    if (lds > 64 * 1024) {
+        static std::atomic<uint64_t> done{0};                   // the devices on which the larger LDS was asked for
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorNotSupported;
+        if (!(done.load(std::memory_order_acquire) & (1ull << dev))) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_cells_lloyd_assign<G>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            if (e != hipSuccess) {
+                (void)hipGetLastError();
+                return hipErrorNotSupported;
+            }
+            done.fetch_or(1ull << dev, std::memory_order_release);
+        }
+    }
+    const unsigned kb = (unsigned)((2 * K + LL_THREADS - 1) / LL_THREADS);
+    const long long want = (n + 2 * LC_THREADS - 1) / (2 * LC_THREADS);
+    const unsigned blocks = (unsigned)(want < LC_MAX_BLOCKS ? want : LC_MAX_BLOCKS);
+    hipLaunchKernelGGL(k_cells_lloyd_init, dim3(kb), dim3(LL_THREADS), 0, stream, K, a, codebook);
+    LloydState s{0.0, LC_RUNNING};
+    for (int t = 0; s.stopped_at == LC_RUNNING;) {
+        const int until = max_iters - t < LC_AHEAD ? max_iters : t + LC_AHEAD;
+        for (; t < until; ++t) {
+            hipLaunchKernelGGL(k_cells_lloyd_table<G>, dim3((G / 8) * (G / 8)), dim3(CP_THREADS), 0, stream, K, a, t);
+            hipLaunchKernelGGL(k_cells_lloyd_assign<G>, dim3(blocks), dim3(LC_THREADS), lds, stream,
+                               reinterpret_cast<const float2 *>(samples), n, K, a, t);
+            hipLaunchKernelGGL(k_cells_lloyd_move, dim3(K / LC_POINTS), dim3(LC_THREADS), 0, stream, n, K, a, t, (int)blocks, max_iters, tol);
+        }
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        e = hipMemcpyAsync(&s, a.state, sizeof s, hipMemcpyDeviceToHost, stream);
+        if (e != hipSuccess) return e;
+        e = hipStreamSynchronize(stream);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(k_cells_lloyd_finish, dim3(kb), dim3(LL_THREADS), 0, stream, K, a, codebook);
+    if (mse_out) *mse_out = s.D;
+    if (iters_out) *iters_out = s.stopped_at + 1;
+    const hipError_t e = hipStreamSynchronize(stream);
+    return e != hipSuccess ? e : hipGetLastError();
+}
+
+// With a cell table from 64 points on: with fewer the distances to all of them are sooner computed than a table made.
+static bool lloyd_has_cells(int K) { return K >= 64 && K <= 2048; }
+size_t lloyd_least_workspace_bytes(int K) { return (size_t)K * (2 * sizeof(double) + 3 * sizeof(long long)) + 64; }
+size_t lloyd_workspace_bytes(int K) {
+    const size_t least = lloyd_least_workspace_bytes(K);
+    return lloyd_has_cells(K) && lloyd_cells_bytes(K) > least ? lloyd_cells_bytes(K) : least;
+}
 
 static LloydAcc lloyd_layout(void *workspace, int K) {
     LloydAcc a;
@@ -141,7 +381,14 @@ static LloydAcc lloyd_layout(void *workspace, int K) {
 // read back; stop when |D_prev - D| < tol * D_prev (from the second assignment on) or after max_iters assignments;
 // the points are not moved after the last assignment.  Blocks the host on the stream once per iteration.
 hipError_t run_lloyd(const float *samples, long long n, int K, float *codebook, int max_iters, double tol, void *workspace,
-                     double *mse_out, int *iters_out, hipStream_t stream) {
+                     size_t workspace_bytes, double *mse_out, int *iters_out, hipStream_t stream) {
+    if (lloyd_has_cells(K) && workspace_bytes >= lloyd_cells_bytes(K)) {
+        hipError_t e;
+        if (lc_side(K) == 112) e = run_lloyd_cells<112>(samples, n, K, codebook, max_iters, tol, workspace, mse_out, iters_out, stream);
+        else if (lc_side(K) == 96) e = run_lloyd_cells<96>(samples, n, K, codebook, max_iters, tol, workspace, mse_out, iters_out, stream);
+        else e = run_lloyd_cells<64>(samples, n, K, codebook, max_iters, tol, workspace, mse_out, iters_out, stream);
+        if (e != hipErrorNotSupported) return e;                // nothing was launched
+    }
     const LloydAcc acc = lloyd_layout(workspace, K);
     double *report = reinterpret_cast<double *>(reinterpret_cast<char *>(acc.err) + 16);
     const unsigned kb = (unsigned)((K + LL_THREADS - 1) / LL_THREADS);
