@@ -351,8 +351,8 @@ int qamw_decode_batch(const qamw_decode_item *items, int n_items, const float *c
 /* Measurement aid for the decoder of Sec. 3.2: the launch of qamw_decode_batch for these items with every load and
  * store it issues (same addresses, widths, order and launch shape) and none of the arithmetic in between.  The time of
  * this launch is what the memory system allows the decoder's access pattern, i.e. the ceiling its bandwidth figure is
- * to be read against.  W_out of every item is OVERWRITTEN WITH MEANINGLESS VALUES.  Only for shapes the fast decoder
- * takes (bits in {7, 8, 11}, hadamard_block >= 64, d_in a multiple of max(hadamard_block, 16), 16-byte aligned outputs
+ * to be read against.  W_out of every item is OVERWRITTEN WITH MEANINGLESS VALUES.  Only for the paper's three rates and the
+ * fast decoder's shapes (bits in {7, 8, 11}, hadamard_block >= 64, d_in a multiple of max(hadamard_block, 16), 16-byte aligned outputs
  * and side vectors, 4-byte aligned packed rows); anything else -> QAMW_ERR_UNSUPPORTED, nothing launched.
  * Errors otherwise as qamw_decode_batch. */
 int qamw_decode_traffic_probe(const qamw_decode_item *items, int n_items, const float *codebook, int bits,

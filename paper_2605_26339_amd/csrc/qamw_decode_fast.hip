@@ -23,12 +23,17 @@ constexpr int DF_THREADS = QAMW_DF_THREADS;
 constexpr int DF_WAVES = DF_THREADS / WAVE;
 constexpr int SLAB = 1024;
 constexpr int DF_MAX_BATCH = QAMW_DECODE_MAX_BATCH;
-constexpr int DF_MAX_K = 2048;
 // Rows of one unit of work: a wave requests the packed words of all of them at the start, in two halves, and
 // computes and stores one half while the other is still on its way.  Small units mean many waves per launch and a
 // short dependent chain per wave; measured best (7B and 13B shapes): 8 rows at 11 bits (704 packed bytes per row
 // and slab), 16 rows at 7 and 8 bits (448 / 512 bytes).
 constexpr int df_unit_rows(int bits) { return bits >= 10 ? 8 : 16; }
+// A launch that does not fill the chip several times over is as long as one wave's walk through its rows, so its units are
+// shorter: by the number of (row, slab) pairs of the launch, 2 rows below the first line, 4 below the second (bf16 output).
+// Measured, us at 2 / 4 / full units: 7 bits, 256 x 2048 (512 pairs) 4.7 / 6.1 / 14.4; 11 bits, 2048 x 2048 (4096 pairs)
+// 5.6 / 6.0 / 8.0; 1024 x 8192 (8192) 7.4 / 7.2 / 8.5; 9 bits, 4096 x 4096 (16384) 10.7 / 9.7 / 12.5; 7 bits,
+// 8192 x 4096 (32768) 16.2 / 16.2 / 16.9 (two runs of the last differ by as much).
+constexpr int64_t DF_TWO_ROWS_PAIRS = 8192, DF_FOUR_ROWS_PAIRS = 32768;
 
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float floatx2_t __attribute__((ext_vector_type(2)));
@@ -126,12 +131,13 @@ struct DecodeBatch {
 // left out -- what is stored is a meaningless mix of what was loaded.  It measures what the memory system gives this
 // access pattern, i.e. the ceiling of the decoder proper.
 // Register budget: the bf16 kernel with 8-row units fits 80 registers (6 waves per SIMD) without spilling; the
-// 16-row units, the fp32 output and blocks beyond 256 (their swap stages) need more and are left at 4.
-#define QAMW_DF_WAVES_PER_EU ((R > 4 || !OUT_BF16 || B > 256) ? 4 : 6)
+// 16-row units, the fp32 output and blocks beyond 256 (their swap stages) need more and are left at 4; at 12 bits the
+// codebook's 32 KB of LDS allow 5.
+#define QAMW_DF_WAVES_PER_EU ((R > 4 || !OUT_BF16 || B > 256 || BITS > 11) ? 4 : 6)
 template <int BITS, int B, bool OUT_BF16, int R, bool TRAFFIC_ONLY = false>
 __global__ __launch_bounds__(DF_THREADS) __attribute__((amdgpu_waves_per_eu(QAMW_DF_WAVES_PER_EU))) void k_decode_fast(DecodeBatch bt, int n_waves) {
     constexpr int UNIT = 2 * R;                                 // rows of a unit: two halves of R rows
-    __shared__ float2 cb_lds[DF_MAX_K];                         // K <= DF_MAX_K codewords; a static array: its address folds into the gathers' offset field
+    __shared__ float2 cb_lds[BITS > 11 ? 4096 : 2048];          // the codewords; a static array: its address folds into the gathers' offset field
     typedef u32x4_t u32x4_a4_t __attribute__((aligned(4)));     // a 16-byte load that is only 4-byte aligned
     const int lane = threadIdx.x & (WAVE - 1);
     const int wid = threadIdx.x >> 6;
@@ -325,7 +331,9 @@ __global__ __launch_bounds__(DF_THREADS) __attribute__((amdgpu_waves_per_eu(QAMW
 bool fast_decode_supported(const Problem &p) {
     const int unit = p.block > 16 ? p.block : 16;
     if (p.d_in % unit) return false;
-    if (p.bits != 7 && p.bits != 8 && p.bits != 11) return false;
+    // A lane reads 16 bytes from the dword its `bits` bytes begin in, up to 16 - bits bytes into the next row, and no
+    // further: a row has at least 4 bits bytes (64 columns).
+    if (p.bits < 4 || p.bits > 12) return false;
     return p.block >= 64;                                        // 64, 128, 256, 512, 1024
 }
 
@@ -339,9 +347,9 @@ static bool decode_alignment_ok(const DecodeItem &it, bool out_bf16) {
     return (reinterpret_cast<uintptr_t>(it.packed) & 3) == 0;
 }
 
-template <int BITS, int B>
-static hipError_t launch_bb(const DecodeItem *items, int n, const Problem &p, bool out_bf16, bool traffic_only) {
-    constexpr int UNIT = df_unit_rows(BITS), R = UNIT / 2;
+template <int BITS, int B, int UNIT>
+static hipError_t launch_bbu(const DecodeItem *items, int n, const Problem &p, bool out_bf16, bool traffic_only) {
+    constexpr int R = UNIT / 2;
     DecodeBatch bt;
     int64_t units = 0;
     for (int i = 0; i < n; ++i) {
@@ -372,15 +380,23 @@ static hipError_t launch_bb(const DecodeItem *items, int n, const Problem &p, bo
     // stride was measured slower on HBM-bound sizes: its waves move in lockstep through read and write phases.)
     const int64_t n_waves = units;
     const unsigned blocks = (unsigned)((n_waves + DF_WAVES - 1) / DF_WAVES);
-    if (p.K > DF_MAX_K) return hipErrorNotSupported;
-    const size_t lds = 0;
-    if (traffic_only)                                            // the access pattern does not depend on the block size
-        hipLaunchKernelGGL((k_decode_fast<BITS, 64, true, R, true>), dim3(blocks), dim3(DF_THREADS), lds, p.stream, bt, (int)n_waves);
-    else if (out_bf16)
-        hipLaunchKernelGGL((k_decode_fast<BITS, B, true, R>), dim3(blocks), dim3(DF_THREADS), lds, p.stream, bt, (int)n_waves);
-    else
-        hipLaunchKernelGGL((k_decode_fast<BITS, B, false, R>), dim3(blocks), dim3(DF_THREADS), lds, p.stream, bt, (int)n_waves);
+    if (traffic_only) {                                          // the access pattern does not depend on the block size
+        if constexpr (UNIT == df_unit_rows(BITS) && (BITS == 7 || BITS == 8 || BITS == 11))
+            hipLaunchKernelGGL((k_decode_fast<BITS, 64, true, R, true>), dim3(blocks), dim3(DF_THREADS), 0, p.stream, bt, (int)n_waves);
+    } else if (out_bf16)
+        hipLaunchKernelGGL((k_decode_fast<BITS, B, true, R>), dim3(blocks), dim3(DF_THREADS), 0, p.stream, bt, (int)n_waves);
+    else if constexpr (UNIT != 4)
+        hipLaunchKernelGGL((k_decode_fast<BITS, B, false, R>), dim3(blocks), dim3(DF_THREADS), 0, p.stream, bt, (int)n_waves);
     return hipGetLastError();
+}
+
+template <int BITS, int B>
+static hipError_t launch_bb(const DecodeItem *items, int n, const Problem &p, bool out_bf16, bool traffic_only) {
+    int64_t pairs = 0;
+    for (int i = 0; i < n; ++i) pairs += (int64_t)((items[i].d_in + SLAB - 1) / SLAB) * items[i].d_out;
+    if (!traffic_only && pairs < DF_TWO_ROWS_PAIRS) return launch_bbu<BITS, B, 2>(items, n, p, out_bf16, false);
+    if (!traffic_only && out_bf16 && pairs < DF_FOUR_ROWS_PAIRS) return launch_bbu<BITS, B, 4>(items, n, p, true, false);
+    return launch_bbu<BITS, B, df_unit_rows(BITS)>(items, n, p, out_bf16, traffic_only);
 }
 
 template <int BITS>
@@ -405,10 +421,20 @@ hipError_t launch_decode_batch_fast(const DecodeItem *items, int n, const Proble
         q.d_in = items[i].d_in;
         if (!fast_decode_supported(q) || !decode_alignment_ok(items[i], out_bf16)) return hipErrorNotSupported;
     }
-    if (p.bits == 11) return launch_b<11>(items, n, p, out_bf16, traffic_only);
-    if (p.bits == 8) return launch_b<8>(items, n, p, out_bf16, traffic_only);
-    if (p.bits == 7) return launch_b<7>(items, n, p, out_bf16, traffic_only);
-    return hipErrorNotSupported;
+    const bool papers = p.bits == 7 || p.bits == 8 || p.bits == 11;   // the paper's three rates
+    if (!papers && (traffic_only || (reinterpret_cast<uintptr_t>(p.codebook) & 15))) return hipErrorNotSupported;
+    switch (p.bits) {
+        case 4: return launch_b<4>(items, n, p, out_bf16, false);
+        case 5: return launch_b<5>(items, n, p, out_bf16, false);
+        case 6: return launch_b<6>(items, n, p, out_bf16, false);
+        case 7: return launch_b<7>(items, n, p, out_bf16, traffic_only);
+        case 8: return launch_b<8>(items, n, p, out_bf16, traffic_only);
+        case 9: return launch_b<9>(items, n, p, out_bf16, false);
+        case 10: return launch_b<10>(items, n, p, out_bf16, false);
+        case 11: return launch_b<11>(items, n, p, out_bf16, traffic_only);
+        case 12: return launch_b<12>(items, n, p, out_bf16, false);
+        default: return hipErrorNotSupported;
+    }
 }
 
 hipError_t launch_decode_fast(const uint8_t *packed, const float *norms, const Problem &p, void *out, int64_t ldo,
