@@ -12,35 +12,52 @@
 //                     (no arctangent).  The origin has phase bin 0.
 // Index = amplitude index * Np + phase index, packed like the joint code, so the decoder is the
 // joint decoder with the 2^B-entry table {level_ia * (cos, sin)((2 ip + 1) h)}.
+#include <algorithm>
+
 #include "qamw_front.hpp"
 
 namespace qamw {
 
-constexpr int PF_THREADS = 256;
+constexpr int PF_THREADS = 512;
 constexpr int PF_WAVES = PF_THREADS / WAVE;
 constexpr int PSLAB = 1024;
 constexpr int PF_MAX_LEVELS = 64;      // amplitude levels
 constexpr int PF_MAX_BINS = 4096;      // phase bins
+constexpr int PF_MAX_ROWS = 32;        // rows of a workgroup
+constexpr int PF_ITEMS = 48;           // (row, slab) items of a workgroup in a large launch
+constexpr int PF_CUS = 256;
+constexpr int PF_MAX_ITEMS = 64;       // (row, slab) items of a workgroup, unless one row has more
 
+// A workgroup of 8 waves owns `rows` consecutive rows: first the slab sums of all their (row, slab) items, dealt to the
+// waves, then -- after the barrier the table set-up needs anyway -- the items once more, in slab-major order, each wave a
+// consecutive share of them.  So every slab is summed once (a workgroup of four consecutive items summed each row again
+// for each of its items: 11 slabs per row, 3 to 5 times), and a wave loads, divides and combines the scales, signs and
+// gains of a slab once for all rows it has of it.
+//   Bound by vector-ALU issue (about 250 instructions of the front half and 40 per pair of the two searches for a
+// wave's 512 pairs), so the searches of the lane's 8 pairs go side by side: eight table reads in flight per step.
+// 4096 x 11008 bf16 at 5 + 6 bits, 90 MB read: 115 -> 85 us (264 Gpairs/s).
 template <int DTYPE, int B>
 __global__ __launch_bounds__(PF_THREADS) void k_encode_polar(const void *__restrict__ W, int64_t ldw, Problem p,
                                                              const float *__restrict__ levels, int bits_a, int bits_p,
                                                              const float *__restrict__ norms_in, float *__restrict__ norms_out,
-                                                             uint8_t *__restrict__ packed, int n_slabs, int n_items,
-                                                             int n_blocks) {
+                                                             uint8_t *__restrict__ packed, int n_slabs, int rows) {
     extern __shared__ __align__(16) float lds_raw[];
     const int Na = 1 << bits_a, Np = 1 << bits_p;
     float *thr2 = lds_raw;                                      // Na: thr2[i] = (midpoint of levels i-1, i)^2, i >= 1
     float2 *bdir = reinterpret_cast<float2 *>(lds_raw + (Na < 2 ? 2 : Na));   // Np boundary directions (cos, sin)(2 k h), 8-byte aligned
-    __shared__ double norm_part[2 * FUSED_NORM_MAX_SLABS];
+    __shared__ double norm_part[PF_MAX_ITEMS];                 // [row][slab]
+    __shared__ float norm_row[PF_MAX_ROWS];
     const int lane = threadIdx.x & (WAVE - 1);
-    const int wid = threadIdx.x >> 6;
-    // norms_in == NULL: the workgroup computes the norms of the rows its items touch (and writes them out); the
-    // barrier after the table set-up below also publishes the slab sums.
-    const bool fused = norms_in == nullptr;
-    const int item0 = (fused ? fused_norm_block(blockIdx.x, n_blocks) : (int)blockIdx.x) * PF_WAVES;
-    if (fused && item0 < n_items) block_slab_sums<DTYPE, PF_WAVES>(norm_part, W, ldw, p, item0, n_items, n_slabs, lane, wid);
-
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int row0 = (int)blockIdx.x * rows, n_rows = min(rows, p.d_out - row0), n_items = n_rows * n_slabs;
+    // norms_in == NULL: the workgroup computes its rows' norms (and writes them out)
+    if (norms_in == nullptr) {
+        for (int t = wid; t < n_items; t += PF_WAVES) {
+            const int dr = t / n_slabs, slab = t - dr * n_slabs;
+            const double s2 = slab_sum_of_squares<DTYPE>(W, (int64_t)(row0 + dr) * ldw, slab, p, lane);
+            if (lane == 0) norm_part[t] = s2;
+        }
+    }
     for (int i = threadIdx.x; i < Na; i += PF_THREADS) {
         const float t = (i > 0) ? 0.5f * (levels[i - 1] + levels[i]) : 0.0f;
         thr2[i] = t * t;
@@ -51,59 +68,86 @@ __global__ __launch_bounds__(PF_THREADS) void k_encode_polar(const void *__restr
         bdir[k] = make_float2(cs, sn);
     }
     __syncthreads();
-
-    const int item = __builtin_amdgcn_readfirstlane(item0 + wid);
-    if (item >= n_items) return;
-    const int row = item / n_slabs, slab = item - row * n_slabs;
-    float rnorm;
-    if (fused) {
-        rnorm = row_norm_from_slab_sums(norm_part, row, item0, n_slabs);
-        if (slab == 0 && lane == 0) norms_out[row] = rnorm;
-    } else {
-        rnorm = norms_in[row];
+    if ((int)threadIdx.x < n_rows) {
+        const int dr = threadIdx.x;
+        float r;
+        if (norms_in == nullptr) {
+            r = row_norm_from_slab_sums(norm_part, dr, 0, n_slabs);
+            norms_out[row0 + dr] = r;
+        } else {
+            r = norms_in[row0 + dr];
+        }
+        norm_row[dr] = r;
     }
+    __syncthreads();
+
     const LaneSigns<B> ls(lane);
     const int pos = slab_pos(lane);
-    const int col0 = slab * PSLAB + 16 * pos;
-    const bool active = col0 < p.d_in;
-    const int c = active ? col0 : 0;
+    const float unit = ls.parity * p.inv_sqrt_block;
+    const int per = (n_items + PF_WAVES - 1) / PF_WAVES;
+    const int first = wid * per, last = min(n_items, first + per);
+    int c = 0, cur_slab = -1;
+    bool active = false;
+    float sc[16], g[8];
+    for (int item = first; item < last; ++item) {
+        const int slab = item / n_rows, row = row0 + item - slab * n_rows;
+        if (slab != cur_slab) {
+            cur_slab = slab;
+            const int col0 = slab * PSLAB + 16 * pos;
+            active = col0 < p.d_in;
+            c = active ? col0 : 0;
+            load_signed_scales(sc, p, c);
+            load_pair_gains(g, p, c);
+        }
 
-    // ---------------- front half: x_k = (F S (W D_s / r))_pair k / sigma_k, in registers
-    float x[16];
-    rotated_unit_row<DTYPE, B>(x, W, (int64_t)row * ldw, c, rnorm, p, ls);
-    {
-        float g[8];
-        load_pair_gains(g, p, c);
+        // ---------------- front half: x_k = (F S (W D_s / r))_pair k / sigma_k, in registers
+        RawRow<DTYPE> raw;
+        load_raw_row<DTYPE>(raw, W, (int64_t)row * ldw, c);
+        float x[16];
+        widen_raw_row<DTYPE>(x, raw);
 #pragma unroll
-        for (int e = 0; e < 16; ++e) x[e] = x[e] * g[e >> 1];
-    }
+        for (int e = 0; e < 16; ++e) x[e] = x[e] * sc[e];       // sign included: a sign commutes with every rounding below
+        divide_by_norm(x, norm_row[row - row0]);
+        fwht_wave<B>(x, ls);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) x[e] = (x[e] * unit) * g[e >> 1];
 
-    // ---------------- amplitude level and phase bin of the lane's 8 pairs
-    unsigned idx[8];
+        // ---------------- amplitude level and phase bin of the lane's 8 pairs
+        float a2[8];
+        int ia[8], ip[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const float x0 = x[2 * k], x1 = x[2 * k + 1];
-        const float a2 = __builtin_fmaf(x1, x1, x0 * x0);
-        int ia = 0;
+        for (int k = 0; k < 8; ++k) {
+            const float x0 = x[2 * k], x1 = x[2 * k + 1];
+            a2[k] = __builtin_fmaf(x1, x1, x0 * x0);
+            ia[k] = 0;
+            const bool upper = (x1 < 0.0f) || (x1 == 0.0f && x0 < 0.0f);   // angle in [pi, 2 pi)
+            ip[k] = upper ? (Np >> 1) : 0;
+        }
+#pragma unroll 1
         for (int step = Na >> 1; step; step >>= 1) {
-            const int cand = ia + step;
-            ia = (a2 > thr2[cand]) ? cand : ia;                 // on the threshold: the lower level
+            float t[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) t[k] = thr2[ia[k] + step];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) ia[k] = (a2[k] > t[k]) ? ia[k] + step : ia[k];   // on the threshold: the lower level
         }
-        const bool upper = (x1 < 0.0f) || (x1 == 0.0f && x0 < 0.0f);   // angle in [pi, 2 pi)
-        int ip = upper ? (Np >> 1) : 0;
+#pragma unroll 1
         for (int step = Np >> 2; step; step >>= 1) {
-            const int cand = ip + step;
-            const float2 b = bdir[cand];
-            const float cr = __builtin_fmaf(b.x, x1, -(b.y * x0));     // sin(angle - 2 cand h) * |x|
-            ip = (cr >= 0.0f) ? cand : ip;
+            float2 b[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) b[k] = bdir[ip[k] + step];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const float cr = __builtin_fmaf(b[k].x, x[2 * k + 1], -(b[k].y * x[2 * k]));   // sin(angle - 2 cand h) * |x|
+                ip[k] = (cr >= 0.0f) ? ip[k] + step : ip[k];
+            }
         }
-        if (a2 == 0.0f) ip = 0;
-        idx[k] = (unsigned)(ia * Np + ip);
-    }
+        unsigned idx[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) idx[k] = (unsigned)((ia[k] << bits_p) + (a2[k] == 0.0f ? 0 : ip[k]));
 
-    // ---------------- pack: the lane's 8 fields are exactly `bits` bytes, byte aligned in the row
-    if (active) {
-        store_packed_fields(packed, row, c, col0, idx, p);
+        // ---------------- pack: the lane's 8 fields are exactly `bits` bytes, byte aligned in the row
+        if (active) store_fields(packed + (int64_t)row * p.row_bytes, p.row_bytes, p.d_in, c, idx, p.bits);
     }
 }
 
@@ -118,14 +162,15 @@ template <int DTYPE, int B>
 static hipError_t launch_pdb(const void *W, int64_t ldw, const Problem &p, const float *levels, int bits_a, int bits_p,
                              float *norms, bool norms_ready, uint8_t *packed) {
     const int n_slabs = (p.d_in + PSLAB - 1) / PSLAB;
-    const int64_t n_items = (int64_t)p.d_out * n_slabs;
-    if (n_items > 0x7fffffff) return hipErrorNotSupported;
-    if (!norms_ready && n_slabs > FUSED_NORM_MAX_SLABS) return hipErrorNotSupported;
-    const int n_blocks = (int)((n_items + PF_WAVES - 1) / PF_WAVES);
-    const unsigned blocks = (unsigned)(norms_ready ? n_blocks : fused_norm_grid(n_blocks));
+    if (!norms_ready && n_slabs > PF_MAX_ITEMS) return hipErrorNotSupported;   // a row's slab sums have to fit the workgroup's list
+    // About PF_ITEMS items per workgroup, so that a wave meets a slab several times; fewer while the launch does not give
+    // every CU two workgroups (their memory and arithmetic phases alternate), down to one per wave.
+    int rows = std::max(1, std::min(PF_MAX_ROWS, PF_ITEMS / n_slabs));
+    while (rows > 1 && (p.d_out + rows - 1) / rows < 2 * PF_CUS && (rows + 1) / 2 * n_slabs >= PF_WAVES) rows = (rows + 1) / 2;
+    const unsigned blocks = (unsigned)((p.d_out + rows - 1) / rows);
     const size_t lds = ((size_t)(bits_a ? (1 << bits_a) : 2) + 2 * (size_t)(1 << bits_p)) * sizeof(float);
     hipLaunchKernelGGL((k_encode_polar<DTYPE, B>), dim3(blocks), dim3(PF_THREADS), lds, p.stream, W, ldw, p, levels, bits_a,
-                       bits_p, norms_ready ? norms : nullptr, norms, packed, n_slabs, (int)n_items, n_blocks);
+                       bits_p, norms_ready ? norms : nullptr, norms, packed, n_slabs, rows);
     return hipGetLastError();
 }
 

@@ -293,6 +293,29 @@ __device__ __forceinline__ void load_pair_gains(float (&g)[8], const Problem &p,
     }
 }
 
+// The lane's 16 channel scales with the sign mask in the sign bit: what a kernel that stays on one slab of a matrix keeps
+// instead of both.  Scaling by it is exact as regards the sign: rounding commutes with negation, and a quotient, a sum of
+// squares or a smallest magnitude does not see it.
+__device__ __forceinline__ void load_signed_scales(float (&sc)[16], const Problem &p, int c) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) sc[e] = 1.0f;
+    if (p.chan_scale) {
+        const float4 *s4 = reinterpret_cast<const float4 *>(p.chan_scale + c);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const float4 v = s4[t];
+            sc[4 * t] = v.x; sc[4 * t + 1] = v.y; sc[4 * t + 2] = v.z; sc[4 * t + 3] = v.w;
+        }
+    }
+    if (p.signs) {
+        const uint4 sg = *reinterpret_cast<const uint4 *>(p.signs + c);
+        const uint32_t wds[4] = {sg.x, sg.y, sg.z, sg.w};
+#pragma unroll
+        for (int e = 0; e < 16; ++e)                            // int8 -1: sign bit of the byte
+            sc[e] = __uint_as_float(__float_as_uint(sc[e]) ^ (((wds[e >> 2] >> (8 * (e & 3) + 7)) & 1u) << 31));
+    }
+}
+
 // Writes the lane's 8 indices into the row's bit stream: 8 fields of p.bits bits are exactly p.bits bytes, byte aligned
 // at byte (c / 16) * bits of the row.  The lane that holds the row's last 16 columns (col0 + 16 == d_in) zeroes the
 // padding bytes of the row.
