@@ -531,7 +531,7 @@ void k_qgemm(GemvBatch bt) {
     extern __shared__ __align__(16) uint32_t gm_lds[];
     uint32_t *cbh = gm_lds;                                     // K codewords as (bf16 c0) | (bf16 c1) << 16
     // after the codebook: per wave a 32-row tile of packed bytes (pitch PITCH) during the loop, and, after it, the
-    // partial tiles of waves 1..7: [7 waves][MT][16][64 lanes]
+    // waves' partial tiles: [8 waves][32 activation rows][32 + 1 weight rows]
     float *red = reinterpret_cast<float *>(gm_lds + bt.K);
     constexpr int PITCH = 16 * BITS + 8;                        // bytes; an odd number of 8-byte words: the lanes' 8-byte reads spread over all banks
     const int lane = threadIdx.x & (WAVE - 1);
@@ -654,29 +654,31 @@ void k_qgemm(GemvBatch bt) {
         }
     }
 
-    // the eight waves' tiles, summed in wave order by wave 0 (the buffer overlies the packed tiles: everybody is done with those)
-    __syncthreads();
-    if (wid > 0) {
-        float *dst = red + (size_t)(wid - 1) * (MT * 16 * WAVE);
+    // The eight waves' tiles, summed in wave order.  All waves leave theirs in LDS (over the packed tiles: everybody is done
+    // with those), 32 activation rows at a time, then each takes an eighth of the sums, lanes along the weight rows: 128
+    // consecutive bytes of Y per half-wave.  Wave 0 alone with lanes along the activation rows (112 reads and 16 stores of
+    // 64 scattered words) took longer: the four calls of a 7B
+    // layer at 32 activation rows 104 us, so 94.
+    constexpr int RED_PITCH = GM_ROWS + 1;                      // floats of one activation row's 32 sums
+    constexpr int RED_WAVE = 32 * RED_PITCH;
+    const int row = row0 + r;
+    const bool row_ok = row_used && row <= last_row;
+    const float norm = M.norms[min(row, last_row)];
 #pragma unroll
-        for (int t = 0; t < MT; ++t)
+    for (int t = 0; t < MT; ++t) {
+        __syncthreads();
+        float *dst = red + wid * RED_WAVE + r * RED_PITCH + 4 * h;     // the accumulator's column is the activation row
 #pragma unroll
-            for (int i = 0; i < 16; ++i) dst[(t * 16 + i) * WAVE + lane] = acc[t][i];
-    }
-    __syncthreads();
-    if (wid == 0) {
+        for (int i = 0; i < 16; ++i) dst[8 * (i >> 2) + (i & 3)] = acc[t][i];   // accumulator i of half h: the tile's row
+        __syncthreads();
 #pragma unroll
-        for (int t = 0; t < MT; ++t) {
-            const int tok = 32 * t + r;                         // the accumulator's column is the activation row
+        for (int q = 0; q < 2; ++q) {
+            const int col = 16 * q + 2 * wid + h, tok = 32 * t + col;
+            const float *src = red + col * RED_PITCH + r;
+            float s = src[0];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                float s = acc[t][i];
-#pragma unroll
-                for (int w2 = 0; w2 < GM_WAVES - 1; ++w2) s += red[(size_t)w2 * (MT * 16 * WAVE) + (t * 16 + i) * WAVE + lane];
-                const int tile_row = 8 * (i >> 2) + 4 * h + (i & 3);    // accumulator i of half h
-                const int row = row0 + tile_row;
-                if (tok < m && tile_row < rows && row <= last_row) M.Y[(int64_t)tok * M.ldy + row] = M.norms[row] * s;
-            }
+            for (int w2 = 1; w2 < GM_WAVES; ++w2) s += src[w2 * RED_WAVE];
+            if (row_ok && tok < m) M.Y[(int64_t)tok * M.ldy + row] = norm * s;
         }
     }
 }
@@ -1008,7 +1010,7 @@ template <int BITS>
 static hipError_t launch_qgemm(const GemvBatch &bt, hipStream_t stream) {
     const unsigned blocks = (unsigned)bt.grp_begin[bt.n];
     const int mt = (bt.m + 31) / 32;
-    const size_t red_bytes = (size_t)(GM_WAVES - 1) * mt * 16 * WAVE * sizeof(float);
+    const size_t red_bytes = (size_t)GM_WAVES * 32 * (GM_ROWS + 1) * sizeof(float);
     const size_t tile_bytes = (size_t)GM_WAVES * GM_ROWS * (16 * BITS + 8);
     const size_t lds = (size_t)bt.K * sizeof(uint32_t) + (red_bytes > tile_bytes ? red_bytes : tile_bytes);
     if (mt == 1) hipLaunchKernelGGL((k_qgemm<BITS, 1>), dim3(blocks), dim3(GM_THREADS), lds, stream, bt);
