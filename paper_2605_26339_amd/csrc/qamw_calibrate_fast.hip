@@ -8,7 +8,9 @@ namespace qamw {
 constexpr int CF_THREADS = 256;
 constexpr int CF_WAVES = CF_THREADS / WAVE;
 constexpr int CSLAB = 1024;
-constexpr int CAL_ROWS = 8;     // calibration rows a wave accumulates before writing a partial sum
+constexpr int CAL_ROWS = 8;     // calibration rows of a workgroup, one partial sum per pair
+constexpr int CAL_THREADS = 512;
+constexpr int CAL_WAVES = CAL_THREADS / WAVE;
 
 // ---------------------------------------------------------------------------------------------
 // Row norms, one wave per row.
@@ -39,9 +41,13 @@ bool launch_row_norms_fast(const void *W, int dtype, int64_t ldw, int n_rows, co
 
 // ---------------------------------------------------------------------------------------------
 // Calibration of up to CAL_MAX_BATCH matrices in one pair of launches.
-// Step 1: one workgroup per chunk of CAL_ROWS consecutive rows of one matrix.  It first computes the norms of its
-// rows (slab sums in LDS, as the encoders do: the head rows are fetched from memory once), then wave w takes the slabs
-// w, w + CF_WAVES, ... and sums |z_k| over the chunk's rows, row by row, in fp64, and writes one partial sum per pair.
+// Step 1: one workgroup of 8 waves per chunk of CAL_ROWS consecutive rows of one matrix.  It first computes the norms of
+// its rows (slab sums in LDS, as the encoders do: the head rows are fetched from memory once), then wave w takes the slabs
+// w, w + CAL_WAVES, ... and sums |z_k| over the chunk's rows, row by row, in fp64, and writes one partial sum per pair.  A
+// small matrix is as long as one wave's chain, so rows of at most four slabs are split among the waves: 256 x 2048, the
+// only launch of 32 workgroups, 20.4 -> 12.2 us; 1024 head rows of 4096 columns 24.3 -> 16.1.  A layer's 1024 head rows of
+// seven matrices are bound by vector-ALU issue, the fp64 square roots above all: 87.8 -> 69.1 us with sqrt_magnitude(), the
+// scales and signs once per slab and the next row on its way.
 // Step 2: per pair, the partial sums added in chunk order, then Eq. 1.
 // ---------------------------------------------------------------------------------------------
 struct CalMat {
@@ -62,9 +68,25 @@ struct CalBatch {
     float inv_sqrt_block;
 };
 
+// sqrt(a) of a >= 0 that is exact to a few fp64 roundings: the fp32 reciprocal square root (2^-23) and two Newton steps
+// (2^-46, then below 2^-53).  Outside the range of normal fp32, zero included, the library's square root; a wave takes that
+// for all its lanes.  8 fp64 operations instead of the 18 of sqrt(), whose scaling and special cases are not met here.
+__device__ __forceinline__ double sqrt_magnitude(double a) {
+    const float af = (float)a;
+    if (__ballot(!(af >= 1.0e-36f && af <= 1.0e36f)) != 0ull) return sqrt(a);
+    const float rf = __builtin_amdgcn_rsqf(af);
+    const double r = (double)rf, half = (double)(0.5f * rf);
+    double s = a * r;
+    s = __builtin_fma(__builtin_fma(-s, s, a), half, s);
+    return __builtin_fma(__builtin_fma(-s, s, a), half, s);
+}
+
+// Rows of few slabs: S waves share a slab's 8 rows, so that all 8 waves have one, and add their sums through LDS.
 template <int DTYPE, int B>
-__global__ __launch_bounds__(CF_THREADS) void k_calibrate_partial(CalBatch bt) {
+__global__ __launch_bounds__(CAL_THREADS) void k_calibrate_partial(CalBatch bt) {
     __shared__ double norm_part[CAL_ROWS * FUSED_NORM_MAX_SLABS];
+    __shared__ float norm_row[CAL_ROWS];
+    __shared__ double shared_acc[CAL_WAVES][8][WAVE];
     const int lane = threadIdx.x & (WAVE - 1);
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int mi = 0;
@@ -74,7 +96,6 @@ __global__ __launch_bounds__(CF_THREADS) void k_calibrate_partial(CalBatch bt) {
     p.d_in = M.d_in;
     p.chan_scale = M.chan_scale;
     p.signs = M.signs;
-    p.inv_sqrt_block = bt.inv_sqrt_block;
     const void *__restrict__ W = M.W;
     const int64_t ldw = M.ldw;
     const int n_rows = M.n_rows, n_slabs = M.n_slabs;
@@ -82,41 +103,65 @@ __global__ __launch_bounds__(CF_THREADS) void k_calibrate_partial(CalBatch bt) {
     const int chunk = (int)blockIdx.x - bt.chunk_begin[mi];
     const int row0 = chunk * CAL_ROWS, row1 = min(n_rows, row0 + CAL_ROWS);
     const int tasks = (row1 - row0) * n_slabs;
-    for (int t = wid; t < tasks; t += CF_WAVES) {
+    for (int t = wid; t < tasks; t += CAL_WAVES) {
         const int dr = t / n_slabs, slab = t - dr * n_slabs;
         const double s2 = slab_sum_of_squares<DTYPE>(W, (int64_t)(row0 + dr) * ldw, slab, p, lane);
         if (lane == 0) norm_part[t] = s2;
     }
     __syncthreads();
-    float rn[CAL_ROWS];
-#pragma unroll
-    for (int dr = 0; dr < CAL_ROWS; ++dr) {
-        double s2 = 0.0;
-        if (row0 + dr < row1)
-            for (int s = 0; s < n_slabs; ++s) s2 += norm_part[dr * n_slabs + s];
-        rn[dr] = (float)sqrt(s2);
-    }
+    if ((int)threadIdx.x < row1 - row0) norm_row[threadIdx.x] = row_norm_from_slab_sums(norm_part, threadIdx.x, 0, n_slabs);
+    __syncthreads();
+    const int shift = n_slabs > 4 ? 0 : n_slabs > 2 ? 1 : n_slabs > 1 ? 2 : 3, S = 1 << shift;   // S n_slabs <= 8 units, or S == 1
+    const int rows_per = CAL_ROWS >> shift;
     const LaneSigns<B> ls(lane);
-    for (int slab = wid; slab < n_slabs; slab += CF_WAVES) {
+    const float unit_factor = ls.parity * bt.inv_sqrt_block;
+    double acc[8];
+    for (int unit = wid; unit < n_slabs << shift; unit += CAL_WAVES) {
+        const int slab = unit >> shift, from = row0 + (unit & (S - 1)) * rows_per, to = min(row1, from + rows_per);
         const int col0 = slab * CSLAB + 16 * slab_pos(lane);
         const bool active = col0 < p.d_in;
         const int c = active ? col0 : 0;
-        double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        float sc[16];
+        load_signed_scales(sc, p, c);
 #pragma unroll
-        for (int dr = 0; dr < CAL_ROWS; ++dr) {
-            if (row0 + dr < row1) {
-                float y[16];
-                rotated_unit_row<DTYPE, B>(y, W, (int64_t)(row0 + dr) * ldw, c, rn[dr], p, ls);
+        for (int k = 0; k < 8; ++k) acc[k] = 0.0;
+        RawRow<DTYPE> next;
+        if (from < to) load_raw_row<DTYPE>(next, W, (int64_t)from * ldw, c);
+#pragma unroll 1
+        for (int row = from; row < to; ++row) {
+            const RawRow<DTYPE> raw = next;
+            if (row + 1 < to) load_raw_row<DTYPE>(next, W, (int64_t)(row + 1) * ldw, c);
+            float y[16];
+            widen_raw_row<DTYPE>(y, raw);
 #pragma unroll
-                for (int k = 0; k < 8; ++k)
-                    acc[k] += sqrt((double)y[2 * k] * (double)y[2 * k] + (double)y[2 * k + 1] * (double)y[2 * k + 1]);
-            }
+            for (int e = 0; e < 16; ++e) y[e] = y[e] * sc[e];
+            divide_by_norm(y, norm_row[row - row0]);
+            fwht_wave<B>(y, ls);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) y[e] = y[e] * unit_factor;
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                acc[k] += sqrt_magnitude((double)y[2 * k] * (double)y[2 * k] + (double)y[2 * k + 1] * (double)y[2 * k + 1]);
         }
-        if (active) {
+        if (S == 1 && active) {
             double *dst = partial + (int64_t)chunk * (p.d_in >> 1) + (c >> 1);
 #pragma unroll
             for (int k = 0; k < 8; ++k) dst[k] = acc[k];
         }
+    }
+    if (S == 1) return;                                         // the same for the whole workgroup
+    if (wid < n_slabs << shift) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) shared_acc[wid][k][lane] = acc[k];
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < n_slabs * 8 * WAVE; i += CAL_THREADS) {
+        const int slab = i / (8 * WAVE), l = (i & (8 * WAVE - 1)) >> 3, k = i & 7;   // consecutive threads: consecutive pairs of a lane
+        const int col0 = slab * CSLAB + 16 * slab_pos(l);
+        if (col0 >= p.d_in) continue;
+        double s = shared_acc[slab << shift][k][l];
+        for (int q = 1; q < S; ++q) s += shared_acc[(slab << shift) + q][k][l];
+        partial[(int64_t)chunk * (p.d_in >> 1) + (col0 >> 1) + k] = s;
     }
 }
 
@@ -151,7 +196,7 @@ size_t calibrate_partial_bytes(int d_in, int n_rows) {
 }
 
 template <int DTYPE, int B> static hipError_t launch_cal(const CalBatch &bt, hipStream_t stream) {
-    hipLaunchKernelGGL((k_calibrate_partial<DTYPE, B>), dim3(bt.chunk_begin[bt.n]), dim3(CF_THREADS), 0, stream, bt);
+    hipLaunchKernelGGL((k_calibrate_partial<DTYPE, B>), dim3(bt.chunk_begin[bt.n]), dim3(CAL_THREADS), 0, stream, bt);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_calibrate_finish, dim3(bt.fin_begin[bt.n]), dim3(CF_THREADS), 0, stream, bt);
