@@ -18,6 +18,11 @@
 
 namespace qamw {
 
+// Launches at 2^11 points of at most this many (row, slab) items read the records from memory.  In us a call, from LDS / from
+// memory (bf16): 256 x 2048, 512 items, 27.0 / 23.6; 1500 x 2048, 3000 items, 28.1 / 26.4; 2048 x 2048, 4096 items, 30.8 / 30.0;
+// 1024 x 8192, 8192 items, 36.0 / 37.5; 4096 x 4096 48.5 / 52.1.  The smaller tables (32 to 72 KB) are staged in less than the
+// second L2 round trip takes: 1024 x 2048 at 10 bits 20.3 / 19.6, at 7 bits 18.7 / 25.1.
+constexpr int CELLS_DIRECT_MAX_ITEMS = 3072;
 constexpr int CELLS_MIN_ITEMS = 1024;                          // (row, slab) items of a launch from which small codebooks use the table
 
 struct CellsMat {
@@ -62,24 +67,30 @@ __global__ __launch_bounds__(CP_THREADS) void k_cells_prepare(CellsBatch bt) {
 }
 
 // ------------------------------------------------------------------------------------------------ the encoder
+constexpr int CELLS_DIRECT_THREADS = 256;
 constexpr int cells_threads(int G) { return G == 128 ? 1024 : 512; }
 constexpr int cells_codewords(int G) { return G == 128 ? 2048 : G == 96 ? 1024 : 512; }
 constexpr size_t cells_lds_bytes(int G) { return (size_t)cells_codewords(G) * 8 + (size_t)G * G * 8; }
 
-template <int DTYPE, int B, int G>
-__global__ __launch_bounds__(cells_threads(G)) void k_encode_cells(CellsBatch bt) {
-    constexpr int THREADS = cells_threads(G), WAVES = THREADS / WAVE;
+// STAGED: the table in LDS beside the codebook.  Otherwise its records are read from memory (L2): in a launch of few items a
+// workgroup would stage 128 KB for an item or two per wave, and small workgroups reach more CUs.
+template <int DTYPE, int B, int G, bool STAGED>
+__global__ __launch_bounds__(STAGED ? cells_threads(G) : CELLS_DIRECT_THREADS) void k_encode_cells(CellsBatch bt) {
+    constexpr int THREADS = STAGED ? cells_threads(G) : CELLS_DIRECT_THREADS, WAVES = THREADS / WAVE;
     extern __shared__ __align__(16) float2 cells_lds[];        // codebook, then the table
     const float2 *cb = cells_lds;
-    char *table = reinterpret_cast<char *>(cells_lds + cells_codewords(G));
+    const char *table = STAGED ? reinterpret_cast<const char *>(cells_lds + cells_codewords(G)) : reinterpret_cast<const char *>(bt.table);
     const int K = bt.K, bits = bt.bits;
     {
         const float2 *cbk = reinterpret_cast<const float2 *>(bt.codebook);
-        for (int i = threadIdx.x; i < K; i += THREADS) cells_lds[i] = cbk[i];
-        const uint4 *src = reinterpret_cast<const uint4 *>(bt.table);
-        uint4 *dst = reinterpret_cast<uint4 *>(table);
 #pragma unroll 8
-        for (int i = threadIdx.x; i < G * G / 2; i += THREADS) dst[i] = src[i];
+        for (int i = threadIdx.x; i < K; i += THREADS) cells_lds[i] = cbk[i];
+        if (STAGED) {
+            const uint4 *src = reinterpret_cast<const uint4 *>(bt.table);
+            uint4 *dst = reinterpret_cast<uint4 *>(cells_lds + cells_codewords(G));
+#pragma unroll 8
+            for (int i = threadIdx.x; i < G * G / 2; i += THREADS) dst[i] = src[i];
+        }
     }
     __syncthreads();
 
@@ -116,27 +127,13 @@ __global__ __launch_bounds__(cells_threads(G)) void k_encode_cells(CellsBatch bt
 
         // the slab's constants: scale x sign per column, gain per pair
         float sc[16], g[8];
-#pragma unroll
-        for (int e = 0; e < 16; ++e) sc[e] = 1.0f;
-        if (M.chan_scale) {
-            const float4 *s4 = reinterpret_cast<const float4 *>(M.chan_scale + c);
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const float4 v = s4[t];
-                sc[4 * t] = v.x; sc[4 * t + 1] = v.y; sc[4 * t + 2] = v.z; sc[4 * t + 3] = v.w;
-            }
-        }
-        if (M.signs) {
-            const uint4 sg = *reinterpret_cast<const uint4 *>(M.signs + c);
-            const uint32_t wds[4] = {sg.x, sg.y, sg.z, sg.w};
-#pragma unroll
-            for (int e = 0; e < 16; ++e)                        // int8 -1: sign bit of the byte
-                sc[e] = __uint_as_float(__float_as_uint(sc[e]) ^ (((wds[e >> 2] >> (8 * (e & 3) + 7)) & 1u) << 31));
-        }
         {
             Problem p;
+            p.chan_scale = M.chan_scale;
+            p.signs = M.signs;
             p.pair_sigma = M.pair_sigma;
             p.g_default = M.g_default;
+            load_signed_scales(sc, p, c);
             load_pair_gains(g, p, c);
         }
 
@@ -201,7 +198,7 @@ template <int DTYPE, int B, int G> static bool cells_allow_large_lds(int dev) {
     static std::atomic<uint64_t> done{0};
     if (dev < 0 || dev >= 64) return false;
     if (done.load(std::memory_order_acquire) & (1ull << dev)) return true;
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_encode_cells<DTYPE, B, G>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_encode_cells<DTYPE, B, G, true>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)cells_lds_bytes(G));
     if (e != hipSuccess) {
         (void)hipGetLastError();
@@ -219,7 +216,6 @@ static hipError_t launch_cells_dbg(CellsBatch &bt, hipStream_t stream) {
         (void)hipGetLastError();
         return hipErrorNotSupported;
     }
-    if (cells_lds_bytes(G) > 64 * 1024 && !cells_allow_large_lds<DTYPE, B, G>(dev)) return hipErrorNotSupported;
     constexpr int WAVES = cells_threads(G) / WAVE;
     int64_t items = 0;
     int norm_blocks = 0, most_slabs = 1;
@@ -231,15 +227,28 @@ static hipError_t launch_cells_dbg(CellsBatch &bt, hipStream_t stream) {
         if (M.n_slabs > most_slabs) most_slabs = M.n_slabs;
     }
     for (int i = bt.n; i <= QAMW_ENCODE_MAX_BATCH; ++i) bt.norm_begin[i] = norm_blocks;
+    const unsigned prep = (unsigned)((G / 8) * (G / 8) + norm_blocks);
+    if constexpr (G == 128) {
+        if (items <= CELLS_DIRECT_MAX_ITEMS) {
+            constexpr int DIRECT_WAVES = CELLS_DIRECT_THREADS / WAVE;
+            const unsigned direct = (unsigned)((items + most_slabs + DIRECT_WAVES - 1) / DIRECT_WAVES);   // an item per wave, whole rows
+            hipLaunchKernelGGL((k_cells_prepare<DTYPE, G>), dim3(prep), dim3(CP_THREADS), 0, stream, bt);
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+            hipLaunchKernelGGL((k_encode_cells<DTYPE, B, G, false>), dim3(direct), dim3(CELLS_DIRECT_THREADS),
+                               (size_t)cells_codewords(G) * sizeof(float2), stream, bt);
+            return hipGetLastError();
+        }
+    }
+    if (cells_lds_bytes(G) > 64 * 1024 && !cells_allow_large_lds<DTYPE, B, G>(dev)) return hipErrorNotSupported;
     const int per_cu = G == 128 ? 1 : 2;          // workgroups that fit a CU's LDS and registers
     int64_t blocks = (items + WAVES - 1) / WAVES;
     if (blocks > (int64_t)cus * per_cu) blocks = (int64_t)cus * per_cu;
     if (blocks * WAVES < most_slabs) return hipErrorNotSupported;   // every wave keeps to one slab: at least a row's worth of waves
-    const unsigned prep = (unsigned)((G / 8) * (G / 8) + norm_blocks);
     hipLaunchKernelGGL((k_cells_prepare<DTYPE, G>), dim3(prep), dim3(CP_THREADS), 0, stream, bt);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_encode_cells<DTYPE, B, G>), dim3((unsigned)blocks), dim3(cells_threads(G)), cells_lds_bytes(G), stream, bt);
+    hipLaunchKernelGGL((k_encode_cells<DTYPE, B, G, true>), dim3((unsigned)blocks), dim3(cells_threads(G)), cells_lds_bytes(G), stream, bt);
     return hipGetLastError();
 }
 
