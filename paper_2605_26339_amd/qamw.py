@@ -23,7 +23,7 @@ EXPORTS = [
     "qamw_matmul_workspace_bytes", "qamw_matmul", "qamw_matmul_batch", "qamw_encode_stats",
     "qamw_normalised_pairs", "qamw_lloyd_workspace_bytes", "qamw_lloyd_device",
     "qamw_search_grid_size", "qamw_search_grid_build", "qamw_encode_pruned", "qamw_calibrate_sigma_static", "qamw_decode_traffic_probe", "qamw_encode_batch", "qamw_calibrate_sigma_batch",
-    "qamw_encode_workspace_bytes", "qamw_encode_ws", "qamw_encode_batch_ws",
+    "qamw_encode_workspace_bytes", "qamw_encode_ws", "qamw_encode_batch_ws", "qamw_encode_pruned_ws",
 ]
 
 
@@ -112,6 +112,7 @@ def lib() -> C.CDLL:
         L.qamw_search_grid_size.argtypes = [i32, C.POINTER(i32), C.POINTER(C.c_size_t)]
         L.qamw_search_grid_build.argtypes = [vp, i32, vp, C.c_size_t, C.POINTER(i32), C.POINTER(u64)]
         L.qamw_encode_pruned.argtypes = [vp, i32, i32, i32, i64, vp, vp, vp, vp, i32, i32, vp, vp, vp, vp, vp]
+        L.qamw_encode_pruned_ws.argtypes = [vp, i32, i32, i32, i64, vp, vp, vp, vp, i32, i32, vp, vp, C.c_size_t, vp, vp, vp, vp]
         for name in EXPORTS:
             if name != "qamw_status_string":
                 getattr(L, name).restype = C.c_int
@@ -374,9 +375,10 @@ def encode_pruned(W, codebook, grid, bits: int, block: int, chan_scale=None, sig
         norms = torch.empty(d_out, dtype=torch.float32, device=W.device)
     else:
         packed, norms = out
-    _check(lib().qamw_encode_pruned(_ptr(W), _dtype_code(W), d_out, d_in, W.stride(0), _ptr(chan_scale), _ptr(signs),
-                                    _ptr(pair_sigma), _ptr(codebook), bits, block, _ptr(grid), _ptr(packed), _ptr(norms),
-                                    _ptr(full_scans), _stream(stream)), "qamw_encode_pruned")
+    ws, n = _encode_scratch(bits, W.device, stream)
+    _check(lib().qamw_encode_pruned_ws(_ptr(W), _dtype_code(W), d_out, d_in, W.stride(0), _ptr(chan_scale), _ptr(signs),
+                                       _ptr(pair_sigma), _ptr(codebook), bits, block, _ptr(grid), _ptr(ws), n, _ptr(packed),
+                                       _ptr(norms), _ptr(full_scans), _stream(stream)), "qamw_encode_pruned_ws")
     return packed, norms
 
 

@@ -138,3 +138,51 @@ def test_batches_strides_streams_and_workspaces(dtype):
     one = qamw.encode(Ws[0], cb, bits, block, stream=st)      # outputs and scratch allocated here, used on the other stream
     torch.cuda.synchronize()
     assert torch.equal(one[0], want[0][0])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_records_from_memory_and_from_lds(dtype):
+    # at 11 bits the launch's item count decides where the records are read from: both sides of the line, a slab count that
+    # does not divide the waves, and a batch whose matrices share a launch
+    bits, block = 11, 128
+    cb = torch.from_numpy(_codebook(bits, "lloyd")).cuda()
+    for d_out, d_in in [(1, 128), (1024, 3072), (1025, 3072), (279, 11008), (280, 11008), (3, 14336)]:
+        say(f"[cells] records {d_out}x{d_in} {dtype}")
+        W = synth.weight_device(d_out, d_out, d_in, 0.5, dtype)
+        _both(W, cb, bits, block)
+    Ws = [synth.weight_device(i, d_out, d_in, 0.5, dtype) for i, (d_out, d_in) in enumerate([(5, 11008), (1, 1024), (64, 3072), (40, 14336)])]
+    outs = [(torch.full((W.shape[0], qamw.packed_row_bytes(W.shape[1], bits)), 0xAA, dtype=torch.uint8, device="cuda"),
+             torch.zeros(W.shape[0], device="cuda")) for W in Ws]
+    qamw.encode_batch(qamw.make_encode_items([(W, None, None, None, p, r) for W, (p, r) in zip(Ws, outs)]), cb, bits, block)
+    torch.cuda.synchronize()
+    scans = torch.zeros(1, dtype=torch.int64, device="cuda")
+    for W, (p, r) in zip(Ws, outs):
+        wp, wr = qamw.encode(W, cb, bits, block, full_scans=scans)
+        assert torch.equal(p, wp) and torch.equal(r, wr)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("bits", [3, 7, 11, 12])
+def test_pruned_call_with_scratch(bits):
+    # the pruned entry point: with scratch, from the caller's table (which counts its scans), and over the whole codebook
+    say(f"[cells] pruned B={bits}")
+    host = _codebook(bits, "lloyd")
+    cb, grid = torch.from_numpy(host).cuda(), torch.from_numpy(qamw.search_grid(host, bits)[0]).cuda()
+    L = qamw.lib()
+    for d_out, d_in, block, dtype in [(37, 1152, 128, "bf16"), (1200, 4096, 256, "f32"), (3, 192, 64, "bf16")]:
+        W = synth.weight_device(d_in, d_out, d_in, 0.5, dtype)
+        scans = torch.zeros(1, dtype=torch.int64, device="cuda")
+        want = qamw.encode(W, cb, bits, block, full_scans=scans)
+        for kw in ({}, {"full_scans": scans}):
+            got = qamw.encode_pruned(W, cb, grid, bits, block, **kw)
+            torch.cuda.synchronize()
+            assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]), kw
+    # what was refused stays refused, with scratch or without
+    W = synth.weight_device(1, 8, 96, 0.5, "f32")
+    with pytest.raises(qamw.QamwError) as e:
+        qamw.encode_pruned(W, cb, grid, bits, 32)
+    assert e.value.status == qamw.ERR_UNSUPPORTED
+    ptr = lambda t: C.c_void_p(t.data_ptr())
+    args = (ptr(W), 0, 8, 96, 96, None, None, None, ptr(cb), bits, 32, ptr(grid))
+    assert L.qamw_encode_pruned_ws(*args, C.c_void_p(cb.data_ptr() + 8), 1 << 20, ptr(W), ptr(W), None, None) != qamw.OK
