@@ -21,8 +21,9 @@ __global__ __launch_bounds__(CF_THREADS) void k_row_norms_vec(const void *__rest
     const int lane = threadIdx.x & (WAVE - 1);
     const int row = __builtin_amdgcn_readfirstlane(blockIdx.x * CF_WAVES + (threadIdx.x >> 6));
     if (row >= n_rows) return;
-    const double s2 = wave_row_sum_of_squares<DTYPE>(W, row, ldw, d_in, s, lane);
-    if (lane == 0) norms[row] = (float)sqrt(s2);
+    double s2[1];
+    wave_rows_sum_of_squares<DTYPE, 1>(s2, W, row, 1, ldw, d_in, s, lane);
+    if (lane == 0) norms[row] = (float)sqrt(s2[0]);
 }
 
 bool launch_row_norms_fast(const void *W, int dtype, int64_t ldw, int n_rows, const Problem &p, float *norms,

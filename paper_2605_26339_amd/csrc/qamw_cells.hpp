@@ -44,9 +44,21 @@ __device__ __forceinline__ float cells_dist2(float mx, float my, float2 c) {
     return ex * ex + ey * ey;
 }
 
+// The lanes' smallest distance and its codeword, in every lane.
+__device__ __forceinline__ void wave_nearest(float &d, float2 &c) {
+    const float least = wave_min(d);
+    const int at = __ffsll((long long)__ballot(d == least)) - 1;
+    d = least;
+    c = make_float2(lane_value(c.x, at), lane_value(c.y, at));
+}
+
 // Candidate lists of 8 x 8 cells by one workgroup; wave w takes their w-th quarter of 4 x 4 cells.
+// stopped_at, t: nothing is made once *stopped_at < t (looked at while the codewords are on their way).
+//   Bound by latency, one workgroup per CU: hence minima and prefix sums by DPP moves and ballots instead of shuffles, and
+// LDS reads four to eight at a time (2048 points, 16 x 16 regions: 8.2 us; 14 x 14 with shuffles and one read at a time 11.3).
 template <int G>
-__device__ __forceinline__ void cells_build_region(const float *codebook, int K, uint2 *table, int region) {
+__device__ __forceinline__ void cells_build_region(const float *codebook, int K, uint2 *table, int region, const int *stopped_at = nullptr,
+                                                   int t = 0) {
     __shared__ float2 reg_c[CP_REGION_LIST];
     __shared__ uint16_t reg_i[CP_REGION_LIST];
     __shared__ float2 blk_c[CP_WAVES][CP_BLOCK_LIST];
@@ -65,27 +77,22 @@ __device__ __forceinline__ void cells_build_region(const float *codebook, int K,
     const int per = (K + CP_THREADS - 1) / CP_THREADS, first = (int)threadIdx.x * per;
     float2 c[CP_PER_THREAD];
     float d2[CP_PER_THREAD];
+    const int stop = stopped_at ? *stopped_at : t;
+#pragma unroll
+    for (int j = 0; j < CP_PER_THREAD; ++j) c[j] = cbk[j < per && first + j < K ? first + j : 0];
+    if (stop < t) return;
     float mx = ((float)x0 + 3.5f - 0.5f * G) * h, my = ((float)y0 + 3.5f - 0.5f * G) * h, w = 4.0f * h + slack;
     float nd = 3.0e38f;
     float2 nc = make_float2(0.0f, 0.0f);
 #pragma unroll
     for (int j = 0; j < CP_PER_THREAD; ++j) {
-        const bool have = j < per && first + j < K;
-        c[j] = cbk[have ? first + j : 0];
         d2[j] = cells_dist2(mx, my, c[j]);
         if (d2[j] < nd) {
             nd = d2[j];
             nc = c[j];
         }
     }
-#pragma unroll
-    for (int s = 1; s < WAVE; s <<= 1) {
-        const float od = __shfl_xor(nd, s, WAVE), ox = __shfl_xor(nc.x, s, WAVE), oy = __shfl_xor(nc.y, s, WAVE);
-        if (od < nd) {
-            nd = od;
-            nc = make_float2(ox, oy);
-        }
-    }
+    wave_nearest(nd, nc);
     if (lane == 0) {
         red_d[wid] = nd;
         red_c[wid] = nc;
@@ -106,9 +113,9 @@ __device__ __forceinline__ void cells_build_region(const float *codebook, int K,
         if (j < per && first + j < K && !cells_dominated(c[j], d2[j], nc, nd, w)) keep |= 1u << j;
     int below = __popc(keep);                                   // inclusive sum over the lanes up to this one
 #pragma unroll
-    for (int s = 1; s < WAVE; s <<= 1) {
-        const int o = __shfl_up(below, s, WAVE);
-        if (lane >= s) below += o;
+    for (int j = 0; j < CP_PER_THREAD; ++j) {
+        const unsigned long long mask = __ballot((keep >> j) & 1u);
+        below += __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
     }
     if (lane == WAVE - 1) red_n[wid] = below;
     __syncthreads();
@@ -138,32 +145,30 @@ __device__ __forceinline__ void cells_build_region(const float *codebook, int K,
     my = ((float)by + 1.5f - 0.5f * G) * h;
     w = 2.0f * h + slack;
     nd = 3.0e38f;
-    for (int e = lane; e < n_reg; e += WAVE) {
-        const float2 ce = reg_c[e];
-        const float d = cells_dist2(mx, my, ce);
-        if (d < nd) {
-            nd = d;
-            nc = ce;
-        }
-    }
+    constexpr int RUNS = CP_REGION_LIST / WAVE;
+    float2 ce[RUNS];
+    float de[RUNS];
 #pragma unroll
-    for (int s = 1; s < WAVE; s <<= 1) {
-        const float od = __shfl_xor(nd, s, WAVE), ox = __shfl_xor(nc.x, s, WAVE), oy = __shfl_xor(nc.y, s, WAVE);
-        if (od < nd) {
-            nd = od;
-            nc = make_float2(ox, oy);
+    for (int u = 0; u < RUNS; ++u) ce[u] = reg_c[u * WAVE + lane < n_reg ? u * WAVE + lane : 0];
+#pragma unroll
+    for (int u = 0; u < RUNS; ++u) {
+        de[u] = cells_dist2(mx, my, ce[u]);
+        if (u * WAVE + lane < n_reg && de[u] < nd) {
+            nd = de[u];
+            nc = ce[u];
         }
     }
+    wave_nearest(nd, nc);
     int n_blk = 0;
-    for (int e0 = 0; e0 < n_reg; e0 += WAVE) {
-        const int e = e0 + lane;
-        const float2 ce = reg_c[e < n_reg ? e : 0];
-        const bool k = e < n_reg && !cells_dominated(ce, cells_dist2(mx, my, ce), nc, nd, w);
+#pragma unroll
+    for (int u = 0; u < RUNS; ++u) {
+        if (u * WAVE >= n_reg) break;
+        const bool k = u * WAVE + lane < n_reg && !cells_dominated(ce[u], de[u], nc, nd, w);
         const unsigned long long mask = __ballot(k);
-        const int pos = n_blk + __popcll(mask & ((1ull << lane) - 1ull));
+        const int pos = n_blk + __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
         if (k && pos < CP_BLOCK_LIST) {
-            blk_c[wid][pos] = ce;
-            blk_i[wid][pos] = reg_i[e];
+            blk_c[wid][pos] = ce[u];
+            blk_i[wid][pos] = reg_i[u * WAVE + lane];
         }
         n_blk += __popcll(mask);
     }
@@ -180,24 +185,23 @@ __device__ __forceinline__ void cells_build_region(const float *codebook, int K,
     const int quarter = (n_blk + 3) >> 2, e_begin = part * quarter, e_end = min(n_blk, e_begin + quarter);
     float da = 3.0e38f, db = 3.0e38f;                           // nearest and second nearest
     float2 ca = make_float2(0.0f, 0.0f), cb = ca;
-    for (int e = e_begin; e < e_end; ++e) {
-        const float2 ce = blk_c[wid][e];
-        const float d = cells_dist2(mx, my, ce);
-        if (d < da) {
-            db = da;
-            cb = ca;
-            da = d;
-            ca = ce;
-        } else if (d < db) {
-            db = d;
-            cb = ce;
+    for (int e0 = e_begin; e0 < e_end; e0 += 4) {
+        float2 c4[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) c4[q] = blk_c[wid][min(e0 + q, e_end - 1)];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float d = e0 + q < e_end ? cells_dist2(mx, my, c4[q]) : 3.0e38f;
+            const bool first_of_all = d < da, second = d < db;
+            cb.x = first_of_all ? ca.x : second ? c4[q].x : cb.x;
+            cb.y = first_of_all ? ca.y : second ? c4[q].y : cb.y;
+            db = first_of_all ? da : second ? d : db;
+            ca.x = first_of_all ? c4[q].x : ca.x;
+            ca.y = first_of_all ? c4[q].y : ca.y;
+            da = first_of_all ? d : da;
         }
     }
-#pragma unroll
-    for (int s = 1; s <= 2; s <<= 1) {
-        const float oda = __shfl_xor(da, s, WAVE), odb = __shfl_xor(db, s, WAVE);
-        const float2 oca = make_float2(__shfl_xor(ca.x, s, WAVE), __shfl_xor(ca.y, s, WAVE));
-        const float2 ocb = make_float2(__shfl_xor(cb.x, s, WAVE), __shfl_xor(cb.y, s, WAVE));
+    auto merge = [&](float oda, float odb, float2 oca, float2 ocb) {
         // each side's two, sorted: the first is the smaller head, the second the smaller of the other head and its own second
         const bool swap = oda < da;
         const float hd = swap ? da : oda, td = swap ? odb : db;
@@ -209,22 +213,27 @@ __device__ __forceinline__ void cells_build_region(const float *codebook, int K,
         const bool head = hd < td;
         db = head ? hd : td;
         cb = head ? hc : tc;
-    }
+    };
+    merge(dpp_move<DPP_XOR1>(da), dpp_move<DPP_XOR1>(db), make_float2(dpp_move<DPP_XOR1>(ca.x), dpp_move<DPP_XOR1>(ca.y)),
+          make_float2(dpp_move<DPP_XOR1>(cb.x), dpp_move<DPP_XOR1>(cb.y)));
+    merge(dpp_move<DPP_XOR2>(da), dpp_move<DPP_XOR2>(db), make_float2(dpp_move<DPP_XOR2>(ca.x), dpp_move<DPP_XOR2>(ca.y)),
+          make_float2(dpp_move<DPP_XOR2>(cb.x), dpp_move<DPP_XOR2>(cb.y)));
     unsigned kept = 0;                                          // bit e - e_begin (a quarter is at most 32 candidates)
-    for (int e = e_begin; e < e_end; ++e) {
-        const float2 ce = blk_c[wid][e];
-        const float d = cells_dist2(mx, my, ce);
-        const bool out = cells_dominated(ce, d, ca, da, w) || (db < 3.0e38f && cells_dominated(ce, d, cb, db, w));
-        if (!out) kept |= 1u << (e - e_begin);
+    for (int e0 = e_begin; e0 < e_end; e0 += 4) {
+        float2 c4[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) c4[q] = blk_c[wid][min(e0 + q, e_end - 1)];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float d = cells_dist2(mx, my, c4[q]);
+            const bool out = cells_dominated(c4[q], d, ca, da, w) || (db < 3.0e38f && cells_dominated(c4[q], d, cb, db, w));
+            if (!out && e0 + q < e_end) kept |= 1u << (e0 + q - e_begin);
+        }
     }
     const int mine = __popc(kept);
-    int before = 0, total = 0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int o = __shfl(mine, (lane & ~3) | q, WAVE);
-        if (q < part) before += o;
-        total += o;
-    }
+    const int n0 = dpp_move<dpp_quad_lane(0)>(mine), n1 = dpp_move<dpp_quad_lane(1)>(mine), n2 = dpp_move<dpp_quad_lane(2)>(mine);
+    int before = (part > 0 ? n0 : 0) + (part > 1 ? n1 : 0) + (part > 2 ? n2 : 0);
+    const int total = n0 + n1 + n2 + dpp_move<dpp_quad_lane(3)>(mine);
     while (kept) {
         const int e = e_begin + __ffs((int)kept) - 1;
         kept &= kept - 1u;
@@ -250,24 +259,27 @@ __device__ __forceinline__ void cells_build_region(const float *codebook, int K,
 
 
 // ------------------------------------------------------------------------------------------------ the search
-// The record of the cell that holds (x0, x1): table in LDS.  The lookup rounds x G / 8 + G / 2 to the nearest integer and
-// clamps it to the border, whose records say "whole codebook".
-template <int G> __device__ __forceinline__ uint2 cells_record(const char *table, float x0, float x1) {
+// Byte offset, from 8 times `base`, of the record of the cell that holds (x0, x1).  The lookup rounds x G / 8 + G / 2 to the
+// nearest integer and clamps it to the border, whose records say "whole codebook".
+constexpr uint32_t CELLS_MAGIC_BITS = 0x4B000000u;             // 2^23: adding it rounds to an integer, left in the low bits
+template <int G> __device__ __forceinline__ uint32_t cells_record_at(float x0, float x1, uint32_t table_at) {
     constexpr float inv_h = G / (2.0f * CELLS_HALF);
-    constexpr float magic = 8388608.0f;                        // 2^23: adding it rounds to an integer, left in the low bits
+    constexpr float magic = 8388608.0f;
     const float vx = fminf(fmaxf(__builtin_fmaf(x0, inv_h, magic + G / 2), magic), magic + (G - 1));
     const float vy = fminf(fmaxf(__builtin_fmaf(x1, inv_h, magic + G / 2), magic), magic + (G - 1));
-    const unsigned at = (__float_as_uint(vy) & 0xffffu) * (G * 8) + (__float_as_uint(vx) & 0xffffu) * 8;
-    return *reinterpret_cast<const uint2 *>(table + at);
+    // (iy G + ix) 8 + table_at mod 2^32, the two numbers' exponent bits taken out with the one constant
+    const uint32_t cell = __float_as_uint(vy) * G + __float_as_uint(vx);
+    return (cell << 3) + (table_at - ((CELLS_MAGIC_BITS * G + CELLS_MAGIC_BITS) << 3));
 }
 __device__ __forceinline__ bool cells_scan(uint2 rec) { return rec.y >> 31; }
-// The nearest of the record's candidates, as its byte offset in the codebook (LDS); m: its squared distance.  All lanes of
-// the wave call it together.  FIVE: nearly every wave holds a pair with more than three candidates.
-template <bool FIVE> __device__ __forceinline__ unsigned cells_nearest(uint2 rec, float x0, float x1, const float2 *cb, float &m) {
+// The nearest of the record's candidates, as its byte offset in the codebook (LDS, at byte address cb_at); m: its squared
+// distance.  All lanes of the wave call it together.  FIVE: nearly every wave holds a pair with more than three candidates.
+template <bool FIVE> __device__ __forceinline__ unsigned cells_nearest(uint2 rec, float x0, float x1, uint32_t cb_at, float &m) {
     const unsigned lo = rec.x, hi = rec.y;
     const unsigned o0 = lo & 0x7ff8u, o1 = (lo >> 12) & 0x7ff8u, o2 = __builtin_amdgcn_alignbit(hi, lo, 24) & 0x7ff8u;
     auto dist = [&](unsigned o) {
-        return exact_dist2(x0, x1, *reinterpret_cast<const float2 *>(reinterpret_cast<const char *>(cb) + o));
+        const lds_f32x2_t c = lds_read<lds_f32x2_t>(cb_at + o);
+        return exact_dist2(x0, x1, make_float2(c[0], c[1]));
     };
     const float d0 = dist(o0), d1 = dist(o1), d2 = dist(o2);
     m = fminf(fminf(d0, d1), d2);

@@ -46,11 +46,44 @@ __device__ __forceinline__ uint32_t unpack_field(const uint32_t *row, int row_dw
     return (uint32_t)(((hi << 32) | lo) >> sh) & ((1u << bits) - 1u);
 }
 
+// LDS by byte address.  In a kernel without statically sized LDS the dynamic block begins at 0: the constant part of an
+// address then goes into the instruction's offset, where a pointer to the block costs an addition of 0 at every access.
+template <typename T> __device__ __forceinline__ T lds_read(uint32_t at) {
+    return *reinterpret_cast<const __attribute__((address_space(3))) T *>(at);
+}
+template <typename T> __device__ __forceinline__ void lds_write(uint32_t at, T v) {
+    *reinterpret_cast<__attribute__((address_space(3))) T *>(at) = v;
+}
+typedef float lds_f32x2_t __attribute__((ext_vector_type(2)));
+typedef uint32_t lds_u32x2_t __attribute__((ext_vector_type(2)));
+typedef uint32_t lds_u32x4_t __attribute__((ext_vector_type(4)));
+
 // Sum over the 64 lanes of a wave in a fixed butterfly order (the same in every lane).
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
     for (int m = 1; m < WAVE; m <<= 1) v += __shfl_xor(v, m, WAVE);
     return v;
 }
+
+
+// The value of the lane whose number differs in bit 0 or 1, and that of lane Q of the lane's group of four: one DPP move each
+// (a shuffle through LDS takes some 120 cycles to come back).
+template <int CTRL> __device__ __forceinline__ int dpp_move(int v) { return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, false); }
+template <int CTRL> __device__ __forceinline__ float dpp_move(float v) { return __int_as_float(dpp_move<CTRL>(__float_as_int(v))); }
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_MIRROR = 0x140;
+constexpr int dpp_quad_lane(int q) { return q * 0x55; }
+
+// The smallest of the 64 lanes' values, in every lane; no NaN among them.
+__device__ __forceinline__ float wave_min(float v) {
+    v = fminf(v, dpp_move<DPP_XOR1>(v));
+    v = fminf(v, dpp_move<DPP_XOR2>(v));
+    v = fminf(v, dpp_move<DPP_HALF_MIRROR>(v));
+    v = fminf(v, dpp_move<DPP_MIRROR>(v));
+    auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fminf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fminf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float lane_value(float v, int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane)); }
 
 }  // namespace qamw

@@ -23,6 +23,7 @@ namespace qamw {
 // 1024 x 8192, 8192 items, 36.0 / 37.5; 4096 x 4096 48.5 / 52.1.  The smaller tables (32 to 72 KB) are staged in less than the
 // second L2 round trip takes: 1024 x 2048 at 10 bits 20.3 / 19.6, at 7 bits 18.7 / 25.1.
 constexpr int CELLS_DIRECT_MAX_ITEMS = 3072;
+constexpr int CELLS_ROWS_TOGETHER = 8192;                      // rows of a launch from which a wave sums four
 constexpr int CELLS_MIN_ITEMS = 1024;                          // (row, slab) items of a launch from which small codebooks use the table
 
 struct CellsMat {
@@ -47,8 +48,10 @@ struct CellsBatch {
 };
 
 // ------------------------------------------------------------------------------------------------ table and norms
-// Workgroups 0 .. (G/8)^2 - 1 make the table; the rest compute the row norms, one wave per row.
-template <int DTYPE, int G>
+// Workgroups 0 .. (G/8)^2 - 1 make the table; the rest compute the row norms.
+// R rows per wave: large launches take four, which fetches the channel scales (twice the bytes of bf16 weights) a quarter as
+// often.  A 7B layer, 405 MB: 87 us with one row per wave, 77 so.
+template <int DTYPE, int G, int R>
 __global__ __launch_bounds__(CP_THREADS) void k_cells_prepare(CellsBatch bt) {
     constexpr int REGIONS = (G / 8) * (G / 8);
     if (blockIdx.x < REGIONS) {
@@ -60,10 +63,16 @@ __global__ __launch_bounds__(CP_THREADS) void k_cells_prepare(CellsBatch bt) {
     while (mi + 1 < bt.n && b >= bt.norm_begin[mi + 1]) ++mi;
     const CellsMat &M = bt.m[mi];
     const int lane = threadIdx.x & (WAVE - 1);
-    const int row = __builtin_amdgcn_readfirstlane((b - bt.norm_begin[mi]) * CP_WAVES + (int)(threadIdx.x >> 6));
+    const int row = __builtin_amdgcn_readfirstlane(((b - bt.norm_begin[mi]) * CP_WAVES + (int)(threadIdx.x >> 6)) * R);
     if (row >= M.d_out) return;
-    const double s2 = wave_row_sum_of_squares<DTYPE>(M.W, row, M.ldw, M.d_in, M.chan_scale, lane);
-    if (lane == 0) M.norms[row] = (float)sqrt(s2);
+    const int n_rows = min(R, M.d_out - row);
+    double s2[R];
+    wave_rows_sum_of_squares<DTYPE, R>(s2, M.W, row, n_rows, M.ldw, M.d_in, M.chan_scale, lane);
+    if (lane == 0) {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (r < n_rows) M.norms[row + r] = (float)sqrt(s2[r]);
+    }
 }
 
 // ------------------------------------------------------------------------------------------------ the encoder
@@ -76,20 +85,18 @@ constexpr size_t cells_lds_bytes(int G) { return (size_t)cells_codewords(G) * 8 
 // workgroup would stage 128 KB for an item or two per wave, and small workgroups reach more CUs.
 template <int DTYPE, int B, int G, bool STAGED>
 __global__ __launch_bounds__(STAGED ? cells_threads(G) : CELLS_DIRECT_THREADS) void k_encode_cells(CellsBatch bt) {
+    static_assert(STAGED || (G & (G - 1)) == 0, "the mask of the record's offset");
     constexpr int THREADS = STAGED ? cells_threads(G) : CELLS_DIRECT_THREADS, WAVES = THREADS / WAVE;
-    extern __shared__ __align__(16) float2 cells_lds[];        // codebook, then the table
-    const float2 *cb = cells_lds;
-    const char *table = STAGED ? reinterpret_cast<const char *>(cells_lds + cells_codewords(G)) : reinterpret_cast<const char *>(bt.table);
+    constexpr uint32_t TABLE_AT = cells_codewords(G) * 8;      // LDS: the codebook at 0, then the table
     const int K = bt.K, bits = bt.bits;
     {
-        const float2 *cbk = reinterpret_cast<const float2 *>(bt.codebook);
+        const lds_f32x2_t *cbk = reinterpret_cast<const lds_f32x2_t *>(bt.codebook);
 #pragma unroll 8
-        for (int i = threadIdx.x; i < K; i += THREADS) cells_lds[i] = cbk[i];
+        for (int i = threadIdx.x; i < K; i += THREADS) lds_write(8 * i, cbk[i]);
         if (STAGED) {
-            const uint4 *src = reinterpret_cast<const uint4 *>(bt.table);
-            uint4 *dst = reinterpret_cast<uint4 *>(cells_lds + cells_codewords(G));
+            const lds_u32x4_t *src = reinterpret_cast<const lds_u32x4_t *>(bt.table);
 #pragma unroll 8
-            for (int i = threadIdx.x; i < G * G / 2; i += THREADS) dst[i] = src[i];
+            for (int i = threadIdx.x; i < G * G / 2; i += THREADS) lds_write(TABLE_AT + 16 * i, src[i]);
         }
     }
     __syncthreads();
@@ -99,6 +106,9 @@ __global__ __launch_bounds__(STAGED ? cells_threads(G) : CELLS_DIRECT_THREADS) v
     const LaneSigns<B> ls(lane);
     const int pos = slab_pos(lane);
     const float unit = ls.parity * bt.inv_sqrt_block;
+    // 1/sqrt(B) is a power of two: both products are one, to the same bits (what that could lose below the smallest normal
+    // number is nothing to a distance from a codeword)
+    constexpr bool UNIT_EXACT = B == 64 || B == 256 || B == 1024;
 
     // The waves of the launch take the (row, slab) items of a matrix in turn, `step` at a time, a multiple of the slab
     // count: a wave stays on its slab.  The next matrix begins with the wave after the last one that got an item.
@@ -135,6 +145,8 @@ __global__ __launch_bounds__(STAGED ? cells_threads(G) : CELLS_DIRECT_THREADS) v
             p.g_default = M.g_default;
             load_signed_scales(sc, p, c);
             load_pair_gains(g, p, c);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) g[k] = UNIT_EXACT ? unit * g[k] : g[k];
         }
 
         RawRow<DTYPE> next;
@@ -156,38 +168,45 @@ __global__ __launch_bounds__(STAGED ? cells_threads(G) : CELLS_DIRECT_THREADS) v
             divide_by_norm(x, norm);
             fwht_wave<B>(x, ls);
 #pragma unroll
-            for (int e = 0; e < 16; ++e) x[e] = (x[e] * unit) * g[e >> 1];
+            for (int e = 0; e < 16; ++e) x[e] = (UNIT_EXACT ? x[e] : x[e] * unit) * g[e >> 1];
 
             // ---------------- the cells' records
             uint2 rec[8];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) rec[k] = cells_record<G>(table, x[2 * k], x[2 * k + 1]);
-            unsigned idx[8];
-            unsigned scan = 0;                                  // bit k: pair k needs the whole codebook
+            for (int k = 0; k < 8; ++k) {
+                const uint32_t at = cells_record_at<G>(x[2 * k], x[2 * k + 1], STAGED ? TABLE_AT : 0u);
+                if (STAGED) {
+                    const lds_u32x2_t r = lds_read<lds_u32x2_t>(at);
+                    rec[k] = make_uint2(r[0], r[1]);
+                } else {
+                    rec[k] = *reinterpret_cast<const uint2 *>(reinterpret_cast<const char *>(bt.table) + (at & (G * G * 8u - 1u)));   // in range whatever x is
+                }
+            }
+            unsigned idx8[8];                                   // 8 times the index: the codeword's byte offset
+            unsigned any = 0;
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
-                scan |= (unsigned)cells_scan(rec[k]) << k;
+                any |= rec[k].y;
                 float m;
-                idx[k] = cells_nearest<G == 128>(rec[k], x[2 * k], x[2 * k + 1], cb, m) >> 3;
+                idx8[k] = cells_nearest<G == 128>(rec[k], x[2 * k], x[2 * k + 1], 0u, m);
             }
 
             // ---------------- the exact scan for the rest: the whole wave works on one pair at a time
-            if (!active) scan = 0;
-            if (__ballot(scan != 0)) {
+            if (__ballot(active && (any & CELLS_SCAN))) {
 #pragma unroll
                 for (int k = 0; k < 8; ++k) {
-                    unsigned long long mask = __ballot((scan >> k) & 1u);
+                    unsigned long long mask = __ballot(active && cells_scan(rec[k]));
                     while (mask) {
                         const int src = __ffsll((long long)mask) - 1;
                         mask &= mask - 1;
                         const float x0 = __shfl(x[2 * k], src, WAVE), x1 = __shfl(x[2 * k + 1], src, WAVE);
-                        const int bi = wave_exact_scan(x0, x1, cb, K, lane);
-                        if (lane == src) idx[k] = (unsigned)bi;
+                        const int bi = wave_exact_scan(x0, x1, 0u, K, lane);
+                        if (lane == src) idx8[k] = 8u * (unsigned)bi;
                     }
                 }
             }
 
-            if (active) store_fields(M.packed + (int64_t)row * M.row_bytes, M.row_bytes, M.d_in, c, idx, bits);
+            if (active) store_fields<3>(M.packed + (int64_t)row * M.row_bytes, M.row_bytes, M.d_in, c, idx8, bits);
         }
     }
 }
@@ -217,23 +236,29 @@ static hipError_t launch_cells_dbg(CellsBatch &bt, hipStream_t stream) {
         return hipErrorNotSupported;
     }
     constexpr int WAVES = cells_threads(G) / WAVE;
-    int64_t items = 0;
+    int64_t items = 0, rows = 0;
     int norm_blocks = 0, most_slabs = 1;
+    for (int i = 0; i < bt.n; ++i) rows += bt.m[i].d_out;
+    const int per_wave = rows >= CELLS_ROWS_TOGETHER ? 4 : 1;
     for (int i = 0; i < bt.n; ++i) {
         const CellsMat &M = bt.m[i];
         items += (int64_t)M.d_out * M.n_slabs;
         bt.norm_begin[i] = norm_blocks;
-        norm_blocks += (M.d_out + CP_WAVES - 1) / CP_WAVES;
+        norm_blocks += (M.d_out + CP_WAVES * per_wave - 1) / (CP_WAVES * per_wave);
         if (M.n_slabs > most_slabs) most_slabs = M.n_slabs;
     }
     for (int i = bt.n; i <= QAMW_ENCODE_MAX_BATCH; ++i) bt.norm_begin[i] = norm_blocks;
     const unsigned prep = (unsigned)((G / 8) * (G / 8) + norm_blocks);
+    auto prepare = [&]() {
+        if (per_wave == 4) hipLaunchKernelGGL((k_cells_prepare<DTYPE, G, 4>), dim3(prep), dim3(CP_THREADS), 0, stream, bt);
+        else hipLaunchKernelGGL((k_cells_prepare<DTYPE, G, 1>), dim3(prep), dim3(CP_THREADS), 0, stream, bt);
+        return hipGetLastError();
+    };
     if constexpr (G == 128) {
         if (items <= CELLS_DIRECT_MAX_ITEMS) {
             constexpr int DIRECT_WAVES = CELLS_DIRECT_THREADS / WAVE;
             const unsigned direct = (unsigned)((items + most_slabs + DIRECT_WAVES - 1) / DIRECT_WAVES);   // an item per wave, whole rows
-            hipLaunchKernelGGL((k_cells_prepare<DTYPE, G>), dim3(prep), dim3(CP_THREADS), 0, stream, bt);
-            const hipError_t e = hipGetLastError();
+            const hipError_t e = prepare();
             if (e != hipSuccess) return e;
             hipLaunchKernelGGL((k_encode_cells<DTYPE, B, G, false>), dim3(direct), dim3(CELLS_DIRECT_THREADS),
                                (size_t)cells_codewords(G) * sizeof(float2), stream, bt);
@@ -245,8 +270,7 @@ static hipError_t launch_cells_dbg(CellsBatch &bt, hipStream_t stream) {
     int64_t blocks = (items + WAVES - 1) / WAVES;
     if (blocks > (int64_t)cus * per_cu) blocks = (int64_t)cus * per_cu;
     if (blocks * WAVES < most_slabs) return hipErrorNotSupported;   // every wave keeps to one slab: at least a row's worth of waves
-    hipLaunchKernelGGL((k_cells_prepare<DTYPE, G>), dim3(prep), dim3(CP_THREADS), 0, stream, bt);
-    hipError_t e = hipGetLastError();
+    const hipError_t e = prepare();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_encode_cells<DTYPE, B, G, true>), dim3((unsigned)blocks), dim3(cells_threads(G)), cells_lds_bytes(G), stream, bt);
     return hipGetLastError();

@@ -27,6 +27,7 @@ constexpr int PF_MAX_ROWS = 32;        // rows of a workgroup
 constexpr int PF_ITEMS = 48;           // (row, slab) items of a workgroup in a large launch
 constexpr int PF_CUS = 256;
 constexpr int PF_MAX_ITEMS = 64;       // (row, slab) items of a workgroup, unless one row has more
+constexpr uint32_t PF_DIR_AT = 4 * PF_MAX_LEVELS + 8 * PF_MAX_ITEMS + 4 * PF_MAX_ROWS;   // LDS before the directions
 
 // A workgroup of 8 waves owns `rows` consecutive rows: first the slab sums of all their (row, slab) items, dealt to the
 // waves, then -- after the barrier the table set-up needs anyway -- the items once more, in slab-major order, each wave a
@@ -41,12 +42,11 @@ __global__ __launch_bounds__(PF_THREADS) void k_encode_polar(const void *__restr
                                                              const float *__restrict__ levels, int bits_a, int bits_p,
                                                              const float *__restrict__ norms_in, float *__restrict__ norms_out,
                                                              uint8_t *__restrict__ packed, int n_slabs, int rows) {
-    extern __shared__ __align__(16) float lds_raw[];
+    // LDS: thr2[i] = (midpoint of levels i-1, i)^2, i >= 1; the slab sums [row][slab]; the rows' norms; then the Np boundary
+    // directions (cos, sin)(2 k h)
+    constexpr uint32_t THR_AT = 0, PART_AT = 4 * PF_MAX_LEVELS, NORM_AT = PART_AT + 8 * PF_MAX_ITEMS, DIR_AT = PF_DIR_AT;
+    static_assert(DIR_AT == NORM_AT + 4 * PF_MAX_ROWS, "layout");
     const int Na = 1 << bits_a, Np = 1 << bits_p;
-    float *thr2 = lds_raw;                                      // Na: thr2[i] = (midpoint of levels i-1, i)^2, i >= 1
-    float2 *bdir = reinterpret_cast<float2 *>(lds_raw + (Na < 2 ? 2 : Na));   // Np boundary directions (cos, sin)(2 k h), 8-byte aligned
-    __shared__ double norm_part[PF_MAX_ITEMS];                 // [row][slab]
-    __shared__ float norm_row[PF_MAX_ROWS];
     const int lane = threadIdx.x & (WAVE - 1);
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int row0 = (int)blockIdx.x * rows, n_rows = min(rows, p.d_out - row0), n_items = n_rows * n_slabs;
@@ -55,29 +55,31 @@ __global__ __launch_bounds__(PF_THREADS) void k_encode_polar(const void *__restr
         for (int t = wid; t < n_items; t += PF_WAVES) {
             const int dr = t / n_slabs, slab = t - dr * n_slabs;
             const double s2 = slab_sum_of_squares<DTYPE>(W, (int64_t)(row0 + dr) * ldw, slab, p, lane);
-            if (lane == 0) norm_part[t] = s2;
+            if (lane == 0) lds_write<double>(PART_AT + 8 * t, s2);
         }
     }
     for (int i = threadIdx.x; i < Na; i += PF_THREADS) {
         const float t = (i > 0) ? 0.5f * (levels[i - 1] + levels[i]) : 0.0f;
-        thr2[i] = t * t;
+        lds_write<float>(THR_AT + 4 * i, t * t);
     }
     for (int k = threadIdx.x; k < Np; k += PF_THREADS) {
         float sn, cs;
         sincospif(2.0f * (float)k / (float)Np, &sn, &cs);      // the angle 2 k h = pi * (2k / Np), argument exact
-        bdir[k] = make_float2(cs, sn);
+        lds_write<lds_f32x2_t>(DIR_AT + 8 * k, lds_f32x2_t{cs, sn});
     }
     __syncthreads();
     if ((int)threadIdx.x < n_rows) {
         const int dr = threadIdx.x;
         float r;
         if (norms_in == nullptr) {
-            r = row_norm_from_slab_sums(norm_part, dr, 0, n_slabs);
+            double s2 = 0.0;                                    // in slab order, as row_norm_from_slab_sums()
+            for (int s = 0; s < n_slabs; ++s) s2 += lds_read<double>(PART_AT + 8 * (dr * n_slabs + s));
+            r = (float)sqrt(s2);
             norms_out[row0 + dr] = r;
         } else {
             r = norms_in[row0 + dr];
         }
-        norm_row[dr] = r;
+        lds_write<float>(NORM_AT + 4 * dr, r);
     }
     __syncthreads();
 
@@ -107,44 +109,44 @@ __global__ __launch_bounds__(PF_THREADS) void k_encode_polar(const void *__restr
         widen_raw_row<DTYPE>(x, raw);
 #pragma unroll
         for (int e = 0; e < 16; ++e) x[e] = x[e] * sc[e];       // sign included: a sign commutes with every rounding below
-        divide_by_norm(x, norm_row[row - row0]);
+        divide_by_norm(x, lds_read<float>(NORM_AT + 4 * (row - row0)));
         fwht_wave<B>(x, ls);
 #pragma unroll
         for (int e = 0; e < 16; ++e) x[e] = (x[e] * unit) * g[e >> 1];
 
         // ---------------- amplitude level and phase bin of the lane's 8 pairs
         float a2[8];
-        int ia[8], ip[8];
+        unsigned ia[8], ip[8];                                  // times 4 and 8: byte offsets into the tables
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
             const float x0 = x[2 * k], x1 = x[2 * k + 1];
             a2[k] = __builtin_fmaf(x1, x1, x0 * x0);
             ia[k] = 0;
             const bool upper = (x1 < 0.0f) || (x1 == 0.0f && x0 < 0.0f);   // angle in [pi, 2 pi)
-            ip[k] = upper ? (Np >> 1) : 0;
+            ip[k] = upper ? 8u * (unsigned)(Np >> 1) : 0u;
         }
 #pragma unroll 1
-        for (int step = Na >> 1; step; step >>= 1) {
+        for (unsigned step = 4u * (unsigned)(Na >> 1); step >= 4u; step >>= 1) {
             float t[8];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) t[k] = thr2[ia[k] + step];
+            for (int k = 0; k < 8; ++k) t[k] = lds_read<float>(THR_AT + ia[k] + step);
 #pragma unroll
             for (int k = 0; k < 8; ++k) ia[k] = (a2[k] > t[k]) ? ia[k] + step : ia[k];   // on the threshold: the lower level
         }
 #pragma unroll 1
-        for (int step = Np >> 2; step; step >>= 1) {
-            float2 b[8];
+        for (unsigned step = 8u * (unsigned)(Np >> 2); step >= 8u; step >>= 1) {
+            lds_f32x2_t b[8];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) b[k] = bdir[ip[k] + step];
+            for (int k = 0; k < 8; ++k) b[k] = lds_read<lds_f32x2_t>(DIR_AT + ip[k] + step);
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
-                const float cr = __builtin_fmaf(b[k].x, x[2 * k + 1], -(b[k].y * x[2 * k]));   // sin(angle - 2 cand h) * |x|
+                const float cr = __builtin_fmaf(b[k][0], x[2 * k + 1], -(b[k][1] * x[2 * k]));   // sin(angle - 2 cand h) * |x|
                 ip[k] = (cr >= 0.0f) ? ip[k] + step : ip[k];
             }
         }
         unsigned idx[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) idx[k] = (unsigned)((ia[k] << bits_p) + (a2[k] == 0.0f ? 0 : ip[k]));
+        for (int k = 0; k < 8; ++k) idx[k] = ((ia[k] >> 2) << bits_p) + (a2[k] == 0.0f ? 0u : ip[k] >> 3);
 
         // ---------------- pack: the lane's 8 fields are exactly `bits` bytes, byte aligned in the row
         if (active) store_fields(packed + (int64_t)row * p.row_bytes, p.row_bytes, p.d_in, c, idx, p.bits);
@@ -168,7 +170,7 @@ static hipError_t launch_pdb(const void *W, int64_t ldw, const Problem &p, const
     int rows = std::max(1, std::min(PF_MAX_ROWS, PF_ITEMS / n_slabs));
     while (rows > 1 && (p.d_out + rows - 1) / rows < 2 * PF_CUS && (rows + 1) / 2 * n_slabs >= PF_WAVES) rows = (rows + 1) / 2;
     const unsigned blocks = (unsigned)((p.d_out + rows - 1) / rows);
-    const size_t lds = ((size_t)(bits_a ? (1 << bits_a) : 2) + 2 * (size_t)(1 << bits_p)) * sizeof(float);
+    const size_t lds = PF_DIR_AT + 8 * (size_t)(1 << bits_p);
     hipLaunchKernelGGL((k_encode_polar<DTYPE, B>), dim3(blocks), dim3(PF_THREADS), lds, p.stream, W, ldw, p, levels, bits_a,
                        bits_p, norms_ready ? norms : nullptr, norms, packed, n_slabs, rows);
     return hipGetLastError();

@@ -199,52 +199,67 @@ __device__ __forceinline__ float row_norm_from_slab_sums(const double *part, int
     return (float)sqrt(s2);
 }
 
-// Sum of squares of a row's scaled weights, by one wave: 16-byte loads, squares exact in fp64, the lane-strided sums
-// combined with the fixed butterfly of wave_sum().  The same in every lane.
-template <int DTYPE>
-__device__ __forceinline__ double wave_row_sum_of_squares(const void *__restrict__ W, int row, int64_t ldw, int d_in,
-                                                          const float *__restrict__ s, int lane) {
+// Sums of squares of R consecutive rows' scaled weights, by one wave: 16-byte loads, squares exact in fp64, the lane-strided
+// sums combined with the fixed butterfly of wave_sum().  The same in every lane, and the same whatever R is.  n_rows <= R
+// rows exist.  The scales are fetched once for the R rows.
+template <int DTYPE, int R>
+__device__ __forceinline__ void wave_rows_sum_of_squares(double (&sum)[R], const void *__restrict__ W, int row, int n_rows, int64_t ldw,
+                                                         int d_in, const float *__restrict__ s, int lane) {
     constexpr int V = DTYPE == 0 ? 4 : 8;                       // elements per 16-byte load
-    constexpr int U = 4;                                        // loads requested together: a wave alone on its row has
+    constexpr int U = R == 1 ? 4 : 2;                           // loads per row requested together: a wave alone on its row has
                                                                 // nothing else to hide the memory round trip behind
-    const char *base = reinterpret_cast<const char *>(W) + (int64_t)row * ldw * (DTYPE == 0 ? 4 : 2);
-    double acc = 0.0;
+    const char *base[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        base[r] = reinterpret_cast<const char *>(W) + (int64_t)(row + (r < n_rows ? r : 0)) * ldw * (DTYPE == 0 ? 4 : 2);
+        sum[r] = 0.0;
+    }
     for (int j0 = lane * V; j0 < d_in; j0 += U * WAVE * V) {
-        uint4 raw[U];
+        uint4 raw[R][U];
+        float4 sv[U][V / 4];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int j = j0 + u * WAVE * V;
-            raw[u] = make_uint4(0, 0, 0, 0);
-            if (j < d_in) raw[u] = *reinterpret_cast<const uint4 *>(base + (int64_t)j * (DTYPE == 0 ? 4 : 2));
+            const bool have = j < d_in;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                raw[r][u] = make_uint4(0, 0, 0, 0);
+                if (have) raw[r][u] = *reinterpret_cast<const uint4 *>(base[r] + (int64_t)j * (DTYPE == 0 ? 4 : 2));
+            }
+#pragma unroll
+            for (int t = 0; t < V / 4; ++t) {
+                sv[u][t] = make_float4(1.0f, 1.0f, 1.0f, 1.0f);
+                if (s && have) sv[u][t] = *reinterpret_cast<const float4 *>(s + j + 4 * t);
+            }
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int j = j0 + u * WAVE * V;
-            if (j >= d_in) break;
-            float w[V];
-            const uint32_t q4[4] = {raw[u].x, raw[u].y, raw[u].z, raw[u].w};
-            if (DTYPE == 0) {
+            if (j0 + u * WAVE * V >= d_in) break;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) w[q] = __uint_as_float(q4[q]);
-            } else {
+            for (int r = 0; r < R; ++r) {
+                float w[V];
+                const uint32_t q4[4] = {raw[r][u].x, raw[r][u].y, raw[r][u].z, raw[r][u].w};
+                if (DTYPE == 0) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    w[2 * q] = __uint_as_float(q4[q] << 16);
-                    w[2 * q + 1] = __uint_as_float(q4[q] & 0xFFFF0000u);
+                    for (int q = 0; q < 4; ++q) w[q] = __uint_as_float(q4[q]);
+                } else {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        w[2 * q] = __uint_as_float(q4[q] << 16);
+                        w[2 * q + 1] = __uint_as_float(q4[q] & 0xFFFF0000u);
+                    }
                 }
-            }
-            if (s) {
 #pragma unroll
-                for (int t = 0; t < V; t += 4) {
-                    float4 sv = *reinterpret_cast<const float4 *>(s + j + t);
-                    w[t] *= sv.x; w[t + 1] *= sv.y; w[t + 2] *= sv.z; w[t + 3] *= sv.w;
+                for (int t = 0; t < V / 4; ++t) {
+                    w[4 * t] *= sv[u][t].x; w[4 * t + 1] *= sv[u][t].y; w[4 * t + 2] *= sv[u][t].z; w[4 * t + 3] *= sv[u][t].w;
                 }
-            }
 #pragma unroll
-            for (int t = 0; t < V; ++t) acc += (double)w[t] * (double)w[t];
+                for (int t = 0; t < V; ++t) sum[r] += (double)w[t] * (double)w[t];
+            }
         }
     }
-    return wave_sum(acc);
+#pragma unroll
+    for (int r = 0; r < R; ++r) sum[r] = wave_sum(sum[r]);
 }
 
 // Exact squared distance as every encoder decides with it: fma(e1, e1, e0 * e0), e = x - c.
@@ -255,27 +270,45 @@ __device__ __forceinline__ float exact_dist2(float x0, float x1, float2 c) {
 
 // The nearest of the K codewords in LDS to the point (x0, x1) (the same in all lanes), found by the whole wave: lane l
 // scans the codewords l, l + 64, ..., then a lexicographic (distance, index) reduction over the lanes; the lowest index
-// wins a tie.  Every lane returns the index (0 if every distance is NaN).
-__device__ __forceinline__ int wave_exact_scan(float x0, float x1, const float2 *cb_lds, int K, int lane) {
+// wins a tie.  Every lane returns the index (0 if every distance is NaN).  codeword(k): from wherever the caller keeps them.
+template <typename F> __device__ __forceinline__ int wave_exact_scan_of(float x0, float x1, F codeword, int K, int lane) {
+    // Codewords requested together: the scan is a chain of LDS latencies otherwise.  0.065 % of Gaussian pairs come here at 2^11
+    // points, one in three of a wave's 512-pair items: 13824 x 5120, the whole encode call, 156 us one at a time, 137 so.
+    constexpr int AHEAD = 8;
     float bd = 3.0e38f;
     int bi = 0x7fffffff;
-    for (int k = lane; k < K; k += WAVE) {
-        const float dd = exact_dist2(x0, x1, cb_lds[k]);
-        if (dd < bd) {
-            bd = dd;
-            bi = k;
-        }
-    }
+    for (int k = lane; k < K; k += AHEAD * WAVE) {
+        float2 c[AHEAD];
 #pragma unroll
-    for (int m = 1; m < WAVE; m <<= 1) {
-        const float od = __shfl_xor(bd, m, WAVE);
-        const int oi = __shfl_xor(bi, m, WAVE);
-        if (od < bd || (od == bd && oi < bi)) {
-            bd = od;
-            bi = oi;
+        for (int j = 0; j < AHEAD; ++j) c[j] = codeword(min(k + j * WAVE, K - 1));
+#pragma unroll
+        for (int j = 0; j < AHEAD; ++j) {
+            const float dd = exact_dist2(x0, x1, c[j]);
+            if (dd < bd) {                                      // (past the end: the last codeword again, found before or below)
+                bd = dd;
+                bi = min(k + j * WAVE, K - 1);
+            }
         }
     }
-    return bi == 0x7fffffff ? 0 : bi;
+    const float least = wave_min(bd);
+    unsigned long long at = __ballot(bd == least);
+    int best = 0x7fffffff;
+    while (at) {
+        const int l = __ffsll((long long)at) - 1;
+        at &= at - 1;
+        best = min(best, __builtin_amdgcn_readlane(bi, l));
+    }
+    return best == 0x7fffffff ? 0 : best;
+}
+__device__ __forceinline__ int wave_exact_scan(float x0, float x1, const float2 *cb_lds, int K, int lane) {
+    return wave_exact_scan_of(x0, x1, [&](int k) { return cb_lds[k]; }, K, lane);
+}
+// the codewords at LDS byte address cb_at
+__device__ __forceinline__ int wave_exact_scan(float x0, float x1, uint32_t cb_at, int K, int lane) {
+    return wave_exact_scan_of(x0, x1, [&](int k) {
+        const lds_f32x2_t c = lds_read<lds_f32x2_t>(cb_at + 8u * (uint32_t)k);
+        return make_float2(c[0], c[1]);
+    }, K, lane);
 }
 
 // The lane's 8 pair gains g_k = 1 / sigma_k (IEEE division), or sqrt(d_in) when no pair scales are given; c = first of
@@ -336,7 +369,7 @@ __device__ __forceinline__ void store_packed_fields(uint8_t *__restrict__ packed
 
 // The same with the bit count known to the compiler: the fields are shifted into dwords and stored as one or two unaligned
 // dword groups and the one to three bytes that remain.
-template <int BITS> __device__ __forceinline__ void store_fields_n(uint8_t *dst, const unsigned (&idx)[8]) {
+template <int BITS, int UP> __device__ __forceinline__ void store_fields_n(uint8_t *dst, const unsigned (&idx)[8]) {
     typedef uint32_t u32_a1_t __attribute__((aligned(1)));
     typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
     typedef u32x2_t u32x2_a1_t __attribute__((aligned(1)));
@@ -347,8 +380,8 @@ template <int BITS> __device__ __forceinline__ void store_fields_n(uint8_t *dst,
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
         const int bit = k * BITS, word = bit >> 5, off = bit & 31;
-        w[word] |= idx[k] << off;
-        if (off + BITS > 32) w[word + 1] |= idx[k] >> (32 - off);
+        w[word] |= off >= UP ? idx[k] << (off - UP) : idx[k] >> (UP - off);
+        if (off + BITS > 32) w[word + 1] |= idx[k] >> (32 - off + UP);
     }
     int at = 0;
     if (BITS >= 8) {
@@ -369,22 +402,23 @@ template <int BITS> __device__ __forceinline__ void store_fields_n(uint8_t *dst,
         dst[at] = (uint8_t)w[at / 4];
     }
 }
-// row: the row's packed bytes; c: first of the lane's 16 columns.
+// row: the row's packed bytes; c: first of the lane's 16 columns; idx: the indices times 2^UP.
+template <int UP = 0>
 __device__ __forceinline__ void store_fields(uint8_t *row, int64_t row_bytes, int d_in, int c, const unsigned (&idx)[8], int bits) {
     uint8_t *dst = row + (int64_t)(c >> 4) * bits;
     switch (bits) {
-        case 1: store_fields_n<1>(dst, idx); break;
-        case 2: store_fields_n<2>(dst, idx); break;
-        case 3: store_fields_n<3>(dst, idx); break;
-        case 4: store_fields_n<4>(dst, idx); break;
-        case 5: store_fields_n<5>(dst, idx); break;
-        case 6: store_fields_n<6>(dst, idx); break;
-        case 7: store_fields_n<7>(dst, idx); break;
-        case 8: store_fields_n<8>(dst, idx); break;
-        case 9: store_fields_n<9>(dst, idx); break;
-        case 10: store_fields_n<10>(dst, idx); break;
-        case 11: store_fields_n<11>(dst, idx); break;
-        default: store_fields_n<12>(dst, idx); break;
+        case 1: store_fields_n<1, UP>(dst, idx); break;
+        case 2: store_fields_n<2, UP>(dst, idx); break;
+        case 3: store_fields_n<3, UP>(dst, idx); break;
+        case 4: store_fields_n<4, UP>(dst, idx); break;
+        case 5: store_fields_n<5, UP>(dst, idx); break;
+        case 6: store_fields_n<6, UP>(dst, idx); break;
+        case 7: store_fields_n<7, UP>(dst, idx); break;
+        case 8: store_fields_n<8, UP>(dst, idx); break;
+        case 9: store_fields_n<9, UP>(dst, idx); break;
+        case 10: store_fields_n<10, UP>(dst, idx); break;
+        case 11: store_fields_n<11, UP>(dst, idx); break;
+        default: store_fields_n<12, UP>(dst, idx); break;
     }
     if (c + 16 == d_in)                                         // the lane with the row's last columns zeroes the padding
         for (int64_t t = (int64_t)(d_in >> 4) * bits; t < row_bytes; ++t) row[t] = 0;

@@ -10,7 +10,6 @@
 // k_lloyd_update: every point to the mean of its cell (an empty cell keeps its point).
 // k_cells_lloyd_*: the same iteration for 64 to 2048 points with a cell table (qamw_cells.hpp) made from every iteration's
 // points, the sums of a workgroup in LDS, and the stopping rule on the device, so the host launches ahead.
-#include <atomic>
 #include <cmath>
 
 #include "qamw_cells.hpp"
@@ -127,9 +126,8 @@ __global__ __launch_bounds__(LL_THREADS) void k_lloyd_init(int K, LloydAcc acc, 
 // Per iteration t, points in buffer t mod 2: k_cells_lloyd_table makes the table, k_cells_lloyd_assign assigns every sample
 // and leaves each workgroup's sums, k_cells_lloyd_move adds them up, decides whether to stop and writes the next points to
 // the other buffer.  Once it has stopped, the kernels of later iterations return at once.
-//   What bounds it: the assignment reads 8 bytes per sample and does some 50 instructions per wave of them; at 2^20 samples
-// the three launches, each a few us of staging and latency, are most of an iteration (2048 points: 401 us a pass for the
-// distances to all of them before).
+//   What bounds it: three launches that are each mostly latency.  2048 points, 2^20 samples (8 MB): 8.2 + 11.5 + 7.5 us an
+// iteration (the distances to all points took 401); the kernels ask for what they work on before they look whether to stop.
 struct LloydState {
     double D;
     int stopped_at;                       // the last iteration, LC_RUNNING before it is known
@@ -139,7 +137,7 @@ constexpr int LC_THREADS = 1024;
 constexpr int LC_POINTS = 16;                                  // points per workgroup of k_cells_lloyd_move
 constexpr int LC_MAX_BLOCKS = 256;                             // one workgroup per CU: a workgroup's sums are 20 bytes per point in LDS and in the workspace
 constexpr int LC_AHEAD = 16;                                   // iterations launched before the host looks whether it has stopped
-constexpr int lc_side(int K) { return K == 2048 ? 112 : K == 1024 ? 96 : 64; }   // beside the sums 128 x 128 records do not fit the LDS
+constexpr int lc_side(int K) { return K >= 1024 ? 128 : 64; }
 
 struct LloydCells {
     double *cb64[2];
@@ -183,61 +181,76 @@ __global__ __launch_bounds__(LL_THREADS) void k_cells_lloyd_init(int K, LloydCel
 }
 
 template <int G> __global__ __launch_bounds__(CP_THREADS) void k_cells_lloyd_table(int K, LloydCells a, int t) {
-    if (a.state->stopped_at < t) return;
-    cells_build_region<G>(a.cb32[t & 1], K, a.table, (int)blockIdx.x);
+    cells_build_region<G>(a.cb32[t & 1], K, a.table, (int)blockIdx.x, &a.state->stopped_at, t);
 }
 
+// The records come from memory (L2), four samples' at a time: staging them took as long as the samples of a workgroup do, and
+// a table of 112 x 112 cells was all that fitted beside the sums, with 1.1 % of Gaussian samples in cells of six candidates --
+// a scan of the whole codebook in most waves, against 0.05 % with 128 x 128.  2048 points, 2^20 samples: 23.5 -> 11.5 us.
 template <int G>
 __global__ __launch_bounds__(LC_THREADS) void k_cells_lloyd_assign(const float2 *__restrict__ samples, long long n, int K, LloydCells a, int t) {
-    extern __shared__ __align__(16) float2 lc_lds[];           // points, table, then the sums: x, y (64 bits), count (32)
-    if (a.state->stopped_at < t) return;
-    char *table = reinterpret_cast<char *>(lc_lds + K);
-    unsigned long long *sx = reinterpret_cast<unsigned long long *>(table + G * G * 8), *sy = sx + K;
-    unsigned *cnt = reinterpret_cast<unsigned *>(sy + K);
-    __shared__ unsigned long long err_sum;
-    const float2 *cbk = reinterpret_cast<const float2 *>(a.cb32[t & 1]);
-    for (int i = threadIdx.x; i < K; i += LC_THREADS) {
-        lc_lds[i] = cbk[i];
-        sx[i] = 0;
-        sy[i] = 0;
-        cnt[i] = 0;
-    }
-    if (threadIdx.x == 0) err_sum = 0;
-    const uint4 *src = reinterpret_cast<const uint4 *>(a.table);
-    uint4 *dst = reinterpret_cast<uint4 *>(table);
-#pragma unroll 8
-    for (int i = threadIdx.x; i < G * G / 2; i += LC_THREADS) dst[i] = src[i];
-    __syncthreads();
-
+    // points (at LDS address 0), then the sums: x, y (64 bits), count (32), error (64)
+    extern __shared__ __align__(16) float2 lc_lds[];
+    constexpr int U = 4;
+    static_assert((G & (G - 1)) == 0, "the mask of the record's offset");
+    const int stopped_at = a.state->stopped_at;
     const int lane = threadIdx.x & (WAVE - 1);
     const long long stride = (long long)gridDim.x * LC_THREADS;
-    double err = 0.0;
     long long i = (long long)blockIdx.x * LC_THREADS + threadIdx.x;
-    float2 next = i < n ? samples[i] : make_float2(0.0f, 0.0f);
-    for (; i - lane < n; i += stride) {                         // the wave's lanes stay together
-        const bool active = i < n;
-        const float2 x = next;
-        if (i + stride < n) next = samples[i + stride];
-        const uint2 rec = cells_record<G>(table, x.x, x.y);
-        float d;
-        int bi = (int)(cells_nearest<(G > 64)>(rec, x.x, x.y, lc_lds, d) >> 3);
-        unsigned long long mask = __ballot(active && cells_scan(rec));
-        while (mask) {                                          // outside the table, or too many candidates: the whole codebook
-            const int at = __ffsll((long long)mask) - 1;
-            mask &= mask - 1;
-            const float x0 = __shfl(x.x, at, WAVE), x1 = __shfl(x.y, at, WAVE);
-            const int found = wave_exact_scan(x0, x1, lc_lds, K, lane);
-            if (lane == at) {
-                bi = found;
-                d = fminf(exact_dist2(x0, x1, lc_lds[found]), 3.0e38f);
-            }
+    const float2 *cbk = reinterpret_cast<const float2 *>(a.cb32[t & 1]);
+    float2 next[U];
+    auto request = [&](long long at) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) next[u] = at + u * stride < n ? samples[at + u * stride] : make_float2(0.0f, 0.0f);
+    };
+    request(i);
+    unsigned long long *sx = reinterpret_cast<unsigned long long *>(lc_lds + K), *sy = sx + K;
+    unsigned *cnt = reinterpret_cast<unsigned *>(sy + K);
+    unsigned long long &err_sum = *reinterpret_cast<unsigned long long *>(cnt + K);
+    for (int k = threadIdx.x; k < K; k += LC_THREADS) {
+        lc_lds[k] = cbk[k];
+        sx[k] = 0;
+        sy[k] = 0;
+        cnt[k] = 0;
+    }
+    if (threadIdx.x == 0) err_sum = 0;
+    if (stopped_at < t) return;
+    __syncthreads();
+
+    double err = 0.0;
+    for (; i - lane < n; i += U * stride) {                     // the wave's lanes stay together
+        float2 x[U];
+        uint2 rec[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            x[u] = next[u];
+            rec[u] = *reinterpret_cast<const uint2 *>(reinterpret_cast<const char *>(a.table) +
+                                                      (cells_record_at<G>(x[u].x, x[u].y, 0u) & (G * G * 8u - 1u)));   // in range whatever x is
         }
-        if (active) {
-            const float cx = fminf(fmaxf(x.x, -LL_CLAMP), LL_CLAMP), cy = fminf(fmaxf(x.y, -LL_CLAMP), LL_CLAMP);
-            atomicAdd(sx + bi, (unsigned long long)__double2ll_rn((double)cx * LL_SCALE));
-            atomicAdd(sy + bi, (unsigned long long)__double2ll_rn((double)cy * LL_SCALE));
-            atomicAdd(cnt + bi, 1u);
-            err += (double)fminf(d, 2.0f * LL_CLAMP * LL_CLAMP);
+        request(i + U * stride);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool active = i + u * stride < n;
+            float d;
+            int bi = (int)(cells_nearest<(G > 64)>(rec[u], x[u].x, x[u].y, 0u, d) >> 3);
+            unsigned long long mask = __ballot(active && cells_scan(rec[u]));
+            while (mask) {                                      // outside the table, or too many candidates: the whole codebook
+                const int at = __ffsll((long long)mask) - 1;
+                mask &= mask - 1;
+                const float x0 = __shfl(x[u].x, at, WAVE), x1 = __shfl(x[u].y, at, WAVE);
+                const int found = wave_exact_scan(x0, x1, 0u, K, lane);
+                if (lane == at) {
+                    bi = found;
+                    d = fminf(exact_dist2(x0, x1, lc_lds[found]), 3.0e38f);
+                }
+            }
+            if (active) {
+                const float cx = fminf(fmaxf(x[u].x, -LL_CLAMP), LL_CLAMP), cy = fminf(fmaxf(x[u].y, -LL_CLAMP), LL_CLAMP);
+                atomicAdd(sx + bi, (unsigned long long)__double2ll_rn((double)cx * LL_SCALE));
+                atomicAdd(sy + bi, (unsigned long long)__double2ll_rn((double)cy * LL_SCALE));
+                atomicAdd(cnt + bi, 1u);
+                err += (double)fminf(d, 2.0f * LL_CLAMP * LL_CLAMP);
+            }
         }
     }
 #pragma unroll
@@ -256,12 +269,14 @@ __global__ __launch_bounds__(LC_THREADS) void k_cells_lloyd_assign(const float2 
 // LC_POINTS points per workgroup, 1024 / LC_POINTS threads per point share the workgroups' sums (integers: any order gives
 // the same).  stopped_at becomes t in iteration t's own launch, so `< t` means the same to all its workgroups.
 __global__ __launch_bounds__(LC_THREADS) void k_cells_lloyd_move(long long n, int K, LloydCells a, int t, int n_blocks, int max_iters, double tol) {
-    constexpr int P = LC_POINTS, Q = LC_THREADS / P;
-    __shared__ long long red[2][Q][P + 1];
-    __shared__ unsigned red_n[Q][P + 1];
+    constexpr int P = LC_POINTS, Q = LC_THREADS / P, NW = LC_THREADS / WAVE;
+    static_assert(P == 16 && LC_MAX_BLOCKS <= LC_THREADS, "a wave holds four threads of each point");
+    __shared__ long long red[2][NW][P];
+    __shared__ unsigned red_n[NW][P];
     __shared__ unsigned long long err;
-    if (a.state->stopped_at < t) return;
+    const int stopped_at = a.state->stopped_at;
     const int p = threadIdx.x % P, q = threadIdx.x / P, k = blockIdx.x * P + p;
+    const unsigned long long my_err = blockIdx.x == 0 && (int)threadIdx.x < n_blocks ? a.perr[threadIdx.x] : 0ull;
     if (threadIdx.x == 0) err = 0;
     long long sx = 0, sy = 0;
     unsigned c = 0;
@@ -271,14 +286,24 @@ __global__ __launch_bounds__(LC_THREADS) void k_cells_lloyd_move(long long n, in
         sy += a.psy[(size_t)b * K + k];
         c += a.pcnt[(size_t)b * K + k];
     }
-    red[0][q][p] = sx;
-    red[1][q][p] = sy;
-    red_n[q][p] = c;
+    if (stopped_at < t) return;
+#pragma unroll
+    for (int s = 16; s < WAVE; s <<= 1) {
+        sx += __shfl_xor(sx, s, WAVE);
+        sy += __shfl_xor(sy, s, WAVE);
+        c += __shfl_xor(c, s, WAVE);
+    }
+    const int wid = threadIdx.x / WAVE;
+    if ((threadIdx.x & (WAVE - 1)) < P) {
+        red[0][wid][p] = sx;
+        red[1][wid][p] = sy;
+        red_n[wid][p] = c;
+    }
     __syncthreads();
-    if (blockIdx.x == 0 && (int)threadIdx.x < n_blocks) atomicAdd(&err, a.perr[threadIdx.x]);
+    if (my_err) atomicAdd(&err, my_err);
     if (q == 0) {
-#pragma unroll 16
-        for (int r = 1; r < Q; ++r) {
+#pragma unroll
+        for (int r = 1; r < NW; ++r) {
             sx += red[0][r][p];
             sy += red[1][r][p];
             c += red_n[r][p];
@@ -312,21 +337,8 @@ template <int G>
 static hipError_t run_lloyd_cells(const float *samples, long long n, int K, float *codebook, int max_iters, double tol,
                                   void *workspace, double *mse_out, int *iters_out, hipStream_t stream) {
     const LloydCells a = lloyd_cells_layout(workspace, K);
-    const size_t lds = (size_t)K * 28 + (size_t)G * G * 8;
-    if (lds > 64 * 1024) {
-        static std::atomic<uint64_t> done{0};                   // the devices on which the larger LDS was asked for
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorNotSupported;
-        if (!(done.load(std::memory_order_acquire) & (1ull << dev))) {
-            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_cells_lloyd_assign<G>),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess) {
-                (void)hipGetLastError();
-                return hipErrorNotSupported;
-            }
-            done.fetch_or(1ull << dev, std::memory_order_release);
-        }
-    }
+    const size_t lds = (size_t)K * 28 + 8;
+    static_assert(2048 * 28 + 8 <= 64 * 1024, "what a workgroup may have without asking");
     const unsigned kb = (unsigned)((2 * K + LL_THREADS - 1) / LL_THREADS);
     const long long want = (n + 2 * LC_THREADS - 1) / (2 * LC_THREADS);
     const unsigned blocks = (unsigned)(want < LC_MAX_BLOCKS ? want : LC_MAX_BLOCKS);
@@ -383,11 +395,8 @@ static LloydAcc lloyd_layout(void *workspace, int K) {
 hipError_t run_lloyd(const float *samples, long long n, int K, float *codebook, int max_iters, double tol, void *workspace,
                      size_t workspace_bytes, double *mse_out, int *iters_out, hipStream_t stream) {
     if (lloyd_has_cells(K) && workspace_bytes >= lloyd_cells_bytes(K)) {
-        hipError_t e;
-        if (lc_side(K) == 112) e = run_lloyd_cells<112>(samples, n, K, codebook, max_iters, tol, workspace, mse_out, iters_out, stream);
-        else if (lc_side(K) == 96) e = run_lloyd_cells<96>(samples, n, K, codebook, max_iters, tol, workspace, mse_out, iters_out, stream);
-        else e = run_lloyd_cells<64>(samples, n, K, codebook, max_iters, tol, workspace, mse_out, iters_out, stream);
-        if (e != hipErrorNotSupported) return e;                // nothing was launched
+        if (lc_side(K) == 128) return run_lloyd_cells<128>(samples, n, K, codebook, max_iters, tol, workspace, mse_out, iters_out, stream);
+        return run_lloyd_cells<64>(samples, n, K, codebook, max_iters, tol, workspace, mse_out, iters_out, stream);
     }
     const LloydAcc acc = lloyd_layout(workspace, K);
     double *report = reinterpret_cast<double *>(reinterpret_cast<char *>(acc.err) + 16);

@@ -705,15 +705,6 @@ constexpr int GW_STAGE = 4;                // matrix instructions of depth per s
 
 constexpr int gw_ahead(int tt) { return tt == 2 ? 2 : 4; }      // 136 and 120 KB of LDS
 
-// LDS by byte address: the kernel has no static LDS, so the dynamic block begins at 0 and constant parts of an address go
-// into the instruction's offset.
-template <typename T> __device__ __forceinline__ T gw_lds_read(uint32_t at) {
-    return *reinterpret_cast<const __attribute__((address_space(3))) T *>(at);
-}
-template <typename T> __device__ __forceinline__ void gw_lds_write(uint32_t at, T v) {
-    *reinterpret_cast<__attribute__((address_space(3))) T *>(at) = v;
-}
-
 template <int BITS, int TT>
 __global__ __launch_bounds__(GW_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_qgemm_wide(GemvBatch bt) {
@@ -758,7 +749,7 @@ void k_qgemm_wide(GemvBatch bt) {
         for (int i = threadIdx.x; i < KC; i += GW_THREADS) {
             const float2 c = cbk[i];
             const gv_f32x2_t v = {c.x, c.y};
-            gw_lds_write<uint32_t>(4 * i, __builtin_bit_cast(uint32_t, __builtin_convertvector(v, gv_bf16x2_t)));
+            lds_write<uint32_t>(4 * i, __builtin_bit_cast(uint32_t, __builtin_convertvector(v, gv_bf16x2_t)));
         }
     }
 
@@ -811,7 +802,7 @@ void k_qgemm_wide(GemvBatch bt) {
         for (int i = 0; i < 4; ++i) {
             const int bit = (4 * j + i) * BITS, word = bit >> 5, off = bit & 31;
             const uint32_t v = (off + BITS <= 32) ? (f[word] >> off) : __builtin_amdgcn_alignbit(f[word + 1], f[word], off);
-            a[i] = gw_lds_read<uint32_t>((v & (KC - 1u)) << 2);
+            a[i] = lds_read<uint32_t>((v & (KC - 1u)) << 2);
         }
         return a;
     };
@@ -832,8 +823,8 @@ void k_qgemm_wide(GemvBatch bt) {
     {
         uint32_t f[3];
         align_piece(pc[0], 0, f);
-        gw_lds_write(a_write, gather(f, 0));
-        gw_lds_write(a_write + 1024, gather(f, 1));
+        lds_write(a_write, gather(f, 0));
+        lds_write(a_write + 1024, gather(f, 1));
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);                        // vmcnt(0): the wave's activations have landed
     __syncthreads();
@@ -864,9 +855,9 @@ void k_qgemm_wide(GemvBatch bt) {
             const uint32_t zr = z_read + z_now;
             auto operands = [&](int j) {
 #pragma unroll
-                for (int a = 0; a < 2; ++a) av[j & 1][a] = gw_lds_read<gv_bf16x8_t>(a_read + cur * A_BYTES + (a * GW_STAGE + j) * 1024);
+                for (int a = 0; a < 2; ++a) av[j & 1][a] = lds_read<gv_bf16x8_t>(a_read + cur * A_BYTES + (a * GW_STAGE + j) * 1024);
 #pragma unroll
-                for (int t = 0; t < TT; ++t) bv[j & 1][t] = gw_lds_read<gv_bf16x8_t>(zr + t * 4096 + j * 512);
+                for (int t = 0; t < TT; ++t) bv[j & 1][t] = lds_read<gv_bf16x8_t>(zr + t * 4096 + j * 512);
             };
             operands(0);
             uint32_t f[3];
@@ -882,7 +873,7 @@ void k_qgemm_wide(GemvBatch bt) {
 #pragma unroll
                     for (int t = 0; t < TT; ++t)
                         acc[a][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[j & 1][a], bv[j & 1][t], acc[a][t], 0, 0, 0);
-                if (j >= 1 && j < 3) gw_lds_write(a_write + nxt * A_BYTES + (j - 1) * 1024, cw[j - 1]);
+                if (j >= 1 && j < 3) lds_write(a_write + nxt * A_BYTES + (j - 1) * 1024, cw[j - 1]);
                 __builtin_amdgcn_sched_barrier(0);
             }
             // The next stage's activations have landed.  What was requested since may be under way: a piece, then AHEAD - 1
