@@ -49,7 +49,7 @@ bool launch_row_norms_fast(const void *W, int dtype, int64_t ldw, int n_rows, co
 // only launch of 32 workgroups, 20.4 -> 12.2 us; 1024 head rows of 4096 columns 24.3 -> 16.1.  A layer's 1024 head rows of
 // seven matrices are bound by vector-ALU issue, the fp64 square roots above all: 87.8 -> 69.1 us with sqrt_magnitude(), the
 // scales and signs once per slab and the next row on its way.
-// Step 2: per pair, the partial sums added in chunk order, then Eq. 1.
+// Step 2: per pair, the partial sums added up, then Eq. 1.
 // ---------------------------------------------------------------------------------------------
 struct CalMat {
     const void *W;
@@ -166,24 +166,38 @@ __global__ __launch_bounds__(CAL_THREADS) void k_calibrate_partial(CalBatch bt) 
     }
 }
 
+// CF_PAIRS pairs per workgroup, CF_GROUPS threads per pair: each adds a consecutive run of the chunks, the runs' sums are
+// added in order.  Bound by memory latency: with one thread per pair a matrix of 2048 pairs was 8 workgroups that each made
+// eight round trips (4096 x 4096, 128 chunks: 6.7 us, so 2.8).
+constexpr int CF_PAIRS = 32, CF_GROUPS = CF_THREADS / CF_PAIRS;
 __global__ __launch_bounds__(CF_THREADS) void k_calibrate_finish(CalBatch bt) {
+    __shared__ double sums[CF_GROUPS][CF_PAIRS];
     int mi = 0;
     while (mi + 1 < bt.n && (int)blockIdx.x >= bt.fin_begin[mi + 1]) ++mi;
     const CalMat &M = bt.m[mi];
     const int n_pairs = M.d_in >> 1, n_chunks = M.n_chunks;
     const double *__restrict__ partial = M.partial;
-    const int k = ((int)blockIdx.x - bt.fin_begin[mi]) * CF_THREADS + threadIdx.x;
-    if (k >= n_pairs) return;
+    const int lp = threadIdx.x % CF_PAIRS, group = threadIdx.x / CF_PAIRS;
+    const int k = ((int)blockIdx.x - bt.fin_begin[mi]) * CF_PAIRS + lp;
+    const int per = (n_chunks + CF_GROUPS - 1) / CF_GROUPS;
+    const int end = min(n_chunks, (group + 1) * per);
     double acc = 0.0;
-    int q = 0;
-    for (; q + 16 <= n_chunks; q += 16) {                       // 16 loads in flight, added in chunk order
-        double v[16];
+    if (k < n_pairs) {
+        int q = group * per;
+        for (; q + 16 <= end; q += 16) {                        // 16 loads in flight, added in chunk order
+            double v[16];
 #pragma unroll
-        for (int t = 0; t < 16; ++t) v[t] = partial[(int64_t)(q + t) * n_pairs + k];
+            for (int t = 0; t < 16; ++t) v[t] = partial[(int64_t)(q + t) * n_pairs + k];
 #pragma unroll
-        for (int t = 0; t < 16; ++t) acc += v[t];
+            for (int t = 0; t < 16; ++t) acc += v[t];
+        }
+        for (; q < end; ++q) acc += partial[(int64_t)q * n_pairs + k];
     }
-    for (; q < n_chunks; ++q) acc += partial[(int64_t)q * n_pairs + k];
+    sums[group][lp] = acc;
+    __syncthreads();
+    if (group != 0 || k >= n_pairs) return;
+#pragma unroll
+    for (int g = 1; g < CF_GROUPS; ++g) acc += sums[g][lp];
     const double sqrt_half_pi = 1.2533141373155002512078826424055;
     const float s = (float)((acc / (double)M.n_rows) / sqrt_half_pi);
     M.sigma_out[k] = (s > 0.0f) ? s : M.sigma_default;
@@ -242,7 +256,7 @@ hipError_t launch_calibrate_batch_fast(const CalItem *items, int n, int dtype, i
         bt.chunk_begin[i] = (int)chunks;
         bt.fin_begin[i] = (int)fin;
         chunks += M.n_chunks;
-        fin += (items[i].d_in / 2 + CF_THREADS - 1) / CF_THREADS;
+        fin += (items[i].d_in / 2 + CF_PAIRS - 1) / CF_PAIRS;
         if (chunks > 0x3fffffff || fin > 0x3fffffff) return hipErrorNotSupported;
     }
     for (int i = n; i <= CAL_MAX_BATCH; ++i) {
