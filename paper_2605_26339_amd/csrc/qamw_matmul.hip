@@ -577,9 +577,7 @@ void k_qgemm(GemvBatch bt) {
         const int piece = 64 * i + lane, row = piece / BITS, c16 = piece - row * BITS;
         return row * PITCH + 16 * c16;
     };
-    const uint16_t *zrow[MT];
-#pragma unroll
-    for (int t = 0; t < MT; ++t) zrow[t] = Zb + ((int64_t)t * n_chunks * 2 + h) * 16 * 256 + r * 8;   // padded rows exist and are zero
+    const uint32_t z_lane = (uint32_t)(h * 16 * 256 + r * 8) * 2;     // bytes; padded rows exist and are zero
 
     gv_f32x16_t acc[MT];
 #pragma unroll
@@ -599,8 +597,25 @@ void k_qgemm(GemvBatch bt) {
         for (int i = 0; i < PIECES; ++i)
             if (64 * i + lane < tile_pieces) v[i] = *reinterpret_cast<const u32x4_a4_t *>(src + src_off(i));
     }
+    // Activations.  One tile of activation rows: 8 instructions' worth at a time.  Two tiles: the registers hold 2, so each slot
+    // is filled again as soon as its instruction has been issued (in batches a wave waited for L2 eight times a chunk: 64 rows
+    // against 4096 x 11008, 7 bits, 31.7 -> 26.7 us, 11 bits 34.4 -> 31.8; with one tile the slots cost registers and time, 11008 x
+    // 4096 twice, 32 rows, 8 bits: 22.8 -> 25.2).
+    constexpr int ZB = MT == 1 ? 8 : 2;
+    constexpr bool RING = MT == 2;
+    gv_u32x4_t zb[MT][ZB];
+    const char *zbytes = reinterpret_cast<const char *>(Zb);
+    auto load_zb = [&](int ch, int step, int slot) {
+#pragma unroll
+        for (int t = 0; t < MT; ++t) zb[t][slot] = *reinterpret_cast<const gv_u32x4_t *>(zbytes + (((int64_t)t * n_chunks + ch) * 32 + step) * 512 + z_lane);
+    };
+    if (RING && wid < n_chunks) {
+#pragma unroll
+        for (int j = 0; j < ZB; ++j) load_zb(wid, j, j);
+    }
 #pragma unroll 1
     for (int ch = wid; ch < n_chunks; ch += GM_WAVES) {
+        const int next_ch = ch + GM_WAVES < n_chunks ? ch + GM_WAVES : ch;   // past the end: the same chunk again (unused)
         // the chunk's packed bytes go through LDS: written piece by piece, read back as the lane's stream of 64 pairs
 #pragma unroll
         for (int i = 0; i < PIECES; ++i) {
@@ -619,19 +634,11 @@ void k_qgemm(GemvBatch bt) {
                 w[2 * q + 1] = x2[1];
             }
         }
-        // activations of this chunk, ZB instructions' worth at a time: 8, or 2 with two tiles of activation rows (the
-        // kernel has 128 registers)
-        constexpr int ZB = 8 / (MT * MT);
-        gv_u32x4_t zb[MT][ZB];
-        auto load_zb = [&](int first) {
+        auto load_batch = [&](int first) {
 #pragma unroll
-            for (int t = 0; t < MT; ++t) {
-                const uint16_t *src = zrow[t] + ((int64_t)ch * 2 * 16 + first) * 256;
-#pragma unroll
-                for (int j = 0; j < ZB; ++j) zb[t][j] = *reinterpret_cast<const gv_u32x4_t *>(src + j * 256);
-            }
+            for (int j = 0; j < ZB; ++j) load_zb(ch, first + j, j);
         };
-        load_zb(0);
+        if (!RING) load_batch(0);
         if (ch + GM_WAVES < n_chunks) {                         // the next chunk's packed bytes
             const uint8_t *src = M.packed + (int64_t)(ch + GM_WAVES) * (16 * BITS);
 #pragma unroll
@@ -640,7 +647,7 @@ void k_qgemm(GemvBatch bt) {
         }
 #pragma unroll
         for (int step = 0; step < 16; ++step) {                 // instruction of the chunk: pairs 4 step .. 4 step + 3 of the lane's 64
-            if (step > 0 && step % ZB == 0) load_zb(step);
+            if (!RING && step > 0 && step % ZB == 0) load_batch(step);
             gv_u32x4_t a = {0u, 0u, 0u, 0u};                    // the unused half of a 16-row workgroup's tile: zeros, no gathers
             if (row_used) {
 #pragma unroll
@@ -651,6 +658,8 @@ void k_qgemm(GemvBatch bt) {
 #pragma unroll
             for (int t = 0; t < MT; ++t)
                 acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, __builtin_bit_cast(gv_bf16x8_t, zb[t][step % ZB]), acc[t], 0, 0, 0);
+            // the slot is free: the activations of ZB instructions later, of the wave's next chunk at the end of this one
+            if (RING) load_zb(step + ZB < 16 ? ch : next_ch, (step + ZB) % 16, step % ZB);
         }
     }
 
