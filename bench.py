@@ -18,8 +18,8 @@ warm-up and two steps each and 10 decode-only passes, and reported as sub-record
 
 Beside the step: N decode-only passes over the set; the decoder's loads and stores without its arithmetic
 (`roofline_decode.ceiling_gb_per_s`: what the memory system gives that access pattern); one encode pass with the
-shortlist on the vector ALU instead of the matrix cores (`roofline.valu_only`); one encode pass with the pruned
-nearest-codeword search (`pruned_search`; same indices, not part of `value` or of a roofline fraction); the fused
+search over the whole codebook on the vector ALU (`roofline.valu_only`); one encode pass through the pruned entry point
+(`pruned_search`; same indices, not part of `value` or of a roofline fraction); the fused
 dequantise-and-multiply for M activation rows, 1 by default (`fused_matmul`; `--matmul 0` skips it); on request the
 polar baseline (`polar_baseline`).
 
@@ -43,8 +43,8 @@ PEAK_FP32_TFLOPS = 157.3          # MI355X vector fp32 (published)
 PEAK_HBM_GBS = 8000.0             # MI355X HBM3E (published)
 PEAK_BF16_TFLOPS = 2500.0         # MI355X dense bf16 matrix cores (published)
 FLOPS_PER_EVAL = 4.0              # one distance evaluation = 2 FMA
-SHORTLIST_UNIT = ("shortlist scores on the bf16 matrix cores (v_mfma_f32_32x32x16_bf16, fp32 operands split exactly into "
-                  "three bf16 pieces); min-reduction, exact fp32 recheck and whole-codebook scans on the vector ALU")
+ENCODE_LIMIT = ("vector-ALU issue in the search (about 830 vector instructions and 64 LDS instructions per 512 pairs: butterflies, "
+                "correctly rounded division, five exact fp32 distances per pair), then the second read of W after the row norms")
 
 
 def build_workload(wl, layers, device):
@@ -194,7 +194,7 @@ def measure_workload(wl, layers, steps, warmup, decode_passes, dev, cb, valu_pat
     pairs_step = sum(m["d_out"] * m["d_in"] // 2 for m in mats)
     full_scan_fraction = float(scans.item()) / sum(m["d_out"] * m["d_in"] // 2 for m in mats[:per_layer])
 
-    # the same encode with the shortlist on the vector ALU (no matrix cores): the path the fp32-ALU roofline describes
+    # the same encode by a search over the whole codebook on the vector ALU: the work the fp32-ALU roofline describes
     valu = None
     if valu_path:
         prev = qamw.set_kernel_path(2)
@@ -207,7 +207,7 @@ def measure_workload(wl, layers, steps, warmup, decode_passes, dev, cb, valu_pat
         finally:
             qamw.set_kernel_path(prev)
         tf = pairs_step * wl.K * FLOPS_PER_EVAL / (ms * 1e-3) / 1e12
-        valu = {"kernel": "qamw_encode with qamw_set_kernel_path(2): shortlist, recheck and scans all on the vector ALU",
+        valu = {"kernel": "qamw_encode with qamw_set_kernel_path(2): a search over the whole codebook, all on the vector ALU",
                 "gpairs_per_s": pairs_step / (ms * 1e-3) / 1e9, "achieved": tf, "peak": PEAK_FP32_TFLOPS,
                 "unit": "TFLOP/s", "frac": tf / PEAK_FP32_TFLOPS, "ms_per_pass": ms}
 
@@ -224,7 +224,6 @@ def measure_workload(wl, layers, steps, warmup, decode_passes, dev, cb, valu_pat
     dec_gbs = dec_bytes / (dec_ms * 1e-3) / 1e9
     ceiling_gbs = dec_bytes_step / (median(probe_ms) * 1e-3) / 1e9
     traffic, traffic_source = measured_traffic(wl.name) if layers == wl.layers else (None, None)
-    mfma_tf = evals * 32.0 / (enc_ms * 1e-3) / 1e12
     rec = {
         "value": pairs / ((enc_ms + cal_ms) * 1e-3) / 1e9,
         "unit": "Gpairs/s",
@@ -244,18 +243,17 @@ def measure_workload(wl, layers, steps, warmup, decode_passes, dev, cb, valu_pat
                    "pass_gb_per_s_median": pass_ms and dec_bytes_step / (median(pass_ms) * 1e-3) / 1e9,
                    "pass_gb_per_s_best": pass_ms and dec_bytes_step / (min(pass_ms) * 1e-3) / 1e9,
                    "pass_frac_of_peak_median": pass_ms and dec_bytes_step / (median(pass_ms) * 1e-3) / 1e9 / PEAK_HBM_GBS},
-        "roofline": {"kernel": "qamw_encode_batch (one launch per layer, %d matrices: row norms + nearest-codeword search)" % per_layer, "bound": "alu",
-                     "unit_doing_the_work": SHORTLIST_UNIT,
-                     "achieved": enc_tflops, "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s",
-                     "frac": enc_tflops / PEAK_FP32_TFLOPS,
-                     "strict_roofline_gpairs_per_s": PEAK_FP32_TFLOPS * 1e3 / FLOPS_PER_EVAL / wl.K,
-                     "traffic": traffic and traffic["encode"] * per_layer, "traffic_source": traffic_source,
-                     "avg_launch_ms": enc_ms / n_launch,
-                     "algorithmic_flops_per_launch": evals * FLOPS_PER_EVAL / n_launch,
-                     # what the shortlist spends on the matrix cores to get there: one 32x32x16 bf16 tile
-                     # (32768 flop) per 1024 evaluations, against the dense bf16 peak
-                     "matrix_core": {"instruction": "v_mfma_f32_32x32x16_bf16", "tflops": mfma_tf,
-                                     "peak": PEAK_BF16_TFLOPS, "frac": mfma_tf / PEAK_BF16_TFLOPS},
+        # What the call cannot do without is to read W and write the packed rows: priced against HBM.  The distances that the
+        # cell table makes unnecessary are not work done; their count over the time is given for comparison with an encoder
+        # that evaluates all K of them, and is not a fraction of any peak.
+        "roofline": {"kernel": "qamw_encode_batch_ws (two launches per layer of %d matrices: cell table + row norms, then the search)" % per_layer,
+                     "bound": "hbm", "limited_by": ENCODE_LIMIT,
+                     "achieved": enc_in_bytes / (enc_ms * 1e-3) / 1e9, "peak": PEAK_HBM_GBS, "unit": "GB/s",
+                     "frac": enc_in_bytes / (enc_ms * 1e-3) / 1e9 / PEAK_HBM_GBS,
+                     "whole_codebook_equivalent_tflops": enc_tflops,
+                     "traffic": traffic and traffic.get("encode") and traffic["encode"] * per_layer, "traffic_source": traffic_source,
+                     "avg_call_ms": enc_ms / n_launch,
+                     "algorithmic_bytes_per_call": enc_in_bytes / n_launch,
                      "valu_only": valu},
         "roofline_decode": {"kernel": "qamw_decode_batch (one launch per %d layers, %d matrices)" % (lpd, lpd * per_layer), "bound": "hbm",
                             "achieved": dec_gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": dec_gbs / PEAK_HBM_GBS,
@@ -410,9 +408,8 @@ def polar_leg(wl, mats, dev):
 
 
 def pruned_leg(wl, mats, cb, cb_host, dev):
-    """The encoder with the pruned nearest-codeword search (same indices, far fewer distance evaluations): one encode
-    pass over the set with the pair scales already calibrated.  Not part of `value` or the roofline: the roofline
-    accounts a search over all K codewords."""
+    """The pruned entry point (same indices from a table in hand, or with scratch from one made on the device): one encode
+    pass over the set with the pair scales already calibrated.  Not part of `value` or the roofline."""
     import torch
 
     from paper_2605_26339_amd import qamw
@@ -422,13 +419,15 @@ def pruned_leg(wl, mats, cb, cb_host, dev):
     table, longest, overflow = qamw.search_grid(cb_host, wl.bits)
     build_s = time.perf_counter() - t_b
     grid = torch.from_numpy(table).to(dev)
-    first = [qamw.encode(m["W"], cb, wl.bits, wl.block, chan_scale=m["s"], signs=m["sg"], pair_sigma=m["sigma"])
+    scans_w, scans_p = (torch.zeros(1, dtype=torch.int64, device=dev) for _ in range(2))
+    first = [qamw.encode(m["W"], cb, wl.bits, wl.block, chan_scale=m["s"], signs=m["sg"], pair_sigma=m["sigma"], full_scans=scans_w)
              for m in mats[:per_layer]]                          # the whole-codebook encoder's output, first layer
-    scans_p = torch.zeros(1, dtype=torch.int64, device=dev)
-    for m in mats[:per_layer]:
-        qamw.encode_pruned(m["W"], cb, grid, wl.bits, wl.block, chan_scale=m["s"], signs=m["sg"], pair_sigma=m["sigma"],
-                           out=(m["packed"], m["norms"]), full_scans=scans_p)
-    same = all(torch.equal(m["packed"], f[0]) and torch.equal(m["norms"], f[1]) for m, f in zip(mats[:per_layer], first))
+    same = True
+    for kw in ({"full_scans": scans_p}, {}):                     # from the table in hand; from one made on the device
+        for m in mats[:per_layer]:
+            qamw.encode_pruned(m["W"], cb, grid, wl.bits, wl.block, chan_scale=m["s"], signs=m["sg"], pair_sigma=m["sigma"],
+                               out=(m["packed"], m["norms"]), **kw)
+        same = same and all(torch.equal(m["packed"], f[0]) and torch.equal(m["norms"], f[1]) for m, f in zip(mats[:per_layer], first))
 
     def one_pass():
         for m in mats:
