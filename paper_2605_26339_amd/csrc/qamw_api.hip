@@ -511,7 +511,7 @@ static int matmul_batch_impl(const qamw_matmul_item *items, int n_items, int x_d
     if (m > QAMW_MATMUL_TILE_ROWS) {
         const size_t fit = workspace_bytes / per_row / 32 * 32;
         const int most = fit < (size_t)m ? (int)fit : m, tiles = most > 0 ? (m + most - 1) / most : m;
-        if (qamw::matmul_wide((m + tiles - 1) / tiles)) tile = (m + tiles - 1) / tiles;
+        if (qamw::matmul_wide(its, n_items, (m + tiles - 1) / tiles)) tile = (m + tiles - 1) / tiles;
     }
     qamw::Problem p = make_problem(items[0].d_out, items[0].d_in, nullptr, nullptr, nullptr, codebook, bits, hadamard_block, stream);
     const size_t x_elem = x_dtype == QAMW_DTYPE_F32 ? sizeof(float) : sizeof(uint16_t);

@@ -81,7 +81,6 @@ bool polar_encode_launchable(const void *W, int dtype, int64_t ldw, const Proble
 hipError_t launch_encode_polar(const void *W, int dtype, int64_t ldw, const Problem &p, const float *levels, int bits_a,
                                int bits_p, float *norms, bool norms_ready, uint8_t *packed);
 bool matmul_supported(const Problem &p, int m);
-bool matmul_wide(int m);                 // a launch of m activation rows goes to the kernel for many rows
 size_t matmul_workspace_bytes(int d_in, int d_out, int m);
 constexpr int QAMW_MATMUL_MAX_BATCH = 16;
 struct MatmulItem {
@@ -95,6 +94,7 @@ struct MatmulItem {
     int64_t ldy;
     int d_out, d_in;
 };
+bool matmul_wide(const MatmulItem *items, int n, int m);   // m activation rows at once go to the kernel for many rows
 hipError_t launch_matmul_batch(const MatmulItem *items, int n, int xdtype, int m, const Problem &p, void *workspace, int variant);
 size_t lloyd_workspace_bytes(int K);          // with room for the cell table and the workgroups' sums
 size_t lloyd_least_workspace_bytes(int K);    // what the search over all points needs

@@ -708,7 +708,6 @@ void k_qgemm(GemvBatch bt) {
 // kernels computes it; that is why the kernel keeps two accumulators.
 constexpr int GW_ROWS = 128;               // weight rows of a workgroup
 constexpr int GW_WAVES = 8, GW_THREADS = GW_WAVES * WAVE;
-constexpr int GW_MIN_M = 192;              // more activation rows than this
 constexpr int GW_CUS = 256;                // one workgroup per CU at a time
 constexpr int GW_STAGE = 4;                // matrix instructions of depth per stage
 
@@ -948,11 +947,22 @@ bool matmul_supported(const Problem &p, int m) {
     return m >= 1;
 }
 
-// Whether a tile of m activation rows is better taken whole, by the wide kernel.  Up to three tiles of 64 the smaller kernel, once per tile, is
-// sooner done: a wide workgroup walks all columns, 0.8 us per 64 of them, whatever the number of rows (4096 x 4096: 54 us
-// in three tiles, 70 in four, 63-65 wide; 1024 x 2048: 39, 51, 39; 4096 x 11008: 108, 142, 142; 11008 x 4096, the other way
-// round from three tiles on: 78, 103, 65).
-bool matmul_wide(int m) { return m > GW_MIN_M; }
+// Whether m activation rows are better taken whole, by the wide kernel, than 64 at a time.  A wide workgroup walks all columns,
+// 0.8 us per 64 of them, whatever the number of rows, so up to three tiles of 64 the smaller kernel is sooner done; with four it
+// still is where the columns are many and the wide tiles leave half of the chip idle.  In us, four tiles / wide, 256 rows at 11
+// bits: 4096 x 4096 61.9 / 64.2 (7 bits 55.2 / 60.2), 4096 x 11008 124.7 / 142.2 (104.4 / 131.6), 2048 x 5632 73.9 / 82.6; but
+// 1024 x 2048 46.0 / 39.3, 11008 x 4096 91.9 / 64.8; five tiles, 300 rows: 76.6 / 64.9, 154 / 142, 91.9 / 83.3.
+bool matmul_wide(const MatmulItem *items, int n, int m) {
+    if (m <= 3 * GM_MAX_M) return false;
+    if (m > 4 * GM_MAX_M) return true;
+    int64_t groups = 0;
+    bool deep = true;
+    for (int i = 0; i < n; ++i) {
+        groups += (int64_t)((items[i].d_out + GW_ROWS - 1) / GW_ROWS) * ((m + 127) / 128);
+        deep = deep && items[i].d_in >= 4096;
+    }
+    return !(deep && 2 * groups <= GW_CUS);
+}
 
 size_t matmul_workspace_bytes(int d_in, int d_out, int m) {
     (void)d_out;

@@ -75,3 +75,13 @@ def test_wide_batch_equals_single_products():
     assert all(torch.equal(a, b) for a, b in zip(Y, before))
     assert qamw.lib().qamw_matmul_batch(items[0], len(shapes), items[3], m, C.c_void_p(cb.data_ptr()), bits, block,
                                         C.c_void_p(ws.data_ptr()), need - 1, None) == qamw.ERR_INVALID_ARG
+
+
+# 193 to 256 rows: in tiles of 64 where the rows are long and the wide tiles few, wide otherwise; both sides of the three lines
+@pytest.mark.parametrize("d_out,d_in,m", [(130, 4096, 193), (130, 3840, 193), (8192, 4096, 200), (8193, 4096, 200), (4096, 4352, 256), (4096, 4352, 257)])
+def test_either_kernel_around_four_tiles(d_out, d_in, m):
+    say(f"[wide] four tiles {d_out}x{d_in} m={m}")
+    X, packed, norms, s, sg, sigma, cb = _product(m, d_out, d_in, m, 7, torch.bfloat16)
+    kw = dict(chan_scale=s, signs=sg, pair_sigma=sigma)
+    least = torch.empty(qamw.matmul_workspace_bytes(d_in, d_out, m), dtype=torch.uint8, device="cuda")
+    assert torch.equal(qamw.matmul(X, packed, norms, cb, 7, 128, **kw), qamw.matmul(X, packed, norms, cb, 7, 128, workspace=least, **kw))
