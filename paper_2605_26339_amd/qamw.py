@@ -180,8 +180,8 @@ def normalised_pairs(W, block: int, chan_scale=None, signs=None, pair_sigma=None
     if W.dim() != 2 or W.stride(1) != 1:
         raise ValueError("W must be 2-D with unit column stride")
     d_out, d_in = W.shape
-    pairs = torch.empty((d_out, d_in // 2, 2), dtype=torch.float32, device=W.device)
-    norms = torch.empty(d_out, dtype=torch.float32, device=W.device)
+    pairs = _empty((d_out, d_in // 2, 2), torch.float32, W.device, stream)
+    norms = _empty(d_out, torch.float32, W.device, stream)
     _check(lib().qamw_normalised_pairs(_ptr(W), _dtype_code(W), d_out, d_in, W.stride(0), _ptr(chan_scale), _ptr(signs),
                                        _ptr(pair_sigma), block, _ptr(pairs), _ptr(norms), _stream(stream)),
            "qamw_normalised_pairs")
@@ -194,11 +194,13 @@ def lloyd_device(samples, init_codebook, bits: int, max_iters: int = 200, tol: f
     import torch
 
     _require_cuda(samples, init_codebook)
-    samples = samples.contiguous()
-    cb = init_codebook.to(torch.float32).contiguous().clone()
     need = C.c_size_t()
     _check(lib().qamw_lloyd_workspace_bytes(bits, C.byref(need)), "qamw_lloyd_workspace_bytes")
-    ws = torch.empty(need.value, dtype=torch.uint8, device=samples.device)
+    cb = _empty(init_codebook.shape, torch.float32, init_codebook.device, stream)
+    ws = _empty(need.value, torch.uint8, samples.device, stream)
+    with torch.cuda.stream(_call_stream(stream, samples.device)):   # the copies too belong on the call's stream
+        samples = samples.contiguous()
+        cb.copy_(init_codebook)
     mse, it = C.c_double(), C.c_int()
     _check(lib().qamw_lloyd_device(_ptr(samples), samples.shape[0], bits, _ptr(cb), max_iters, tol, _ptr(ws), need.value,
                                    C.byref(mse), C.byref(it), _stream(stream)), "qamw_lloyd_device")
@@ -236,6 +238,30 @@ def _stream(stream):
     return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
+def _call_stream(stream, device):
+    """The torch stream of a call that names one, None for the current stream."""
+    import torch
+
+    if stream is None or stream == torch.cuda.current_stream(device):
+        return None
+    return stream if isinstance(stream, torch.cuda.Stream) else torch.cuda.ExternalStream(stream.cuda_stream, device=device)
+
+
+def _empty(shape, dtype, device, stream):
+    """Memory that a call makes for itself or returns, for use on `stream`.  It is allocated on that stream: the allocator
+    hands a block that was freed on the current stream out at once, while kernels there may still be using it, and nothing
+    makes another stream wait for them.  The current stream is recorded, so that the caller may use and drop a result there."""
+    import torch
+
+    side = _call_stream(stream, device)
+    if side is None:
+        return torch.empty(shape, dtype=dtype, device=device)
+    with torch.cuda.stream(side):
+        t = torch.empty(shape, dtype=dtype, device=device)
+    t.record_stream(torch.cuda.current_stream(device))
+    return t
+
+
 def _dtype_code(W):
     import torch
 
@@ -268,9 +294,9 @@ def calibrate_sigma(W, block: int, chan_scale=None, signs=None, max_rows: int = 
     _require_cuda(W, chan_scale, signs, workspace, out)
     d_out, d_in = W.shape
     if workspace is None:
-        workspace = torch.empty(calibrate_workspace_bytes(d_in, d_out, max_rows), dtype=torch.uint8, device=W.device)
+        workspace = _empty(calibrate_workspace_bytes(d_in, d_out, max_rows), torch.uint8, W.device, stream)
     if out is None:
-        out = torch.empty(d_in // 2, dtype=torch.float32, device=W.device)
+        out = _empty(d_in // 2, torch.float32, W.device, stream)
     _check(lib().qamw_calibrate_sigma(_ptr(W), _dtype_code(W), d_out, d_in, W.stride(0), _ptr(chan_scale), _ptr(signs),
                                       block, max_rows, _ptr(workspace), workspace.numel(), _ptr(out), _stream(stream)),
            "qamw_calibrate_sigma")
@@ -297,20 +323,11 @@ def encode_workspace_bytes(bits: int) -> int:
     return int(out.value)
 
 
-def _scratch(nbytes: int, device, stream):
-    """Device scratch for one call.  Its memory goes back to torch's allocator when the caller drops it, which is safe
-    on the stream it was allocated on; on another stream the allocator is told to wait for that stream's work."""
+def _encode_scratch(bits: int, device, stream):
     import torch
 
-    ws = torch.empty(nbytes, dtype=torch.uint8, device=device)
-    if stream is not None and stream != torch.cuda.current_stream(device):
-        ws.record_stream(stream)
-    return ws
-
-
-def _encode_scratch(bits: int, device, stream):
     n = encode_workspace_bytes(bits) if 1 <= bits <= 12 else 0
-    return (_scratch(n, device, stream), n) if n else (None, 0)
+    return (_empty(n, torch.uint8, device, stream), n) if n else (None, 0)
 
 
 def encode(W, codebook, bits: int, block: int, chan_scale=None, signs=None, pair_sigma=None, out=None, stream=None,
@@ -326,8 +343,8 @@ def encode(W, codebook, bits: int, block: int, chan_scale=None, signs=None, pair
     d_out, d_in = W.shape
     rb = packed_row_bytes(d_in, bits)
     if out is None:
-        packed = torch.empty((d_out, rb), dtype=torch.uint8, device=W.device)
-        norms = torch.empty(d_out, dtype=torch.float32, device=W.device)
+        packed = _empty((d_out, rb), torch.uint8, W.device, stream)
+        norms = _empty(d_out, torch.float32, W.device, stream)
     else:
         packed, norms = out
     if full_scans is not None:
@@ -378,8 +395,8 @@ def encode_pruned(W, codebook, grid, bits: int, block: int, chan_scale=None, sig
     d_out, d_in = W.shape
     rb = packed_row_bytes(d_in, bits)
     if out is None:
-        packed = torch.empty((d_out, rb), dtype=torch.uint8, device=W.device)
-        norms = torch.empty(d_out, dtype=torch.float32, device=W.device)
+        packed = _empty((d_out, rb), torch.uint8, W.device, stream)
+        norms = _empty(d_out, torch.float32, W.device, stream)
     else:
         packed, norms = out
     ws, n = _encode_scratch(bits, W.device, stream)
@@ -401,8 +418,8 @@ def encode_polar(W, levels, bits_a: int, bits_p: int, block: int, chan_scale=Non
     d_out, d_in = W.shape
     rb = packed_row_bytes(d_in, bits_a + bits_p)
     if out is None:
-        packed = torch.empty((d_out, rb), dtype=torch.uint8, device=W.device)
-        norms = torch.empty(d_out, dtype=torch.float32, device=W.device)
+        packed = _empty((d_out, rb), torch.uint8, W.device, stream)
+        norms = _empty(d_out, torch.float32, W.device, stream)
     else:
         packed, norms = out
     _check(lib().qamw_encode_polar(_ptr(W), _dtype_code(W), d_out, d_in, W.stride(0), _ptr(chan_scale), _ptr(signs),
@@ -419,7 +436,7 @@ def decode(packed, row_norms, d_in: int, codebook, bits: int, block: int, chan_s
     _require_cuda(packed, row_norms, codebook, chan_scale, signs, pair_sigma)
     d_out = row_norms.shape[0]
     if out is None:
-        out = torch.empty((d_out, d_in), dtype=torch.float32 if f32 else torch.bfloat16, device=packed.device)
+        out = _empty((d_out, d_in), torch.float32 if f32 else torch.bfloat16, packed.device, stream)
     fn = lib().qamw_decode_f32 if f32 else lib().qamw_decode
     _check(fn(_ptr(packed), _ptr(row_norms), d_out, d_in, _ptr(chan_scale), _ptr(signs), _ptr(pair_sigma),
               _ptr(codebook), bits, block, _ptr(out), out.stride(0), _stream(stream)),
@@ -458,9 +475,9 @@ def matmul(X, packed, row_norms, codebook, bits: int, block: int, chan_scale=Non
     m, d_in = X.shape
     d_out = row_norms.shape[0]
     if workspace is None:
-        workspace = _scratch(_matmul_scratch_bytes(d_in, d_out, m), X.device, stream)
+        workspace = _empty(_matmul_scratch_bytes(d_in, d_out, m), torch.uint8, X.device, stream)
     if out is None:
-        out = torch.empty((m, d_out), dtype=torch.float32, device=X.device)
+        out = _empty((m, d_out), torch.float32, X.device, stream)
     _check(lib().qamw_matmul(_ptr(X), _dtype_code(X), m, X.stride(0), _ptr(packed), _ptr(row_norms), d_out, d_in,
                              _ptr(chan_scale), _ptr(signs), _ptr(pair_sigma), _ptr(codebook), bits, block,
                              _ptr(workspace), workspace.numel() * workspace.element_size(), _ptr(out), out.stride(0),
