@@ -209,10 +209,13 @@ typedef struct qamw_encode_item {
 int qamw_encode_batch(const qamw_encode_item *items, int n_items, int dtype, const float *codebook, int bits,
                       int hadamard_block, void *stream);
 
-/* qamw_encode / qamw_encode_batch with device scratch: the same bytes and norms, several times sooner.  With
+/* qamw_encode / qamw_encode_batch with device scratch: the same bytes and norms, several times sooner where the codewords
+ * are spread as a Lloyd codebook's are and most pairs lie among them, whatever their common scale.  With
  * qamw_encode_workspace_bytes() bytes (128 KB at 11 bits; 0 = scratch is of no use at these bits) the call first makes, on
- * the device, a table of the codewords that can be nearest to a point of each cell of a grid -- from this call's codebook,
- * every time -- and then searches only those.  workspace: device, 16-byte aligned, owned by the caller until the call's
+ * the device, a table of the codewords that can be nearest to a point of each cell of a grid that covers them -- from this
+ * call's codebook, every time -- and then searches only those.  Pairs far outside the codebook, or among codewords crowded
+ * in a few places, are decided without the table; a call in which most are takes up to a quarter longer than without
+ * scratch, and 10 us.  workspace: device, 16-byte aligned, owned by the caller until the call's
  * work on the stream has finished, contents unspecified afterwards; calls that overlap need one each.  NULL or too small,
  * or a shape outside the fast kernels' range: as qamw_encode / qamw_encode_batch.  (The counting qamw_encode_stats always
  * searches the whole codebook.)

@@ -36,7 +36,8 @@ def hipcc() -> str:
 # scores need no copies out of the accumulation register file.
 EXTRA_FLAGS = {"qamw_encode_fast.hip": ["-fno-honor-nans"],
                "qamw_encode_polar.hip": ["-fno-honor-nans"],
-               "qamw_encode_cells.hip": ["-fno-honor-nans"],
+               "qamw_encode_cells.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form=1"],
+               "qamw_lloyd.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
                "qamw_encode_mfma.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 
 

@@ -1,8 +1,14 @@
 // The cell table of the pruned nearest-codeword search (Sec. 3.1 / Sec. 3.5), made on the device: shared by the encoder
 // and the device's codebook training.
 //
-// The square [-4, 4)^2 is cut into G x G cells; a cell's record lists, in ascending index order, every codeword that can be
+// A square [-R, R)^2 is cut into G x G cells; a cell's record lists, in ascending index order, every codeword that can be
 // nearest to a point of the cell, at most five, or says that the whole codebook has to be searched.
+//
+// R follows the codebook's scale: 4 where the codewords lie as those of a Lloyd codebook of the unit Gaussian (which holds
+// 99.99 % of the pairs such a codebook is for), in proportion to their mean |coordinate| otherwise, rounded to four
+// significant bits.  Every workgroup that makes a part of the table finds the same R, the first leaves it in the table
+// (cells_put_half).  A fixed square is of no use to a codebook of another scale: 4096 x 4096 bf16, 2048 points, codebook and
+// pairs / 16: 3960 us with [-4, 4)^2, where the search over the whole codebook takes 615; 36 so.
 //
 // Which codewords a cell lists.  For two codewords a and c the difference |x - c|^2 - |x - a|^2 is linear in x, so on a
 // box of half-width w around m it is at least |m - c|^2 - |m - a|^2 - 2 w (|c.x - a.x| + |c.y - a.y|).  c is left out
@@ -16,7 +22,6 @@
 
 namespace qamw {
 
-constexpr float CELLS_HALF = 4.0f;                             // the table covers [-4, 4)^2 less a border of one cell
 constexpr int CELLS_LIST = 5;                                  // candidates of a record
 constexpr uint32_t CELLS_SCAN = 0x80000000u;                   // in the record's upper word: decided by the whole codebook
 constexpr uint32_t CELLS_MORE = 1u;                            // in its lower word: more than three candidates
@@ -25,6 +30,23 @@ constexpr uint32_t CELLS_MORE = 1u;                            // in its lower w
 // Cells per side.  Four cells per codeword spacing at the centre of a Lloyd codebook keep the lists within a record;
 // the LDS holds 128 x 128 records beside 2048 codewords.
 constexpr int cells_side(int bits) { return bits >= 11 ? 128 : bits == 10 ? 96 : 64; }
+
+// R over the sum of the magnitudes of n = min(K, CP_SAMPLE) codewords' coordinates: 4 over 2 n times the mean |coordinate| of
+// a Lloyd codebook of the unit Gaussian with K = 2^bits points (qamw_train_codebook; 3 % more or less with the samples and
+// the iterations).
+constexpr int CP_SAMPLE = 256;                                 // 32 evenly spread runs of eight: a cache line each
+inline float cells_half_per_sum(int bits) {
+    constexpr float mean[12] = {0.53f, 0.716f, 0.82f, 0.905f, 0.99f, 1.03f, 1.07f, 1.10f, 1.113f, 1.122f, 1.125f, 1.125f};
+    const int n = 1 << bits < CP_SAMPLE ? 1 << bits : CP_SAMPLE;
+    return 4.0f / (mean[bits - 1] * 2.0f * (float)n);
+}
+// R is kept in the first record, a border cell's, whose candidates do not matter: its upper 12 bits as the first index.
+__device__ __forceinline__ uint32_t cells_put_half(float half) { return (__float_as_uint(half) >> 20) << 3; }
+__device__ __forceinline__ float cells_half(const uint2 *table) { return __uint_as_float((table[0].x >> 3) << 20); }
+// Cells per unit length, G / 2R, one rounding or two off (the table's slack is 2^-19 of R).
+template <int G> __device__ __forceinline__ float cells_inv_width(float half) {
+    return 0.5f * G * __builtin_amdgcn_rcpf(__uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(half))));
+}
 
 // ------------------------------------------------------------------------------------------------ the table
 constexpr int CP_THREADS = 256;
@@ -57,8 +79,8 @@ __device__ __forceinline__ void wave_nearest(float &d, float2 &c) {
 //   Bound by latency, one workgroup per CU: hence minima and prefix sums by DPP moves and ballots instead of shuffles, and
 // LDS reads four to eight at a time (2048 points, 16 x 16 regions: 8.2 us; 14 x 14 with shuffles and one read at a time 11.3).
 template <int G>
-__device__ __forceinline__ void cells_build_region(const float *codebook, int K, uint2 *table, int region, const int *stopped_at = nullptr,
-                                                   int t = 0) {
+__device__ __forceinline__ void cells_build_region(const float *codebook, int K, float half_per_sum, uint2 *table, int region,
+                                                   const int *stopped_at = nullptr, int t = 0) {
     __shared__ float2 reg_c[CP_REGION_LIST];
     __shared__ uint16_t reg_i[CP_REGION_LIST];
     __shared__ float2 blk_c[CP_WAVES][CP_BLOCK_LIST];
@@ -67,8 +89,6 @@ __device__ __forceinline__ void cells_build_region(const float *codebook, int K,
     __shared__ float red_d[CP_WAVES];
     __shared__ float2 red_c[CP_WAVES];
     __shared__ int red_n[CP_WAVES];
-    constexpr float h = 2.0f * CELLS_HALF / G;
-    constexpr float slack = CELLS_HALF / 524288.0f;            // the fp32 roundings of the centres and of the cell lookup
     const int lane = threadIdx.x & (WAVE - 1), wid = threadIdx.x >> 6;
     const float2 *cbk = reinterpret_cast<const float2 *>(codebook);
     const int x0 = (region % (G / 8)) * 8, y0 = (region / (G / 8)) * 8;
@@ -78,9 +98,21 @@ __device__ __forceinline__ void cells_build_region(const float *codebook, int K,
     float2 c[CP_PER_THREAD];
     float d2[CP_PER_THREAD];
     const int stop = stopped_at ? *stopped_at : t;
+    float2 sample[CP_SAMPLE / WAVE];                            // the same in every wave of every workgroup
+    const int spread = max(K / CP_SAMPLE, 1);
+#pragma unroll
+    for (int q = 0; q < CP_SAMPLE / WAVE; ++q) sample[q] = cbk[min(((lane >> 3) + 8 * q) * 8 * spread + (lane & 7), K - 1)];
 #pragma unroll
     for (int j = 0; j < CP_PER_THREAD; ++j) c[j] = cbk[j < per && first + j < K ? first + j : 0];
     if (stop < t) return;
+    float s = 0.0f;
+#pragma unroll
+    for (int q = 0; q < CP_SAMPLE / WAVE; ++q) s += q * WAVE + lane < K ? fabsf(sample[q].x) + fabsf(sample[q].y) : 0.0f;
+    s = wave_add(s) * half_per_sum;
+    // squares of distances inside a cell stay normal numbers
+    const float half = __uint_as_float((__float_as_uint(fminf(fmaxf(s, 0x1p-40f), 0x1p40f)) + 0x80000u) & 0xFFF00000u);
+    const float h = 2.0f * half / G;
+    const float slack = half * 0x1p-19f;                        // the fp32 roundings of the centres and of the cell lookup
     float mx = ((float)x0 + 3.5f - 0.5f * G) * h, my = ((float)y0 + 3.5f - 0.5f * G) * h, w = 4.0f * h + slack;
     float nd = 3.0e38f;
     float2 nc = make_float2(0.0f, 0.0f);
@@ -253,17 +285,17 @@ __device__ __forceinline__ void cells_build_region(const float *codebook, int K,
             r.x = (i5[0] << 3) | (i5[1] << 15) | (i5[2] << 27) | (total > 3 ? CELLS_MORE : 0u);
             r.y = (i5[2] >> 5) | (i5[3] << 7) | (i5[4] << 19);
         }
+        if (ix == 0 && iy == 0) r.x = cells_put_half(half);
         table[iy * G + ix] = r;
     }
 }
 
 
 // ------------------------------------------------------------------------------------------------ the search
-// Byte offset, from 8 times `base`, of the record of the cell that holds (x0, x1).  The lookup rounds x G / 8 + G / 2 to the
-// nearest integer and clamps it to the border, whose records say "whole codebook".
+// Byte offset from table_at of the record of the cell that holds (x0, x1); inv_h: cells per unit length, G / 2R.  The lookup
+// rounds x inv_h + G / 2 to the nearest integer and clamps it to the border, whose records say "whole codebook".
 constexpr uint32_t CELLS_MAGIC_BITS = 0x4B000000u;             // 2^23: adding it rounds to an integer, left in the low bits
-template <int G> __device__ __forceinline__ uint32_t cells_record_at(float x0, float x1, uint32_t table_at) {
-    constexpr float inv_h = G / (2.0f * CELLS_HALF);
+template <int G> __device__ __forceinline__ uint32_t cells_record_at(float x0, float x1, float inv_h, uint32_t table_at) {
     constexpr float magic = 8388608.0f;
     const float vx = fminf(fmaxf(__builtin_fmaf(x0, inv_h, magic + G / 2), magic), magic + (G - 1));
     const float vy = fminf(fmaxf(__builtin_fmaf(x1, inv_h, magic + G / 2), magic), magic + (G - 1));
@@ -294,5 +326,154 @@ template <bool FIVE> __device__ __forceinline__ unsigned cells_nearest(uint2 rec
     o = (d1 == m) ? o1 : o;                                     // the lowest index among equals: the candidates ascend
     return (d0 == m) ? o0 : o;
 }
+
+// ------------------------------------------------------------------------------------------------ without the table
+typedef float cells_f32x16_t __attribute__((ext_vector_type(16)));
+typedef __bf16 cells_bf16x8_t __attribute__((ext_vector_type(8)));
+typedef uint32_t cells_u32x4_t __attribute__((ext_vector_type(4)));
+
+// (lower half of the wave: a there, upper half: b of the lane 32 below) and (a of the lane 32 above, b)
+__device__ __forceinline__ void half_swap(float a, float b, float &lo, float &hi) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    lo = __uint_as_float(r[0]);
+    hi = __uint_as_float(r[1]);
+}
+// the value of the lane whose number differs in bit 5
+__device__ __forceinline__ float other_half(float v, int hs) {
+    float lo, hi;
+    half_swap(v, v, lo, hi);
+    return hs ? lo : hi;
+}
+__device__ __forceinline__ int other_half(int v, int hs) { return __float_as_int(other_half(__int_as_float(v), hs)); }
+
+// Nearest codewords of P points per lane among all K (a power of two; the codebook in LDS at byte address cb_at): idx[p] = 8
+// times the index of the nearest to (x0[p], x1[p]) by exact fp32 squared distance, lowest index on ties.  All lanes call it;
+// a point with its bit of `wanted` clear gets some index below K.
+//   K >= 64.  A shortlist by matrix instructions, with the operands of the whole-codebook
+// encoder (qamw_encode_mfma.hip: scores |c|^2 - 2 x.c from exact bf16 pieces, error at most 2^-19 (|c| + n1)^2, n1 = |x0| +
+// |x1|), built from registers: point block 2 p + b are the points p of the lanes of half b.  A chunk is the 16 rows of each of
+// CH 32-codeword blocks that a lane holds (two halve the bookkeeping of the loop, one halves the exact distances after it).  bd, the smallest exact distance in the best chunk, bounds the score of whatever is
+// nearest: it is not in another chunk if the least score there exceeds bd - |x|^2 by more than the score's error for a
+// codeword within sqrt(bd) of x and the roundings.  Else the whole codebook is scanned.  The margin has no scale of its own;
+// outside 1e-30 .. 1e30 the products of the pieces are
+// no longer exact or overflow, so those points are scanned.
+//   For pairs that no table helps.  The whole call, 4096 x 4096 bf16, pairs three times as wide as the codebook: 2048 points,
+// one scan after the other 1440 us, so 670 (the encoder without a table 575 to 600); 128 points 692 us, so 121 (102).
+template <int P, int CH>
+__device__ __forceinline__ void nearest_of_all(const float (&x0)[P], const float (&x1)[P], unsigned (&idx)[P], unsigned wanted, uint32_t cb_at,
+                                               int K, int lane) {
+    constexpr float BIG = 3.0e38f;
+    auto dist = [&](float a, float b, int ci) {
+        const lds_f32x2_t c = lds_read<lds_f32x2_t>(cb_at + 8u * (uint32_t)ci);
+        return exact_dist2(a, b, make_float2(c[0], c[1]));
+    };
+    const int j = lane & 31, hs = lane >> 5;
+    cells_bf16x8_t bop[2 * P];
+    float m1[2 * P], m2[2 * P];
+    int best[2 * P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        float v[2];
+        half_swap(x0[p], x1[p], v[0], v[1]);
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            uint32_t h, m, l;
+            split3(-2.0f * v[b], h, m, l);
+            const cells_u32x4_t u = {pack2(h, m), pack2(h, l), pack2(m, h), 0x3F803F80u};   // h m h l m h 1 1
+            bop[2 * p + b] = __builtin_bit_cast(cells_bf16x8_t, u);
+            m1[2 * p + b] = m2[2 * p + b] = BIG;
+            best[2 * p + b] = 0;
+        }
+    }
+    cells_f32x16_t zero;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) zero[i] = 0.0f;
+#pragma unroll 1
+    for (int cb = 0; cb < K; cb += 32 * CH) {
+        cells_bf16x8_t aop[CH];
+#pragma unroll
+        for (int u = 0; u < CH; ++u) {
+            const lds_f32x2_t c = lds_read<lds_f32x2_t>(cb_at + 8u * (uint32_t)(cb + 32 * u + j));
+            uint32_t h, m, l, nh, nm, nl;
+            split3(hs ? c[1] : c[0], h, m, l);
+            split3(__builtin_fmaf(c[1], c[1], c[0] * c[0]), nh, nm, nl);
+            const cells_u32x4_t ua = {pack2(h, h), pack2(m, h), pack2(m, l), hs ? pack2(nl, 0u) : pack2(nh, nm)};
+            aop[u] = __builtin_bit_cast(cells_bf16x8_t, ua);
+        }
+#pragma unroll
+        for (int q = 0; q < 2 * P; ++q) {
+            auto min3 = [](float a, float b, float c3) { return __builtin_fminf(__builtin_fminf(a, b), c3); };
+            float part[2 * CH];
+#pragma unroll
+            for (int u = 0; u < CH; ++u) {
+                const cells_f32x16_t d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aop[u], bop[q], zero, 0, 0, 0);
+                const float t0 = min3(d[0], d[1], d[2]), t1 = min3(d[3], d[4], d[5]), t2 = min3(d[6], d[7], d[8]);
+                const float t3 = min3(d[9], d[10], d[11]), t4 = min3(d[12], d[13], d[14]);
+                part[2 * u] = min3(t0, t1, t2);
+                part[2 * u + 1] = min3(t3, t4, d[15]);
+            }
+            const float least = CH == 1 ? __builtin_fminf(part[0], part[1]) : __builtin_fminf(min3(part[0], part[1], part[2]), part[2 * CH - 1]);
+            best[q] = least < m1[q] ? cb : best[q];
+            m2[q] = __builtin_amdgcn_fmed3f(m1[q], m2[q], least);              // m1 <= m2: the second smallest
+            m1[q] = __builtin_fminf(m1[q], least);
+        }
+    }
+    unsigned unsafe = 0;
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        float ax[2], ay[2];
+        half_swap(x0[p], x0[p], ax[0], ax[1]);
+        half_swap(x1[p], x1[p], ay[0], ay[1]);
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            const int q = 2 * p + b;
+            const float o1 = other_half(m1[q], hs), o2 = other_half(m2[q], hs);
+            const int ob = other_half(best[q], hs);
+            const bool other = o1 < m1[q];
+            const float least_elsewhere = fminf(fmaxf(m1[q], o1), fminf(m2[q], o2));
+            const int first = (other ? ob : best[q]) + 4 * (other ? hs ^ 1 : hs);   // the chunk's rows: first + 8 q + t
+            float bd = BIG;
+            int bi = first;
+#pragma unroll
+            for (int i = 0; i < 8 * CH; ++i) {                  // this lane's half of them, ascending
+                const int ci = first + 32 * (i >> 3) + 16 * hs + 8 * ((i >> 2) & 1) + (i & 3);
+                const float dd = dist(ax[b], ay[b], ci);
+                if (dd < bd) {
+                    bd = dd;
+                    bi = ci;
+                }
+            }
+            const float od = other_half(bd, hs);
+            const int oi = other_half(bi, hs);
+            if (od < bd || (od == bd && oi < bi)) {
+                bd = od;
+                bi = oi;
+            }
+            const float n1 = fabsf(ax[b]) + fabsf(ay[b]), xx = __builtin_fmaf(ay[b], ay[b], ax[b] * ax[b]);
+            const float reach = 2.0f * n1 + sqrtf(bd);
+            const float margin = 4e-6f * reach * reach;         // 2^-19 (|c| + n1)^2 with |c| <= n1 + sqrt(bd), and 2e-6 (bd + xx)
+            const bool safe = least_elsewhere - (bd - xx) > margin && margin > 1e-30f && margin < 1e30f;
+            if (hs == b) {
+                idx[p] = 8u * (unsigned)bi;
+                if (!safe) unsafe |= 1u << p;
+            }
+        }
+    }
+    unsafe &= wanted;
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        unsigned long long mask = __ballot((unsafe >> p) & 1u);
+        while (mask) {
+            const int src = __ffsll((long long)mask) - 1;
+            mask &= mask - 1;
+            const int bi = wave_exact_scan(lane_value(x0[p], src), lane_value(x1[p], src), cb_at, K, lane);
+            if (lane == src) idx[p] = 8u * (unsigned)bi;
+        }
+    }
+}
+// Above this many of a wave's 512 pairs a search of all of them without the table is sooner done than one scan of the codebook
+// after the other: by the listing 60 + K / 11 vector instructions a scan, 2000 + 9 K for nearest_of_all() and 512 pairs, 41 K for
+// the distances to up to 32 codewords.
+constexpr int cells_dense_above(int K) { return K > 32 ? 32 + K / 48 : 16; }
 
 }  // namespace qamw

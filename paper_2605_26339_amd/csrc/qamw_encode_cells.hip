@@ -1,11 +1,15 @@
 // QAM-W encoder with a cell table made on the device (Sec. 3.1 / Sec. 3.5; the index is the one the search over the
 // whole codebook returns, lowest index on ties).
 //
-// k_cells_prepare cuts the square [-4, 4)^2 -- where 99.99 % of the normalised pairs lie -- into G x G cells and lists,
-// per cell, every codeword that can be nearest to a point of the cell; the same launch computes the row norms.
-// k_encode_cells keeps the codebook and the whole table in LDS and decides a pair by the exact fp32 squared distances to
-// its cell's candidates, at most five.  A pair outside the table, or in a cell that lists more, is decided by the exact
-// scan of the whole codebook (64 lanes x K/64 codewords).
+// k_cells_prepare cuts a square that follows the codebook's scale -- 99.99 % of the pairs that a Lloyd codebook is for lie in
+// it -- into G x G cells and lists, per cell, every codeword that can be nearest to a point of the cell; the same launch
+// computes the row norms.  k_encode_cells keeps the codebook and the whole table in LDS and decides a pair by the exact fp32
+// squared distances to its cell's candidates, at most five.  A pair outside the table, or in a cell that lists more, is
+// decided by the exact scan of the whole codebook (64 lanes x K/64 codewords).
+//   Where that meets many of an item's pairs -- pairs much wider than the codebook, codewords that no Lloyd iteration has spread
+// -- the item is put off: once the wave has walked its rows it takes those without the table, all 512 pairs together
+// (nearest_of_all(); all distances up to 32 codewords).  That loop comes after the other and not inside it so that it costs
+// the other no registers.  After an item was put off the next is too, then the next 3, 7, 15, without a try.
 //
 // What bounds k_encode_cells: vector-ALU issue, with the LDS gathers (one record and five codewords per pair) close
 // behind.  Hence one workgroup of 16 waves per CU that stages its 144 KB once and walks the rows; a wave keeps to one
@@ -24,7 +28,7 @@ namespace qamw {
 // second L2 round trip takes: 1024 x 2048 at 10 bits 20.3 / 19.6, at 7 bits 18.7 / 25.1.
 constexpr int CELLS_DIRECT_MAX_ITEMS = 3072;
 constexpr int CELLS_ROWS_TOGETHER = 8192;                      // rows of a launch from which a wave sums four
-constexpr int CELLS_MIN_ITEMS = 1024;                          // (row, slab) items of a launch from which small codebooks use the table
+constexpr int CELLS_MIN_ITEMS = 4096;                          // (row, slab) items of a launch from which small codebooks use the table
 
 struct CellsMat {
     const void *W;
@@ -42,7 +46,8 @@ struct CellsBatch {
     CellsMat m[QAMW_ENCODE_MAX_BATCH];
     int norm_begin[QAMW_ENCODE_MAX_BATCH + 1];   // k_cells_prepare: first norm workgroup of each matrix
     int n, bits, K;
-    float inv_sqrt_block;
+    float inv_sqrt_block, half_per_sum;
+    int dense_above;                             // with more undecided pairs than this all pairs of an item are searched anew
     const float *codebook;
     uint2 *table;                                // G x G records
 };
@@ -55,7 +60,7 @@ template <int DTYPE, int G, int R>
 __global__ __launch_bounds__(CP_THREADS) void k_cells_prepare(CellsBatch bt) {
     constexpr int REGIONS = (G / 8) * (G / 8);
     if (blockIdx.x < REGIONS) {
-        cells_build_region<G>(bt.codebook, bt.K, bt.table, (int)blockIdx.x);
+        cells_build_region<G>(bt.codebook, bt.K, bt.half_per_sum, bt.table, (int)blockIdx.x);
         return;
     }
     const int b = (int)blockIdx.x - REGIONS;
@@ -81,14 +86,69 @@ constexpr int cells_threads(int G) { return G == 128 ? 1024 : 512; }
 constexpr int cells_codewords(int G) { return G == 128 ? 2048 : G == 96 ? 1024 : 512; }
 constexpr size_t cells_lds_bytes(int G) { return (size_t)cells_codewords(G) * 8 + (size_t)G * G * 8; }
 
+// 1/sqrt(B) is a power of two: its product with the gain is exact, and so one multiplication gives the bits of two (what that
+// could lose below the smallest normal number is nothing to a distance from a codeword).
+constexpr bool cells_unit_exact(int B) { return B == 64 || B == 256 || B == 1024; }
+// The constants of a lane's 16 columns from c on: scale x sign per column, gain per pair.
+template <int B> __device__ __forceinline__ void cells_constants(float (&sc)[16], float (&g)[8], const CellsMat &M, int c, float unit) {
+    Problem p;
+    p.chan_scale = M.chan_scale;
+    p.signs = M.signs;
+    p.pair_sigma = M.pair_sigma;
+    p.g_default = M.g_default;
+    load_signed_scales(sc, p, c);
+    load_pair_gains(g, p, c);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) g[k] = cells_unit_exact(B) ? unit * g[k] : g[k];
+}
+// A lane's pairs from its raw words: rotated_unit_row with the sign folded into the scale (exact).
+template <int DTYPE, int B>
+__device__ __forceinline__ void cells_pairs(float (&x)[16], const RawRow<DTYPE> &raw, float norm, const float (&sc)[16], const float (&g)[8],
+                                            const LaneSigns<B> &ls, float unit) {
+    widen_raw_row<DTYPE>(x, raw);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) x[e] = x[e] * sc[e];
+    divide_by_norm(x, norm);
+    fwht_wave<B>(x, ls);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) x[e] = (cells_unit_exact(B) ? x[e] : x[e] * unit) * g[e >> 1];
+}
+
+// The waves of the launch take the (row, slab) items of a matrix in turn, `step` at a time, a multiple of the slab count: a
+// wave stays on its slab.  The next matrix begins with the wave after the last one that got an item.
+struct CellsShare {
+    int row, rows_step, slab;                                  // the wave's rows of the matrix: row, row + rows_step, ... of one slab
+};
+// False: the wave has no item of M.  gw: the wave's number; turn: the wave that takes M's first item, on return the next matrix's.
+__device__ __forceinline__ bool cells_share(CellsShare &out, const CellsMat &M, int gw, int n_waves, int &turn) {
+    const int n_slabs = M.n_slabs, n_items = M.d_out * n_slabs;
+    const int rows_step = n_waves / n_slabs, step = rows_step * n_slabs;
+    int local = gw - turn;
+    if (local < 0) local += n_waves;
+    turn += n_items % step;
+    if (turn >= n_waves) turn -= n_waves;
+    if (local >= step || local >= n_items) return false;
+    out.row = local / n_slabs;
+    out.slab = local - out.row * n_slabs;
+    out.rows_step = rows_step;
+    return true;
+}
+constexpr int cells_together(int G, int B) { return G == 64 && B <= 256 ? 4 : 2; }   // pairs of a lane that nearest_of_all() takes: what the registers hold
+constexpr int CELLS_FEW_LANES = 12;                            // lanes with an undecided pair: up to here their pairs are scanned one by one
+constexpr int CELLS_PUT_OFF = 256;                             // items of a wave that can be put off, a bit each (in scalar registers)
+
+// Registers: two workgroups of 8 waves per CU for the smaller tables.  With fp32 weights that would cost spills, and one is left.
+#define QAMW_CELLS_WAVES_PER_EU ((STAGED && (G == 128 || DTYPE == 1)) ? 4 : 2)
 // STAGED: the table in LDS beside the codebook.  Otherwise its records are read from memory (L2): in a launch of few items a
 // workgroup would stage 128 KB for an item or two per wave, and small workgroups reach more CUs.
 template <int DTYPE, int B, int G, bool STAGED>
-__global__ __launch_bounds__(STAGED ? cells_threads(G) : CELLS_DIRECT_THREADS) void k_encode_cells(CellsBatch bt) {
+__global__ __launch_bounds__(STAGED ? cells_threads(G) : CELLS_DIRECT_THREADS) __attribute__((amdgpu_waves_per_eu(QAMW_CELLS_WAVES_PER_EU)))
+void k_encode_cells(CellsBatch bt) {
     static_assert(STAGED || (G & (G - 1)) == 0, "the mask of the record's offset");
     constexpr int THREADS = STAGED ? cells_threads(G) : CELLS_DIRECT_THREADS, WAVES = THREADS / WAVE;
     constexpr uint32_t TABLE_AT = cells_codewords(G) * 8;      // LDS: the codebook at 0, then the table
     const int K = bt.K, bits = bt.bits;
+    const float half = cells_half(bt.table);                    // on its way while the LDS is filled
     {
         const lds_f32x2_t *cbk = reinterpret_cast<const lds_f32x2_t *>(bt.codebook);
 #pragma unroll 8
@@ -106,75 +166,60 @@ __global__ __launch_bounds__(STAGED ? cells_threads(G) : CELLS_DIRECT_THREADS) v
     const LaneSigns<B> ls(lane);
     const int pos = slab_pos(lane);
     const float unit = ls.parity * bt.inv_sqrt_block;
-    // 1/sqrt(B) is a power of two: both products are one, to the same bits (what that could lose below the smallest normal
-    // number is nothing to a distance from a codeword)
-    constexpr bool UNIT_EXACT = B == 64 || B == 256 || B == 1024;
 
-    // The waves of the launch take the (row, slab) items of a matrix in turn, `step` at a time, a multiple of the slab
-    // count: a wave stays on its slab.  The next matrix begins with the wave after the last one that got an item.
+    const float inv_h = cells_inv_width<G>(half);
+
     const int n_waves = (int)gridDim.x * WAVES;
     const int gw = (int)blockIdx.x * WAVES + wid;
+    unsigned long long put_off[CELLS_PUT_OFF / 64] = {};        // items that the table does not help
+    auto put = [&](int n) {
+#pragma unroll
+        for (int q = 0; q < CELLS_PUT_OFF / 64; ++q) put_off[q] |= n >> 6 == q ? 1ull << (n & 63) : 0ull;
+    };
+    bool any_put_off = false;
+    int skip = 0, streak = 0;                                   // items still to be put off untried; how many at a time
+    int n = 0;                                                  // the wave's items so far
     int turn = 0;
 #pragma unroll 1
     for (int mi = 0; mi < bt.n; ++mi) {
         const CellsMat &M = bt.m[mi];
-        const int n_slabs = M.n_slabs, n_items = M.d_out * n_slabs;
-        const int rows_step = n_waves / n_slabs, step = rows_step * n_slabs;
-        int local = gw - turn;
-        if (local < 0) local += n_waves;
-        turn += n_items % step;
-        if (turn >= n_waves) turn -= n_waves;
-        if (local >= step || local >= n_items) continue;
-        int row = local / n_slabs;
-        const int slab = local - row * n_slabs;
-        const int col0 = slab * 1024 + 16 * pos;
+        CellsShare share;
+        if (!cells_share(share, M, gw, n_waves, turn)) continue;
+        const int rows_step = share.rows_step;
+        const int col0 = share.slab * 1024 + 16 * pos;
         const bool active = col0 < M.d_in;
         const int c = active ? col0 : 0;
         const void *__restrict__ W = M.W;
         const int64_t ldw = M.ldw;
         const float *__restrict__ norms = M.norms;
         const int d_out = M.d_out;
-
-        // the slab's constants: scale x sign per column, gain per pair
         float sc[16], g[8];
-        {
-            Problem p;
-            p.chan_scale = M.chan_scale;
-            p.signs = M.signs;
-            p.pair_sigma = M.pair_sigma;
-            p.g_default = M.g_default;
-            load_signed_scales(sc, p, c);
-            load_pair_gains(g, p, c);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) g[k] = UNIT_EXACT ? unit * g[k] : g[k];
-        }
+        cells_constants<B>(sc, g, M, c, unit);
 
+        int row = share.row;
         RawRow<DTYPE> next;
         load_raw_row<DTYPE>(next, W, (int64_t)row * ldw, c);
         float norm_next = norms[row];
-        for (; row < d_out; row += rows_step) {
+        for (; row < d_out; row += rows_step, ++n) {
             const RawRow<DTYPE> raw = next;
             const float norm = norm_next;
             if (row + rows_step < d_out) {                      // the wave's next row is on its way while this one is searched
                 load_raw_row<DTYPE>(next, W, (int64_t)(row + rows_step) * ldw, c);
                 norm_next = norms[row + rows_step];
             }
-
-            // ---------------- front half (rotated_unit_row with the sign folded into the scale: exact)
+            if (skip > 0 && n < CELLS_PUT_OFF) {
+                --skip;
+                put(n);
+                continue;
+            }
             float x[16];
-            widen_raw_row<DTYPE>(x, raw);
-#pragma unroll
-            for (int e = 0; e < 16; ++e) x[e] = x[e] * sc[e];
-            divide_by_norm(x, norm);
-            fwht_wave<B>(x, ls);
-#pragma unroll
-            for (int e = 0; e < 16; ++e) x[e] = (UNIT_EXACT ? x[e] : x[e] * unit) * g[e >> 1];
+            cells_pairs<DTYPE, B>(x, raw, norm, sc, g, ls, unit);
 
             // ---------------- the cells' records
             uint2 rec[8];
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
-                const uint32_t at = cells_record_at<G>(x[2 * k], x[2 * k + 1], STAGED ? TABLE_AT : 0u);
+                const uint32_t at = cells_record_at<G>(x[2 * k], x[2 * k + 1], inv_h, STAGED ? TABLE_AT : 0u);
                 if (STAGED) {
                     const lds_u32x2_t r = lds_read<lds_u32x2_t>(at);
                     rec[k] = make_uint2(r[0], r[1]);
@@ -191,8 +236,23 @@ __global__ __launch_bounds__(STAGED ? cells_threads(G) : CELLS_DIRECT_THREADS) v
                 idx8[k] = cells_nearest<G == 128>(rec[k], x[2 * k], x[2 * k + 1], 0u, m);
             }
 
-            // ---------------- the exact scan for the rest: the whole wave works on one pair at a time
-            if (__ballot(active && (any & CELLS_SCAN))) {
+            // ---------------- the rest: a few by the exact scan, the whole wave on one pair at a time; many later
+            const unsigned long long flagged = __ballot(active && (any & CELLS_SCAN));
+            if (flagged) {
+                // many: without the table, later
+                bool many = __popcll(flagged) > CELLS_FEW_LANES && n < CELLS_PUT_OFF;
+                if (many) {
+                    int n_scan = 0;
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) n_scan += __popcll(__ballot(active && cells_scan(rec[k])));
+                    many = n_scan > bt.dense_above;
+                }
+                if (many) {
+                    put(n);
+                    any_put_off = true;
+                    skip = streak = min(2 * streak + 1, 15);
+                    continue;
+                }
 #pragma unroll
                 for (int k = 0; k < 8; ++k) {
                     unsigned long long mask = __ballot(active && cells_scan(rec[k]));
@@ -205,7 +265,81 @@ __global__ __launch_bounds__(STAGED ? cells_threads(G) : CELLS_DIRECT_THREADS) v
                     }
                 }
             }
+            streak = 0;
 
+            if (active) store_fields<3>(M.packed + (int64_t)row * M.row_bytes, M.row_bytes, M.d_in, c, idx8, bits);
+        }
+    }
+    if (!any_put_off) return;
+
+    // ---------------- the items put off: all their pairs against the whole codebook.  All that follows from the lane is made
+    // again: it is not worth registers during the search above.
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    const LaneSigns<B> ls2(ln);
+    const float unit2 = ls2.parity * bt.inv_sqrt_block;
+    n = 0;
+    turn = 0;
+#pragma unroll 1
+    for (int mi = 0; mi < bt.n; ++mi) {
+        const CellsMat &M = bt.m[mi];
+        CellsShare share;
+        if (!cells_share(share, M, gw, n_waves, turn)) continue;
+        const int col0 = share.slab * 1024 + 16 * slab_pos(ln);
+        const bool active = col0 < M.d_in;
+        const int c = active ? col0 : 0;
+        for (int row = share.row; row < M.d_out; row += share.rows_step, ++n) {
+            unsigned long long bits64 = 0;
+#pragma unroll
+            for (int q = 0; q < CELLS_PUT_OFF / 64; ++q) bits64 = n >> 6 == q ? put_off[q] : bits64;
+            if (!((bits64 >> (n & 63)) & 1ull)) continue;
+            float x[16];
+            {
+                float sc[16], g[8];
+                cells_constants<B>(sc, g, M, c, unit2);
+                RawRow<DTYPE> raw;
+                load_raw_row<DTYPE>(raw, M.W, (int64_t)row * M.ldw, c);
+                cells_pairs<DTYPE, B>(x, raw, M.norms[row], sc, g, ls2, unit2);
+            }
+            unsigned idx8[8];
+            bool decided = false;
+            if (G == 64 && K <= 32) {                           // few codewords: all distances
+                decided = true;
+                float bd[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    bd[k] = 3.0e38f;
+                    idx8[k] = 0;
+                }
+#pragma unroll 1
+                for (uint32_t at = 0; at < 8u * (uint32_t)K; at += 8) {
+                    const lds_f32x2_t cw = lds_read<lds_f32x2_t>(at);
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) {
+                        const float dd = exact_dist2(x[2 * k], x[2 * k + 1], make_float2(cw[0], cw[1]));
+                        idx8[k] = dd < bd[k] ? at : idx8[k];
+                        bd[k] = fminf(bd[k], dd);
+                    }
+                }
+            }
+#pragma unroll 1
+            for (int q = 0; q < 8 / cells_together(G, B) && !decided; ++q) {   // some of the lane's pairs at a time, the rest moved up
+                constexpr int P = cells_together(G, B);
+                float x0[P], x1[P];
+                unsigned got[P];
+#pragma unroll
+                for (int p = 0; p < P; ++p) {
+                    x0[p] = x[2 * p];
+                    x1[p] = x[2 * p + 1];
+                }
+                nearest_of_all<P, (G == 64 ? 1 : 2)>(x0, x1, got, active ? (1u << P) - 1u : 0u, 0u, K, ln);
+#pragma unroll
+                for (int e = 0; e < 16 - 2 * P; ++e) x[e] = x[e + 2 * P];
+#pragma unroll
+                for (int k = 0; k < 8 - P; ++k) idx8[k] = idx8[k + P];
+#pragma unroll
+                for (int p = 0; p < P; ++p) idx8[8 - P + p] = got[p];
+            }
             if (active) store_fields<3>(M.packed + (int64_t)row * M.row_bytes, M.row_bytes, M.d_in, c, idx8, bits);
         }
     }
@@ -331,15 +465,17 @@ hipError_t launch_encode_cells(const EncodeItem *items, int n, int dtype, const 
         if ((int64_t)M.d_out * M.n_slabs > 0x3fffffff) return hipErrorNotSupported;
         items_total += (int64_t)M.d_out * M.n_slabs;
     }
-    // Two launches of 12 us at the least: codebooks of up to 32 points are searched whole sooner in small matrices (32
-    // points, bf16: 256 x 2048, 512 items, 11.4 us against 12.7; 1024 x 2048, 2048 items, 14.2 against 12.8).  With 64
-    // points and more the table wins from the smallest matrix on (48 x 512: 17.7 against 11.6; 2048 points: 89 against 23).
+    // Two launches of 11 us at the least: codebooks of up to 32 points are searched whole sooner in small matrices (32 points,
+    // bf16, us whole / table: 1024 x 2048, 2048 items, 12.9 / 14.9; 2048 x 2048 20.8 / 15.4).  With 64 points and more the table
+    // wins from the smallest matrix on (48 x 512: 17.3 / 14.0; 2048 points 83 / 17).
     if (p.bits < 6 && items_total < CELLS_MIN_ITEMS) return hipErrorNotSupported;
     for (int i = n; i < QAMW_ENCODE_MAX_BATCH; ++i) bt.m[i] = bt.m[0];
     bt.n = n;
     bt.bits = p.bits;
     bt.K = p.K;
     bt.inv_sqrt_block = p.inv_sqrt_block;
+    bt.half_per_sum = cells_half_per_sum(p.bits);
+    bt.dense_above = cells_dense_above(p.K);
     bt.codebook = p.codebook;
     bt.table = static_cast<uint2 *>(table);
     return dtype == 0 ? launch_cells_d<0>(bt, p.block, p.stream) : launch_cells_d<1>(bt, p.block, p.stream);

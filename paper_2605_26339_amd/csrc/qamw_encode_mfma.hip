@@ -44,17 +44,6 @@ typedef uint32_t u4v_t __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ float mmin3(float a, float b, float c) { return __builtin_fminf(__builtin_fminf(a, b), c); }
 
-// x = h + m + l exactly, each piece with at most 8 significant bits (a bf16 value held as fp32).
-__device__ __forceinline__ void split3(float x, uint32_t &h, uint32_t &m, uint32_t &l) {
-    h = __float_as_uint(x) & 0xFFFF0000u;
-    const float r1 = x - __uint_as_float(h);
-    m = __float_as_uint(r1) & 0xFFFF0000u;
-    const float r2 = r1 - __uint_as_float(m);
-    l = __float_as_uint(r2) & 0xFFFF0000u;
-}
-// two bf16 (given as fp32 bit patterns with a zero low half) into one dword: `even` in the low half
-__device__ __forceinline__ uint32_t pack2(uint32_t even, uint32_t odd) { return (even >> 16) | odd; }
-
 // CH: 32-codeword blocks per chunk.  Two halve the tracking work of the main loop; one halves the exact distances
 // of the decision stage (8 instead of 16 per lane and point), which is what matters for a small codebook.
 // One matrix of an encode launch, as the kernel sees it, and the work list of the launch: workgroups are numbered

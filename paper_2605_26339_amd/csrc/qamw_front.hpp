@@ -262,6 +262,17 @@ __device__ __forceinline__ void wave_rows_sum_of_squares(double (&sum)[R], const
     for (int r = 0; r < R; ++r) sum[r] = wave_sum(sum[r]);
 }
 
+// x = h + m + l exactly, each piece with at most 8 significant bits (a bf16 value held as fp32).
+__device__ __forceinline__ void split3(float x, uint32_t &h, uint32_t &m, uint32_t &l) {
+    h = __float_as_uint(x) & 0xFFFF0000u;
+    const float r1 = x - __uint_as_float(h);
+    m = __float_as_uint(r1) & 0xFFFF0000u;
+    const float r2 = r1 - __uint_as_float(m);
+    l = __float_as_uint(r2) & 0xFFFF0000u;
+}
+// two bf16 (given as fp32 bit patterns with a zero low half) into one dword: `even` in the low half
+__device__ __forceinline__ uint32_t pack2(uint32_t even, uint32_t odd) { return (even >> 16) | odd; }
+
 // Exact squared distance as every encoder decides with it: fma(e1, e1, e0 * e0), e = x - c.
 __device__ __forceinline__ float exact_dist2(float x0, float x1, float2 c) {
     const float e0 = x0 - c.x, e1 = x1 - c.y;

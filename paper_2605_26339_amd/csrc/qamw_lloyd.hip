@@ -10,6 +10,7 @@
 // k_lloyd_update: every point to the mean of its cell (an empty cell keeps its point).
 // k_cells_lloyd_*: the same iteration for 64 to 2048 points with a cell table (qamw_cells.hpp) made from every iteration's
 // points, the sums of a workgroup in LDS, and the stopping rule on the device, so the host launches ahead.
+#include <algorithm>
 #include <cmath>
 
 #include "qamw_cells.hpp"
@@ -137,6 +138,7 @@ constexpr int LC_THREADS = 1024;
 constexpr int LC_POINTS = 16;                                  // points per workgroup of k_cells_lloyd_move
 constexpr int LC_MAX_BLOCKS = 256;                             // one workgroup per CU: a workgroup's sums are 20 bytes per point in LDS and in the workspace
 constexpr int LC_AHEAD = 16;                                   // iterations launched before the host looks whether it has stopped
+constexpr int LC_DENSE_ABOVE = 16;                             // of a wave's 64 samples
 constexpr int lc_side(int K) { return K >= 1024 ? 128 : 64; }
 
 struct LloydCells {
@@ -180,8 +182,8 @@ __global__ __launch_bounds__(LL_THREADS) void k_cells_lloyd_init(int K, LloydCel
     if (i == 0) *a.state = LloydState{0.0, LC_RUNNING};
 }
 
-template <int G> __global__ __launch_bounds__(CP_THREADS) void k_cells_lloyd_table(int K, LloydCells a, int t) {
-    cells_build_region<G>(a.cb32[t & 1], K, a.table, (int)blockIdx.x, &a.state->stopped_at, t);
+template <int G> __global__ __launch_bounds__(CP_THREADS) void k_cells_lloyd_table(int K, float half_per_sum, LloydCells a, int t) {
+    cells_build_region<G>(a.cb32[t & 1], K, half_per_sum, a.table, (int)blockIdx.x, &a.state->stopped_at, t);
 }
 
 // The records come from memory (L2), four samples' at a time: staging them took as long as the samples of a workgroup do, and
@@ -194,6 +196,7 @@ __global__ __launch_bounds__(LC_THREADS) void k_cells_lloyd_assign(const float2 
     constexpr int U = 4;
     static_assert((G & (G - 1)) == 0, "the mask of the record's offset");
     const int stopped_at = a.state->stopped_at;
+    const float half = cells_half(a.table);
     const int lane = threadIdx.x & (WAVE - 1);
     const long long stride = (long long)gridDim.x * LC_THREADS;
     long long i = (long long)blockIdx.x * LC_THREADS + threadIdx.x;
@@ -215,6 +218,7 @@ __global__ __launch_bounds__(LC_THREADS) void k_cells_lloyd_assign(const float2 
     }
     if (threadIdx.x == 0) err_sum = 0;
     if (stopped_at < t) return;
+    const float inv_h = cells_inv_width<G>(half);
     __syncthreads();
 
     double err = 0.0;
@@ -225,7 +229,7 @@ __global__ __launch_bounds__(LC_THREADS) void k_cells_lloyd_assign(const float2 
         for (int u = 0; u < U; ++u) {
             x[u] = next[u];
             rec[u] = *reinterpret_cast<const uint2 *>(reinterpret_cast<const char *>(a.table) +
-                                                      (cells_record_at<G>(x[u].x, x[u].y, 0u) & (G * G * 8u - 1u)));   // in range whatever x is
+                                                      (cells_record_at<G>(x[u].x, x[u].y, inv_h, 0u) & (G * G * 8u - 1u)));   // in range whatever x is
         }
         request(i + U * stride);
 #pragma unroll
@@ -234,7 +238,18 @@ __global__ __launch_bounds__(LC_THREADS) void k_cells_lloyd_assign(const float2 
             float d;
             int bi = (int)(cells_nearest<(G > 64)>(rec[u], x[u].x, x[u].y, 0u, d) >> 3);
             unsigned long long mask = __ballot(active && cells_scan(rec[u]));
-            while (mask) {                                      // outside the table, or too many candidates: the whole codebook
+            // outside the table, or too many candidates: the whole codebook, for many samples at once or one after the other
+            if (__popcll(mask) > LC_DENSE_ABOVE) {
+                const float x0[1] = {x[u].x}, x1[1] = {x[u].y};
+                unsigned found[1];
+                nearest_of_all<1, (G == 64 ? 1 : 2)>(x0, x1, found, (mask >> lane) & 1u, 0u, K, lane);
+                if ((mask >> lane) & 1u) {
+                    bi = (int)(found[0] >> 3);
+                    d = fminf(exact_dist2(x[u].x, x[u].y, lc_lds[bi]), 3.0e38f);
+                }
+                mask = 0;
+            }
+            while (mask) {
                 const int at = __ffsll((long long)mask) - 1;
                 mask &= mask - 1;
                 const float x0 = __shfl(x[u].x, at, WAVE), x1 = __shfl(x[u].y, at, WAVE);
@@ -337,17 +352,19 @@ template <int G>
 static hipError_t run_lloyd_cells(const float *samples, long long n, int K, float *codebook, int max_iters, double tol,
                                   void *workspace, double *mse_out, int *iters_out, hipStream_t stream) {
     const LloydCells a = lloyd_cells_layout(workspace, K);
-    const size_t lds = (size_t)K * 28 + 8;
+    // points and sums; and no less than the table's first record, which does not hold indices, can point to
+    const size_t lds = std::max((size_t)K * 28 + 8, (size_t)4096 * 8);
     static_assert(2048 * 28 + 8 <= 64 * 1024, "what a workgroup may have without asking");
+    const float half_per_sum = cells_half_per_sum(__builtin_ctz((unsigned)K));
     const unsigned kb = (unsigned)((2 * K + LL_THREADS - 1) / LL_THREADS);
-    const long long want = (n + 2 * LC_THREADS - 1) / (2 * LC_THREADS);
+    const long long want = (n + LC_THREADS - 1) / LC_THREADS;
     const unsigned blocks = (unsigned)(want < LC_MAX_BLOCKS ? want : LC_MAX_BLOCKS);
     hipLaunchKernelGGL(k_cells_lloyd_init, dim3(kb), dim3(LL_THREADS), 0, stream, K, a, codebook);
     LloydState s{0.0, LC_RUNNING};
     for (int t = 0; s.stopped_at == LC_RUNNING;) {
         const int until = max_iters - t < LC_AHEAD ? max_iters : t + LC_AHEAD;
         for (; t < until; ++t) {
-            hipLaunchKernelGGL(k_cells_lloyd_table<G>, dim3((G / 8) * (G / 8)), dim3(CP_THREADS), 0, stream, K, a, t);
+            hipLaunchKernelGGL(k_cells_lloyd_table<G>, dim3((G / 8) * (G / 8)), dim3(CP_THREADS), 0, stream, K, half_per_sum, a, t);
             hipLaunchKernelGGL(k_cells_lloyd_assign<G>, dim3(blocks), dim3(LC_THREADS), lds, stream,
                                reinterpret_cast<const float2 *>(samples), n, K, a, t);
             hipLaunchKernelGGL(k_cells_lloyd_move, dim3(K / LC_POINTS), dim3(LC_THREADS), 0, stream, n, K, a, t, (int)blocks, max_iters, tol);
