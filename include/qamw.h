@@ -292,7 +292,7 @@ int qamw_encode_pruned(const void *W, int dtype, int d_out, int d_in, int64_t ld
                        unsigned long long *full_scans, void *stream);
 /* qamw_encode_pruned with device scratch of qamw_encode_workspace_bytes() bytes (16-byte aligned, as for qamw_encode_ws): the
  * same arguments, refusals and bytes, but where the scratch is of use and full_scans is NULL the cells' records are made anew
- * on the device, smaller, and the grid's are not read. */
+ * on the device, smaller, and the grid's are read only in rows where those leave many pairs undecided. */
 int qamw_encode_pruned_ws(const void *W, int dtype, int d_out, int d_in, int64_t ldw, const float *chan_scale,
                           const int8_t *signs, const float *pair_sigma, const float *codebook, int bits,
                           int hadamard_block, const void *grid, void *workspace, size_t workspace_bytes,

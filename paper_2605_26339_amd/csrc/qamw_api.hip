@@ -391,11 +391,11 @@ static int encode_pruned_impl(const void *W, int dtype, int d_out, int d_in, int
     if (!qamw::grid_encode_launchable(W, dtype, ldw, p, g)) return QAMW_ERR_UNSUPPORTED;
     if (workspace && (reinterpret_cast<uintptr_t>(workspace) & 15)) return QAMW_ERR_INVALID_ARG;
     // With scratch for it the records are made anew on the device, sized for LDS and with the longer lists cut down (five
-    // candidates against eight, nothing left to fetch from the table in memory): the same index from either.  13824 x 5120
-    // at 11 bits: 215 us from the caller's table, 160 so.  Counting the scans keeps to the caller's table.
+    // candidates against eight), and the caller's are read where those leave many pairs undecided: the same index from either.
+    // 13824 x 5120 at 11 bits: 215 us from the caller's table, 139 so.  Counting the scans keeps to the caller's table.
     if (!full_scans && g.variant == 0 && workspace && qamw::encode_cells_bytes(bits) && workspace_bytes >= qamw::encode_cells_bytes(bits)) {
         const qamw::EncodeItem it{W, ldw, chan_scale, signs, pair_sigma, row_norms_out, packed_out, d_out, d_in};
-        const hipError_t e = qamw::launch_encode_cells(&it, 1, dtype, p, workspace);
+        const hipError_t e = qamw::launch_encode_cells(&it, 1, dtype, p, workspace, &g);
         if (e != hipErrorNotSupported) return e == hipSuccess ? QAMW_OK : QAMW_ERR_DEVICE;
     }
     if (launch_norms(W, dtype, ldw, d_out, p, row_norms_out) != hipSuccess) return QAMW_ERR_DEVICE;

@@ -28,7 +28,8 @@ namespace qamw {
 // second L2 round trip takes: 1024 x 2048 at 10 bits 20.3 / 19.6, at 7 bits 18.7 / 25.1.
 constexpr int CELLS_DIRECT_MAX_ITEMS = 3072;
 constexpr int CELLS_ROWS_TOGETHER = 8192;                      // rows of a launch from which a wave sums four
-constexpr int CELLS_MIN_ITEMS = 4096;                          // (row, slab) items of a launch from which small codebooks use the table
+constexpr int CELLS_MIN_ITEMS = 4096;                          // (row, slab) items of a launch from which small codebooks use the table,
+constexpr int CELLS_GRID_MIN_ITEMS = 1024;                     // and from which the pruned search does
 
 struct CellsMat {
     const void *W;
@@ -48,6 +49,8 @@ struct CellsBatch {
     int n, bits, K;
     float inv_sqrt_block, half_per_sum;
     int dense_above;                             // with more undecided pairs than this all pairs of an item are searched anew
+    int grid_side;
+    const uint32_t *grid;                        // the caller's table (qamw_search_grid_build), nullable
     const float *codebook;
     uint2 *table;                                // G x G records
 };
@@ -239,9 +242,9 @@ void k_encode_cells(CellsBatch bt) {
             // ---------------- the rest: a few by the exact scan, the whole wave on one pair at a time; many later
             const unsigned long long flagged = __ballot(active && (any & CELLS_SCAN));
             if (flagged) {
-                // many: without the table, later
+                // many: without the table, later.  (A grid decides most of them; otherwise as many as dense_above.)
                 bool many = __popcll(flagged) > CELLS_FEW_LANES && n < CELLS_PUT_OFF;
-                if (many) {
+                if (many && !bt.grid) {
                     int n_scan = 0;
 #pragma unroll
                     for (int k = 0; k < 8; ++k) n_scan += __popcll(__ballot(active && cells_scan(rec[k])));
@@ -319,6 +322,41 @@ void k_encode_cells(CellsBatch bt) {
                         const float dd = exact_dist2(x[2 * k], x[2 * k + 1], make_float2(cw[0], cw[1]));
                         idx8[k] = dd < bd[k] ? at : idx8[k];
                         bd[k] = fminf(bd[k], dd);
+                    }
+                }
+            } else if (bt.grid) {                                      // the caller's table has smaller cells and eight candidates
+                const uint4 *cells = reinterpret_cast<const uint4 *>(bt.grid + 8);
+                const float grid_inv_h = __uint_as_float(bt.grid[4]);
+                uint4 rec[8];
+                unsigned scan = 0;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    bool inside;
+                    rec[k] = cells[grid_cell(x[2 * k], x[2 * k + 1], grid_inv_h, bt.grid_side, inside)];
+                    if (!inside) scan |= 1u << k;
+                }
+                int n_scan = 0;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    bool overflow;
+                    idx8[k] = 8u * grid_nearest(rec[k], x[2 * k], x[2 * k + 1], (unsigned)K - 1u, overflow, [&](unsigned ci) {
+                        const lds_f32x2_t cw = lds_read<lds_f32x2_t>(8u * ci);
+                        return make_float2(cw[0], cw[1]);
+                    });
+                    if (overflow) scan |= 1u << k;
+                    n_scan += __popcll(__ballot(active && ((scan >> k) & 1u)));
+                }
+                decided = n_scan <= bt.dense_above;
+                if (decided) {
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) {
+                        unsigned long long mask = __ballot(active && ((scan >> k) & 1u));
+                        while (mask) {
+                            const int src = __ffsll((long long)mask) - 1;
+                            mask &= mask - 1;
+                            const int bi = wave_exact_scan(lane_value(x[2 * k], src), lane_value(x[2 * k + 1], src), 0u, K, ln);
+                            if (ln == src) idx8[k] = 8u * (unsigned)bi;
+                        }
                     }
                 }
             }
@@ -436,7 +474,7 @@ size_t encode_cells_bytes(int bits) { return bits <= 11 ? (size_t)cells_side(bit
 // n <= QAMW_ENCODE_MAX_BATCH matrices that share codebook, bits, block and element type; table: encode_cells_bytes(bits)
 // bytes of device scratch, 16-byte aligned.  Returns hipErrorNotSupported (nothing launched) when any item is outside the
 // kernel's range.
-hipError_t launch_encode_cells(const EncodeItem *items, int n, int dtype, const Problem &p, void *table) {
+hipError_t launch_encode_cells(const EncodeItem *items, int n, int dtype, const Problem &p, void *table, const SearchGridView *grid) {
     if (n < 1 || n > QAMW_ENCODE_MAX_BATCH || p.bits > 11 || !table || (reinterpret_cast<uintptr_t>(table) & 15) ||
         (reinterpret_cast<uintptr_t>(p.codebook) & 7))
         return hipErrorNotSupported;
@@ -467,8 +505,9 @@ hipError_t launch_encode_cells(const EncodeItem *items, int n, int dtype, const 
     }
     // Two launches of 11 us at the least: codebooks of up to 32 points are searched whole sooner in small matrices (32 points,
     // bf16, us whole / table: 1024 x 2048, 2048 items, 12.9 / 14.9; 2048 x 2048 20.8 / 15.4).  With 64 points and more the table
-    // wins from the smallest matrix on (48 x 512: 17.3 / 14.0; 2048 points 83 / 17).
-    if (p.bits < 6 && items_total < CELLS_MIN_ITEMS) return hipErrorNotSupported;
+    // wins from the smallest matrix on (48 x 512: 17.3 / 14.0; 2048 points 83 / 17).  The pruned search's caller has a table in
+    // hand, good for a little more (2048 points, us caller's / this one: 256 x 2048, 512 items, 16.6 / 18.7; 512 x 2048 21.9 / 17.8).
+    if (grid ? items_total < CELLS_GRID_MIN_ITEMS : p.bits < 6 && items_total < CELLS_MIN_ITEMS) return hipErrorNotSupported;
     for (int i = n; i < QAMW_ENCODE_MAX_BATCH; ++i) bt.m[i] = bt.m[0];
     bt.n = n;
     bt.bits = p.bits;
@@ -476,6 +515,12 @@ hipError_t launch_encode_cells(const EncodeItem *items, int n, int dtype, const 
     bt.inv_sqrt_block = p.inv_sqrt_block;
     bt.half_per_sum = cells_half_per_sum(p.bits);
     bt.dense_above = cells_dense_above(p.K);
+    bt.grid = nullptr;
+    bt.grid_side = 0;
+    if (grid && p.K > 32) {                                     // (up to 32 codewords all distances are as soon computed)
+        bt.grid = static_cast<const uint32_t *>(grid->table);
+        bt.grid_side = grid->G;
+    }
     bt.codebook = p.codebook;
     bt.table = static_cast<uint2 *>(table);
     return dtype == 0 ? launch_cells_d<0>(bt, p.block, p.stream) : launch_cells_d<1>(bt, p.block, p.stream);

@@ -48,7 +48,6 @@ __global__ __launch_bounds__(GF_THREADS) void k_encode_grid(const void *__restri
     if (item >= n_items) return;
     // the table: a 32-byte header (word 4 = cells per unit length, as a float), then G x G records of 8 x 16 bits
     const float inv_h = __uint_as_float(table[4]);
-    const float half_g = 0.5f * (float)G, g_f = (float)G;
     const uint4 *cells = reinterpret_cast<const uint4 *>(table + 8);
     const int row = item / n_slabs, slab = item - row * n_slabs;
     const LaneSigns<B> ls(lane);
@@ -72,33 +71,16 @@ __global__ __launch_bounds__(GF_THREADS) void k_encode_grid(const void *__restri
     unsigned scan = 0;                                          // bit k: pair k needs the whole-codebook scan
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-        // clamped to [-1, G] before the conversion (a NaN becomes -1): outside the square either way
-        const int ix = (int)floorf(fminf(fmaxf(__builtin_fmaf(x[2 * k], inv_h, half_g), -1.0f), g_f));
-        const int iy = (int)floorf(fminf(fmaxf(__builtin_fmaf(x[2 * k + 1], inv_h, half_g), -1.0f), g_f));
-        const bool inside = (unsigned)ix < (unsigned)G && (unsigned)iy < (unsigned)G;
-        rec[k] = cells[inside ? iy * G + ix : 0];
+        bool inside;
+        rec[k] = cells[grid_cell(x[2 * k], x[2 * k + 1], inv_h, G, inside)];
         if (!inside) scan |= 1u << k;
     }
     unsigned idx[8];
-    const unsigned kmask = (unsigned)K - 1u;
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-        const float x0 = x[2 * k], x1 = x[2 * k + 1];
-        const unsigned cand[8] = {rec[k].x & 0xffffu, rec[k].x >> 16, rec[k].y & 0xffffu, rec[k].y >> 16,
-                                  rec[k].z & 0xffffu, rec[k].z >> 16, rec[k].w & 0xffffu, rec[k].w >> 16};
-        if (cand[7] == 0xffffu) scan |= 1u << k;                // more candidates than a record holds
-        float bd = GBIG;
-        unsigned bi = 0;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const unsigned ci = cand[j] & kmask;                // (the overflow mark stays inside the codebook)
-            const float dd = exact_dist2(x0, x1, gcb[ci]);
-            if (dd < bd) {
-                bd = dd;
-                bi = ci;
-            }
-        }
-        idx[k] = bi;
+        bool overflow;
+        idx[k] = grid_nearest(rec[k], x[2 * k], x[2 * k + 1], (unsigned)K - 1u, overflow, [&](unsigned ci) { return gcb[ci]; });
+        if (overflow) scan |= 1u << k;
     }
 
     // ---------------- the exact scan for the pairs that need it: the whole wave works on one pair at a time

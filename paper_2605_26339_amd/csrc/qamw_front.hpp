@@ -279,6 +279,35 @@ __device__ __forceinline__ float exact_dist2(float x0, float x1, float2 c) {
     return __builtin_fmaf(e1, e1, e0 * e0);
 }
 
+// The pruned search's table (layout: qamw_search_grid_build): the record of the cell that holds (x0, x1), the first one's for
+// a point outside the square.
+__device__ __forceinline__ int grid_cell(float x0, float x1, float inv_h, int G, bool &inside) {
+    const float half_g = 0.5f * (float)G, g_f = (float)G;
+    // clamped to [-1, G] before the conversion (a NaN becomes -1): outside the square either way
+    const int ix = (int)floorf(fminf(fmaxf(__builtin_fmaf(x0, inv_h, half_g), -1.0f), g_f));
+    const int iy = (int)floorf(fminf(fmaxf(__builtin_fmaf(x1, inv_h, half_g), -1.0f), g_f));
+    inside = (unsigned)ix < (unsigned)G && (unsigned)iy < (unsigned)G;
+    return inside ? iy * G + ix : 0;
+}
+// The nearest of a record's eight candidates, the lowest index on ties; overflow: the cell has more candidates than that.
+template <typename F>
+__device__ __forceinline__ unsigned grid_nearest(const uint4 &rec, float x0, float x1, unsigned kmask, bool &overflow, F codeword) {
+    const unsigned cand[8] = {rec.x & 0xffffu, rec.x >> 16, rec.y & 0xffffu, rec.y >> 16, rec.z & 0xffffu, rec.z >> 16, rec.w & 0xffffu, rec.w >> 16};
+    overflow = cand[7] == 0xffffu;
+    float bd = 3.0e38f;
+    unsigned bi = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const unsigned ci = cand[j] & kmask;                    // (the overflow mark stays inside the codebook)
+        const float dd = exact_dist2(x0, x1, codeword(ci));
+        if (dd < bd) {
+            bd = dd;
+            bi = ci;
+        }
+    }
+    return bi;
+}
+
 // The nearest of the K codewords in LDS to the point (x0, x1) (the same in all lanes), found by the whole wave: lane l
 // scans the codewords l, l + 64, ..., then a lexicographic (distance, index) reduction over the lanes; the lowest index
 // wins a tie.  Every lane returns the index (0 if every distance is NaN).  codeword(k): from wherever the caller keeps them.

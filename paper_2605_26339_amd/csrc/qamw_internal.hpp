@@ -128,7 +128,8 @@ struct EncodeItem {
 };
 // The encoder with a cell table made on the device: table is encode_cells_bytes(bits) bytes of scratch (0: no such encoder).
 size_t encode_cells_bytes(int bits);
-hipError_t launch_encode_cells(const EncodeItem *items, int n, int dtype, const Problem &p, void *table);
+// grid: where its cells do not decide, the caller's are looked up before the whole codebook is searched; nullable.
+hipError_t launch_encode_cells(const EncodeItem *items, int n, int dtype, const Problem &p, void *table, const SearchGridView *grid = nullptr);
 hipError_t launch_encode_batch_mfma(const EncodeItem *items, int n, int dtype, const Problem &p, bool norms_ready);
 
 }  // namespace qamw
