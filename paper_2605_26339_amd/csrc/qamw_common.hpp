@@ -58,20 +58,30 @@ typedef float lds_f32x2_t __attribute__((ext_vector_type(2)));
 typedef uint32_t lds_u32x2_t __attribute__((ext_vector_type(2)));
 typedef uint32_t lds_u32x4_t __attribute__((ext_vector_type(4)));
 
-// Sum over the 64 lanes of a wave in a fixed butterfly order (the same in every lane).
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int m = 1; m < WAVE; m <<= 1) v += __shfl_xor(v, m, WAVE);
-    return v;
-}
-
-
 // The value of the lane whose number differs in bit 0 or 1, and that of lane Q of the lane's group of four: one DPP move each
 // (a shuffle through LDS takes some 120 cycles to come back).
 template <int CTRL> __device__ __forceinline__ int dpp_move(int v) { return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, false); }
 template <int CTRL> __device__ __forceinline__ float dpp_move(float v) { return __int_as_float(dpp_move<CTRL>(__float_as_int(v))); }
 constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_MIRROR = 0x140;
 constexpr int dpp_quad_lane(int q) { return q * 0x55; }
+
+// Sum over the 64 lanes of a wave in a fixed butterfly order (the same in every lane): lanes that differ in bit 0, then 1, ...
+// The mirrors serve for bits 2 and 3, since the lanes of a group of four, then eight, hold the same by then.
+__device__ __forceinline__ double wave_sum(double v) {
+    auto step = [](double x, auto move) {
+        return __hiloint2double(move(__double2hiint(x)), move(__double2loint(x)));
+    };
+    v += step(v, [](int w) { return dpp_move<DPP_XOR1>(w); });
+    v += step(v, [](int w) { return dpp_move<DPP_XOR2>(w); });
+    v += step(v, [](int w) { return dpp_move<DPP_HALF_MIRROR>(w); });
+    v += step(v, [](int w) { return dpp_move<DPP_MIRROR>(w); });
+    const auto h16 = __builtin_amdgcn_permlane16_swap((uint32_t)__double2hiint(v), (uint32_t)__double2hiint(v), false, false);
+    const auto l16 = __builtin_amdgcn_permlane16_swap((uint32_t)__double2loint(v), (uint32_t)__double2loint(v), false, false);
+    v = __hiloint2double((int)h16[0], (int)l16[0]) + __hiloint2double((int)h16[1], (int)l16[1]);
+    const auto h32 = __builtin_amdgcn_permlane32_swap((uint32_t)__double2hiint(v), (uint32_t)__double2hiint(v), false, false);
+    const auto l32 = __builtin_amdgcn_permlane32_swap((uint32_t)__double2loint(v), (uint32_t)__double2loint(v), false, false);
+    return __hiloint2double((int)h32[0], (int)l32[0]) + __hiloint2double((int)h32[1], (int)l32[1]);
+}
 
 // The smallest of the 64 lanes' values, in every lane; no NaN among them.
 __device__ __forceinline__ float wave_min(float v) {

@@ -40,7 +40,7 @@ struct CellsMat {
     float *norms;
     uint8_t *packed;
     int64_t row_bytes;
-    int d_in, d_out, n_slabs;
+    int d_in, d_out, n_slabs, slab_sums;
     float g_default;
 };
 struct CellsBatch {
@@ -75,7 +75,8 @@ __global__ __launch_bounds__(CP_THREADS) void k_cells_prepare(CellsBatch bt) {
     if (row >= M.d_out) return;
     const int n_rows = min(R, M.d_out - row);
     double s2[R];
-    wave_rows_sum_of_squares<DTYPE, R>(s2, M.W, row, n_rows, M.ldw, M.d_in, M.chan_scale, lane);
+    if (M.slab_sums) wave_rows_slab_sums<DTYPE, R>(s2, M.W, row, n_rows, M.ldw, M.d_in, M.chan_scale, lane);
+    else wave_rows_sum_of_squares<DTYPE, R>(s2, M.W, row, n_rows, M.ldw, M.d_in, M.chan_scale, lane);
     if (lane == 0) {
 #pragma unroll
         for (int r = 0; r < R; ++r)
@@ -500,6 +501,11 @@ hipError_t launch_encode_cells(const EncodeItem *items, int n, int dtype, const 
         M.d_out = items[i].d_out;
         M.n_slabs = (items[i].d_in + 1023) / 1024;
         M.g_default = (float)std::sqrt((double)items[i].d_in);
+        // The norms of the call without scratch, to the bit: in the order of the kernel that serves it (the pruned search's, the
+        // general kernels' and those of longer rows come from a launch of their own).
+        q.d_in = items[i].d_in;
+        M.slab_sums = !grid && fused_norms_supported(q) && (mfma_encode_supported(q) || fast_encode_supported(q)) &&
+                      (reinterpret_cast<uintptr_t>(p.codebook) & 15) == 0;
         if ((int64_t)M.d_out * M.n_slabs > 0x3fffffff) return hipErrorNotSupported;
         items_total += (int64_t)M.d_out * M.n_slabs;
     }

@@ -262,6 +262,48 @@ __device__ __forceinline__ void wave_rows_sum_of_squares(double (&sum)[R], const
     for (int r = 0; r < R; ++r) sum[r] = wave_sum(sum[r]);
 }
 
+// The same sums in the order of slab_sum_of_squares() and row_norm_from_slab_sums(): to the bit what the kernels that compute
+// their own row norms get.
+template <int DTYPE, int R>
+__device__ __forceinline__ void wave_rows_slab_sums(double (&sum)[R], const void *__restrict__ W, int row, int n_rows, int64_t ldw, int d_in,
+                                                    const float *__restrict__ s, int lane) {
+    constexpr int U = R == 1 ? 2 : 1;                           // slabs requested together
+#pragma unroll
+    for (int r = 0; r < R; ++r) sum[r] = 0.0;
+    for (int slab = 0; slab * 1024 < d_in; slab += U) {
+        RawRow<DTYPE> raw[U][R];
+        float sc[U][16];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int c = (slab + u) * 1024 + 16 * lane, at = c < d_in ? c : 0;
+#pragma unroll
+            for (int r = 0; r < R; ++r) load_raw_row<DTYPE>(raw[u][r], W, (int64_t)(row + (r < n_rows ? r : 0)) * ldw, at);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const float4 v = s ? reinterpret_cast<const float4 *>(s + at)[t] : make_float4(1.0f, 1.0f, 1.0f, 1.0f);
+                sc[u][4 * t] = v.x; sc[u][4 * t + 1] = v.y; sc[u][4 * t + 2] = v.z; sc[u][4 * t + 3] = v.w;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if ((slab + u) * 1024 >= d_in) break;
+            const bool have = (slab + u) * 1024 + 16 * lane < d_in;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                float w[16];
+                widen_raw_row<DTYPE>(w, raw[u][r]);
+                double acc = 0.0;
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const float ws = w[e] * sc[u][e];
+                    acc += (double)ws * (double)ws;
+                }
+                sum[r] += wave_sum(have ? acc : 0.0);
+            }
+        }
+    }
+}
+
 // x = h + m + l exactly, each piece with at most 8 significant bits (a bf16 value held as fp32).
 __device__ __forceinline__ void split3(float x, uint32_t &h, uint32_t &m, uint32_t &l) {
     h = __float_as_uint(x) & 0xFFFF0000u;
