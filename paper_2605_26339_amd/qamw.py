@@ -131,7 +131,7 @@ def _check(status: int, where: str):
 
 
 # ------------------------------------------------------------------------------ host helpers
-@functools.lru_cache(maxsize=256)   # of its numbers alone; a call through ctypes costs 1 us
+@functools.lru_cache(maxsize=256, typed=True)   # of its numbers alone; a call through ctypes costs 1 us
 def packed_row_bytes(d_in: int, bits: int) -> int:
     out = C.c_size_t()
     _check(lib().qamw_packed_row_bytes(d_in, bits, C.byref(out)), "qamw_packed_row_bytes")
@@ -278,7 +278,7 @@ def _require_cuda(*tensors):
             raise ValueError("device entry points take CUDA (HIP) tensors")
 
 
-@functools.lru_cache(maxsize=256)   # of its numbers alone; a call through ctypes costs 1 us
+@functools.lru_cache(maxsize=256, typed=True)   # of its numbers alone; a call through ctypes costs 1 us
 def calibrate_workspace_bytes(d_in: int, d_out: int, max_rows: int = 1024) -> int:
     out = C.c_size_t()
     _check(lib().qamw_calibrate_workspace_bytes(d_in, d_out, max_rows, C.byref(out)), "qamw_calibrate_workspace_bytes")
@@ -316,7 +316,7 @@ def calibrate_sigma_static(W, block: int, out, chan_scale=None, signs=None, max_
     return out
 
 
-@functools.lru_cache(maxsize=256)   # of its numbers alone; a call through ctypes costs 1 us
+@functools.lru_cache(maxsize=256, typed=True)   # of its numbers alone; a call through ctypes costs 1 us
 def encode_workspace_bytes(bits: int) -> int:
     out = C.c_size_t()
     _check(lib().qamw_encode_workspace_bytes(bits, C.byref(out)), "qamw_encode_workspace_bytes")
@@ -449,7 +449,7 @@ MATMUL_TILE_ROWS = 64
 MATMUL_VECTOR_ROWS = 8
 
 
-@functools.lru_cache(maxsize=256)   # of its numbers alone; a call through ctypes costs 1 us
+@functools.lru_cache(maxsize=256, typed=True)   # of its numbers alone; a call through ctypes costs 1 us
 def matmul_workspace_bytes(d_in: int, d_out: int, m: int) -> int:
     out = C.c_size_t()
     _check(lib().qamw_matmul_workspace_bytes(d_in, d_out, m, C.byref(out)), "qamw_matmul_workspace_bytes")

@@ -413,3 +413,13 @@ def test_trainer_is_deterministic_across_thread_counts(monkeypatch):
     monkeypatch.setenv("QAMW_NUM_THREADS", "7")
     b = qamw.train_codebook(6, 1 << 14, seed=9, max_iters=15, tol=0.0)
     assert np.array_equal(a[0], b[0]) and a[1] == b[1] and a[2] == b[2]
+
+
+def test_size_helpers_refuse_what_is_not_a_whole_number():
+    # also after the same size has been asked for as a whole number: a remembered answer must not let 4096.0 pass
+    for call, good, bad in [(qamw.packed_row_bytes, (4096, 11), (4096.0, 11)), (qamw.calibrate_workspace_bytes, (4096, 64), (4096, 64.0)),
+                            (qamw.encode_workspace_bytes, (11,), (11.0,)), (qamw.matmul_workspace_bytes, (4096, 64, 1), (4096.0, 64, 1))]:
+        call(*good)
+        with pytest.raises(C.ArgumentError):
+            call(*bad)
+        assert call(*(np.int64(v) for v in good)) == call(*good)
