@@ -197,12 +197,12 @@ def lloyd_device(samples, init_codebook, bits: int, max_iters: int = 200, tol: f
     need = C.c_size_t()
     _check(lib().qamw_lloyd_workspace_bytes(bits, C.byref(need)), "qamw_lloyd_workspace_bytes")
     cb = _empty(init_codebook.shape, torch.float32, init_codebook.device, stream)
-    ws = _empty(need.value, torch.uint8, samples.device, stream)
+    ws = _scratch(need.value, (40 << bits) + 64, samples.device, stream)   # the least: 40 bytes a point
     with torch.cuda.stream(_call_stream(stream, samples.device)):   # the copies too belong on the call's stream
         samples = samples.contiguous()
         cb.copy_(init_codebook)
     mse, it = C.c_double(), C.c_int()
-    _check(lib().qamw_lloyd_device(_ptr(samples), samples.shape[0], bits, _ptr(cb), max_iters, tol, _ptr(ws), need.value,
+    _check(lib().qamw_lloyd_device(_ptr(samples), samples.shape[0], bits, _ptr(cb), max_iters, tol, _ptr(ws), ws.numel(),
                                    C.byref(mse), C.byref(it), _stream(stream)), "qamw_lloyd_device")
     return cb, float(mse.value), int(it.value)
 
@@ -323,11 +323,21 @@ def encode_workspace_bytes(bits: int) -> int:
     return int(out.value)
 
 
-def _encode_scratch(bits: int, device, stream):
+def _scratch(nbytes: int, least: int, device, stream):
+    """Device scratch of nbytes, or, where the card has no room for that, of the least that the call works with."""
     import torch
 
-    n = encode_workspace_bytes(bits) if 1 <= bits <= 12 else 0
-    return (_empty(n, torch.uint8, device, stream), n) if n else (None, 0)
+    try:
+        return _empty(nbytes, torch.uint8, device, stream) if nbytes else None
+    except torch.cuda.OutOfMemoryError:
+        if least >= nbytes:
+            raise
+    return _empty(least, torch.uint8, device, stream) if least else None
+
+
+def _encode_scratch(bits: int, device, stream):
+    ws = _scratch(encode_workspace_bytes(bits) if 1 <= bits <= 12 else 0, 0, device, stream)
+    return ws, 0 if ws is None else ws.numel()
 
 
 def encode(W, codebook, bits: int, block: int, chan_scale=None, signs=None, pair_sigma=None, out=None, stream=None,
@@ -475,7 +485,7 @@ def matmul(X, packed, row_norms, codebook, bits: int, block: int, chan_scale=Non
     m, d_in = X.shape
     d_out = row_norms.shape[0]
     if workspace is None:
-        workspace = _empty(_matmul_scratch_bytes(d_in, d_out, m), torch.uint8, X.device, stream)
+        workspace = _scratch(_matmul_scratch_bytes(d_in, d_out, m), matmul_workspace_bytes(d_in, d_out, m), X.device, stream)
     if out is None:
         out = _empty((m, d_out), torch.float32, X.device, stream)
     _check(lib().qamw_matmul(_ptr(X), _dtype_code(X), m, X.stride(0), _ptr(packed), _ptr(row_norms), d_out, d_in,

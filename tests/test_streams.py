@@ -89,6 +89,46 @@ def test_memory_is_allocated_and_copied_on_the_stream_of_the_call(monkeypatch):
         assert made and all(s is main for s in made) and not recorded, name
 
 
+def test_calls_make_do_with_the_least_scratch(monkeypatch):
+    """Where the card has no room for the scratch that makes a call fast it takes the least, as it always did; what the least does
+    not fit either is refused."""
+    L = qamw.lib()
+    monkeypatch.setattr(qamw, "_require_cuda", lambda *t: None)
+    calls = _calls("cpu", _outputs("cpu"))
+    asked, room, real_empty = [], 0, torch.empty
+
+    def empty(shape, **kw):
+        if kw.get("dtype") == torch.uint8 and isinstance(shape, int):
+            if shape > room:
+                raise torch.cuda.OutOfMemoryError("no room")
+            asked.append(shape)
+        return real_empty(shape, **kw)
+    given = {}
+    fake = types.SimpleNamespace(**{n: getattr(L, n) if n.endswith(("_bytes", "_size")) else
+                                    (lambda *a, n=n: (given.__setitem__(n, a), qamw.OK)[1]) for n in qamw.EXPORTS})
+    monkeypatch.setattr(qamw, "lib", lambda: fake)
+    monkeypatch.setattr(torch, "empty", empty)
+    monkeypatch.setattr(qamw, "_stream", lambda s: 0)
+    calls["encode, outputs given"](None)
+    calls["encode_pruned, outputs given"](None)
+    calls["encode_batch"](None)
+    assert not asked and given["qamw_encode_ws"][11:13] == (None, 0) and given["qamw_encode_pruned_ws"][12:14] == (None, 0)
+    assert given["qamw_encode_batch_ws"][6:8] == (None, 0)
+    for name, entry, at, least in (("matmul", "qamw_matmul", 15, qamw.matmul_workspace_bytes(D_IN, D_OUT, M)),
+                                   ("lloyd_device", "qamw_lloyd_device", 7, (40 << BITS) + 64)):
+        asked.clear()
+        room = least - 1
+        with pytest.raises(torch.cuda.OutOfMemoryError):
+            calls[name](None)
+        room = least
+        calls[name](None)
+        assert asked == [least] and given[entry][at] == least, name
+        room = 1 << 40
+        asked.clear()
+        calls[name](None)
+        assert asked[0] > least and given[entry][at] == asked[0], name
+
+
 @pytest.mark.gpu
 def test_scratch_is_not_memory_that_the_current_stream_still_writes():
     """Blocks of the sizes the calls ask for, freed on the current stream behind long work that ends by writing them, must not
