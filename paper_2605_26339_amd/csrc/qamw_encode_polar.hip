@@ -75,7 +75,7 @@ __global__ __launch_bounds__(PF_THREADS) void k_encode_polar(const void *__restr
             double s2 = 0.0;                                    // in slab order, as row_norm_from_slab_sums()
             for (int s = 0; s < n_slabs; ++s) s2 += lds_read<double>(PART_AT + 8 * (dr * n_slabs + s));
             r = (float)sqrt(s2);
-            norms_out[row0 + dr] = r;
+            if (blockIdx.y == 0) norms_out[row0 + dr] = r;
         } else {
             r = norms_in[row0 + dr];
         }
@@ -86,8 +86,10 @@ __global__ __launch_bounds__(PF_THREADS) void k_encode_polar(const void *__restr
     const LaneSigns<B> ls(lane);
     const int pos = slab_pos(lane);
     const float unit = ls.parity * p.inv_sqrt_block;
-    const int per = (n_items + PF_WAVES - 1) / PF_WAVES;
-    const int first = wid * per, last = min(n_items, first + per);
+    // the workgroup's part of the items (all of them unless a long row is shared by several)
+    const int parts = (int)gridDim.y, from = n_items * (int)blockIdx.y / parts, to = n_items * ((int)blockIdx.y + 1) / parts;
+    const int per = (to - from + PF_WAVES - 1) / PF_WAVES;
+    const int first = from + wid * per, last = min(to, first + per);
     int c = 0, cur_slab = -1;
     bool active = false;
     float sc[16], g[8];
@@ -170,8 +172,12 @@ static hipError_t launch_pdb(const void *W, int64_t ldw, const Problem &p, const
     int rows = std::max(1, std::min(PF_MAX_ROWS, PF_ITEMS / n_slabs));
     while (rows > 1 && (p.d_out + rows - 1) / rows < 2 * PF_CUS && (rows + 1) / 2 * n_slabs >= PF_WAVES) rows = (rows + 1) / 2;
     const unsigned blocks = (unsigned)((p.d_out + rows - 1) / rows);
+    // Few rows of many slabs: several workgroups share a row, down to an item per wave, each with all slab sums of its own
+    // (us at 5 + 6 bits, bf16, one workgroup a row / so: 16 x 40960 23.2 / 9.7, 64 x 65536 35.7 / 15.6).
+    int parts = 1;
+    if (rows == 1) parts = std::max(1, std::min((n_slabs + PF_WAVES - 1) / PF_WAVES, 2 * PF_CUS / p.d_out));
     const size_t lds = PF_DIR_AT + 8 * (size_t)(1 << bits_p);
-    hipLaunchKernelGGL((k_encode_polar<DTYPE, B>), dim3(blocks), dim3(PF_THREADS), lds, p.stream, W, ldw, p, levels, bits_a,
+    hipLaunchKernelGGL((k_encode_polar<DTYPE, B>), dim3(blocks, (unsigned)parts), dim3(PF_THREADS), lds, p.stream, W, ldw, p, levels, bits_a,
                        bits_p, norms_ready ? norms : nullptr, norms, packed, n_slabs, rows);
     return hipGetLastError();
 }

@@ -65,3 +65,33 @@ def test_rows_are_the_same_in_any_workgroup(d_out, d_in, bits_a, bits_p, block, 
     assert torch.equal((got >> bits_p)[clear_a], ia[clear_a])
     assert torch.equal((got & ((1 << bits_p) - 1))[clear_p], ip[clear_p])
     assert clear_a.double().mean() > 0.99 and clear_p.double().mean() > 0.8
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_a_long_row_shared_by_workgroups(dtype):
+    # one row is shared by as many workgroups as it has eight slabs; 600 such rows are not shared: the same bytes and norms, and no
+    # more time for few rows than the matrix-at-once kernel's share (4-wave workgroups of four items took 14.4 us for 16 x 40960,
+    # one workgroup a row 23)
+    block, bits_a, bits_p = 64, 5, 6
+    levels = torch.from_numpy(qamw.polar_codebook(bits_a, bits_p)[0]).cuda()
+    for d_in in (8192, 9216, 40960, 66560):
+        print(f"[polar rows] shared 600x{d_in} {dtype}", flush=True)
+        W = synth.weight_device(d_in, 600, d_in, 1.0, dtype)
+        want = qamw.encode_polar(W, levels, bits_a, bits_p, block)
+        for lo, n in ((0, 1), (17, 16), (300, 100), (0, 300)):
+            got = qamw.encode_polar(W[lo:lo + n], levels, bits_a, bits_p, block)
+            torch.cuda.synchronize()
+            assert torch.equal(got[0], want[0][lo:lo + n]) and torch.equal(got[1], want[1][lo:lo + n]), (d_in, lo, n)
+    W = synth.weight_device(1, 16, 40960, 1.0, dtype)
+    out = qamw.encode_polar(W, levels, bits_a, bits_p, block)
+    best = 1e9
+    for _ in range(20):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(20):
+            qamw.encode_polar(W, levels, bits_a, bits_p, block, out=out)
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) / 20 * 1e3)
+    print(f"[polar rows] 16x40960: {best:.1f} us", flush=True)
+    assert best < 19.0
