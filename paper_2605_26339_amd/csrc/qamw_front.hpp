@@ -202,9 +202,9 @@ __device__ __forceinline__ float row_norm_from_slab_sums(const double *part, int
 // Sums of squares of R consecutive rows' scaled weights, by one wave: 16-byte loads, squares exact in fp64, the lane-strided
 // sums combined with the fixed butterfly of wave_sum().  The same in every lane, and the same whatever R is.  n_rows <= R
 // rows exist.  The scales are fetched once for the R rows.
-template <int DTYPE, int R>
-__device__ __forceinline__ void wave_rows_sum_of_squares(double (&sum)[R], const void *__restrict__ W, int row, int n_rows, int64_t ldw,
-                                                         int d_in, const float *__restrict__ s, int lane) {
+template <int DTYPE, int R, bool SCALED>
+__device__ __forceinline__ void wave_rows_sum_of_squares_as(double (&sum)[R], const void *__restrict__ W, int row, int n_rows, int64_t ldw,
+                                                            int d_in, const float *__restrict__ s, int lane) {
     constexpr int V = DTYPE == 0 ? 4 : 8;                       // elements per 16-byte load
     constexpr int U = R == 1 ? 4 : 2;                           // loads per row requested together: a wave alone on its row has
                                                                 // nothing else to hide the memory round trip behind
@@ -219,26 +219,23 @@ __device__ __forceinline__ void wave_rows_sum_of_squares(double (&sum)[R], const
         float4 sv[U][V / 4];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int j = j0 + u * WAVE * V;
-            const bool have = j < d_in;
+            // past the end: the row's start again, taken as zeros (a branch would let the compiler move a load behind the sums
+            // of those before it, one round trip each)
+            const int j = j0 + u * WAVE * V, at = j < d_in ? j : 0;
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-                raw[r][u] = make_uint4(0, 0, 0, 0);
-                if (have) raw[r][u] = *reinterpret_cast<const uint4 *>(base[r] + (int64_t)j * (DTYPE == 0 ? 4 : 2));
-            }
+            for (int r = 0; r < R; ++r) raw[r][u] = *reinterpret_cast<const uint4 *>(base[r] + (int64_t)at * (DTYPE == 0 ? 4 : 2));
+            if (SCALED) {
 #pragma unroll
-            for (int t = 0; t < V / 4; ++t) {
-                sv[u][t] = make_float4(1.0f, 1.0f, 1.0f, 1.0f);
-                if (s && have) sv[u][t] = *reinterpret_cast<const float4 *>(s + j + 4 * t);
+                for (int t = 0; t < V / 4; ++t) sv[u][t] = *reinterpret_cast<const float4 *>(s + at + 4 * t);
             }
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            if (j0 + u * WAVE * V >= d_in) break;
+            const uint32_t mask = j0 + u * WAVE * V < d_in ? 0xFFFFFFFFu : 0u;
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 float w[V];
-                const uint32_t q4[4] = {raw[r][u].x, raw[r][u].y, raw[r][u].z, raw[r][u].w};
+                const uint32_t q4[4] = {raw[r][u].x & mask, raw[r][u].y & mask, raw[r][u].z & mask, raw[r][u].w & mask};
                 if (DTYPE == 0) {
 #pragma unroll
                     for (int q = 0; q < 4; ++q) w[q] = __uint_as_float(q4[q]);
@@ -249,9 +246,11 @@ __device__ __forceinline__ void wave_rows_sum_of_squares(double (&sum)[R], const
                         w[2 * q + 1] = __uint_as_float(q4[q] & 0xFFFF0000u);
                     }
                 }
+                if (SCALED) {
 #pragma unroll
-                for (int t = 0; t < V / 4; ++t) {
-                    w[4 * t] *= sv[u][t].x; w[4 * t + 1] *= sv[u][t].y; w[4 * t + 2] *= sv[u][t].z; w[4 * t + 3] *= sv[u][t].w;
+                    for (int t = 0; t < V / 4; ++t) {
+                        w[4 * t] *= sv[u][t].x; w[4 * t + 1] *= sv[u][t].y; w[4 * t + 2] *= sv[u][t].z; w[4 * t + 3] *= sv[u][t].w;
+                    }
                 }
 #pragma unroll
                 for (int t = 0; t < V; ++t) sum[r] += (double)w[t] * (double)w[t];
@@ -260,6 +259,13 @@ __device__ __forceinline__ void wave_rows_sum_of_squares(double (&sum)[R], const
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) sum[r] = wave_sum(sum[r]);
+}
+// (Without scales a loop of its own: multiplying by 1 cost a lone wave on a long fp32 row a fifth of its time.)
+template <int DTYPE, int R>
+__device__ __forceinline__ void wave_rows_sum_of_squares(double (&sum)[R], const void *__restrict__ W, int row, int n_rows, int64_t ldw,
+                                                         int d_in, const float *__restrict__ s, int lane) {
+    if (s) wave_rows_sum_of_squares_as<DTYPE, R, true>(sum, W, row, n_rows, ldw, d_in, s, lane);
+    else wave_rows_sum_of_squares_as<DTYPE, R, false>(sum, W, row, n_rows, ldw, d_in, s, lane);
 }
 
 // The same sums in the order of slab_sum_of_squares() and row_norm_from_slab_sums(): to the bit what the kernels that compute
