@@ -88,6 +88,7 @@ __global__ __launch_bounds__(CP_THREADS) void k_cells_prepare(CellsBatch bt) {
 constexpr int CELLS_DIRECT_THREADS = 256;
 constexpr int cells_threads(int G) { return G == 128 ? 1024 : 512; }
 constexpr int cells_codewords(int G) { return G == 128 ? 2048 : G == 96 ? 1024 : 512; }
+constexpr int cells_least_k(int G) { return G == 128 ? 2048 : G == 96 ? 1024 : 2; }
 constexpr size_t cells_lds_bytes(int G) { return (size_t)cells_codewords(G) * 8 + (size_t)G * G * 8; }
 
 // 1/sqrt(B) is a power of two: its product with the gain is exact, and so one multiplication gives the bits of two (what that
@@ -264,7 +265,7 @@ void k_encode_cells(CellsBatch bt) {
                         const int src = __ffsll((long long)mask) - 1;
                         mask &= mask - 1;
                         const float x0 = __shfl(x[2 * k], src, WAVE), x1 = __shfl(x[2 * k + 1], src, WAVE);
-                        const int bi = wave_exact_scan(x0, x1, 0u, K, lane);
+                        const int bi = wave_exact_scan<cells_least_k(G), cells_codewords(G)>(x0, x1, 0u, K, lane);
                         if (lane == src) idx8[k] = 8u * (unsigned)bi;
                     }
                 }
@@ -355,7 +356,7 @@ void k_encode_cells(CellsBatch bt) {
                         while (mask) {
                             const int src = __ffsll((long long)mask) - 1;
                             mask &= mask - 1;
-                            const int bi = wave_exact_scan(lane_value(x[2 * k], src), lane_value(x[2 * k + 1], src), 0u, K, ln);
+                            const int bi = wave_exact_scan<cells_least_k(G), cells_codewords(G)>(lane_value(x[2 * k], src), lane_value(x[2 * k + 1], src), 0u, K, ln);
                             if (ln == src) idx8[k] = 8u * (unsigned)bi;
                         }
                     }
@@ -371,7 +372,7 @@ void k_encode_cells(CellsBatch bt) {
                     x0[p] = x[2 * p];
                     x1[p] = x[2 * p + 1];
                 }
-                nearest_of_all<P, (G == 64 ? 1 : 2)>(x0, x1, got, active ? (1u << P) - 1u : 0u, 0u, K, ln);
+                nearest_of_all<P, (G == 64 ? 1 : 2), cells_least_k(G), cells_codewords(G)>(x0, x1, got, active ? (1u << P) - 1u : 0u, 0u, K, ln);
 #pragma unroll
                 for (int e = 0; e < 16 - 2 * P; ++e) x[e] = x[e + 2 * P];
 #pragma unroll

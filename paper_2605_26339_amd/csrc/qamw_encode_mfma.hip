@@ -275,7 +275,7 @@ __global__ __launch_bounds__(MF_THREADS) void k_encode_mfma(EncodeBatch bt, int 
                 const int src = __ffsll((long long)mask) - 1;      // a lane below 32: point src of block pbg
                 mask &= mask - 1;
                 const float2 x = pts[32 * pbg + src];
-                const int bi = wave_exact_scan(x.x, x.y, c01, K, lane);
+                const int bi = wave_exact_scan<(CH == 1 ? 64 : 512), (CH == 1 ? 256 : 2048)>(x.x, x.y, c01, K, lane);
                 if (lane == src) idxl[32 * pbg + src] = (uint16_t)bi;
             }
         }

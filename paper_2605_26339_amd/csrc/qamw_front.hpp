@@ -359,24 +359,32 @@ __device__ __forceinline__ unsigned grid_nearest(const uint4 &rec, float x0, flo
 // The nearest of the K codewords in LDS to the point (x0, x1) (the same in all lanes), found by the whole wave: lane l
 // scans the codewords l, l + 64, ..., then a lexicographic (distance, index) reduction over the lanes; the lowest index
 // wins a tie.  Every lane returns the index (0 if every distance is NaN).  codeword(k): from wherever the caller keeps them.
-template <typename F> __device__ __forceinline__ int wave_exact_scan_of(float x0, float x1, F codeword, int K, int lane) {
+// K_FROM, K_TO: what the caller knows of K; the loops that it rules out are left out.
+template <int K_FROM, int K_TO, typename F> __device__ __forceinline__ int wave_exact_scan_of(float x0, float x1, F codeword, int K, int lane) {
     // Codewords requested together: the scan is a chain of LDS latencies otherwise.  0.065 % of Gaussian pairs come here at 2^11
     // points, one in three of a wave's 512-pair items: 13824 x 5120, the whole encode call, 156 us one at a time, 137 so.
     constexpr int AHEAD = 8;
     float bd = 3.0e38f;
     int bi = 0x7fffffff;
-    for (int k = lane; k < K; k += AHEAD * WAVE) {
-        float2 c[AHEAD];
-#pragma unroll
-        for (int j = 0; j < AHEAD; ++j) c[j] = codeword(min(k + j * WAVE, K - 1));
-#pragma unroll
-        for (int j = 0; j < AHEAD; ++j) {
-            const float dd = exact_dist2(x0, x1, c[j]);
-            if (dd < bd) {                                      // (past the end: the last codeword again, found before or below)
-                bd = dd;
-                bi = min(k + j * WAVE, K - 1);
-            }
+    auto look = [&](float2 c, int k) {
+        const float dd = exact_dist2(x0, x1, c);
+        if (dd < bd) {
+            bd = dd;
+            bi = k;
         }
+    };
+    if (K_TO >= AHEAD * WAVE && (K_FROM >= AHEAD * WAVE || K >= AHEAD * WAVE)) {   // K is a power of two
+#pragma unroll 1
+        for (int k0 = 0; k0 < K; k0 += AHEAD * WAVE) {
+            float2 c[AHEAD];
+#pragma unroll
+            for (int j = 0; j < AHEAD; ++j) c[j] = codeword(k0 + lane + j * WAVE);
+#pragma unroll
+            for (int j = 0; j < AHEAD; ++j) look(c[j], k0 + lane + j * WAVE);
+        }
+    } else {                                                    // no more of them than there are
+#pragma unroll 1
+        for (int k = lane; k < K; k += WAVE) look(codeword(k), k);
     }
     const float least = wave_min(bd);
     unsigned long long at = __ballot(bd == least);
@@ -388,12 +396,14 @@ template <typename F> __device__ __forceinline__ int wave_exact_scan_of(float x0
     }
     return best == 0x7fffffff ? 0 : best;
 }
+template <int K_FROM = 1, int K_TO = 4096>
 __device__ __forceinline__ int wave_exact_scan(float x0, float x1, const float2 *cb_lds, int K, int lane) {
-    return wave_exact_scan_of(x0, x1, [&](int k) { return cb_lds[k]; }, K, lane);
+    return wave_exact_scan_of<K_FROM, K_TO>(x0, x1, [&](int k) { return cb_lds[k]; }, K, lane);
 }
 // the codewords at LDS byte address cb_at
+template <int K_FROM = 1, int K_TO = 4096>
 __device__ __forceinline__ int wave_exact_scan(float x0, float x1, uint32_t cb_at, int K, int lane) {
-    return wave_exact_scan_of(x0, x1, [&](int k) {
+    return wave_exact_scan_of<K_FROM, K_TO>(x0, x1, [&](int k) {
         const lds_f32x2_t c = lds_read<lds_f32x2_t>(cb_at + 8u * (uint32_t)k);
         return make_float2(c[0], c[1]);
     }, K, lane);

@@ -242,7 +242,7 @@ __global__ __launch_bounds__(LC_THREADS) void k_cells_lloyd_assign(const float2 
             if (__popcll(mask) > LC_DENSE_ABOVE) {
                 const float x0[1] = {x[u].x}, x1[1] = {x[u].y};
                 unsigned found[1];
-                nearest_of_all<1, (G == 64 ? 1 : 2)>(x0, x1, found, (mask >> lane) & 1u, 0u, K, lane);
+                nearest_of_all<1, (G == 64 ? 1 : 2), (G == 64 ? 64 : 1024), (G == 64 ? 512 : 2048)>(x0, x1, found, (mask >> lane) & 1u, 0u, K, lane);
                 if ((mask >> lane) & 1u) {
                     bi = (int)(found[0] >> 3);
                     d = fminf(exact_dist2(x[u].x, x[u].y, lc_lds[bi]), 3.0e38f);
@@ -253,7 +253,7 @@ __global__ __launch_bounds__(LC_THREADS) void k_cells_lloyd_assign(const float2 
                 const int at = __ffsll((long long)mask) - 1;
                 mask &= mask - 1;
                 const float x0 = __shfl(x[u].x, at, WAVE), x1 = __shfl(x[u].y, at, WAVE);
-                const int found = wave_exact_scan(x0, x1, 0u, K, lane);
+                const int found = wave_exact_scan<(G == 64 ? 64 : 1024), (G == 64 ? 512 : 2048)>(x0, x1, 0u, K, lane);
                 if (lane == at) {
                     bi = found;
                     d = fminf(exact_dist2(x0, x1, lc_lds[found]), 3.0e38f);
