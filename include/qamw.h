@@ -36,7 +36,9 @@
  *   g_k = 1/sigma_k (IEEE division), or fp32(sqrt(d_in)) when no sigma is given.
  *   Nearest codeword: exact fp32 squared distances decide; lowest index wins exact ties.
  *   decode: y^ = sigma_k * c[idx];  same butterflies;  times fp32(block^-1/2);  times sign;
- *   times r;  times fp32(1/s_j);  bf16 round-to-nearest-even.
+ *   times r;  times fp32(1/s_j);  bf16 round-to-nearest-even.  At 7, 8 and 11 bits the fast decoder fuses the trailing
+ *   factors, t * fp32(r * block^-1/2) * (sign/s_j), with a reciprocal that may be one unit in the last place off: at most
+ *   two roundings from the order above.
  */
 #ifndef QAMW_H
 #define QAMW_H

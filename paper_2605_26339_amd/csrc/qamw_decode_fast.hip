@@ -58,16 +58,17 @@ template <int BITS> __device__ __forceinline__ uint32_t field_x8(const uint32_t 
 // qs[e] = 1 / s_j carrying the sign mask in its sign bit, sig[k] = sigma of the lane's 8 pairs.
 // (The transform's lane sign is not folded in here: it rides on the row factor, one multiply per row instead of 16
 // per unit.)  Vector loads: the host checks that the arrays are 16-byte aligned.
-__device__ __forceinline__ void load_column_constants(float (&qs)[16], float (&sig)[8], const Problem &p, int c) {
+// ROUNDED: the correctly rounded reciprocal; otherwise it may be one unit in the last place off.
+template <bool ROUNDED> __device__ __forceinline__ void load_column_constants(float (&qs)[16], float (&sig)[8], const Problem &p, int c) {
     if (p.chan_scale) {
         const float4 *s4 = reinterpret_cast<const float4 *>(p.chan_scale + c);
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             float4 v = s4[t];
-            qs[4 * t] = fast_recip(v.x);
-            qs[4 * t + 1] = fast_recip(v.y);
-            qs[4 * t + 2] = fast_recip(v.z);
-            qs[4 * t + 3] = fast_recip(v.w);
+            qs[4 * t] = ROUNDED ? 1.0f / v.x : fast_recip(v.x);
+            qs[4 * t + 1] = ROUNDED ? 1.0f / v.y : fast_recip(v.y);
+            qs[4 * t + 2] = ROUNDED ? 1.0f / v.z : fast_recip(v.z);
+            qs[4 * t + 3] = ROUNDED ? 1.0f / v.w : fast_recip(v.w);
         }
     } else {
 #pragma unroll
@@ -137,6 +138,12 @@ struct DecodeBatch {
 template <int BITS, int B, bool OUT_BF16, int R, bool TRAFFIC_ONLY = false>
 __global__ __launch_bounds__(DF_THREADS) __attribute__((amdgpu_waves_per_eu(QAMW_DF_WAVES_PER_EU))) void k_decode_fast(DecodeBatch bt, int n_waves) {
     constexpr int UNIT = 2 * R;                                 // rows of a unit: two halves of R rows
+    // The paper's three rates fuse the trailing factors, t (r block^-1/2) / s_j.  The other widths round after each, as the
+    // general kernel that served them did, and to its bits: the fused form is 0.25 % further from 64 bits where block^-1/2 is no
+    // power of two (relative error at b = 128, 10 bits: 9.354e-8 fused, 9.331e-8 so; 2048 x 5632 at 10 bits 9.65 us a call
+    // fused, 10.1 so).
+    constexpr bool EACH_ROUNDED = BITS != 7 && BITS != 8 && BITS != 11;
+    constexpr bool THREE_FACTORS = EACH_ROUNDED && (B == 128 || B == 512);
     __shared__ float2 cb_lds[BITS > 11 ? 4096 : 2048];          // the codewords; a static array: its address folds into the gathers' offset field
     typedef u32x4_t u32x4_a4_t __attribute__((aligned(4)));     // a 16-byte load that is only 4-byte aligned
     const int lane = threadIdx.x & (WAVE - 1);
@@ -190,7 +197,7 @@ __global__ __launch_bounds__(DF_THREADS) __attribute__((amdgpu_waves_per_eu(QAMW
         pc.signs = M.signs;
         pc.pair_sigma = M.pair_sigma;
         pc.sigma_default = M.sigma_default;
-        load_column_constants(qs, sig, pc, c);
+        load_column_constants<EACH_ROUNDED>(qs, sig, pc, c);
     }
 
     // FULL: every row of the unit exists and is not the matrix's last row, and the slab has all 1024
@@ -279,7 +286,11 @@ __global__ __launch_bounds__(DF_THREADS) __attribute__((amdgpu_waves_per_eu(QAMW
                     x[2 * k + 1] = sig[k] * cw.y;
                 }
                 fwht_wave<B>(x, ls);
-                const float a = rn[t] * isb_parity;             // row factor r * block^-1/2, with the transform's lane sign
+                const float a = THREE_FACTORS ? rn[t] : rn[t] * isb_parity;   // row factor r * block^-1/2, with the transform's lane sign
+                if (THREE_FACTORS) {
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) x[e] = x[e] * isb_parity;
+                }
                 if (OUT_BF16) {
                     uint32_t o[8];
 #pragma unroll
