@@ -51,6 +51,26 @@ def test_codebook_and_pairs_at_every_scale(bits):
         _check(W, _book(bits, scale), bits, 128, _sigma(2048, scale))
 
 
+# The half-width that the table's first record holds: 4 for Lloyd codebooks of the unit Gaussian however they were trained (with
+# 3.75 the pairs of weights with outlier channels stand outside the square half as often again), in proportion for others.
+@pytest.mark.parametrize("bits", [7, 8, 9, 10, 11])
+@pytest.mark.parametrize("samples,iters", [(1 << 14, 10), (1 << 17, 30), (1 << 20, 40)])
+def test_the_square_of_a_trained_codebook(bits, samples, iters):
+    cb = torch.from_numpy(qamw.train_codebook(bits, max(samples, 8 << bits), max_iters=iters)[0]).cuda()
+    W = _matrix(1024, 1024)
+    ws = torch.zeros(qamw.encode_workspace_bytes(bits), dtype=torch.uint8, device="cuda")
+    packed = torch.empty((1024, qamw.packed_row_bytes(1024, bits)), dtype=torch.uint8, device="cuda")
+    norms = torch.empty(1024, device="cuda")
+    for scale in (1.0, 8.0):
+        book = cb * scale
+        qamw._check(qamw.lib().qamw_encode_ws(W.data_ptr(), qamw._dtype_code(W), 1024, 1024, 1024, None, None, None, book.data_ptr(),
+                                              bits, 128, ws.data_ptr(), ws.numel(), packed.data_ptr(), norms.data_ptr(),
+                                              qamw._stream(None)), "qamw_encode_ws")
+        torch.cuda.synchronize()
+        first = int(ws[:4].cpu().numpy().view(np.uint32)[0])
+        assert np.array([(first >> 3) << 20], dtype=np.uint32).view(np.float32)[0] == 4.0 * scale
+
+
 # pairs wider or narrower than the codebook, so that anything from none to all of a row's pairs is undecided by the table; both
 # sides of "a few are scanned one by one"; the two element types, blocks that need more registers, ragged slabs, few lanes
 @pytest.mark.parametrize("bits", [3, 5, 6, 7, 9, 10, 11])
