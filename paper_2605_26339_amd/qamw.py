@@ -253,7 +253,7 @@ def _empty(shape, dtype, device, stream):
     makes another stream wait for them.  The current stream is recorded, so that the caller may use and drop a result there."""
     import torch
 
-    side = _call_stream(stream, device)
+    side = None if stream is None else _call_stream(stream, device)
     if side is None:
         return torch.empty(shape, dtype=dtype, device=device)
     with torch.cuda.stream(side):
