@@ -126,7 +126,8 @@ int qamw_train_codebook(int bits, uint64_t n_samples, uint64_t seed, int max_ite
 
 /* Eq. 1: sigma_k = mean over the first n = min(d_out, max_rows) rows of |z_k| / sqrt(pi/2), where
  * z_k are the pairs of the unit-normalised, rotated rows (encoder steps 1-3); amplitudes and the
- * mean in fp64; an estimate that is not positive is replaced by 1/sqrt(d_in).
+ * mean in fp64 (the fast kernels' square root is good to a few of its roundings, the rows are added
+ * group by group); an estimate that is not positive is replaced by 1/sqrt(d_in).
  * workspace: device scratch of at least qamw_calibrate_workspace_bytes() bytes, 16-byte aligned,
  * owned by the caller (holds those rows' norms and per-row-group partial sums; contents are
  * unspecified afterwards).  sigma_out: device, P floats.

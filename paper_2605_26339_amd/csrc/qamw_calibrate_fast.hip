@@ -47,8 +47,8 @@ bool launch_row_norms_fast(const void *W, int dtype, int64_t ldw, int n_rows, co
 // w, w + CAL_WAVES, ... and sums |z_k| over the chunk's rows, row by row, in fp64, and writes one partial sum per pair.  A
 // small matrix is as long as one wave's chain, so rows of at most four slabs are split among the waves: 256 x 2048, the
 // only launch of 32 workgroups, 20.4 -> 12.2 us; 1024 head rows of 4096 columns 24.3 -> 16.1.  A layer's 1024 head rows of
-// seven matrices are bound by vector-ALU issue, the fp64 square roots above all: 87.8 -> 69.1 us with sqrt_magnitude(), the
-// scales and signs once per slab and the next row on its way.
+// seven matrices took 87.8 us, 69.1 with sqrt_magnitude(), the scales and signs once per slab and the next row on its way;
+// what is left is half issue (an instruction every 5.3 cycles, fp64 for the most part) and half waiting.
 // Step 2: per pair, the partial sums added up, then Eq. 1.
 // ---------------------------------------------------------------------------------------------
 struct CalMat {

@@ -359,7 +359,7 @@ __device__ __forceinline__ int other_half(int v, int hs) { return __float_as_int
 // outside 1e-30 .. 1e30 the products of the pieces are
 // no longer exact or overflow, so those points are scanned.
 //   For pairs that no table helps.  The whole call, 4096 x 4096 bf16, pairs three times as wide as the codebook: 2048 points,
-// one scan after the other 1440 us, so 670 (the encoder without a table 575 to 600); 128 points 692 us, so 121 (102).
+// one scan after the other 1440 us, so 678 (the encoder without a table 574); 128 points 692 us, so 120 (102).
 template <int P, int CH, int K_FROM, int K_TO>
 __device__ __forceinline__ void nearest_of_all(const float (&x0)[P], const float (&x1)[P], unsigned (&idx)[P], unsigned wanted, uint32_t cb_at,
                                                int K, int lane) {

@@ -58,7 +58,7 @@ struct CellsBatch {
 // ------------------------------------------------------------------------------------------------ table and norms
 // Workgroups 0 .. (G/8)^2 - 1 make the table; the rest compute the row norms.
 // R rows per wave: large launches take four, which fetches the channel scales (twice the bytes of bf16 weights) a quarter as
-// often.  A 7B layer, 405 MB: 87 us with one row per wave, 77 so.
+// often.  A 7B layer, 405 MB: 87 us with one row per wave, 77 so (84 with the sums slab by slab).
 template <int DTYPE, int G, int R>
 __global__ __launch_bounds__(CP_THREADS) void k_cells_prepare(CellsBatch bt) {
     constexpr int REGIONS = (G / 8) * (G / 8);

@@ -699,10 +699,13 @@ void k_qgemm(GemvBatch bt) {
 // once per workgroup: a lane takes 8 pairs of one (row, half), gathers their bf16 codewords and leaves them in LDS in the
 // order the A operand is read; the activations go from memory straight into LDS (k_rotate_x wrote them in B's order).
 // While stage s is multiplied the weights of stage s + 1 are unpacked (two buffers) and the
-// activations of stage s + 2 requested (three: an L2 round trip is longer than a stage); one barrier per stage.
-//   What bounds it: the LDS pipe -- per stage of a 128 x 256 tile 128 KB of operand reads, 8 K codeword gathers and 48 KB
-// of writes against 1024 cycles of matrix instructions per SIMD -- so an unpacked operand has to serve many activation
-// rows; the kernel for up to 64 rows unpacks the matrix again for every launch.
+// activations of stage s + 2 requested (three: an L2 round trip is longer than a stage); one barrier per stage.  (In the
+// fourth stage of a chunk the compiler waits for all that is under way: it does not see the counted wait, and needs the
+// first piece of the next chunk.)
+//   What bounds it: nothing alone.  Per stage of a 128 x 256 tile some 2900 cycles, of which the matrix cores and the LDS
+// (128 KB of operand reads, 8 K codeword gathers, 48 KB of writes) are each busy a good third, and the waves wait two fifths
+// of theirs: two waves per SIMD in step from barrier to barrier.  An unpacked operand has to serve many activation rows; the
+// kernel for up to 64 rows unpacks the matrix again for every launch.
 //   Summation order: exactly that of k_qgemm -- the chunks w, w + 8, ... summed in an accumulator of their own for
 // w = 0 .. 7, those eight then added in order -- so a row of Y has the same bits whatever m is and whichever of the two
 // kernels computes it; that is why the kernel keeps two accumulators.
