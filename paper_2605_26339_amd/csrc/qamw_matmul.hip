@@ -69,6 +69,7 @@ struct GemvMat {
     int d_out, d_in, n_slabs;
     int rows_per_wg;                       // rows one workgroup takes: a multiple of GV_RG, at most GV_MAX_ROWS_PER_WG
     float sigma_default;                   // 1/sqrt(d_in), used when pair_sigma is NULL
+    int tok_tiles;                         // wide kernel: activation rows of a workgroup, in 128s
 };
 // Work lists of one launch: rotation items (activation row, slab) and workgroups (rows_per_wg rows), each numbered
 // matrix-major.
@@ -78,14 +79,16 @@ struct GemvBatch {
     int grp_begin[QAMW_MATMUL_MAX_BATCH + 1];
     int n, m, K;
     int xdtype;                            // element type of X: 0 fp32, 1 bf16
-    int z_bf16;                            // 1: k_rotate_x writes bf16 rows, padded with zero rows to a multiple of 32 (matrix-core kernel)
     int gm_rows;                           // matrix-core kernel: weight rows per workgroup, 32 (a whole tile) or 16 (its upper half unused)
     float inv_sqrt_block;
     const float *codebook;
 };
-__device__ __forceinline__ int gv_find(const int *begin, int n, int u) {
+// The matrix of work item u: begin[] past the last matrix holds the total, so no entry there counts.  All of it is one scalar
+// load; a loop over the matrices was a round trip each.
+__device__ __forceinline__ int gv_find(const int (&begin)[QAMW_MATMUL_MAX_BATCH + 1], int u) {
     int i = 0;
-    while (i + 1 < n && u >= begin[i + 1]) ++i;
+#pragma unroll
+    for (int k = 1; k < QAMW_MATMUL_MAX_BATCH; ++k) i += u >= begin[k] ? 1 : 0;
     return i;
 }
 
@@ -105,27 +108,24 @@ template <int MT> struct GvRotIn {          // what one lane loads: 16 values of
     float x[MT][16], scale[16], sigma[8];
     int8_t sign[16];
 };
-// tok[t]: the activation row that goes into x[t]
+// tok[t]: the activation row that goes into x[t]; spare: 64 readable bytes
 template <int XDTYPE, int MT>
-__device__ __forceinline__ void gv_rotate_load(GvRotIn<MT> &in, const GemvMat &M, const int (&tok)[MT], int slab, int lane) {
+__device__ __forceinline__ void gv_rotate_load(GvRotIn<MT> &in, const GemvMat &M, const float *spare, const int (&tok)[MT], int slab, int lane) {
     const int col0 = slab * GV_SLAB + 16 * slab_pos(lane);
     const int c = col0 < M.d_in ? col0 : 0;
 #pragma unroll
     for (int t = 0; t < MT; ++t)
 #pragma unroll
         for (int e = 0; e < 16; ++e) in.x[t][e] = Elem<XDTYPE>::load(M.X, (int64_t)tok[t] * M.ldx + c + e);
-    if (M.chan_scale) {
+    // Without branches, so that all of it is requested at once: what the call leaves out is read from the codebook, and not used.
+    const float *scale = M.chan_scale ? M.chan_scale + c : spare, *sigma = M.pair_sigma ? M.pair_sigma + (c >> 1) : spare;
+    const int8_t *sign = M.signs ? M.signs + c : reinterpret_cast<const int8_t *>(spare);
 #pragma unroll
-        for (int e = 0; e < 16; ++e) in.scale[e] = M.chan_scale[c + e];
-    }
-    if (M.signs) {
+    for (int e = 0; e < 16; ++e) in.scale[e] = scale[e];
 #pragma unroll
-        for (int e = 0; e < 16; ++e) in.sign[e] = M.signs[c + e];
-    }
-    if (M.pair_sigma) {
+    for (int e = 0; e < 16; ++e) in.sign[e] = sign[e];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) in.sigma[e] = M.pair_sigma[(c >> 1) + e];
-    }
+    for (int e = 0; e < 8; ++e) in.sigma[e] = sigma[e];
 }
 // The arithmetic: x times the reciprocal of the channel scale (the decoder's reciprocal, one Newton step), the sign mask,
 // the transform, and one factor per pair -- lane sign of the transform x 1/sqrt(b) x sigma.
@@ -154,51 +154,73 @@ template <int XDTYPE, int B>
 __device__ __forceinline__ void gv_rotate_slab(float (&y)[16], const GemvBatch &bt, const GemvMat &M, int tok, int slab, int lane) {
     GvRotIn<1> in;
     const int toks[1] = {tok};
-    gv_rotate_load<XDTYPE, 1>(in, M, toks, slab, lane);
+    gv_rotate_load<XDTYPE, 1>(in, M, bt.codebook, toks, slab, lane);
     gv_rotate_compute<B, 1>(y, in, 0, bt, M, lane);
 }
 
-// z = sigma (.) F S (x / s) for every activation row: fp32, row-major [m][d_in], or bf16 in the order above.
+// z = sigma (.) F S (x / s) for every activation row, fp32, row-major [m][d_in]: a wave per row and slab.
 template <int XDTYPE, int B>
 __global__ __launch_bounds__(GV_THREADS) void k_rotate_x(GemvBatch bt) {
     const int lane = threadIdx.x & (WAVE - 1);
     const int wid = threadIdx.x >> 6;
     const int item = __builtin_amdgcn_readfirstlane(blockIdx.x * GV_WAVES + wid);
     if (item >= bt.rot_begin[bt.n]) return;
-    const int mi = gv_find(bt.rot_begin, bt.n, item);
+    const int mi = gv_find(bt.rot_begin, item);
     const GemvMat &M = bt.mat[mi];
     const int local = item - bt.rot_begin[mi];
     const int n_slabs = M.n_slabs;
     const int tok = __builtin_amdgcn_readfirstlane(local / n_slabs), slab = __builtin_amdgcn_readfirstlane(local % n_slabs);
     const int d_in = M.d_in;
-    if (tok >= bt.m) {                                          // a padding row of the bf16 layout: zeros
-        const int col = slab * GV_SLAB + 16 * lane;
-        if (col < d_in) {
-            uint16_t *zb = reinterpret_cast<uint16_t *>(M.Z);
-            *reinterpret_cast<uint4 *>(zb + gm_z_offset(tok, col, d_in)) = make_uint4(0, 0, 0, 0);
-            *reinterpret_cast<uint4 *>(zb + gm_z_offset(tok, col + 8, d_in)) = make_uint4(0, 0, 0, 0);
-        }
-        return;
-    }
     const int col0 = slab * GV_SLAB + 16 * slab_pos(lane);
-    const bool active = col0 < d_in;
-    const int c = active ? col0 : 0;
     float y[16];
     gv_rotate_slab<XDTYPE, B>(y, bt, M, tok, slab, lane);
-    if (active && !bt.z_bf16) {
-        float4 *dst = reinterpret_cast<float4 *>(M.Z + (int64_t)tok * d_in + c);
+    if (col0 < d_in) {
+        float4 *dst = reinterpret_cast<float4 *>(M.Z + (int64_t)tok * d_in + col0);
 #pragma unroll
         for (int t = 0; t < 4; ++t) dst[t] = make_float4(y[4 * t], y[4 * t + 1], y[4 * t + 2], y[4 * t + 3]);
-    } else if (active) {                                        // bf16, round to nearest even
+    }
+}
+
+// The same rounded to bf16 (nearest even), in the order above: a workgroup takes 8 R activation rows of one slab, R a wave, and
+// turns them in LDS, so that 128 R consecutive bytes go to memory: a row by itself would write 16 bytes to each of 128 places
+// (1000 rows of 4096: 11.5 -> 9.4 us).  Rows from m up to the next multiple of 32 are zeros.
+template <int XDTYPE, int B, int R>
+__global__ __launch_bounds__(GM_THREADS) void k_rotate_tile(GemvBatch bt) {
+    constexpr int ROWS = 8 * R, PITCH = 16 * ROWS + 16;         // bytes of eight columns of all rows; the 16 spread the lanes over the banks
+    __shared__ __align__(16) char turned[GV_SLAB / 8 * PITCH];
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int item = blockIdx.x;
+    const int mi = gv_find(bt.rot_begin, item);
+    const GemvMat &M = bt.mat[mi];
+    const int local = item - bt.rot_begin[mi], n_slabs = M.n_slabs;
+    const int group = local / n_slabs, slab = local - group * n_slabs, row0 = group * ROWS;
+    const int d_in = M.d_in, pos = slab_pos(lane);
+    int toks[R];
+#pragma unroll
+    for (int t = 0; t < R; ++t) toks[t] = min(row0 + wid * R + t, bt.m - 1);
+    GvRotIn<R> in;
+    gv_rotate_load<XDTYPE, R>(in, M, bt.codebook, toks, slab, lane);
+#pragma unroll
+    for (int t = 0; t < R; ++t) {
+        float y[16];
+        gv_rotate_compute<B, R>(y, in, t, bt, M, lane);
         uint32_t o[8];
 #pragma unroll
         for (int e = 0; e < 16; e += 2) {
             const gv_f32x2_t v = {y[e], y[e + 1]};
-            o[e >> 1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, gv_bf16x2_t));
+            o[e >> 1] = row0 + wid * R + t < bt.m ? __builtin_bit_cast(uint32_t, __builtin_convertvector(v, gv_bf16x2_t)) : 0u;
         }
-        uint16_t *zb = reinterpret_cast<uint16_t *>(M.Z);
-        *reinterpret_cast<uint4 *>(zb + gm_z_offset(tok, c, d_in)) = make_uint4(o[0], o[1], o[2], o[3]);
-        *reinterpret_cast<uint4 *>(zb + gm_z_offset(tok, c + 8, d_in)) = make_uint4(o[4], o[5], o[6], o[7]);
+        char *dst = turned + 2 * pos * PITCH + 16 * (wid * R + t);
+        *reinterpret_cast<uint4 *>(dst) = make_uint4(o[0], o[1], o[2], o[3]);
+        *reinterpret_cast<uint4 *>(dst + PITCH) = make_uint4(o[4], o[5], o[6], o[7]);
+    }
+    __syncthreads();
+    uint16_t *zb = reinterpret_cast<uint16_t *>(M.Z);
+#pragma unroll
+    for (int i = threadIdx.x; i < GV_SLAB / 8 * ROWS; i += GM_THREADS) {
+        const int j = i / ROWS, row = i % ROWS, col = slab * GV_SLAB + 8 * j;
+        if (col < d_in) *reinterpret_cast<uint4 *>(zb + gm_z_offset(row0 + row, col, d_in)) = *reinterpret_cast<const uint4 *>(turned + j * PITCH + 16 * row);
     }
 }
 
@@ -273,7 +295,7 @@ void k_qgemv(GemvBatch bt) {
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform over the wave: keeps the step bookkeeping scalar
 
     const int grp = blockIdx.x;                                 // the grid is exactly the number of workgroups
-    const int mi = gv_find(bt.grp_begin, bt.n, grp);
+    const int mi = gv_find(bt.grp_begin, grp);
     const GemvMat &M = bt.mat[mi];
     const int rpw = M.rows_per_wg;
     const int row0 = (grp - bt.grp_begin[mi]) * rpw;
@@ -324,8 +346,8 @@ void k_qgemv(GemvBatch bt) {
         int toks[MT];
 #pragma unroll
         for (int t = 0; t < MT; ++t) toks[t] = t < m ? t : 0;
-        if (bt.xdtype == 0) gv_rotate_load<0, MT>(in, M, toks, slab, lane);
-        else gv_rotate_load<1, MT>(in, M, toks, slab, lane);
+        if (bt.xdtype == 0) gv_rotate_load<0, MT>(in, M, bt.codebook, toks, slab, lane);
+        else gv_rotate_load<1, MT>(in, M, bt.codebook, toks, slab, lane);
     };
     auto rot_finish = [&](int slab, const GvRotIn<MT> &in, float (&z)[MT][16]) {
         const bool active = slab * GV_SLAB + 16 * lane < d_in;
@@ -540,7 +562,7 @@ void k_qgemm(GemvBatch bt) {
     char *tile = reinterpret_cast<char *>(gm_lds + bt.K) + (size_t)wid * (GM_ROWS * PITCH);
 
     const int grp = blockIdx.x;
-    const int mi = gv_find(bt.grp_begin, bt.n, grp);
+    const int mi = gv_find(bt.grp_begin, grp);
     const GemvMat &M = bt.mat[mi];
     // rows of the tile this workgroup fills: all 32, or the first 16 (a launch of few workgroups is cut finer so that it
     // covers the chip; a row's sum is the same chunks in the same waves in the same order either way, bit for bit)
@@ -697,15 +719,19 @@ void k_qgemm(GemvBatch bt) {
 // 64 x 32 TT each.
 //   A stage is 4 matrix instructions of depth (64 of the 256 columns of a chunk).  The weights' side of a stage is unpacked
 // once per workgroup: a lane takes 8 pairs of one (row, half), gathers their bf16 codewords and leaves them in LDS in the
-// order the A operand is read; the activations go from memory straight into LDS (k_rotate_x wrote them in B's order).
-// While stage s is multiplied the weights of stage s + 1 are unpacked (two buffers) and the
-// activations of stage s + 2 requested (three: an L2 round trip is longer than a stage); one barrier per stage.  (In the
-// fourth stage of a chunk the compiler waits for all that is under way: it does not see the counted wait, and needs the
-// first piece of the next chunk.)
-//   What bounds it: nothing alone.  Per stage of a 128 x 256 tile some 2900 cycles, of which the matrix cores and the LDS
-// (128 KB of operand reads, 8 K codeword gathers, 48 KB of writes) are each busy a good third, and the waves wait two fifths
-// of theirs: two waves per SIMD in step from barrier to barrier.  An unpacked operand has to serve many activation rows; the
-// kernel for up to 64 rows unpacks the matrix again for every launch.
+// order the A operand is read; the activations go from memory straight into LDS (k_rotate_tile wrote them in B's order).
+// While stage s is multiplied the weights of stage s + 1 are unpacked (two buffers) and the activations of the stages after it
+// are under way (three to five: an L2 round trip is longer than a stage).
+//   One barrier per stage, before its last quarter: by then a wave has read all operands of the stage and left its part of the
+// next one's, and the products still to come hide the first reads of the next stage.  LDS accesses and requests are dealt out
+// between the products, two or three to each: in a block before them they and the products waited for each other, two waves
+// per SIMD in step.  The activations are requested with buffer instructions: the compiler counts those and waits for a piece of
+// weights alone, where it waited for all that was under way, once a chunk, with flat ones.  8192 x 4096, 1024 rows, 256 tiles of
+// 128 x 256: 99 -> 88 us a call, of which 9 for the rotation.
+//   What bounds it: the LDS, with 128 KB of operand reads, 4 K codeword gathers and 48 KB of writes per stage of 2000 cycles
+// (210 instructions, two thirds of the time with the writes from memory), and the matrix cores, busy half the time (without
+// the products 80 us; without gathers, unpacked weights and requests 72).  An unpacked operand has to serve many activation
+// rows; the kernel for up to 64 rows unpacks the matrix again for every launch.
 //   Summation order: exactly that of k_qgemm -- the chunks w, w + 8, ... summed in an accumulator of their own for
 // w = 0 .. 7, those eight then added in order -- so a row of Y has the same bits whatever m is and whichever of the two
 // kernels computes it; that is why the kernel keeps two accumulators.
@@ -714,31 +740,26 @@ constexpr int GW_WAVES = 8, GW_THREADS = GW_WAVES * WAVE;
 constexpr int GW_CUS = 256;                // one workgroup per CU at a time
 constexpr int GW_STAGE = 4;                // matrix instructions of depth per stage
 
-constexpr int gw_ahead(int tt) { return tt == 2 ? 2 : 4; }      // 136 and 120 KB of LDS
+constexpr int gw_buffers(int tt) { return tt == 2 ? 3 : 5; }    // stages of activations in LDS: 136 and 120 KB in all
 
-template <int BITS, int TT>
-__global__ __launch_bounds__(GW_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void k_qgemm_wide(GemvBatch bt) {
-    constexpr int AHEAD = gw_ahead(TT);                         // stages the activations are requested ahead
+template <int BITS, int TT> __device__ __forceinline__ void gw_tile(const GemvBatch &bt, const GemvMat &M, int local) {
+    constexpr int BUFS = gw_buffers(TT);
     constexpr int TILES = 4 * TT;                               // 32-row tiles of activation rows
     constexpr int KC = 1 << BITS;
     constexpr uint32_t A_BYTES = 4 * GW_STAGE * 1024, Z_BYTES = TILES * GW_STAGE * 1024;
     constexpr uint32_t A_AT = KC * 4;                           // after the K codewords, (bf16 c0) | (bf16 c1) << 16:
                                                                 // 2 buffers [4 tiles of 32 rows][4 instructions][64 lanes] x 16 bytes
-    constexpr uint32_t Z_AT = A_AT + 2 * A_BYTES;               // AHEAD + 1 buffers [TILES][2 halves][4 instructions][32 rows] x 16 bytes
+    constexpr uint32_t Z_AT = A_AT + 2 * A_BYTES;               // BUFS buffers [TILES][2 halves][4 instructions][32 rows] x 16 bytes
     const int lane = threadIdx.x & (WAVE - 1);
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 31, h = lane >> 5;
     const int wn = wid & 1, wm = wid >> 1;
 
-    const int grp = blockIdx.x;
-    const int mi = gv_find(bt.grp_begin, bt.n, grp);
-    const GemvMat &M = bt.mat[mi];
     const int m = bt.m, d_out = M.d_out, last_row = d_out - 1;
     const int tok_tiles = (m + 31) >> 5, m_tiles = (tok_tiles + TILES - 1) / TILES;
     // Workgroup b runs on XCD b mod 8: the activation tiles of one weight tile follow one another on the same XCD, so the
     // packed rows come from its L2 after the first.
-    const int local = grp - bt.grp_begin[mi], n_tiles = (d_out + GW_ROWS - 1) / GW_ROWS;
+    const int n_tiles = (d_out + GW_ROWS - 1) / GW_ROWS;
     int nt, mt;
     {
         const int whole = n_tiles / 8 * 8 * m_tiles;            // the last n_tiles mod 8 weight tiles in plain order
@@ -795,27 +816,19 @@ void k_qgemm_wide(GemvBatch bt) {
     const int my_tile = wid * TT / 2;
     const char *zsrc = reinterpret_cast<const char *>(M.Z) + (int64_t)min(tile0 + my_tile, tok_tiles - 1) * n_chunks * 16384 +
                        (TT == 1 ? (wid & 1) * 8192 : 0);        // tiles past the end repeat the last (not stored)
-    auto request_z = [&](int ch, int q, uint32_t buf) {            // buf: byte offset of the buffer
-#pragma unroll
-        for (int u = 0; u < 2 * TT; ++u) {
-            const char *src = zsrc + (int64_t)ch * 16384 + (u >> 1) * 8192 + q * 2048 + (u & 1) * 1024;
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + lane * 16),
-                                             reinterpret_cast<__attribute__((address_space(3))) void *>(Z_AT + buf + (wid * 2 * TT + u) * 1024u), 16, 0, 0);
-        }
+    const auto zres = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(zsrc), 0, n_chunks * 16384 - (TT == 1 ? (wid & 1) * 8192 : 0), 0x00020000);
+    auto request_z = [&](int ch, int q, int u, uint32_t buf) {     // the u-th of them; buf: byte offset of the buffer
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(zres, reinterpret_cast<__attribute__((address_space(3))) void *>(Z_AT + buf + (wid * 2 * TT + u) * 1024u), 16,
+                                                     lane * 16, ch * 16384 + (u >> 1) * 8192 + q * 2048 + (u & 1) * 1024, 0, 0);
     };
     const uint32_t a_write = A_AT + (uint32_t)((wid & 3) * GW_STAGE + 2 * part) * 1024 + lane * 16;
     const uint32_t a_read = A_AT + (uint32_t)(2 * wn) * (GW_STAGE * 1024) + lane * 16;
     const uint32_t z_read = Z_AT + (uint32_t)(wm * TT) * 4096 + h * 2048 + r * 16;
-    // four codewords of an instruction
-    auto gather = [&](const uint32_t (&f)[3], int j) {
-        gv_u32x4_t a;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int bit = (4 * j + i) * BITS, word = bit >> 5, off = bit & 31;
-            const uint32_t v = (off + BITS <= 32) ? (f[word] >> off) : __builtin_amdgcn_alignbit(f[word + 1], f[word], off);
-            a[i] = lds_read<uint32_t>((v & (KC - 1u)) << 2);
-        }
-        return a;
+    // the i-th codeword of a piece
+    auto gather = [&](const uint32_t (&f)[3], int i) {
+        const int bit = i * BITS, word = bit >> 5, off = bit & 31;
+        const uint32_t v = (off + BITS <= 32) ? (f[word] >> off) : __builtin_amdgcn_alignbit(f[word + 1], f[word], off);
+        return lds_read<uint32_t>((v & (KC - 1u)) << 2);
     };
 
     gv_f32x16_t acc[2][TT], total[2][TT];
@@ -825,76 +838,107 @@ void k_qgemm_wide(GemvBatch bt) {
         for (int t = 0; t < TT; ++t)
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[a][t][i] = total[a][t][i] = 0.0f;
+    // operands of a stage's instructions, a set of registers each
+    gv_bf16x8_t av[GW_STAGE][2], bv[GW_STAGE][TT];
+    constexpr int READS = 2 + TT, PRODUCTS = 2 * TT;            // of one instruction's depth
+    auto operand = [&](int j, int i, uint32_t a_buf, uint32_t z_buf) {   // the i-th read, in the order of their use
+        if (i == 0 || i == READS - 1) {
+            const int a = i == 0 ? 0 : 1;
+            av[j][a] = lds_read<gv_bf16x8_t>(a_read + a_buf + (a * GW_STAGE + j) * 1024);
+        } else {
+            bv[j][i - 1] = lds_read<gv_bf16x8_t>(z_read + z_buf + (i - 1) * 4096 + j * 512);
+        }
+    };
+    auto product = [&](int i) {                                 // the i-th of a stage
+        const int j = i / PRODUCTS, a = i % PRODUCTS / TT, t = i % TT;
+        acc[a][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[j][a], bv[j][t], acc[a][t], 0, 0, 0);
+    };
 
 #pragma unroll
     for (int q = 0; q < 4; ++q) load_piece(0, q, pc[q]);
+    // the chunk after c of segment s: the next of the segment (+ 8) or the first of the next segment; at the end the same again (unused)
+    auto after = [&](int c, int s, int &c2, int &s2) {
+        c2 = c + GM_WAVES;
+        s2 = s;
+        if (c2 >= n_chunks) c2 = s2 = s + 1;
+        if (s2 >= GM_WAVES || c2 >= n_chunks) {
+            c2 = c;
+            s2 = s;
+        }
+    };
+    int ch = 0, seg = 0, next, next_seg, later, later_seg;
+    after(ch, seg, next, next_seg);
 #pragma unroll
-    for (int q = 0; q < (AHEAD < 4 ? AHEAD : 4); ++q) request_z(0, q, q * Z_BYTES);
+    for (int q = 0; q < BUFS; ++q)
+#pragma unroll
+        for (int u = 0; u < 2 * TT; ++u) request_z(q < 4 ? 0 : next, q & 3, u, q * Z_BYTES);
     __syncthreads();                                            // the codebook is staged
     {
         uint32_t f[3];
         align_piece(pc[0], 0, f);
-        lds_write(a_write, gather(f, 0));
-        lds_write(a_write + 1024, gather(f, 1));
+#pragma unroll
+        for (int i = 0; i < 2; ++i) lds_write(a_write + 1024 * i, gv_u32x4_t{gather(f, 4 * i), gather(f, 4 * i + 1), gather(f, 4 * i + 2), gather(f, 4 * i + 3)});
+        load_piece(next, 0, pc[0]);
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);                        // vmcnt(0): the wave's activations have landed
     __syncthreads();
-    int ch = 0, seg = 0;
-    uint32_t z_now = 0, z_ask = AHEAD * Z_BYTES;                // the activations' buffers: this stage's, the one being filled
+#pragma unroll
+    for (int i = 0; i < READS; ++i) operand(0, i, 0, 0);
+    uint32_t z_now = 0;                                         // the buffer of this stage's activations
 #pragma unroll 1
-    while (true) {
-        // the chunk after this one: the next of the segment (+ 8), or the first of the next segment
-        int next = ch + GM_WAVES, next_seg = seg;
-        if (next >= n_chunks) {
-            next_seg = seg + 1;
-            next = next_seg;
-        }
-        const bool more = next_seg < GM_WAVES && next < n_chunks;
-        const int load_ch = more ? next : ch;                   // past the end: the same chunk again (unused)
+    for (int left = n_chunks; left > 0; --left) {
+        after(next, next_seg, later, later_seg);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int cur = q & 1, nxt = cur ^ 1;
-            request_z(q + AHEAD < 4 ? ch : load_ch, (q + AHEAD) & 3, z_ask);
-            // the piece of stage q has been used: the next chunk's takes its place.  The one load stays between here and
-            // the wait below: its count relies on it.
-            asm volatile("" ::: "memory");
-            __builtin_amdgcn_sched_barrier(0);
-            load_piece(load_ch, q, pc[q]);
-            asm volatile("" ::: "memory");
-            __builtin_amdgcn_sched_barrier(0);
-            gv_bf16x8_t av[2][2], bv[2][TT];
-            const uint32_t zr = z_read + z_now;
-            auto operands = [&](int j) {
-#pragma unroll
-                for (int a = 0; a < 2; ++a) av[j & 1][a] = lds_read<gv_bf16x8_t>(a_read + cur * A_BYTES + (a * GW_STAGE + j) * 1024);
-#pragma unroll
-                for (int t = 0; t < TT; ++t) bv[j & 1][t] = lds_read<gv_bf16x8_t>(zr + t * 4096 + j * 512);
-            };
-            operands(0);
+            const uint32_t z_next = z_now == (BUFS - 1) * Z_BYTES ? 0 : z_now + Z_BYTES;
+            // What the wave has to ask of LDS and memory, a little before each product, so that both go on at once: first the
+            // rest of this stage's operands and the weights of the next stage, ...
             uint32_t f[3];
             align_piece(pc[(q + 1) & 3], (q + 1) & 3, f);
             gv_u32x4_t cw[2];
+            constexpr int TASKS = 3 * READS + 8 + 3, BEFORE = 3 * PRODUCTS;
+            auto task = [&](int n) {
+                if (n < READS) return operand(1, n, cur * A_BYTES, z_now);
+                n -= READS;
+                if (n < 4) return (void)(cw[0][n] = gather(f, n));
+                n -= 4;
+                if (n < READS) return operand(2, n, cur * A_BYTES, z_now);
+                n -= READS;
+                if (n < 4) return (void)(cw[1][n] = gather(f, 4 + n));
+                n -= 4;
+                if (n < 1) return lds_write(a_write + nxt * A_BYTES, cw[0]);
+                n -= 1;
+                if (n < READS) return operand(3, n, cur * A_BYTES, z_now);
+                n -= READS;
+                if (n < 1) return load_piece(q == 3 ? later : next, (q + 1) & 3, pc[(q + 1) & 3]);   // in the place of the used one
+                lds_write(a_write + nxt * A_BYTES + 1024, cw[1]);
+            };
 #pragma unroll
-            for (int j = 0; j < GW_STAGE; ++j) {
-                if (j < 2) cw[j] = gather(f, j);
-                if (j + 1 < GW_STAGE) operands(j + 1);
-                __builtin_amdgcn_sched_barrier(0);              // the reads go out before the products they are to hide behind
+            for (int i = 0; i < BEFORE; ++i) {
 #pragma unroll
-                for (int a = 0; a < 2; ++a)
-#pragma unroll
-                    for (int t = 0; t < TT; ++t)
-                        acc[a][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[j & 1][a], bv[j & 1][t], acc[a][t], 0, 0, 0);
-                if (j >= 1 && j < 3) lds_write(a_write + nxt * A_BYTES + (j - 1) * 1024, cw[j - 1]);
+                for (int n = 0; n < TASKS; ++n)
+                    if (n * (BEFORE - 1) / TASKS == i) task(n);
+                product(i);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            // The next stage's activations have landed.  What was requested since may be under way: a piece, then AHEAD - 1
-            // times the 2 TT loads of a stage and a piece.
-            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(1 + (AHEAD - 1) * (2 * TT + 1)) : "memory");
+            // Of this stage's buffers all that the wave needs is in its registers, its part of the next stage's weights is written,
+            // and its next activations have landed: since their request a piece, then BUFS - 2 times the 2 TT loads of a stage and a piece.
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(BUFS - 1 + (BUFS - 2) * 2 * TT) : "memory");
             __builtin_amdgcn_sched_barrier(0);
-            z_now = z_now == AHEAD * Z_BYTES ? 0 : z_now + Z_BYTES;
-            z_ask = z_ask == AHEAD * Z_BYTES ? 0 : z_ask + Z_BYTES;
+            // ... then the next stage's first operands and, into this stage's buffer, the activations BUFS stages ahead.
+#pragma unroll
+            for (int i = BEFORE; i < 4 * PRODUCTS; ++i) {
+#pragma unroll
+                for (int n = 0; n < READS; ++n)
+                    if (n * PRODUCTS / READS == i - BEFORE) operand(0, n, nxt * A_BYTES, z_next);
+                request_z(q + BUFS < 4 ? ch : q + BUFS < 8 ? next : later, (q + BUFS) & 3, i - BEFORE, z_now);
+                product(i);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            z_now = z_next;
         }
-        if (next_seg != seg) {
+        if (left == 1 || next_seg != seg) {
 #pragma unroll
             for (int a = 0; a < 2; ++a)
 #pragma unroll
@@ -904,9 +948,10 @@ void k_qgemm_wide(GemvBatch bt) {
                     for (int i = 0; i < 16; ++i) acc[a][t][i] = 0.0f;
                 }
         }
-        if (!more) break;
         ch = next;
         seg = next_seg;
+        next = later;
+        next_seg = later_seg;
     }
 
     // The norms first, all of them, then four consecutive weight rows per store: a load between two stores would wait for
@@ -942,6 +987,15 @@ void k_qgemm_wide(GemvBatch bt) {
     }
 }
 
+template <int BITS>
+__global__ __launch_bounds__(GW_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_qgemm_wide(GemvBatch bt) {
+    const int mi = gv_find(bt.grp_begin, blockIdx.x);
+    const GemvMat &M = bt.mat[mi];
+    const int local = (int)blockIdx.x - bt.grp_begin[mi];
+    if (M.tok_tiles == 2) gw_tile<BITS, 2>(bt, M, local);
+    else gw_tile<BITS, 1>(bt, M, local);
+}
+
 bool matmul_supported(const Problem &p, int m) {
     const int unit = p.block > 16 ? p.block : 16;
     if (p.d_in % unit || p.block < 64) return false;
@@ -957,6 +1011,8 @@ bool matmul_supported(const Problem &p, int m) {
 // 1024 x 2048 46.0 / 39.3, 11008 x 4096 91.9 / 64.8; five tiles, 300 rows: 76.6 / 64.9, 154 / 142, 91.9 / 83.3.
 bool matmul_wide(const MatmulItem *items, int n, int m) {
     if (m <= 3 * GM_MAX_M) return false;
+    for (int i = 0; i < n; ++i)
+        if (items[i].d_in >= 1 << 25) return false;             // a tile's activations: 64 bytes a column, 32-bit offsets
     if (m > 4 * GM_MAX_M) return true;
     int64_t groups = 0;
     bool deep = true;
@@ -979,6 +1035,22 @@ static hipError_t launch_rotate(const GemvBatch &bt, int block, hipStream_t stre
     const unsigned blocks = (unsigned)((bt.rot_begin[bt.n] + GV_WAVES - 1) / GV_WAVES);
 #define QAMW_ROT(BB) \
     case BB: hipLaunchKernelGGL((k_rotate_x<XDTYPE, BB>), dim3(blocks), dim3(GV_THREADS), 0, stream, bt); break;
+    switch (block) {
+        QAMW_ROT(64) QAMW_ROT(128) QAMW_ROT(256) QAMW_ROT(512) QAMW_ROT(1024)
+        default: return hipErrorNotSupported;
+    }
+#undef QAMW_ROT
+    return hipGetLastError();
+}
+// rows: activation rows per workgroup, 8 or 16
+template <int XDTYPE>
+static hipError_t launch_rotate_tile(const GemvBatch &bt, int rows, int block, hipStream_t stream) {
+    const unsigned blocks = (unsigned)bt.rot_begin[bt.n];
+#define QAMW_ROT(BB) \
+    case BB: \
+        if (rows == 16) hipLaunchKernelGGL((k_rotate_tile<XDTYPE, BB, 2>), dim3(blocks), dim3(GM_THREADS), 0, stream, bt); \
+        else hipLaunchKernelGGL((k_rotate_tile<XDTYPE, BB, 1>), dim3(blocks), dim3(GM_THREADS), 0, stream, bt); \
+        break;
     switch (block) {
         QAMW_ROT(64) QAMW_ROT(128) QAMW_ROT(256) QAMW_ROT(512) QAMW_ROT(1024)
         default: return hipErrorNotSupported;
@@ -1031,26 +1103,20 @@ static hipError_t launch_qgemm(const GemvBatch &bt, hipStream_t stream) {
     return hipGetLastError();
 }
 
-template <int BITS, int TT>
-static hipError_t launch_qgemm_wide_t(const GemvBatch &bt, hipStream_t stream) {
-    constexpr size_t lds = ((size_t)4 << BITS) + (2 * 4 + (gw_ahead(TT) + 1) * 4 * TT) * GW_STAGE * 1024;
-    if (lds > 64 * 1024) {
-        static std::atomic<uint64_t> done{0};                   // the devices on which the larger LDS was asked for
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorNotSupported;
-        if (!(done.load(std::memory_order_acquire) & (1ull << dev))) {
-            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_qgemm_wide<BITS, TT>),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess) return e;
-            done.fetch_or(1ull << dev, std::memory_order_release);
-        }
-    }
-    hipLaunchKernelGGL((k_qgemm_wide<BITS, TT>), dim3((unsigned)bt.grp_begin[bt.n]), dim3(GW_THREADS), lds, stream, bt);
-    return hipGetLastError();
-}
 template <int BITS>
-static hipError_t launch_qgemm_wide(const GemvBatch &bt, int tt, hipStream_t stream) {
-    return tt == 2 ? launch_qgemm_wide_t<BITS, 2>(bt, stream) : launch_qgemm_wide_t<BITS, 1>(bt, stream);
+static hipError_t launch_qgemm_wide(const GemvBatch &bt, hipStream_t stream) {
+    auto bytes = [](int tt) { return ((size_t)4 << BITS) + (size_t)(2 * 4 + gw_buffers(tt) * 4 * tt) * GW_STAGE * 1024; };
+    const size_t lds = std::max(bytes(1), bytes(2));            // more than the 64 KB that a workgroup has without asking
+    static std::atomic<uint64_t> done{0};                       // the devices on which it was asked for
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorNotSupported;
+    if (!(done.load(std::memory_order_acquire) & (1ull << dev))) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_qgemm_wide<BITS>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+        done.fetch_or(1ull << dev, std::memory_order_release);
+    }
+    hipLaunchKernelGGL((k_qgemm_wide<BITS>), dim3((unsigned)bt.grp_begin[bt.n]), dim3(GW_THREADS), lds, stream, bt);
+    return hipGetLastError();
 }
 
 // Y_i = X_i W_i^T for n <= QAMW_MATMUL_MAX_BATCH matrices that share codebook, bits, block, m and the element type
@@ -1083,6 +1149,10 @@ hipError_t launch_matmul_batch(const MatmulItem *items, int n, int xdtype, int m
     int64_t groups256 = 0;
     for (int i = 0; i < n; ++i) groups256 += wide_groups(items[i], 2);
     const int tt = groups256 >= GW_CUS ? 2 : 1;
+    // Matrix-core kernels: 16 activation rows per workgroup of the rotation where those are at least one for every CU.
+    int64_t slabs = 0;
+    for (int i = 0; i < n; ++i) slabs += (items[i].d_in + GV_SLAB - 1) / GV_SLAB;
+    const int rot_rows = (m + 31) / 32 * 2 * slabs >= GW_CUS ? 16 : 8;
     for (int i = 0; i < n; ++i) {
         const MatmulItem &it = items[order[i]];
         Problem q = p;
@@ -1120,7 +1190,8 @@ hipError_t launch_matmul_batch(const MatmulItem *items, int n, int xdtype, int m
         }
         bt.rot_begin[i] = (int)rot;
         bt.grp_begin[i] = (int)groups;
-        rot += (int64_t)(m > GV_MAX_M ? (m + 31) / 32 * 32 : m) * M.n_slabs;
+        M.tok_tiles = tt;
+        rot += (int64_t)(m > GV_MAX_M ? (m + 31) / 32 * 32 / rot_rows : m) * M.n_slabs;
         groups += wide ? wide_groups(it, tt) : (M.d_out + M.rows_per_wg - 1) / M.rows_per_wg;
         if (groups > 0x3fffffff || rot > 0x3fffffff) return hipErrorNotSupported;
     }
@@ -1134,41 +1205,39 @@ hipError_t launch_matmul_batch(const MatmulItem *items, int n, int xdtype, int m
     bt.K = p.K;
     bt.inv_sqrt_block = p.inv_sqrt_block;
     bt.codebook = p.codebook;
-    bt.z_bf16 = m > GV_MAX_M ? 1 : 0;
     bt.xdtype = xdtype;
     // One or two activation rows in a small launch (a forward pass issues one product, or the few that share an input,
     // per call): the product kernel rotates the activations itself.  Same results, one launch less.
     // (variant 1: never, 2: whenever there are one or two rows -- for tests and measurements)
     const bool self_rotate = m <= 2 && variant != 1 && (variant == 2 || groups <= GV_SELF_ROTATE_MAX_WGS);
     hipError_t e = hipSuccess;
-    if (!self_rotate) e = xdtype == 0 ? launch_rotate<0>(bt, p.block, p.stream) : launch_rotate<1>(bt, p.block, p.stream);
+    if (m > GV_MAX_M)
+        e = xdtype == 0 ? launch_rotate_tile<0>(bt, rot_rows, p.block, p.stream) : launch_rotate_tile<1>(bt, rot_rows, p.block, p.stream);
+    else if (!self_rotate)
+        e = xdtype == 0 ? launch_rotate<0>(bt, p.block, p.stream) : launch_rotate<1>(bt, p.block, p.stream);
     if (e != hipSuccess) return e;
     if (wide) {
-        auto launch_wide = [&](const GemvBatch &b, int t) {
-            if (p.bits == 11) return launch_qgemm_wide<11>(b, t, p.stream);
-            if (p.bits == 8) return launch_qgemm_wide<8>(b, t, p.stream);
-            return launch_qgemm_wide<7>(b, t, p.stream);
-        };
         // One product whose 256-row tiles leave most of the chip idle in the last round: the weight rows of that round go
-        // into a launch of 128-row tiles, if those are at most a round (11008 x 4096, 1000 rows, 344 tiles: 172 -> 160 us).
+        // into 128-row tiles, if those are at most a round, of the same launch (11008 x 4096, 1000 rows, 344 tiles: in a launch of
+        // their own 136 us a call, so 132).
         const int m_tiles = (m + 255) / 256, n_tiles = (items[0].d_out + GW_ROWS - 1) / GW_ROWS;
         const int first = (int)(groups256 / GW_CUS * GW_CUS) / m_tiles, rest = (n_tiles - first) * ((m + 127) / 128);
         if (n == 1 && tt == 2 && first < n_tiles && rest <= GW_CUS) {
-            GemvBatch b2 = bt;
-            GemvMat &M = bt.mat[0], &M2 = b2.mat[0];
+            GemvMat &M = bt.mat[0], &M2 = bt.mat[1];            // as two matrices
+            M2 = M;
             M.d_out = first * GW_ROWS;
             M2.d_out -= M.d_out;
             M2.packed += (int64_t)M.d_out * M.row_bytes;
             M2.norms += M.d_out;
             M2.Y += M.d_out;
-            for (int i = 1; i <= QAMW_MATMUL_MAX_BATCH; ++i) {
-                bt.grp_begin[i] = first * m_tiles;
-                b2.grp_begin[i] = rest;
-            }
-            e = launch_wide(bt, 2);
-            return e != hipSuccess ? e : launch_wide(b2, 1);
+            M2.tok_tiles = 1;
+            bt.n = 2;
+            bt.grp_begin[1] = first * m_tiles;
+            for (int i = 2; i <= QAMW_MATMUL_MAX_BATCH; ++i) bt.grp_begin[i] = first * m_tiles + rest;
         }
-        return launch_wide(bt, tt);
+        if (p.bits == 11) return launch_qgemm_wide<11>(bt, p.stream);
+        if (p.bits == 8) return launch_qgemm_wide<8>(bt, p.stream);
+        return launch_qgemm_wide<7>(bt, p.stream);
     }
     if (m > GV_MAX_M) {
         if (p.bits == 11) return launch_qgemm<11>(bt, p.stream);
