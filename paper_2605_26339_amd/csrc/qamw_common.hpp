@@ -62,7 +62,7 @@ typedef uint32_t lds_u32x4_t __attribute__((ext_vector_type(4)));
 // (a shuffle through LDS takes some 120 cycles to come back).
 template <int CTRL> __device__ __forceinline__ int dpp_move(int v) { return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, false); }
 template <int CTRL> __device__ __forceinline__ float dpp_move(float v) { return __int_as_float(dpp_move<CTRL>(__float_as_int(v))); }
-constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_MIRROR = 0x140;
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_MIRROR = 0x140, DPP_QUAD_REVERSE = 0x1B, DPP_ROW_ROTATE_8 = 0x128;
 constexpr int dpp_quad_lane(int q) { return q * 0x55; }
 
 // Sum over the 64 lanes of a wave in a fixed butterfly order (the same in every lane): lanes that differ in bit 0, then 1, ...

@@ -26,6 +26,7 @@
 #include <algorithm>
 #include <atomic>
 #include <cmath>
+#include <type_traits>
 
 #include "qamw_common.hpp"
 #include "qamw_internal.hpp"
@@ -104,49 +105,77 @@ __device__ __forceinline__ int64_t gm_z_offset(int tok, int col, int d_in) {
 // slab_pos(l) (the order of the register transform); all 64 lanes of the wave call it together.  Lanes past the end of
 // the row work on columns 0..15 (their blocks hold no lane that counts) and return values nobody uses.
 // In two halves, so that a caller can have other memory requests on their way between the loads and the arithmetic.
-template <int MT> struct GvRotIn {          // what one lane loads: 16 values of each of MT activation rows and their columns' constants
-    float x[MT][16], scale[16], sigma[8];
-    int8_t sign[16];
+template <int MT> struct GvRotIn {          // what one lane loads: 16 values of each of MT activation rows, as they lie in
+    uint32_t x[MT][16], sign[4];            // memory (16 dwords of fp32 or 8 of bf16), and their columns' constants
+    float scale[16], sigma[8];
 };
-// tok[t]: the activation row that goes into x[t]; spare: 64 readable bytes
+// tok[t]: the activation row that goes into x[t].  XDTYPE: the element type, or 2: that of the launch; bf16 rows are then read
+// twice over, as many dwords as of fp32, without a branch.
 template <int XDTYPE, int MT>
-__device__ __forceinline__ void gv_rotate_load(GvRotIn<MT> &in, const GemvMat &M, const float *spare, const int (&tok)[MT], int slab, int lane) {
+__device__ __forceinline__ void gv_rotate_load(GvRotIn<MT> &in, const GemvBatch &bt, const GemvMat &M, const int (&tok)[MT], int slab, int lane) {
+    const float *spare = bt.codebook;                           // 64 readable bytes
+    const int xdtype = XDTYPE == 2 ? bt.xdtype : XDTYPE;
     const int col0 = slab * GV_SLAB + 16 * slab_pos(lane);
     const int c = col0 < M.d_in ? col0 : 0;
+    typedef gv_u32x4_t u32x4_a1_t __attribute__((aligned(1)));   // the rows and the columns' constants may lie anywhere
+    auto load = [](const void *at, int i) { return reinterpret_cast<const u32x4_a1_t *>(at)[i]; };
 #pragma unroll
-    for (int t = 0; t < MT; ++t)
+    for (int t = 0; t < MT; ++t) {
+        const char *row = static_cast<const char *>(M.X) + ((int64_t)tok[t] * M.ldx + c) * (xdtype == 0 ? 4 : 2);
 #pragma unroll
-        for (int e = 0; e < 16; ++e) in.x[t][e] = Elem<XDTYPE>::load(M.X, (int64_t)tok[t] * M.ldx + c + e);
+        for (int i = 0; i < (XDTYPE == 1 ? 2 : 4); ++i) {
+            const gv_u32x4_t v = load(row, xdtype == 0 ? i : i & 1);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) in.x[t][4 * i + k] = v[k];
+        }
+    }
     // Without branches, so that all of it is requested at once: what the call leaves out is read from the codebook, and not used.
     const float *scale = M.chan_scale ? M.chan_scale + c : spare, *sigma = M.pair_sigma ? M.pair_sigma + (c >> 1) : spare;
-    const int8_t *sign = M.signs ? M.signs + c : reinterpret_cast<const int8_t *>(spare);
+    const void *sign = M.signs ? static_cast<const void *>(M.signs + c) : spare;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) in.scale[e] = scale[e];
+    for (int i = 0; i < 4; ++i) {
+        const gv_u32x4_t v = load(scale, i);
 #pragma unroll
-    for (int e = 0; e < 16; ++e) in.sign[e] = sign[e];
+        for (int k = 0; k < 4; ++k) in.scale[4 * i + k] = __uint_as_float(v[k]);
+    }
+    const gv_u32x4_t sg = load(sign, 0);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) in.sigma[e] = sigma[e];
+    for (int k = 0; k < 4; ++k) in.sign[k] = sg[k];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const gv_u32x4_t v = load(sigma, i);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) in.sigma[4 * i + k] = __uint_as_float(v[k]);
+    }
 }
 // The arithmetic: x times the reciprocal of the channel scale (the decoder's reciprocal, one Newton step), the sign mask,
 // the transform, and one factor per pair -- lane sign of the transform x 1/sqrt(b) x sigma.
 template <int B, int MT>
-__device__ __forceinline__ void gv_rotate_compute(float (&y)[16], const GvRotIn<MT> &in, int t, const GemvBatch &bt, const GemvMat &M, int lane) {
+__device__ __forceinline__ void gv_rotate_compute(float (&y)[16], const GvRotIn<MT> &in, int t, int xdtype, const GemvBatch &bt, const GemvMat &M, int lane) {
     const LaneSigns<B> ls(lane);
+    if (xdtype == 0) {
 #pragma unroll
-    for (int e = 0; e < 16; ++e) y[e] = in.x[t][e];
-    if (M.chan_scale) {
+        for (int e = 0; e < 16; ++e) y[e] = __uint_as_float(in.x[t][e]);
+    } else {
 #pragma unroll
-        for (int e = 0; e < 16; ++e) y[e] = y[e] * fast_recip(in.scale[e]);
+        for (int e = 0; e < 16; e += 2) {
+            y[e] = __uint_as_float(in.x[t][e >> 1] << 16);
+            y[e + 1] = __uint_as_float(in.x[t][e >> 1] & 0xFFFF0000u);
+        }
     }
-    if (M.signs) {
+    // (selections, no branches: a load used in one branch alone is moved there, behind all that was to go on beside it)
+    const bool scaled = M.chan_scale != nullptr, given = M.pair_sigma != nullptr;
+    const uint32_t negative = M.signs ? 0x80000000u : 0u;
 #pragma unroll
-        for (int e = 0; e < 16; ++e) y[e] = (in.sign[e] < 0) ? -y[e] : y[e];
+    for (int e = 0; e < 16; ++e) {
+        y[e] = y[e] * fast_recip(scaled ? in.scale[e] : 1.0f);
+        y[e] = __uint_as_float(__float_as_uint(y[e]) ^ ((in.sign[e >> 2] << (24 - 8 * (e & 3))) & negative));   // a negative byte: the other sign
     }
     fwht_wave<B>(y, ls);
     const float k = ls.parity * bt.inv_sqrt_block;
     float g[8];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) g[q] = k * (M.pair_sigma ? in.sigma[q] : M.sigma_default);
+    for (int q = 0; q < 8; ++q) g[q] = k * (given ? in.sigma[q] : M.sigma_default);
 #pragma unroll
     for (int e = 0; e < 16; ++e) y[e] = y[e] * g[e >> 1];
 }
@@ -154,8 +183,8 @@ template <int XDTYPE, int B>
 __device__ __forceinline__ void gv_rotate_slab(float (&y)[16], const GemvBatch &bt, const GemvMat &M, int tok, int slab, int lane) {
     GvRotIn<1> in;
     const int toks[1] = {tok};
-    gv_rotate_load<XDTYPE, 1>(in, M, bt.codebook, toks, slab, lane);
-    gv_rotate_compute<B, 1>(y, in, 0, bt, M, lane);
+    gv_rotate_load<XDTYPE, 1>(in, bt, M, toks, slab, lane);
+    gv_rotate_compute<B, 1>(y, in, 0, XDTYPE, bt, M, lane);
 }
 
 // z = sigma (.) F S (x / s) for every activation row, fp32, row-major [m][d_in]: a wave per row and slab.
@@ -200,11 +229,11 @@ __global__ __launch_bounds__(GM_THREADS) void k_rotate_tile(GemvBatch bt) {
 #pragma unroll
     for (int t = 0; t < R; ++t) toks[t] = min(row0 + wid * R + t, bt.m - 1);
     GvRotIn<R> in;
-    gv_rotate_load<XDTYPE, R>(in, M, bt.codebook, toks, slab, lane);
+    gv_rotate_load<XDTYPE, R>(in, bt, M, toks, slab, lane);
 #pragma unroll
     for (int t = 0; t < R; ++t) {
         float y[16];
-        gv_rotate_compute<B, R>(y, in, t, bt, M, lane);
+        gv_rotate_compute<B, R>(y, in, t, XDTYPE, bt, M, lane);
         uint32_t o[8];
 #pragma unroll
         for (int e = 0; e < 16; e += 2) {
@@ -224,10 +253,12 @@ __global__ __launch_bounds__(GM_THREADS) void k_rotate_tile(GemvBatch bt) {
     }
 }
 
-template <int BITS> __device__ __forceinline__ uint32_t gv_field(const uint32_t (&w)[4], int i) {
-    const int bit = i * BITS, word = bit >> 5, off = bit & 31;
-    uint32_t v = (off + BITS <= 32) ? (w[word] >> off) : __builtin_amdgcn_alignbit(w[word + 1], w[word], off);
-    return v & ((1u << BITS) - 1u);
+// Field i of a lane's stream as a byte offset into the codebook, index times 8: one shift and one AND, with the mask in a register
+// (an AND of two registers issues at twice the rate of one with a literal).
+template <int BITS> __device__ __forceinline__ uint32_t gv_field_x8(const uint32_t (&w)[4], int i, uint32_t mask8) {
+    const int bit = i * BITS, word = bit >> 5, off = bit & 31, s = off - 3;
+    const uint32_t v = s < 0 ? w[word] << -s : off + BITS <= 32 ? w[word] >> s : __builtin_amdgcn_alignbit(w[word + 1], w[word], s);
+    return v & mask8;
 }
 
 // Sums over the 64 lanes of N per-lane values a[0..N), N a power of two <= 64, leaving ONE total per lane:
@@ -242,6 +273,15 @@ template <int N> __device__ __forceinline__ int gv_lane_row(int lane) {
         row += ((lane >> bit) & 1) * n;
     }
     return row;
+}
+// The value of the lane whose number differs in bit BIT, for bits 0 to 3 by DPP moves: a shuffle through LDS is some 120 cycles, four
+// of them after another in every step of a wave.
+template <int BIT> __device__ __forceinline__ float gv_xor_lane(float v) {
+    if constexpr (BIT == 0) return dpp_move<DPP_XOR1>(v);
+    else if constexpr (BIT == 1) return dpp_move<DPP_XOR2>(v);
+    else if constexpr (BIT == 2) return dpp_move<DPP_QUAD_REVERSE>(dpp_move<DPP_HALF_MIRROR>(v));   // l ^ 7, then ^ 3
+    else if constexpr (BIT == 3) return dpp_move<DPP_ROW_ROTATE_8>(v);
+    else return __shfl_xor(v, 1 << BIT, WAVE);
 }
 // one step: LIVE values are live in a[0..LIVE); lane l pairs with lane l ^ 2^BIT
 template <int N, int LIVE, int BIT> __device__ __forceinline__ void gv_reduce_step(float (&a)[N], int lane) {
@@ -258,11 +298,11 @@ template <int N, int LIVE, int BIT> __device__ __forceinline__ void gv_reduce_st
             } else {
                 const bool up = (lane >> BIT) & 1;
                 const float send = up ? a[r] : a[r + H], keep = up ? a[r + H] : a[r];
-                a[r] = keep + __shfl_xor(send, 1 << BIT, WAVE);
+                a[r] = keep + gv_xor_lane<BIT>(send);
             }
         }
     } else {
-        a[0] += __shfl_xor(a[0], 1 << BIT, WAVE);
+        a[0] += gv_xor_lane<BIT>(a[0]);
     }
 }
 template <int N> __device__ __forceinline__ void gv_reduce_rows(float (&a)[N], int lane) {
@@ -290,47 +330,52 @@ void k_qgemv(GemvBatch bt) {
     // statically sized, so that a codeword's address is its index times 8 with nothing to add (bt.K == 2^BITS)
     __shared__ float2 cb_lds[1 << BITS];                        // the codewords
     __shared__ float red[GV_WAVES * UR * MT];                   // [waves][UR rows][MT]
-    typedef gv_u32x4_t u32x4_a4_t __attribute__((aligned(4)));
     const int lane = threadIdx.x & (WAVE - 1);
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform over the wave: keeps the step bookkeeping scalar
 
     const int grp = blockIdx.x;                                 // the grid is exactly the number of workgroups
     const int mi = gv_find(bt.grp_begin, grp);
-    const GemvMat &M = bt.mat[mi];
+    const GemvMat M = bt.mat[mi];
+    // All that the wave needs of the arguments is asked for here, in two round trips of scalar loads: what a branch or a later
+    // use fetches for itself is one more each.
+    asm volatile("" ::"s"(M.X), "s"(M.packed), "s"(M.norms), "s"(M.chan_scale), "s"(M.pair_sigma), "s"(M.signs), "s"(M.Y), "s"(M.ldx),
+                 "s"(M.ldy), "s"(M.row_bytes), "s"(M.d_out), "s"(M.d_in), "s"(M.n_slabs), "s"(M.rows_per_wg), "s"(M.sigma_default),
+                 "s"(bt.codebook), "s"(bt.m), "s"(bt.xdtype), "s"(bt.inv_sqrt_block), "s"(bt.grp_begin[mi]));
     const int rpw = M.rows_per_wg;
     const int row0 = (grp - bt.grp_begin[mi]) * rpw;
     const int n_g = rpw / RG;                                   // row groups of this workgroup
     const int n_slabs = M.n_slabs, m = bt.m;
     const int d_in = M.d_in, last_row = M.d_out - 1;
-    const int64_t row_bytes = M.row_bytes;
+    int64_t row_bytes = M.row_bytes;
     const uint8_t *packed = M.packed;
     const float *Z = M.Z;
-    const unsigned row_dw = (unsigned)(row_bytes >> 2);
 
-    auto lane_col = [&](int slab) {                             // first of the lane's 16 columns (0 for idle lanes)
+    auto lane_col = [&](int slab) __attribute__((always_inline)) {                             // first of the lane's 16 columns (0 for idle lanes)
         const int col0 = slab * GV_SLAB + 16 * lane;           // no transform here: lanes in natural column order
         return col0 < d_in ? col0 : 0;
     };
-    auto fetch = [&](int slab, int g, uint32_t (&d)[RG][4]) {
-        const unsigned lane_b0 = ((unsigned)(lane_col(slab) >> 4) * BITS) & ~3u;   // the lane's 8 fields: BITS bytes, same place in every row
-        const int r0 = row0 + g * RG;
-        if (r0 + RG - 1 < last_row) {
-            // 16 bytes from a 4-byte-aligned address; may run a few bytes into the next row
-            const uint8_t *base = packed + (int64_t)r0 * row_bytes + lane_b0;
+    // A lane's 8 fields are BITS bytes, at the same place in every row of a slab: 16 bytes from a 4-byte-aligned address hold
+    // them, up to 16 - BITS of them the next row's.  Where that could be past the matrix's end -- in a group that reaches its
+    // last row -- they are taken further to the front (field_shift() dwords), and rows past the end re-read the last row.
+    auto last_group = [&](int r0) __attribute__((always_inline)) { return r0 + RG - 1 >= last_row; };
+    auto field_at = [&](int slab) __attribute__((always_inline)) { return (unsigned)(lane_col(slab) >> 4) * BITS; };
+    auto field_base = [&](int slab, int r0) __attribute__((always_inline)) {
+        const unsigned at = field_at(slab) & ~3u;
+        return last_group(r0) ? min(at, (unsigned)row_bytes - 16u) : at;
+    };
+    // The packed words of a group of rows.  Buffer loads without a branch: the compiler then knows how many are under way, and
+    // waits for those that it needs, whatever comes after them.  wanted: otherwise the loads are out of range, read nothing and
+    // give zeros.  (A group's rows lie within 2^31 bytes.)
+    auto fetch = [&](int slab, int g, bool wanted, uint32_t (&d)[RG][4]) __attribute__((always_inline)) {
+        const int r0 = min(row0 + g * RG, last_row);
+        const unsigned at = field_base(slab, r0);
+        const uint32_t rb = (uint32_t)row_bytes, most = wanted ? (uint32_t)min(last_row - r0, RG - 1) * rb : 0u;
+        const auto rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(packed + (int64_t)r0 * row_bytes), 0,
+                                                            wanted ? (int)(most + rb + 16u) : 0, 0x00020000);
 #pragma unroll
-            for (int r = 0; r < RG; ++r) {
-                const gv_u32x4_t v = *reinterpret_cast<const u32x4_a4_t *>(base + (int64_t)r * row_bytes);
-                d[r][0] = v[0]; d[r][1] = v[1]; d[r][2] = v[2]; d[r][3] = v[3];
-            }
-        } else {
-            // the group reaches the matrix's last row: rows past the end re-read the last row, and every
-            // load stays inside its row (the clamped words are beyond the lane's fields)
-#pragma unroll
-            for (int r = 0; r < RG; ++r) {
-                const uint32_t *rw = reinterpret_cast<const uint32_t *>(packed + (int64_t)min(r0 + r, last_row) * row_bytes);
-#pragma unroll
-                for (int k = 0; k < 4; ++k) d[r][k] = rw[min((lane_b0 >> 2) + k, row_dw - 1u)];
-            }
+        for (int r = 0; r < RG; ++r) {
+            const gv_u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(rows, at, min(r * rb, most), 0);
+            d[r][0] = v[0]; d[r][1] = v[1]; d[r][2] = v[2]; d[r][3] = v[3];
         }
     };
     // the lane whose transform sub-block is this lane's natural one (slab_pos permutes inside groups of 16 lanes)
@@ -342,21 +387,20 @@ void k_qgemv(GemvBatch bt) {
     }
     // The slab's rotated activations, zero for missing rows of X and idle lanes: the self-rotating kernels load the
     // inputs (rot_load) and rotate (rot_finish) in two steps, the others read the rotation kernel's output.
-    auto rot_load = [&](int slab, GvRotIn<MT> &in) {
+    auto rot_load = [&](int slab, GvRotIn<MT> &in) __attribute__((always_inline)) {
         int toks[MT];
 #pragma unroll
         for (int t = 0; t < MT; ++t) toks[t] = t < m ? t : 0;
-        if (bt.xdtype == 0) gv_rotate_load<0, MT>(in, M, bt.codebook, toks, slab, lane);
-        else gv_rotate_load<1, MT>(in, M, bt.codebook, toks, slab, lane);
+        gv_rotate_load<2, MT>(in, bt, M, toks, slab, lane);
     };
-    auto rot_finish = [&](int slab, const GvRotIn<MT> &in, float (&z)[MT][16]) {
+    auto rot_finish = [&](int slab, const GvRotIn<MT> &in, float (&z)[MT][16]) __attribute__((always_inline)) {
         const bool active = slab * GV_SLAB + 16 * lane < d_in;
 #pragma unroll
         for (int t = 0; t < MT; ++t) {
             const bool have = active && t < m;
             float y[16];
             constexpr int B = RB > 0 ? RB : 64;
-            gv_rotate_compute<B, MT>(y, in, t, bt, M, lane);
+            gv_rotate_compute<B, MT>(y, in, t, bt.xdtype, bt, M, lane);
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
                 const float v = __int_as_float(__builtin_amdgcn_ds_bpermute(z_from, __float_as_int(y[e])));
@@ -364,7 +408,7 @@ void k_qgemv(GemvBatch bt) {
             }
         }
     };
-    auto load_z = [&](int slab, float (&z)[MT][16]) {
+    auto load_z = [&](int slab, float (&z)[MT][16]) __attribute__((always_inline)) {
         if constexpr (RB > 0) {
             GvRotIn<MT> in;
             rot_load(slab, in);
@@ -388,20 +432,42 @@ void k_qgemv(GemvBatch bt) {
         }
     };
 
+    constexpr int NORMS = (UR * MT + GV_THREADS - 1) / GV_THREADS;   // of the rows whose sums the thread stores: not a round trip at the end
+    float norm[NORMS];
+    auto load_norms = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < NORMS; ++i) norm[i] = M.norms[min(row0 + ((int)threadIdx.x + i * GV_THREADS) / MT, last_row)];
+    };
+
     // The workgroup's work is n_slabs x n_g steps (slab-major: one slab's row groups are consecutive); wave w takes
     // the w-th quarter of them, so the waves are equally loaded whatever the slab count is.
     const int n_steps = n_slabs * n_g;
     const int per_wave = (n_steps + GV_WAVES - 1) / GV_WAVES;
-    const int step0 = wid * per_wave, step1 = min(n_steps, step0 + per_wave);
+    int step0 = wid * per_wave;
+    const int step1 = min(n_steps, step0 + per_wave);
     float z[MT][16];
-    int cur_slab = step0 < step1 ? step0 / n_g : -1;
+    int cur_slab = min(step0, n_steps - 1) / n_g;
     const int my_row = gv_lane_row<RG>(lane);                   // after the reduction: which of the group's rows this lane holds
     float *my_red = red + wid * UR * MT;                        // this wave's running row totals (only this wave touches them until the last barrier)
 
     // one step: the group's 8 x 64 x 8 codeword gathers and multiply-adds, the totals over the lanes, into my_red
-    auto work = [&](int step, const uint32_t (&d)[RG][4]) {
-        const int slab = step / n_g, g = step - slab * n_g;
-        const int sh = (int)(((unsigned)(lane_col(slab) >> 4) * BITS) & 3u) * 8;
+    // (once: no other step of the wave is of these rows)
+    uint32_t mask8;                                             // ((1 << BITS) - 1) * 8 in a register the optimiser cannot fold back into a literal
+    asm volatile("v_mov_b32 %0, %1" : "=v"(mask8) : "n"(((1 << BITS) - 1) * 8));
+    auto work = [&](auto once, int slab, int g, uint32_t (&d)[RG][4]) __attribute__((always_inline)) {
+        const int r0 = row0 + g * RG;
+        const unsigned field = field_at(slab);
+        const int sh = (int)(field & 3u) * 8;
+        if (last_group(r0)) {                                   // words taken from further to the front
+            const unsigned shift = (field & ~3u) - field_base(slab, r0);
+#pragma unroll
+            for (int r = 0; r < RG; ++r) {
+                const uint32_t w1 = d[r][1], w2 = d[r][2], w3 = d[r][3];
+                d[r][0] = shift == 0 ? d[r][0] : shift == 4 ? w1 : w2;
+                d[r][1] = shift == 0 ? w1 : shift == 4 ? w2 : w3;
+                d[r][2] = shift == 0 ? w2 : w3;
+            }
+        }
         float acc[MT][RG];
 #pragma unroll
         for (int t = 0; t < MT; ++t)
@@ -416,7 +482,7 @@ void k_qgemv(GemvBatch bt) {
             w[3] = d[r][3] >> sh;
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
-                const float2 cw = cb_lds[gv_field<BITS>(w, k)];
+                const float2 cw = *reinterpret_cast<const float2 *>(reinterpret_cast<const char *>(cb_lds) + gv_field_x8<BITS>(w, k, mask8));
 #pragma unroll
                 for (int t = 0; t < MT; ++t)
                     acc[t][r] = __builtin_fmaf(cw.y, z[t][2 * k + 1], __builtin_fmaf(cw.x, z[t][2 * k], acc[t][r]));
@@ -428,17 +494,26 @@ void k_qgemv(GemvBatch bt) {
         for (int t = 0; t < MT; ++t) gv_reduce_rows<RG>(acc[t], lane);
         if ((lane & (WAVE / RG - 1)) == 0) {
 #pragma unroll
-            for (int t = 0; t < MT; ++t) my_red[(g * RG + my_row) * MT + t] += acc[t][0];
+            for (int t = 0; t < MT; ++t) {
+                float &sum = my_red[(g * RG + my_row) * MT + t];
+                sum = decltype(once)::value ? acc[t][0] : sum + acc[t][0];
+            }
         }
     };
-    auto fetch_step = [&](int step, uint32_t (&d)[RG][4]) {
-        const int slab = step / n_g;
-        fetch(slab, step - slab * n_g, d);
+    struct Place {                                              // of a step
+        int slab, g;
+    };
+    auto place = [&](int step) __attribute__((always_inline)) { return Place{step / n_g, step - step / n_g * n_g}; };
+    auto advance = [&](Place &at) __attribute__((always_inline)) {
+        if (++at.g == n_g) {
+            at.g = 0;
+            ++at.slab;
+        }
     };
 
     static_assert(!AHEAD || RB > 0, "only the self-rotating kernels run ahead");
     if constexpr (!AHEAD) {
-        if (cur_slab >= 0) load_z(cur_slab, z);                 // on its way while the codebook is staged
+        load_z(cur_slab, z);                                    // on its way while the codebook is staged
         // For more than one activation row the codebook goes from memory straight into LDS: wave w copies the 1 KB
         // pieces w, w + 4, ..., lane l the 16 bytes l of a piece (the instruction places lane l's bytes at base + 16 l);
         // measured 6 % faster at m = 4, 1-3 % slower at m = 1, where it goes through registers.
@@ -458,68 +533,94 @@ void k_qgemv(GemvBatch bt) {
         }
         for (int i = lane; i < UR * MT; i += WAVE) my_red[i] = 0.0f;
         __syncthreads();
+        load_norms();
 #pragma unroll 1
         for (int step = step0; step < step1; ++step) {
-            const int slab = step / n_g;
-            if (slab != cur_slab) {
-                load_z(slab, z);
-                cur_slab = slab;
+            const Place at = place(step);
+            if (at.slab != cur_slab) {
+                load_z(at.slab, z);
+                cur_slab = at.slab;
             }
             uint32_t d[RG][4];
-            fetch_step(step, d);
-            work(step, d);
+            fetch(at.slab, at.g, true, d);
+            work(std::false_type{}, at.slab, at.g, d);
         }
     } else {
         // A launch that rotates the activations itself is a small one -- one to three waves per SIMD, two to four steps
         // per wave -- and lasts as long as one wave's chain of memory round trips.  So the chain is kept short: the
-        // rotation's inputs, the workgroup's share of the codebook and the packed words of the wave's first two steps
+        // rotation's inputs, the workgroup's share of the codebook, the packed words of the wave's first two steps and the norms
         // are requested before anything is waited for (the rotation's first: it has arithmetic to do while the rest
-        // arrives), and from then on the next step's packed words are on their way while a step is worked on.
+        // arrives), and from then on the next step's packed words are on their way while a step is worked on.  What stood in
+        // the way: a branch on the element type or on the matrix's last row, at which the compiler waits for what either side
+        // may have asked for, loads moved into the branch that uses them, a loop of scalar loads, the rotation inputs of a
+        // wave's second and third slab.  A 7B layer's four launches, one row: 67 us, so 61; then issue-bound, 8 instructions
+        // a codeword, where the launch has two waves and more per SIMD (11008 x 4096 twice: 20 us, 62 MB).
         // bt.K == 2^BITS here.
         constexpr int KC = 1 << BITS, CB_PER_THREAD = (KC + GV_THREADS - 1) / GV_THREADS;
         GvRotIn<MT> rin;
-        rot_load(cur_slab >= 0 ? cur_slab : 0, rin);
+        rot_load(cur_slab, rin);
+        // in this order, and the addresses of the packed words not worked out before it is their turn (0.5 us)
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("" : "+s"(row_bytes));
+        asm volatile("" : "+s"(step0));
         float2 cbv[CB_PER_THREAD];
         const float2 *cbk = reinterpret_cast<const float2 *>(bt.codebook);
 #pragma unroll
         for (int j = 0; j < CB_PER_THREAD; ++j) cbv[j] = cbk[min((int)threadIdx.x + j * GV_THREADS, KC - 1)];
+        __builtin_amdgcn_sched_barrier(0);
         uint32_t da[RG][4], db[RG][4];
-        if (step0 < step1) fetch_step(step0, da);
-        if (step0 + 1 < step1) fetch_step(step0 + 1, db);
-        if (cur_slab >= 0) rot_finish(cur_slab, rin, z);
+        Place at = place(min(step0, n_steps - 1)), ask = at;
+        auto fetch_next = [&](int step, uint32_t (&d)[RG][4]) __attribute__((always_inline)) {
+            fetch(ask.slab, ask.g, step < step1, d);            // (past the wave's last step: places that may not exist, not read)
+            advance(ask);
+        };
+        fetch_next(step0, da);
+        fetch_next(step0 + 1, db);
+        load_norms();
+        __builtin_amdgcn_sched_barrier(0);
+        rot_finish(cur_slab, rin, z);
 #pragma unroll
         for (int j = 0; j < CB_PER_THREAD; ++j)
             if ((int)threadIdx.x + j * GV_THREADS < KC) cb_lds[threadIdx.x + j * GV_THREADS] = cbv[j];
         for (int i = lane; i < UR * MT; i += WAVE) my_red[i] = 0.0f;
         __syncthreads();
-        auto keep_z = [&](int step) {
-            const int slab = step / n_g;
-            if (slab != cur_slab) {
-                load_z(slab, z);
-                cur_slab = slab;
+        // SEVERAL: the wave's steps are of more than one slab.  The next one's rotation inputs are then asked for while a slab is
+        // worked on (for one activation row: two rows' inputs would cost registers that are not there).
+        const int last_slab = step0 < step1 ? (step1 - 1) / n_g : cur_slab;
+        auto walk = [&](auto several) __attribute__((always_inline)) {
+            constexpr bool SEVERAL = decltype(several)::value, EARLY = MT == 1;
+            if (SEVERAL && EARLY) rot_load(cur_slab + 1, rin);
+            auto next = [&](uint32_t (&d)[RG][4]) __attribute__((always_inline)) {
+                if (SEVERAL && at.slab != cur_slab) {
+                    if (!EARLY) rot_load(at.slab, rin);
+                    rot_finish(at.slab, rin, z);
+                    if (EARLY) rot_load(min(at.slab + 1, last_slab), rin);
+                    cur_slab = at.slab;
+                }
+                work(std::bool_constant<!SEVERAL>{}, at.slab, at.g, d);
+                advance(at);
+            };
+#pragma unroll 1
+            for (int step = step0; step < step1; step += 2) {
+                next(da);
+                fetch_next(step + 2, da);
+                if (step + 1 < step1) next(db);
+                fetch_next(step + 3, db);
             }
         };
-#pragma unroll 1
-        for (int step = step0; step < step1; step += 2) {
-            keep_z(step);
-            work(step, da);
-            if (step + 2 < step1) fetch_step(step + 2, da);
-            if (step + 1 < step1) {
-                keep_z(step + 1);
-                work(step + 1, db);
-                if (step + 3 < step1) fetch_step(step + 3, db);
-            }
-        }
+        if (last_slab > cur_slab) walk(std::true_type{});
+        else walk(std::false_type{});
     }
     __syncthreads();
     // the 4 waves' sums in wave order, times the row norm
-    for (int o = threadIdx.x; o < rpw * MT; o += GV_THREADS) {
-        const int row = o / MT, t = o - row * MT;
-        if (t < m && row0 + row <= last_row) {
+#pragma unroll
+    for (int i = 0; i < NORMS; ++i) {
+        const int o = threadIdx.x + i * GV_THREADS, row = o / MT, t = o - row * MT;
+        if (o < rpw * MT && t < m && row0 + row <= last_row) {
             float s = 0.0f;
 #pragma unroll
             for (int w = 0; w < GV_WAVES; ++w) s += red[(w * UR + row) * MT + t];
-            M.Y[(int64_t)t * M.ldy + row0 + row] = M.norms[row0 + row] * s;
+            M.Y[(int64_t)t * M.ldy + row0 + row] = norm[i] * s;
         }
     }
 }
@@ -1125,6 +1226,26 @@ static hipError_t launch_qgemm_wide(const GemvBatch &bt, hipStream_t stream) {
 // two-launch / the self-rotating form of the vector kernel.
 hipError_t launch_matmul_batch(const MatmulItem *items, int n, int xdtype, int m, const Problem &p, void *workspace, int variant) {
     if (n < 1 || n > QAMW_MATMUL_MAX_BATCH || p.K != (1 << p.bits)) return hipErrorNotSupported;   // the kernels size the codebook from the bit width
+    // The vector kernel's offsets into a group of rows are 32 bits: rows of 2^28 bytes and more one at a time.
+    constexpr int64_t LONG_ROW = (int64_t)1 << 28;
+    for (int i = 0; i < n && m <= GV_MAX_M; ++i) {
+        const int64_t row_bytes = (((int64_t)(items[i].d_in / 2) * p.bits + 31) / 32) * 4;
+        if (row_bytes < LONG_ROW || items[i].d_out == 1) continue;
+        for (int k = 0; k < n; ++k) {
+            const int64_t kb = (((int64_t)(items[k].d_in / 2) * p.bits + 31) / 32) * 4;
+            const int rows = kb < LONG_ROW ? items[k].d_out : 1;
+            for (int row = 0; row < items[k].d_out; row += rows) {
+                MatmulItem one = items[k];
+                one.d_out = rows;
+                one.packed += row * kb;
+                one.norms += row;
+                one.Y += row;
+                const hipError_t e = launch_matmul_batch(&one, 1, xdtype, m, p, workspace, variant);
+                if (e != hipSuccess) return e;
+            }
+        }
+        return hipSuccess;
+    }
     GemvBatch bt;
     int64_t rot = 0, groups = 0;
     char *ws = static_cast<char *>(workspace);
