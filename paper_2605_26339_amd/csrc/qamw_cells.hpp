@@ -78,7 +78,8 @@ __device__ __forceinline__ void wave_nearest(float &d, float2 &c) {
 // Candidate lists of 8 x 8 cells by one workgroup; wave w takes their w-th quarter of 4 x 4 cells.
 // stopped_at, t: nothing is made once *stopped_at < t (looked at while the codewords are on their way).
 //   Bound by latency, one workgroup per CU: hence minima and prefix sums by DPP moves and ballots instead of shuffles, and
-// LDS reads four to eight at a time (2048 points, 16 x 16 regions: 8.2 us; 14 x 14 with shuffles and one read at a time 11.3).
+// LDS reads four to sixteen at a time (2048 points, 16 x 16 regions: 7.8 us; with a cell's candidates read four at a time, twice,
+// and their indices one by one 9.1; 14 x 14 with shuffles and one read at a time 11.3).
 template <int G>
 __device__ __forceinline__ void cells_build_region(const float *codebook, int K, float half_per_sum, uint2 *table, int region,
                                                    const int *stopped_at = nullptr, int t = 0) {
@@ -216,24 +217,29 @@ __device__ __forceinline__ void cells_build_region(const float *codebook, int K,
     my = ((float)iy - 0.5f * G) * h;
     w = 0.5f * h + slack;
     const int quarter = (n_blk + 3) >> 2, e_begin = part * quarter, e_end = min(n_blk, e_begin + quarter);
+    // The quarter's candidates in registers, in one round of LDS reads; those of a longer list are read again in both passes.
+    constexpr int HELD = CP_BLOCK_LIST / 8;
+    float2 held[HELD];
+    float dh[HELD];
+#pragma unroll
+    for (int q = 0; q < HELD; ++q) held[q] = blk_c[wid][min(e_begin + q, CP_BLOCK_LIST - 1)];
     float da = 3.0e38f, db = 3.0e38f;                           // nearest and second nearest
     float2 ca = make_float2(0.0f, 0.0f), cb = ca;
-    for (int e0 = e_begin; e0 < e_end; e0 += 4) {
-        float2 c4[4];
+    auto rank = [&](float2 c, float d) {
+        const bool first_of_all = d < da, second = d < db;
+        cb.x = first_of_all ? ca.x : second ? c.x : cb.x;
+        cb.y = first_of_all ? ca.y : second ? c.y : cb.y;
+        db = first_of_all ? da : second ? d : db;
+        ca.x = first_of_all ? c.x : ca.x;
+        ca.y = first_of_all ? c.y : ca.y;
+        da = first_of_all ? d : da;
+    };
 #pragma unroll
-        for (int q = 0; q < 4; ++q) c4[q] = blk_c[wid][min(e0 + q, e_end - 1)];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float d = e0 + q < e_end ? cells_dist2(mx, my, c4[q]) : 3.0e38f;
-            const bool first_of_all = d < da, second = d < db;
-            cb.x = first_of_all ? ca.x : second ? c4[q].x : cb.x;
-            cb.y = first_of_all ? ca.y : second ? c4[q].y : cb.y;
-            db = first_of_all ? da : second ? d : db;
-            ca.x = first_of_all ? c4[q].x : ca.x;
-            ca.y = first_of_all ? c4[q].y : ca.y;
-            da = first_of_all ? d : da;
-        }
+    for (int q = 0; q < HELD; ++q) {
+        dh[q] = e_begin + q < e_end ? cells_dist2(mx, my, held[q]) : 3.0e38f;
+        rank(held[q], dh[q]);
     }
+    for (int e = e_begin + HELD; e < e_end; ++e) rank(blk_c[wid][e], cells_dist2(mx, my, blk_c[wid][e]));
     auto merge = [&](float oda, float odb, float2 oca, float2 ocb) {
         // each side's two, sorted: the first is the smaller head, the second the smaller of the other head and its own second
         const bool swap = oda < da;
@@ -252,17 +258,14 @@ __device__ __forceinline__ void cells_build_region(const float *codebook, int K,
     merge(dpp_move<DPP_XOR2>(da), dpp_move<DPP_XOR2>(db), make_float2(dpp_move<DPP_XOR2>(ca.x), dpp_move<DPP_XOR2>(ca.y)),
           make_float2(dpp_move<DPP_XOR2>(cb.x), dpp_move<DPP_XOR2>(cb.y)));
     unsigned kept = 0;                                          // bit e - e_begin (a quarter is at most 32 candidates)
-    for (int e0 = e_begin; e0 < e_end; e0 += 4) {
-        float2 c4[4];
+    auto keeps = [&](float2 c, float d) {
+        return !(cells_dominated(c, d, ca, da, w) || (db < 3.0e38f && cells_dominated(c, d, cb, db, w)));
+    };
 #pragma unroll
-        for (int q = 0; q < 4; ++q) c4[q] = blk_c[wid][min(e0 + q, e_end - 1)];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float d = cells_dist2(mx, my, c4[q]);
-            const bool out = cells_dominated(c4[q], d, ca, da, w) || (db < 3.0e38f && cells_dominated(c4[q], d, cb, db, w));
-            if (!out && e0 + q < e_end) kept |= 1u << (e0 + q - e_begin);
-        }
-    }
+    for (int q = 0; q < HELD; ++q)
+        if (e_begin + q < e_end && keeps(held[q], dh[q])) kept |= 1u << q;
+    for (int e = e_begin + HELD; e < e_end; ++e)
+        if (keeps(blk_c[wid][e], cells_dist2(mx, my, blk_c[wid][e]))) kept |= 1u << (e - e_begin);
     const int mine = __popc(kept);
     const int n0 = dpp_move<dpp_quad_lane(0)>(mine), n1 = dpp_move<dpp_quad_lane(1)>(mine), n2 = dpp_move<dpp_quad_lane(2)>(mine);
     int before = (part > 0 ? n0 : 0) + (part > 1 ? n1 : 0) + (part > 2 ? n2 : 0);
@@ -270,7 +273,7 @@ __device__ __forceinline__ void cells_build_region(const float *codebook, int K,
     while (kept) {
         const int e = e_begin + __ffs((int)kept) - 1;
         kept &= kept - 1u;
-        if (before < CELLS_LIST) rec_i[wid][cell][before] = blk_i[wid][e];
+        if (before < CELLS_LIST) rec_i[wid][cell][before] = (uint16_t)e;   // the place in the list: its index is read once all are in
         ++before;
     }
     __syncthreads();
@@ -281,7 +284,7 @@ __device__ __forceinline__ void cells_build_region(const float *codebook, int K,
         if (inside && total >= 1 && total <= CELLS_LIST) {
             unsigned i5[CELLS_LIST];
 #pragma unroll
-            for (int q = 0; q < CELLS_LIST; ++q) i5[q] = rec_i[wid][cell][q < total ? q : 0];
+            for (int q = 0; q < CELLS_LIST; ++q) i5[q] = blk_i[wid][rec_i[wid][cell][q < total ? q : 0]];
             // ascending; bits 3, 15, 27, 39, 51 onwards, padded with the first
             r.x = (i5[0] << 3) | (i5[1] << 15) | (i5[2] << 27) | (total > 3 ? CELLS_MORE : 0u);
             r.y = (i5[2] >> 5) | (i5[3] << 7) | (i5[4] << 19);
