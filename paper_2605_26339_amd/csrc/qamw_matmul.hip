@@ -210,13 +210,14 @@ __global__ __launch_bounds__(GV_THREADS) void k_rotate_x(GemvBatch bt) {
     }
 }
 
-// The same rounded to bf16 (nearest even), in the order above: a workgroup takes 8 R activation rows of one slab, R a wave, and
-// turns them in LDS, so that 128 R consecutive bytes go to memory: a row by itself would write 16 bytes to each of 128 places
-// (1000 rows of 4096: 11.5 -> 9.4 us).  Rows from m up to the next multiple of 32 are zeros.
-template <int XDTYPE, int B, int R>
+// The same rounded to bf16 (nearest even), in the order above: a workgroup takes 8 R activation rows of one slab, R a wave.
+// TURN: in LDS they are turned, so that 128 R consecutive bytes go to memory, where a row by itself writes 16 bytes to each of 128
+// places (1000 rows of 4096, R = 2: 11.5 -> 9.4 us); few rows are sooner written as they are (64 rows: 0.5 us).  Rows from m up
+// to the next multiple of 32 are zeros.
+template <int XDTYPE, int B, int R, bool TURN>
 __global__ __launch_bounds__(GM_THREADS) void k_rotate_tile(GemvBatch bt) {
     constexpr int ROWS = 8 * R, PITCH = 16 * ROWS + 16;         // bytes of eight columns of all rows; the 16 spread the lanes over the banks
-    __shared__ __align__(16) char turned[GV_SLAB / 8 * PITCH];
+    __shared__ __align__(16) char turned[TURN ? GV_SLAB / 8 * PITCH : 16];
     const int lane = threadIdx.x & (WAVE - 1);
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int item = blockIdx.x;
@@ -240,10 +241,20 @@ __global__ __launch_bounds__(GM_THREADS) void k_rotate_tile(GemvBatch bt) {
             const gv_f32x2_t v = {y[e], y[e + 1]};
             o[e >> 1] = row0 + wid * R + t < bt.m ? __builtin_bit_cast(uint32_t, __builtin_convertvector(v, gv_bf16x2_t)) : 0u;
         }
+        if (!TURN) {
+            const int col = slab * GV_SLAB + 16 * pos;
+            uint16_t *z = reinterpret_cast<uint16_t *>(M.Z) + gm_z_offset(row0 + wid * R + t, col, d_in);
+            if (col < d_in) {                                   // the next eight columns are those of the next instruction
+                *reinterpret_cast<uint4 *>(z) = make_uint4(o[0], o[1], o[2], o[3]);
+                *reinterpret_cast<uint4 *>(z + 32 * 8) = make_uint4(o[4], o[5], o[6], o[7]);
+            }
+            continue;
+        }
         char *dst = turned + 2 * pos * PITCH + 16 * (wid * R + t);
         *reinterpret_cast<uint4 *>(dst) = make_uint4(o[0], o[1], o[2], o[3]);
         *reinterpret_cast<uint4 *>(dst + PITCH) = make_uint4(o[4], o[5], o[6], o[7]);
     }
+    if (!TURN) return;
     __syncthreads();
     uint16_t *zb = reinterpret_cast<uint16_t *>(M.Z);
 #pragma unroll
@@ -648,7 +659,10 @@ template <int BITS> __device__ __forceinline__ uint32_t gm_field_x4(const uint32
     return (v & ((1u << BITS) - 1u)) << 2;
 }
 
-template <int BITS, int MT>
+// ROWS: rows of the tile that a workgroup fills: all 32, or 16 (a launch of few workgroups is cut finer so that it covers the
+// chip; a row's sum is the same chunks in the same waves in the same order either way, bit for bit).  The tile's other rows are
+// then the same 16 again, gathers of the same addresses, and are not stored.
+template <int BITS, int MT, int ROWS>
 __global__ __launch_bounds__(GM_THREADS) __attribute__((amdgpu_waves_per_eu(4, 8)))   // two workgroups per CU: at most 128 registers
 void k_qgemm(GemvBatch bt) {
     extern __shared__ __align__(16) uint32_t gm_lds[];
@@ -665,41 +679,21 @@ void k_qgemm(GemvBatch bt) {
     const int grp = blockIdx.x;
     const int mi = gv_find(bt.grp_begin, grp);
     const GemvMat &M = bt.mat[mi];
-    // rows of the tile this workgroup fills: all 32, or the first 16 (a launch of few workgroups is cut finer so that it
-    // covers the chip; a row's sum is the same chunks in the same waves in the same order either way, bit for bit)
-    const int rows = bt.gm_rows;
-    const bool row_used = r < rows;
-    const int row0 = (grp - bt.grp_begin[mi]) * rows;
+    const int row0 = (grp - bt.grp_begin[mi]) * ROWS;
     const int d_in = M.d_in, last_row = M.d_out - 1, m = bt.m;
     const int64_t row_bytes = M.row_bytes;
-    const uint16_t *Zb = reinterpret_cast<const uint16_t *>(M.Z);
     const int n_chunks = d_in / GM_CHUNK;
 
-    {   // stage the codebook, rounded to bf16
-        const float2 *cbk = reinterpret_cast<const float2 *>(bt.codebook);
-        for (int i = threadIdx.x; i < bt.K; i += GM_THREADS) {
-            const float2 c = cbk[i];
-            const gv_f32x2_t v = {c.x, c.y};
-            cbh[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, gv_bf16x2_t));
-        }
-        __syncthreads();
-    }
-
-    // The chunk's packed bytes of the workgroup's 32 rows -- BITS 16-byte pieces per row -- are loaded with consecutive
-    // lanes on consecutive pieces (piece 64 i + lane of the row-major 32 x BITS array) and laid down in LDS row by row.
-    // Rows past the end of the matrix re-read the last row (their results are not stored); the pieces past the tile's
-    // last row (rows x BITS is not always a multiple of 64) are neither loaded nor written to LDS.
-    // (the offsets are recomputed where they are used: the vector ALU is idle here and the registers are not)
-    constexpr int PIECES = (GM_ROWS * BITS + 63) / 64;
-    const int tile_pieces = rows * BITS;
-    auto src_off = [&](int i) {
-        const int piece = 64 * i + lane, row = piece / BITS, c16 = piece - row * BITS;
-        return min(row0 + row, last_row) * (int)row_bytes + 16 * c16;
-    };
-    auto dst_off = [&](int i) {
-        const int piece = 64 * i + lane, row = piece / BITS, c16 = piece - row * BITS;
-        return row * PITCH + 16 * c16;
-    };
+    // The chunk's packed bytes of the workgroup's rows -- BITS 16-byte pieces per row -- are loaded with consecutive
+    // lanes on consecutive pieces (piece 64 i + lane of the row-major ROWS x BITS array) and laid down in LDS row by row.
+    // Rows past the end of the matrix re-read the last row (their results are not stored); lanes past the last piece
+    // read and write that one once more.
+    constexpr int PIECES = (ROWS * BITS + 63) / 64;
+    auto piece_row = [&](int i) { return min(64 * i + lane, ROWS * BITS - 1) / BITS; };
+    auto piece_col = [&](int i) { return 16 * (min(64 * i + lane, ROWS * BITS - 1) % BITS); };
+    uint32_t src_off[PIECES];
+#pragma unroll
+    for (int i = 0; i < PIECES; ++i) src_off[i] = (uint32_t)min(row0 + piece_row(i), last_row) * (uint32_t)row_bytes + piece_col(i);
     const uint32_t z_lane = (uint32_t)(h * 16 * 256 + r * 8) * 2;     // bytes; padded rows exist and are zero
 
     gv_f32x16_t acc[MT];
@@ -709,80 +703,92 @@ void k_qgemm(GemvBatch bt) {
         for (int i = 0; i < 16; ++i) acc[t][i] = 0.0f;
 
     // Wave w takes the chunks w, w + 8, ...: at any time the eight waves read neighbouring pieces of the same rows.
-    // The packed bytes of the wave's next chunk are requested before the current chunk's matrix instructions start.
-    typedef gv_u32x4_t u32x4_a4_t __attribute__((aligned(4)));
+    //   Loads come back in the order they were asked for, so an instruction's activations (from L2) must not be asked for behind
+    // the next chunk's packed bytes (from memory), or it waits for those.  Hence a ring of ZB instructions' activations, a slot
+    // filled again as soon as its instruction has been issued, and the packed bytes of the wave's next chunk requested when all
+    // activations of this one are on their way.  All loads are buffer loads without a branch around them, out of range where
+    // there is no next chunk: behind a branch the compiler waits for what either side may have asked for.  The first chunk's are
+    // requested before the codebook is staged.  (A wave without a chunk reads another's.)  The four launches of a 7B layer at 32
+    // rows, in a trace: 24.2 + 10.2 + 20 + 17.4 us, so 21.6 + 7.8 + 18 + 15.0; 4096 x 11008, 64 rows, a call: 31.4 -> 26.0.
+    //   Ring: four slots for one tile of activation rows, two for two, what the registers hold.
     gv_u32x4_t v[PIECES];
+    const int packed_bytes = M.d_out * (int)row_bytes;
+    auto load_packed = [&](int ch, bool wanted) {
+        const int at = ch * (16 * BITS);
+        const auto res = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(M.packed + at), 0, wanted ? packed_bytes - at : 0, 0x00020000);
 #pragma unroll
-    for (int i = 0; i < PIECES; ++i) v[i] = gv_u32x4_t{0u, 0u, 0u, 0u};
-    if (wid < n_chunks) {
-        const uint8_t *src = M.packed + (int64_t)wid * (16 * BITS);
-#pragma unroll
-        for (int i = 0; i < PIECES; ++i)
-            if (64 * i + lane < tile_pieces) v[i] = *reinterpret_cast<const u32x4_a4_t *>(src + src_off(i));
-    }
-    // Activations.  One tile of activation rows: 8 instructions' worth at a time.  Two tiles: the registers hold 2, so each slot
-    // is filled again as soon as its instruction has been issued (in batches a wave waited for L2 eight times a chunk: 64 rows
-    // against 4096 x 11008, 7 bits, 31.7 -> 26.7 us, 11 bits 34.4 -> 31.8; with one tile the slots cost registers and time, 11008 x
-    // 4096 twice, 32 rows, 8 bits: 22.8 -> 25.2).
-    constexpr int ZB = MT == 1 ? 8 : 2;
-    constexpr bool RING = MT == 2;
-    gv_u32x4_t zb[MT][ZB];
-    const char *zbytes = reinterpret_cast<const char *>(Zb);
-    auto load_zb = [&](int ch, int step, int slot) {
-#pragma unroll
-        for (int t = 0; t < MT; ++t) zb[t][slot] = *reinterpret_cast<const gv_u32x4_t *>(zbytes + (((int64_t)t * n_chunks + ch) * 32 + step) * 512 + z_lane);
+        for (int i = 0; i < PIECES; ++i) v[i] = __builtin_amdgcn_raw_buffer_load_b128(res, src_off[i], 0, 0);
     };
-    if (RING && wid < n_chunks) {
+    constexpr int ZB = MT == 1 ? 4 : 2;
+    gv_u32x4_t zb[MT][ZB];
+    // the activations of instruction `step` of chunk ch
+    auto load_zb = [&](int ch, int step, bool wanted) {
 #pragma unroll
-        for (int j = 0; j < ZB; ++j) load_zb(wid, j, j);
+        for (int t = 0; t < MT; ++t) {
+            const char *at = reinterpret_cast<const char *>(M.Z) + ((int64_t)t * n_chunks + ch) * (32 * 512);
+            const auto res = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(at), 0, wanted ? 32 * 512 : 0, 0x00020000);
+            zb[t][step % ZB] = __builtin_amdgcn_raw_buffer_load_b128(res, z_lane + step * 512, 0, 0);
+        }
+    };
+    const int first_ch = min(wid, n_chunks - 1);
+    load_packed(first_ch, true);
+#pragma unroll
+    for (int j = 0; j < ZB; ++j) load_zb(first_ch, j, true);
+    const int row = row0 + r;
+    const float norm = M.norms[min(row, last_row)];
+    {   // stage the codebook, rounded to bf16
+        constexpr int KC = 1 << BITS, PER = (KC + GM_THREADS - 1) / GM_THREADS;
+        const float2 *cbk = reinterpret_cast<const float2 *>(bt.codebook);
+        float2 c[PER];
+#pragma unroll
+        for (int j = 0; j < PER; ++j) c[j] = cbk[min((int)threadIdx.x + j * GM_THREADS, KC - 1)];
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const gv_f32x2_t u = {c[j].x, c[j].y};
+            if (KC % GM_THREADS == 0 || (int)threadIdx.x + j * GM_THREADS < KC) cbh[threadIdx.x + j * GM_THREADS] = __builtin_bit_cast(uint32_t, __builtin_convertvector(u, gv_bf16x2_t));
+        }
+        __syncthreads();
     }
 #pragma unroll 1
     for (int ch = wid; ch < n_chunks; ch += GM_WAVES) {
-        const int next_ch = ch + GM_WAVES < n_chunks ? ch + GM_WAVES : ch;   // past the end: the same chunk again (unused)
+        const bool more = ch + GM_WAVES < n_chunks;
+        const int next_ch = more ? ch + GM_WAVES : ch;
         // the chunk's packed bytes go through LDS: written piece by piece, read back as the lane's stream of 64 pairs
 #pragma unroll
         for (int i = 0; i < PIECES; ++i) {
-            if (64 * i + lane >= tile_pieces) continue;
-            gv_u32x2_t *dst = reinterpret_cast<gv_u32x2_t *>(tile + dst_off(i));
+            gv_u32x2_t *dst = reinterpret_cast<gv_u32x2_t *>(tile + piece_row(i) * PITCH + piece_col(i));
             dst[0] = gv_u32x2_t{v[i][0], v[i][1]};
             dst[1] = gv_u32x2_t{v[i][2], v[i][3]};
         }
         uint32_t w[2 * BITS];
-        if (row_used) {
-            const gv_u32x2_t *src = reinterpret_cast<const gv_u32x2_t *>(tile + r * PITCH + 8 * BITS * h);
+        const gv_u32x2_t *src = reinterpret_cast<const gv_u32x2_t *>(tile + (r & (ROWS - 1)) * PITCH + 8 * BITS * h);
 #pragma unroll
-            for (int q = 0; q < BITS; ++q) {
-                const gv_u32x2_t x2 = src[q];
-                w[2 * q] = x2[0];
-                w[2 * q + 1] = x2[1];
-            }
+        for (int q = 0; q < BITS; ++q) {
+            const gv_u32x2_t x2 = src[q];
+            w[2 * q] = x2[0];
+            w[2 * q + 1] = x2[1];
         }
-        auto load_batch = [&](int first) {
+        gv_u32x4_t a[2];                                        // an instruction's codewords are gathered while the one before it runs
+        auto gather = [&](int step) {                           // pairs 4 step .. 4 step + 3 of the lane's 64
 #pragma unroll
-            for (int j = 0; j < ZB; ++j) load_zb(ch, first + j, j);
+            for (int f = 0; f < 4; ++f)
+                a[step & 1][f] = *reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(cbh) + gm_field_x4<BITS>(w, 4 * step + f));
         };
-        if (!RING) load_batch(0);
-        if (ch + GM_WAVES < n_chunks) {                         // the next chunk's packed bytes
-            const uint8_t *src = M.packed + (int64_t)(ch + GM_WAVES) * (16 * BITS);
+        gather(0);
 #pragma unroll
-            for (int i = 0; i < PIECES; ++i)
-                if (64 * i + lane < tile_pieces) v[i] = *reinterpret_cast<const u32x4_a4_t *>(src + src_off(i));
-        }
-#pragma unroll
-        for (int step = 0; step < 16; ++step) {                 // instruction of the chunk: pairs 4 step .. 4 step + 3 of the lane's 64
-            if (!RING && step > 0 && step % ZB == 0) load_batch(step);
-            gv_u32x4_t a = {0u, 0u, 0u, 0u};                    // the unused half of a 16-row workgroup's tile: zeros, no gathers
-            if (row_used) {
-#pragma unroll
-                for (int f = 0; f < 4; ++f)
-                    a[f] = *reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(cbh) + gm_field_x4<BITS>(w, 4 * step + f));
-            }
-            const gv_bf16x8_t av = __builtin_bit_cast(gv_bf16x8_t, a);
+        for (int step = 0; step < 16; ++step) {
+            if (step + 1 < 16) gather(step + 1);
+            const gv_bf16x8_t av = __builtin_bit_cast(gv_bf16x8_t, a[step & 1]);
 #pragma unroll
             for (int t = 0; t < MT; ++t)
                 acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, __builtin_bit_cast(gv_bf16x8_t, zb[t][step % ZB]), acc[t], 0, 0, 0);
-            // the slot is free: the activations of ZB instructions later, of the wave's next chunk at the end of this one
-            if (RING) load_zb(step + ZB < 16 ? ch : next_ch, (step + ZB) % 16, step % ZB);
+            if (step + ZB < 16) load_zb(ch, step + ZB, true);
+            else load_zb(next_ch, step + ZB - 16, more);
+            __builtin_amdgcn_sched_barrier(0);
+            if (step + ZB == 15) {
+                load_packed(next_ch, more);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
     }
 
@@ -793,9 +799,7 @@ void k_qgemm(GemvBatch bt) {
     // layer at 32 activation rows 104 us, so 94.
     constexpr int RED_PITCH = GM_ROWS + 1;                      // floats of one activation row's 32 sums
     constexpr int RED_WAVE = 32 * RED_PITCH;
-    const int row = row0 + r;
-    const bool row_ok = row_used && row <= last_row;
-    const float norm = M.norms[min(row, last_row)];
+    const bool row_ok = r < ROWS && row <= last_row;
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
         __syncthreads();
@@ -1149,8 +1153,9 @@ static hipError_t launch_rotate_tile(const GemvBatch &bt, int rows, int block, h
     const unsigned blocks = (unsigned)bt.rot_begin[bt.n];
 #define QAMW_ROT(BB) \
     case BB: \
-        if (rows == 16) hipLaunchKernelGGL((k_rotate_tile<XDTYPE, BB, 2>), dim3(blocks), dim3(GM_THREADS), 0, stream, bt); \
-        else hipLaunchKernelGGL((k_rotate_tile<XDTYPE, BB, 1>), dim3(blocks), dim3(GM_THREADS), 0, stream, bt); \
+        if (rows == 16) hipLaunchKernelGGL((k_rotate_tile<XDTYPE, BB, 2, true>), dim3(blocks), dim3(GM_THREADS), 0, stream, bt); \
+        else if (bt.m > GM_MAX_M) hipLaunchKernelGGL((k_rotate_tile<XDTYPE, BB, 1, true>), dim3(blocks), dim3(GM_THREADS), 0, stream, bt); \
+        else hipLaunchKernelGGL((k_rotate_tile<XDTYPE, BB, 1, false>), dim3(blocks), dim3(GM_THREADS), 0, stream, bt); \
         break;
     switch (block) {
         QAMW_ROT(64) QAMW_ROT(128) QAMW_ROT(256) QAMW_ROT(512) QAMW_ROT(1024)
@@ -1199,8 +1204,12 @@ static hipError_t launch_qgemm(const GemvBatch &bt, hipStream_t stream) {
     const size_t red_bytes = (size_t)GM_WAVES * 32 * (GM_ROWS + 1) * sizeof(float);
     const size_t tile_bytes = (size_t)GM_WAVES * GM_ROWS * (16 * BITS + 8);
     const size_t lds = (size_t)bt.K * sizeof(uint32_t) + (red_bytes > tile_bytes ? red_bytes : tile_bytes);
-    if (mt == 1) hipLaunchKernelGGL((k_qgemm<BITS, 1>), dim3(blocks), dim3(GM_THREADS), lds, stream, bt);
-    else hipLaunchKernelGGL((k_qgemm<BITS, 2>), dim3(blocks), dim3(GM_THREADS), lds, stream, bt);
+#define QAMW_GM(MM, RR) hipLaunchKernelGGL((k_qgemm<BITS, MM, RR>), dim3(blocks), dim3(GM_THREADS), lds, stream, bt)
+    if (mt == 1 && bt.gm_rows == GM_ROWS) QAMW_GM(1, GM_ROWS);
+    else if (mt == 1) QAMW_GM(1, GM_ROWS / 2);
+    else if (bt.gm_rows == GM_ROWS) QAMW_GM(2, GM_ROWS);
+    else QAMW_GM(2, GM_ROWS / 2);
+#undef QAMW_GM
     return hipGetLastError();
 }
 
