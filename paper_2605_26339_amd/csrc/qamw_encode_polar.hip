@@ -27,25 +27,36 @@ constexpr int PF_MAX_ROWS = 32;        // rows of a workgroup
 constexpr int PF_ITEMS = 48;           // (row, slab) items of a workgroup in a large launch
 constexpr int PF_CUS = 256;
 constexpr int PF_MAX_ITEMS = 64;       // (row, slab) items of a workgroup, unless one row has more
-constexpr uint32_t PF_DIR_AT = 4 * PF_MAX_LEVELS + 8 * PF_MAX_ITEMS + 4 * PF_MAX_ROWS;   // LDS before the directions
+// Lookup tables in place of the two binary searches, for workgroups of at least PF_LUT_ITEMS items (making them takes a
+// workgroup 1 us).  Amplitude: by exponent and five mantissa bits of |x|^2, 16 octaves from 2^-10 on.  Phase: by x0 / (|x0| + |x1|),
+// which falls with the angle in [0, pi), in 256 cells; its slope is at least half of the angle's, so with up to 256 bins no cell
+// holds two boundaries.  An entry says where the cell begins; the one boundary that may lie in it is tested as the searches test it.
+constexpr int PF_LUT_ITEMS = 16;
+constexpr int PF_AMP_CELLS = 512, PF_PHASE_CELLS = 256, PF_LUT_MIN_BINS = 8, PF_LUT_MAX_BINS = 256;
+constexpr uint32_t PF_AMP_BASE = (127 - 10) << 5;
+constexpr float PF_LUT_MAX_A2 = 1e30f;  // beyond, 1 / (|x0| + |x1|) is on its way to the subnormals: the searches
+constexpr uint32_t PF_LUT_AT = 4 * (PF_MAX_LEVELS + 4) + 8 * PF_MAX_ITEMS + 4 * PF_MAX_ROWS;
+constexpr uint32_t PF_DIR_AT = PF_LUT_AT + PF_AMP_CELLS + PF_PHASE_CELLS + 8;   // LDS before the directions
 
 // A workgroup of 8 waves owns `rows` consecutive rows: first the slab sums of all their (row, slab) items, dealt to the
 // waves, then -- after the barrier the table set-up needs anyway -- the items once more, in slab-major order, each wave a
 // consecutive share of them.  So every slab is summed once (a workgroup of four consecutive items summed each row again
 // for each of its items: 11 slabs per row, 3 to 5 times), and a wave loads, divides and combines the scales, signs and
 // gains of a slab once for all rows it has of it.
-//   Bound by vector-ALU issue (about 250 instructions of the front half and 40 per pair of the two searches for a
-// wave's 512 pairs), so the searches of the lane's 8 pairs go side by side: eight table reads in flight per step.
-// 4096 x 11008 bf16 at 5 + 6 bits, 90 MB read: 115 -> 85 us (264 Gpairs/s).
+//   Bound by vector-ALU issue (about 250 instructions of the front half for a wave's 512 pairs, and per pair some 50 of the two
+// binary searches or 25 with the lookup tables), so the lane's 8 pairs go side by side: eight table reads in flight per step.
+// 4096 x 11008 bf16 at 5 + 6 bits, 90 MB read: 115 -> 80 us with searches, 68 so (333 Gpairs/s); 11008 x 4096 at 4 + 4 73 -> 69.
+// (The next item's weights requested ahead: 1 to 3 % slower.)
 template <int DTYPE, int B>
 __global__ __launch_bounds__(PF_THREADS) void k_encode_polar(const void *__restrict__ W, int64_t ldw, Problem p,
                                                              const float *__restrict__ levels, int bits_a, int bits_p,
                                                              const float *__restrict__ norms_in, float *__restrict__ norms_out,
                                                              uint8_t *__restrict__ packed, int n_slabs, int rows) {
-    // LDS: thr2[i] = (midpoint of levels i-1, i)^2, i >= 1; the slab sums [row][slab]; the rows' norms; then the Np boundary
-    // directions (cos, sin)(2 k h)
-    constexpr uint32_t THR_AT = 0, PART_AT = 4 * PF_MAX_LEVELS, NORM_AT = PART_AT + 8 * PF_MAX_ITEMS, DIR_AT = PF_DIR_AT;
-    static_assert(DIR_AT == NORM_AT + 4 * PF_MAX_ROWS, "layout");
+    // LDS: thr2[i] = (midpoint of levels i-1, i)^2, i >= 1, and infinity; the slab sums [row][slab]; the rows' norms; the lookup
+    // tables and whether they serve; then the Np boundary directions (cos, sin)(2 k h), and the first again
+    constexpr uint32_t THR_AT = 0, PART_AT = 4 * (PF_MAX_LEVELS + 4), NORM_AT = PART_AT + 8 * PF_MAX_ITEMS, DIR_AT = PF_DIR_AT;
+    constexpr uint32_t AMP_AT = PF_LUT_AT, PHASE_AT = AMP_AT + PF_AMP_CELLS, NO_LUT_AT = PHASE_AT + PF_PHASE_CELLS;
+    static_assert(AMP_AT == NORM_AT + 4 * PF_MAX_ROWS && DIR_AT == NO_LUT_AT + 8, "layout");
     const int Na = 1 << bits_a, Np = 1 << bits_p;
     const int lane = threadIdx.x & (WAVE - 1);
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -67,7 +78,38 @@ __global__ __launch_bounds__(PF_THREADS) void k_encode_polar(const void *__restr
         sincospif(2.0f * (float)k / (float)Np, &sn, &cs);      // the angle 2 k h = pi * (2k / Np), argument exact
         lds_write<lds_f32x2_t>(DIR_AT + 8 * k, lds_f32x2_t{cs, sn});
     }
+    const bool want_lut = n_items >= PF_LUT_ITEMS && Np >= PF_LUT_MIN_BINS && Np <= PF_LUT_MAX_BINS;
+    if (threadIdx.x == 0) {
+        lds_write<float>(THR_AT + 4 * Na, __builtin_inff());
+        lds_write<lds_f32x2_t>(DIR_AT + 8 * Np, lds_f32x2_t{1.0f, 0.0f});
+        lds_write<uint32_t>(NO_LUT_AT, want_lut ? 0u : 1u);
+    }
     __syncthreads();
+    if (want_lut) {
+        // thresholds below v, the table taken as sorted (checked: thread i looks at the i-th)
+        auto below = [&](float v) {
+            int n = 0;
+            for (int step = Na >> 1; step; step >>= 1) n = lds_read<float>(THR_AT + 4 * (n + step)) < v ? n + step : n;
+            return n;
+        };
+        const uint32_t cell = threadIdx.x;                      // one each
+        static_assert(PF_AMP_CELLS == PF_THREADS, "a cell per thread");
+        const float lo = cell ? __uint_as_float((PF_AMP_BASE + cell) << 18) : 0.0f;
+        const float hi = cell + 1 < PF_AMP_CELLS ? __uint_as_float((PF_AMP_BASE + cell + 1) << 18) : __builtin_inff();
+        const int base = below(lo);
+        const bool sorted = (int)cell < 2 || (int)cell >= Na || lds_read<float>(THR_AT + 4 * cell) > lds_read<float>(THR_AT + 4 * (cell - 1));
+        if (below(hi) > base + 1 || !sorted) lds_write<uint32_t>(NO_LUT_AT, 1u);
+        lds_write<uint8_t>(AMP_AT + cell, (uint8_t)(4 * base));
+        if (cell < PF_PHASE_CELLS) {                            // boundaries of the upper half plane certainly passed: place > the cell's end
+            const float end = (float)(cell + 1) * (2.0f / PF_PHASE_CELLS) - 1.0f + 1e-5f;
+            int n = 0;
+            for (int step = Np >> 2; step; step >>= 1) {
+                const lds_f32x2_t b = lds_read<lds_f32x2_t>(DIR_AT + 8 * (n + step));
+                n = b[0] / (fabsf(b[0]) + fabsf(b[1])) > end ? n + step : n;
+            }
+            lds_write<uint8_t>(PHASE_AT + cell, (uint8_t)n);
+        }
+    }
     if ((int)threadIdx.x < n_rows) {
         const int dr = threadIdx.x;
         float r;
@@ -83,6 +125,7 @@ __global__ __launch_bounds__(PF_THREADS) void k_encode_polar(const void *__restr
     }
     __syncthreads();
 
+    const bool lut = lds_read<uint32_t>(NO_LUT_AT) == 0u;
     const LaneSigns<B> ls(lane);
     const int pos = slab_pos(lane);
     const float unit = ls.parity * p.inv_sqrt_block;
@@ -117,33 +160,57 @@ __global__ __launch_bounds__(PF_THREADS) void k_encode_polar(const void *__restr
         for (int e = 0; e < 16; ++e) x[e] = (x[e] * unit) * g[e >> 1];
 
         // ---------------- amplitude level and phase bin of the lane's 8 pairs
-        float a2[8];
+        float a2[8], most = 0.0f;
         unsigned ia[8], ip[8];                                  // times 4 and 8: byte offsets into the tables
+        bool upper[8];                                          // angle in [pi, 2 pi)
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
             const float x0 = x[2 * k], x1 = x[2 * k + 1];
             a2[k] = __builtin_fmaf(x1, x1, x0 * x0);
-            ia[k] = 0;
-            const bool upper = (x1 < 0.0f) || (x1 == 0.0f && x0 < 0.0f);   // angle in [pi, 2 pi)
-            ip[k] = upper ? 8u * (unsigned)(Np >> 1) : 0u;
+            most = fmaxf(most, a2[k]);
+            upper[k] = (x1 < 0.0f) || (x1 == 0.0f && x0 < 0.0f);
         }
-#pragma unroll 1
-        for (unsigned step = 4u * (unsigned)(Na >> 1); step >= 4u; step >>= 1) {
-            float t[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) t[k] = lds_read<float>(THR_AT + ia[k] + step);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) ia[k] = (a2[k] > t[k]) ? ia[k] + step : ia[k];   // on the threshold: the lower level
-        }
-#pragma unroll 1
-        for (unsigned step = 8u * (unsigned)(Np >> 2); step >= 8u; step >>= 1) {
-            lds_f32x2_t b[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) b[k] = lds_read<lds_f32x2_t>(DIR_AT + ip[k] + step);
+        if (lut && __ballot(!(most <= PF_LUT_MAX_A2)) == 0ull) {
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
-                const float cr = __builtin_fmaf(b[k][0], x[2 * k + 1], -(b[k][1] * x[2 * k]));   // sin(angle - 2 cand h) * |x|
-                ip[k] = (cr >= 0.0f) ? ip[k] + step : ip[k];
+                const int cell = (int)(__float_as_uint(a2[k]) >> 18) - (int)PF_AMP_BASE;
+                ia[k] = lds_read<uint8_t>(AMP_AT + (uint32_t)min(max(cell, 0), PF_AMP_CELLS - 1));
+                const float x0 = x[2 * k], x1 = x[2 * k + 1];
+                const float place = (upper[k] ? -x0 : x0) * __builtin_amdgcn_rcpf(fabsf(x0) + fabsf(x1));
+                const uint32_t at = (uint32_t)__builtin_fmaf(place, 0.5f * PF_PHASE_CELLS, 0.5f * PF_PHASE_CELLS);
+                ip[k] = 8u * lds_read<uint8_t>(PHASE_AT + min(at, (uint32_t)PF_PHASE_CELLS - 1u)) + (upper[k] ? 4u * (unsigned)Np : 0u);
+            }
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const float t = lds_read<float>(THR_AT + 4 + ia[k]);
+                const lds_f32x2_t b = lds_read<lds_f32x2_t>(DIR_AT + 8 + ip[k]);
+                ia[k] = a2[k] > t ? ia[k] + 4u : ia[k];
+                ip[k] = __builtin_fmaf(b[0], x[2 * k + 1], -(b[1] * x[2 * k])) >= 0.0f ? ip[k] + 8u : ip[k];
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                ia[k] = 0;
+                ip[k] = upper[k] ? 8u * (unsigned)(Np >> 1) : 0u;
+            }
+#pragma unroll 1
+            for (unsigned step = 4u * (unsigned)(Na >> 1); step >= 4u; step >>= 1) {
+                float t[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) t[k] = lds_read<float>(THR_AT + ia[k] + step);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) ia[k] = (a2[k] > t[k]) ? ia[k] + step : ia[k];   // on the threshold: the lower level
+            }
+#pragma unroll 1
+            for (unsigned step = 8u * (unsigned)(Np >> 2); step >= 8u; step >>= 1) {
+                lds_f32x2_t b[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) b[k] = lds_read<lds_f32x2_t>(DIR_AT + ip[k] + step);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    const float cr = __builtin_fmaf(b[k][0], x[2 * k + 1], -(b[k][1] * x[2 * k]));   // sin(angle - 2 cand h) * |x|
+                    ip[k] = (cr >= 0.0f) ? ip[k] + step : ip[k];
+                }
             }
         }
         unsigned idx[8];
@@ -176,7 +243,7 @@ static hipError_t launch_pdb(const void *W, int64_t ldw, const Problem &p, const
     // (us at 5 + 6 bits, bf16, one workgroup a row / so: 16 x 40960 23.2 / 9.7, 64 x 65536 35.7 / 15.6).
     int parts = 1;
     if (rows == 1) parts = std::max(1, std::min((n_slabs + PF_WAVES - 1) / PF_WAVES, 2 * PF_CUS / p.d_out));
-    const size_t lds = PF_DIR_AT + 8 * (size_t)(1 << bits_p);
+    const size_t lds = PF_DIR_AT + 8 * ((size_t)(1 << bits_p) + 1);
     hipLaunchKernelGGL((k_encode_polar<DTYPE, B>), dim3(blocks, (unsigned)parts), dim3(PF_THREADS), lds, p.stream, W, ldw, p, levels, bits_a,
                        bits_p, norms_ready ? norms : nullptr, norms, packed, n_slabs, rows);
     return hipGetLastError();
