@@ -248,9 +248,9 @@ int qamw_encode_batch_ws(const qamw_encode_item *items, int n_items, int dtype, 
  * does: relative change of the mean squared error below tol, or max_iters assignments; the points are not
  * moved after the last assignment, so the codebook and *mse_out belong together.
  * The call BLOCKS: it synchronises the stream to learn whether to stop.
- * workspace: device, qamw_lloyd_workspace_bytes() bytes, 16-byte aligned, owned by the caller (11 MB at 11 bits: for 64 to
- * 2048 points a table of the codewords near each cell of a grid, made anew in every iteration, and the workgroups' sums;
- * from 2^bits x 40 + 64 bytes on the call works without them, with the same points, by distances to all of them).
+ * workspace: device, qamw_lloyd_workspace_bytes() bytes, 16-byte aligned, owned by the caller (0.3 MB at 11 bits: for 64 to
+ * 2048 points a table of the codewords near each cell of a grid, made anew in every iteration;
+ * from 2^bits x 40 + 64 bytes on the call works without it, with the same points, by distances to all of them).
  * mse_out / iters_out: host, nullable.
  * Errors: bits outside [1,12], n_samples < 2^bits or > 2^24, max_iters < 1, tol < 0, NULL or misaligned
  * buffers, workspace too small -> INVALID_ARG. */

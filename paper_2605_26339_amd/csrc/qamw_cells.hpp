@@ -75,14 +75,29 @@ __device__ __forceinline__ void wave_nearest(float &d, float2 &c) {
     c = make_float2(lane_value(c.x, at), lane_value(c.y, at));
 }
 
+// What a thread of a workgroup that makes a part of the table holds: a run of consecutive codewords, and its lane's part of
+// the sample that R is found from (the same in every wave of every workgroup).
+struct CellsPoints {
+    float2 run[CP_PER_THREAD], sample[CP_SAMPLE / WAVE];
+};
+// point(i): the i-th of K codewords
+template <class Point> __device__ __forceinline__ CellsPoints cells_points(int K, Point point) {
+    CellsPoints p;
+    const int lane = threadIdx.x & (WAVE - 1), per = (K + CP_THREADS - 1) / CP_THREADS, first = (int)threadIdx.x * per;
+    const int spread = max(K / CP_SAMPLE, 1);
+#pragma unroll
+    for (int q = 0; q < CP_SAMPLE / WAVE; ++q) p.sample[q] = point(min(((lane >> 3) + 8 * q) * 8 * spread + (lane & 7), K - 1));
+#pragma unroll
+    for (int j = 0; j < CP_PER_THREAD; ++j) p.run[j] = point(j < per && first + j < K ? first + j : 0);
+    return p;
+}
+
 // Candidate lists of 8 x 8 cells by one workgroup; wave w takes their w-th quarter of 4 x 4 cells.
-// stopped_at, t: nothing is made once *stopped_at < t (looked at while the codewords are on their way).
 //   Bound by latency, one workgroup per CU: hence minima and prefix sums by DPP moves and ballots instead of shuffles, and
 // LDS reads four to sixteen at a time (2048 points, 16 x 16 regions: 7.8 us; with a cell's candidates read four at a time, twice,
 // and their indices one by one 9.1; 14 x 14 with shuffles and one read at a time 11.3).
 template <int G>
-__device__ __forceinline__ void cells_build_region(const float *codebook, int K, float half_per_sum, uint2 *table, int region,
-                                                   const int *stopped_at = nullptr, int t = 0) {
+__device__ __forceinline__ void cells_build_region(const CellsPoints &points, int K, float half_per_sum, uint2 *table, int region) {
     __shared__ float2 reg_c[CP_REGION_LIST];
     __shared__ uint16_t reg_i[CP_REGION_LIST];
     __shared__ float2 blk_c[CP_WAVES][CP_BLOCK_LIST];
@@ -92,24 +107,15 @@ __device__ __forceinline__ void cells_build_region(const float *codebook, int K,
     __shared__ float2 red_c[CP_WAVES];
     __shared__ int red_n[CP_WAVES];
     const int lane = threadIdx.x & (WAVE - 1), wid = threadIdx.x >> 6;
-    const float2 *cbk = reinterpret_cast<const float2 *>(codebook);
     const int x0 = (region % (G / 8)) * 8, y0 = (region / (G / 8)) * 8;
 
     // ---- 8 x 8 cells: every thread holds a run of consecutive codewords
     const int per = (K + CP_THREADS - 1) / CP_THREADS, first = (int)threadIdx.x * per;
-    float2 c[CP_PER_THREAD];
+    const float2 (&c)[CP_PER_THREAD] = points.run;
     float d2[CP_PER_THREAD];
-    const int stop = stopped_at ? *stopped_at : t;
-    float2 sample[CP_SAMPLE / WAVE];                            // the same in every wave of every workgroup
-    const int spread = max(K / CP_SAMPLE, 1);
-#pragma unroll
-    for (int q = 0; q < CP_SAMPLE / WAVE; ++q) sample[q] = cbk[min(((lane >> 3) + 8 * q) * 8 * spread + (lane & 7), K - 1)];
-#pragma unroll
-    for (int j = 0; j < CP_PER_THREAD; ++j) c[j] = cbk[j < per && first + j < K ? first + j : 0];
-    if (stop < t) return;
     float s = 0.0f;
 #pragma unroll
-    for (int q = 0; q < CP_SAMPLE / WAVE; ++q) s += q * WAVE + lane < K ? fabsf(sample[q].x) + fabsf(sample[q].y) : 0.0f;
+    for (int q = 0; q < CP_SAMPLE / WAVE; ++q) s += q * WAVE + lane < K ? fabsf(points.sample[q].x) + fabsf(points.sample[q].y) : 0.0f;
     s = wave_add(s) * half_per_sum;
     // squares of distances inside a cell stay normal numbers
     const float half = __uint_as_float((__float_as_uint(fminf(fmaxf(s, 0x1p-40f), 0x1p40f)) + 0x80000u) & 0xFFF00000u);

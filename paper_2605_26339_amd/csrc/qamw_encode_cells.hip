@@ -63,7 +63,8 @@ template <int DTYPE, int G, int R>
 __global__ __launch_bounds__(CP_THREADS) void k_cells_prepare(CellsBatch bt) {
     constexpr int REGIONS = (G / 8) * (G / 8);
     if (blockIdx.x < REGIONS) {
-        cells_build_region<G>(bt.codebook, bt.K, bt.half_per_sum, bt.table, (int)blockIdx.x);
+        const float2 *codebook = reinterpret_cast<const float2 *>(bt.codebook);
+        cells_build_region<G>(cells_points(bt.K, [=](int i) { return codebook[i]; }), bt.K, bt.half_per_sum, bt.table, (int)blockIdx.x);
         return;
     }
     const int b = (int)blockIdx.x - REGIONS;

@@ -96,7 +96,7 @@ struct MatmulItem {
 };
 bool matmul_wide(const MatmulItem *items, int n, int m);   // m activation rows at once go to the kernel for many rows
 hipError_t launch_matmul_batch(const MatmulItem *items, int n, int xdtype, int m, const Problem &p, void *workspace, int variant);
-size_t lloyd_workspace_bytes(int K);          // with room for the cell table and the workgroups' sums
+size_t lloyd_workspace_bytes(int K);          // with room for the cell table
 size_t lloyd_least_workspace_bytes(int K);    // what the search over all points needs
 hipError_t run_lloyd(const float *samples, long long n, int K, float *codebook, int max_iters, double tol, void *workspace,
                      size_t workspace_bytes, double *mse_out, int *iters_out, hipStream_t stream);

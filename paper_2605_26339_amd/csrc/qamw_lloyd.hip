@@ -9,7 +9,7 @@
 // result does not depend on the order the atomics land in.
 // k_lloyd_update: every point to the mean of its cell (an empty cell keeps its point).
 // k_cells_lloyd_*: the same iteration for 64 to 2048 points with a cell table (qamw_cells.hpp) made from every iteration's
-// points, the sums of a workgroup in LDS, and the stopping rule on the device, so the host launches ahead.
+// points, the sums of a workgroup in LDS first, and the stopping rule on the device, so the host launches ahead.
 #include <algorithm>
 #include <cmath>
 
@@ -124,35 +124,36 @@ __global__ __launch_bounds__(LL_THREADS) void k_lloyd_init(int K, LloydAcc acc, 
 }
 
 // ------------------------------------------------------------------------------------------------ with a cell table
-// Per iteration t, points in buffer t mod 2: k_cells_lloyd_table makes the table, k_cells_lloyd_assign assigns every sample
-// and leaves each workgroup's sums, k_cells_lloyd_move adds them up, decides whether to stop and writes the next points to
-// the other buffer.  Once it has stopped, the kernels of later iterations return at once.
-//   What bounds it: three launches that are each mostly latency.  2048 points, 2^20 samples (8 MB): 8.2 + 11.5 + 7.5 us an
-// iteration (the distances to all points took 401); the kernels ask for what they work on before they look whether to stop.
+// Per iteration t, points and sums in buffer t mod 2: k_cells_lloyd_table moves the points to the means of their cells in
+// iteration t - 1 and makes the table, k_cells_lloyd_assign assigns every sample and adds to the sums.  After iteration t the
+// next launch decides whether to stop; the kernels of later iterations then return at once.
+//   What bounds it: two launches that are each mostly latency.  2048 points, 2^20 samples (8 MB): 10.2 + 15.2 us an iteration.
+// A copy of the sums per workgroup (10.5 MB, more than the samples), added up by a launch of its own: 9.2 + 13.9 + 7.7; the
+// distances to all points took 401.  The kernels ask for what they work on before they look whether to stop.
 struct LloydState {
-    double D;
+    double D[2];                          // mean squared error of iteration t in D[t mod 2]
     int stopped_at;                       // the last iteration, LC_RUNNING before it is known
 };
 constexpr int LC_RUNNING = 0x7fffffff;
 constexpr int LC_THREADS = 1024;
-constexpr int LC_POINTS = 16;                                  // points per workgroup of k_cells_lloyd_move
-constexpr int LC_MAX_BLOCKS = 256;                             // one workgroup per CU: a workgroup's sums are 20 bytes per point in LDS and in the workspace
+constexpr int LC_MAX_BLOCKS = 256;                             // one workgroup per CU: a workgroup's sums are 20 bytes per point, each added to the one copy
+constexpr long long LC_HALF_UP_TO = 1 << 20;                   // samples up to which half as many workgroups cost less: see k_cells_lloyd_assign
 constexpr int LC_AHEAD = 16;                                   // iterations launched before the host looks whether it has stopped
 constexpr int LC_DENSE_ABOVE = 16;                             // of a wave's 64 samples
 constexpr int lc_side(int K) { return K >= 1024 ? 128 : 64; }
 
 struct LloydCells {
     double *cb64[2];
+    unsigned long long *sx[2], *sy[2];                         // K fixed-point sums
     float *cb32[2];
     uint2 *table;
-    long long *psx, *psy;                                      // [workgroups][K]
-    unsigned *pcnt;
-    unsigned long long *perr;                                  // [workgroups]
+    unsigned *cnt[2];
+    unsigned long long *err;                                   // [2]
     LloydState *state;
 };
 static size_t lloyd_cells_bytes(int K) {
     const size_t G = lc_side(K);
-    return (size_t)K * 2 * (16 + 8) + G * G * 8 + (size_t)LC_MAX_BLOCKS * ((size_t)K * 20 + 8) + 64;
+    return (size_t)K * 2 * (16 + 16 + 8 + 4) + G * G * 8 + 128;
 }
 static LloydCells lloyd_cells_layout(void *workspace, int K) {
     LloydCells a;
@@ -162,33 +163,101 @@ static LloydCells lloyd_cells_layout(void *workspace, int K) {
         p += bytes;
         return at;
     };
-    for (int i = 0; i < 2; ++i) a.cb64[i] = reinterpret_cast<double *>(take((size_t)K * 16));
-    for (int i = 0; i < 2; ++i) a.cb32[i] = reinterpret_cast<float *>(take((size_t)K * 8));
-    a.table = reinterpret_cast<uint2 *>(take((size_t)lc_side(K) * lc_side(K) * 8));
-    a.psx = reinterpret_cast<long long *>(take((size_t)LC_MAX_BLOCKS * K * 8));
-    a.psy = reinterpret_cast<long long *>(take((size_t)LC_MAX_BLOCKS * K * 8));
-    a.perr = reinterpret_cast<unsigned long long *>(take((size_t)LC_MAX_BLOCKS * 8));
     a.state = reinterpret_cast<LloydState *>(take(64));
-    a.pcnt = reinterpret_cast<unsigned *>(take((size_t)LC_MAX_BLOCKS * K * 4));
+    a.err = reinterpret_cast<unsigned long long *>(take(64));
+    for (int i = 0; i < 2; ++i) {
+        a.cb64[i] = reinterpret_cast<double *>(take((size_t)K * 16));
+        a.sx[i] = reinterpret_cast<unsigned long long *>(take((size_t)K * 8));
+        a.sy[i] = reinterpret_cast<unsigned long long *>(take((size_t)K * 8));
+        a.cb32[i] = reinterpret_cast<float *>(take((size_t)K * 8));
+        a.cnt[i] = reinterpret_cast<unsigned *>(take((size_t)K * 4));
+    }
+    a.table = reinterpret_cast<uint2 *>(take((size_t)lc_side(K) * lc_side(K) * 8));
     return a;
 }
 
+// The caller's points as the points of iteration -1, whose cells are all empty.
 __global__ __launch_bounds__(LL_THREADS) void k_cells_lloyd_init(int K, LloydCells a, const float *codebook) {
     const int i = blockIdx.x * LL_THREADS + threadIdx.x;
     if (i < 2 * K) {
-        a.cb64[0][i] = (double)codebook[i];
-        a.cb32[0][i] = codebook[i];
+        a.cb64[1][i] = (double)codebook[i];
+        a.cb32[1][i] = codebook[i];
     }
-    if (i == 0) *a.state = LloydState{0.0, LC_RUNNING};
+    if (i < K) {
+        a.sx[1][i] = 0;
+        a.sy[1][i] = 0;
+        a.cnt[1][i] = 0;
+    }
+    if (i == 0) {
+        a.err[1] = 0;
+        *a.state = LloydState{{0.0, 0.0}, LC_RUNNING};
+    }
 }
 
-template <int G> __global__ __launch_bounds__(CP_THREADS) void k_cells_lloyd_table(int K, float half_per_sum, LloydCells a, int t) {
-    cells_build_region<G>(a.cb32[t & 1], K, half_per_sum, a.table, (int)blockIdx.x, &a.state->stopped_at, t);
+// The mean squared error of iteration t, and whether it was the last.
+__device__ __forceinline__ bool lloyd_stops(const LloydCells &a, long long n, int t, int max_iters, double tol, double &D) {
+    const double prev = a.state->D[(t + 1) & 1];
+    D = (double)a.err[t & 1] / LL_SCALE / (double)n;
+    return (t > 0 && fabs(prev - D) < tol * prev) || t + 1 >= max_iters;
+}
+
+// Every workgroup computes all points, each writes its share of them and clears that share of this iteration's sums.  The
+// sums of iteration t - 1 are read by this launch alone.  One workgroup decides whether t - 1 was the last iteration; what
+// the others make meanwhile is then not looked at.
+template <int G>
+__global__ __launch_bounds__(CP_THREADS) void k_cells_lloyd_table(int K, float half_per_sum, LloydCells a, long long n, int t, int max_iters, double tol) {
+    __shared__ float2 points[2048 + 2048 / 8];                 // a place left out after eight: a thread reads a run of up to eight
+    auto place = [](int i) { return i + (i >> 3); };
+    const int from = (t + 1) & 1, to = t & 1;
+    const int stopped_at = a.state->stopped_at;
+    float2 old[CP_PER_THREAD];
+    long long sx[CP_PER_THREAD], sy[CP_PER_THREAD];
+    unsigned c[CP_PER_THREAD];
+#pragma unroll
+    for (int j = 0; j < CP_PER_THREAD; ++j) {
+        const int k = min((int)threadIdx.x + CP_THREADS * j, K - 1);
+        c[j] = a.cnt[from][k];
+        sx[j] = (long long)a.sx[from][k];
+        sy[j] = (long long)a.sy[from][k];
+        old[j] = reinterpret_cast<const float2 *>(a.cb32[from])[k];
+    }
+    if (stopped_at < t) return;
+    const int share = max(K / (int)gridDim.x, 1);
+#pragma unroll
+    for (int j = 0; j < CP_PER_THREAD; ++j) {
+        const int k = (int)threadIdx.x + CP_THREADS * j;
+        if (k >= K) break;
+        const double px = (double)sx[j] / LL_SCALE / (double)c[j], py = (double)sy[j] / LL_SCALE / (double)c[j];
+        const float2 p = c[j] > 0 ? make_float2((float)px, (float)py) : old[j];   // an empty cell keeps its point
+        points[place(k)] = p;
+        if (k / share == (int)blockIdx.x) {
+            a.cb64[to][2 * k] = c[j] > 0 ? px : a.cb64[from][2 * k];
+            a.cb64[to][2 * k + 1] = c[j] > 0 ? py : a.cb64[from][2 * k + 1];
+            reinterpret_cast<float2 *>(a.cb32[to])[k] = p;
+            a.sx[to][k] = 0;
+            a.sy[to][k] = 0;
+            a.cnt[to][k] = 0;
+        }
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        a.err[to] = 0;
+        if (t > 0) {
+            double D;
+            const bool stops = lloyd_stops(a, n, t - 1, max_iters, tol, D);
+            a.state->D[from] = D;
+            if (stops) a.state->stopped_at = t - 1;
+        }
+    }
+    __syncthreads();
+    cells_build_region<G>(cells_points(K, [&](int i) { return points[place(i)]; }), K, half_per_sum, a.table, (int)blockIdx.x);
 }
 
 // The records come from memory (L2), four samples' at a time: staging them took as long as the samples of a workgroup do, and
 // a table of 112 x 112 cells was all that fitted beside the sums, with 1.1 % of Gaussian samples in cells of six candidates --
 // a scan of the whole codebook in most waves, against 0.05 % with 128 x 128.  2048 points, 2^20 samples: 23.5 -> 11.5 us.
+//   The sums' atomics, three per point and workgroup, are what a workgroup costs whatever its share: 2048 points, 2^20 samples
+// 17.4 us with 256 workgroups, 16.8 with 192, 15.2 with 128, 16.0 with 96.  Beyond LC_HALF_UP_TO the samples weigh more: 16
+// iterations over 2^21 with all / half of the workgroups 570 / 564 us at 2048 points, 402 / 425 at 64.
 template <int G>
 __global__ __launch_bounds__(LC_THREADS) void k_cells_lloyd_assign(const float2 *__restrict__ samples, long long n, int K, LloydCells a, int t) {
     // points (at LDS address 0), then the sums: x, y (64 bits), count (32), error (64)
@@ -272,80 +341,35 @@ __global__ __launch_bounds__(LC_THREADS) void k_cells_lloyd_assign(const float2 
     for (int s = 1; s < WAVE; s <<= 1) err += __shfl_xor(err, s, WAVE);
     if (lane == 0) atomicAdd(&err_sum, (unsigned long long)__double2ll_rn(err * LL_SCALE));
     __syncthreads();
-    const size_t base = (size_t)blockIdx.x * K;
-    for (int k = threadIdx.x; k < K; k += LC_THREADS) {
-        a.psx[base + k] = (long long)sx[k];
-        a.psy[base + k] = (long long)sy[k];
-        a.pcnt[base + k] = cnt[k];
+    // each workgroup begins somewhere else, so that they seldom meet at an address
+    unsigned long long *to_x = a.sx[t & 1], *to_y = a.sy[t & 1];
+    unsigned *to_n = a.cnt[t & 1];
+    for (int i = threadIdx.x; i < K; i += LC_THREADS) {
+        const int k = (i + (int)blockIdx.x * WAVE) & (K - 1);
+        if (cnt[k] == 0) continue;
+        atomicAdd(to_x + k, sx[k]);
+        atomicAdd(to_y + k, sy[k]);
+        atomicAdd(to_n + k, cnt[k]);
     }
-    if (threadIdx.x == 0) a.perr[blockIdx.x] = err_sum;
+    if (threadIdx.x == 0) atomicAdd(a.err + (t & 1), err_sum);
 }
 
-// LC_POINTS points per workgroup, 1024 / LC_POINTS threads per point share the workgroups' sums (integers: any order gives
-// the same).  stopped_at becomes t in iteration t's own launch, so `< t` means the same to all its workgroups.
-__global__ __launch_bounds__(LC_THREADS) void k_cells_lloyd_move(long long n, int K, LloydCells a, int t, int n_blocks, int max_iters, double tol) {
-    constexpr int P = LC_POINTS, Q = LC_THREADS / P, NW = LC_THREADS / WAVE;
-    static_assert(P == 16 && LC_MAX_BLOCKS <= LC_THREADS, "a wave holds four threads of each point");
-    __shared__ long long red[2][NW][P];
-    __shared__ unsigned red_n[NW][P];
-    __shared__ unsigned long long err;
-    const int stopped_at = a.state->stopped_at;
-    const int p = threadIdx.x % P, q = threadIdx.x / P, k = blockIdx.x * P + p;
-    const unsigned long long my_err = blockIdx.x == 0 && (int)threadIdx.x < n_blocks ? a.perr[threadIdx.x] : 0ull;
-    if (threadIdx.x == 0) err = 0;
-    long long sx = 0, sy = 0;
-    unsigned c = 0;
-#pragma unroll 4
-    for (int b = q; b < n_blocks; b += Q) {
-        sx += a.psx[(size_t)b * K + k];
-        sy += a.psy[(size_t)b * K + k];
-        c += a.pcnt[(size_t)b * K + k];
-    }
-    if (stopped_at < t) return;
-#pragma unroll
-    for (int s = 16; s < WAVE; s <<= 1) {
-        sx += __shfl_xor(sx, s, WAVE);
-        sy += __shfl_xor(sy, s, WAVE);
-        c += __shfl_xor(c, s, WAVE);
-    }
-    const int wid = threadIdx.x / WAVE;
-    if ((threadIdx.x & (WAVE - 1)) < P) {
-        red[0][wid][p] = sx;
-        red[1][wid][p] = sy;
-        red_n[wid][p] = c;
-    }
-    __syncthreads();
-    if (my_err) atomicAdd(&err, my_err);
-    if (q == 0) {
-#pragma unroll
-        for (int r = 1; r < NW; ++r) {
-            sx += red[0][r][p];
-            sy += red[1][r][p];
-            c += red_n[r][p];
-        }
-        double px = a.cb64[t & 1][2 * k], py = a.cb64[t & 1][2 * k + 1];
-        if (c > 0) {
-            px = (double)sx / LL_SCALE / (double)c;
-            py = (double)sy / LL_SCALE / (double)c;
-        }
-        const int o = (t + 1) & 1;
-        a.cb64[o][2 * k] = px;
-        a.cb64[o][2 * k + 1] = py;
-        a.cb32[o][2 * k] = (float)px;
-        a.cb32[o][2 * k + 1] = (float)py;
-    }
-    __syncthreads();
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        const double prev = a.state->D, D = (double)err / LL_SCALE / (double)n;
-        a.state->D = D;
-        if ((t > 0 && fabs(prev - D) < tol * prev) || t + 1 >= max_iters) a.state->stopped_at = t;
-    }
-}
-
-// the points of the last assignment
-__global__ __launch_bounds__(LL_THREADS) void k_cells_lloyd_finish(int K, LloydCells a, float *codebook) {
+// After iteration t, the last that was launched: if it has stopped, the points of the last assignment.  stopped_at becomes t
+// here at most, and a workgroup that does not see it yet finds the same.
+__global__ __launch_bounds__(LL_THREADS) void k_cells_lloyd_finish(long long n, int K, LloydCells a, int t, int max_iters, double tol, float *codebook) {
     const int i = blockIdx.x * LL_THREADS + threadIdx.x;
-    if (i < 2 * K) codebook[i] = a.cb32[a.state->stopped_at & 1][i];
+    const float points[2] = {i < 2 * K ? a.cb32[0][i] : 0.0f, i < 2 * K ? a.cb32[1][i] : 0.0f};   // on their way meanwhile
+    int at = a.state->stopped_at;
+    if (at >= t) {
+        double D;
+        if (!lloyd_stops(a, n, t, max_iters, tol, D)) return;
+        at = t;
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            a.state->D[t & 1] = D;
+            a.state->stopped_at = t;
+        }
+    }
+    if (i < 2 * K) codebook[i] = at & 1 ? points[1] : points[0];
 }
 
 template <int G>
@@ -358,17 +382,18 @@ static hipError_t run_lloyd_cells(const float *samples, long long n, int K, floa
     const float half_per_sum = cells_half_per_sum(__builtin_ctz((unsigned)K));
     const unsigned kb = (unsigned)((2 * K + LL_THREADS - 1) / LL_THREADS);
     const long long want = (n + LC_THREADS - 1) / LC_THREADS;
-    const unsigned blocks = (unsigned)(want < LC_MAX_BLOCKS ? want : LC_MAX_BLOCKS);
+    const int most = n > LC_HALF_UP_TO ? LC_MAX_BLOCKS : LC_MAX_BLOCKS / 2;
+    const unsigned blocks = (unsigned)(want < most ? want : most);
     hipLaunchKernelGGL(k_cells_lloyd_init, dim3(kb), dim3(LL_THREADS), 0, stream, K, a, codebook);
-    LloydState s{0.0, LC_RUNNING};
+    LloydState s{{0.0, 0.0}, LC_RUNNING};
     for (int t = 0; s.stopped_at == LC_RUNNING;) {
         const int until = max_iters - t < LC_AHEAD ? max_iters : t + LC_AHEAD;
         for (; t < until; ++t) {
-            hipLaunchKernelGGL(k_cells_lloyd_table<G>, dim3((G / 8) * (G / 8)), dim3(CP_THREADS), 0, stream, K, half_per_sum, a, t);
+            hipLaunchKernelGGL(k_cells_lloyd_table<G>, dim3((G / 8) * (G / 8)), dim3(CP_THREADS), 0, stream, K, half_per_sum, a, n, t, max_iters, tol);
             hipLaunchKernelGGL(k_cells_lloyd_assign<G>, dim3(blocks), dim3(LC_THREADS), lds, stream,
                                reinterpret_cast<const float2 *>(samples), n, K, a, t);
-            hipLaunchKernelGGL(k_cells_lloyd_move, dim3(K / LC_POINTS), dim3(LC_THREADS), 0, stream, n, K, a, t, (int)blocks, max_iters, tol);
         }
+        hipLaunchKernelGGL(k_cells_lloyd_finish, dim3(kb), dim3(LL_THREADS), 0, stream, n, K, a, t - 1, max_iters, tol, codebook);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         e = hipMemcpyAsync(&s, a.state, sizeof s, hipMemcpyDeviceToHost, stream);
@@ -376,11 +401,9 @@ static hipError_t run_lloyd_cells(const float *samples, long long n, int K, floa
         e = hipStreamSynchronize(stream);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(k_cells_lloyd_finish, dim3(kb), dim3(LL_THREADS), 0, stream, K, a, codebook);
-    if (mse_out) *mse_out = s.D;
+    if (mse_out) *mse_out = s.D[s.stopped_at & 1];
     if (iters_out) *iters_out = s.stopped_at + 1;
-    const hipError_t e = hipStreamSynchronize(stream);
-    return e != hipSuccess ? e : hipGetLastError();
+    return hipSuccess;
 }
 
 // With a cell table from 64 points on: with fewer the distances to all of them are sooner computed than a table made.
