@@ -44,12 +44,11 @@ bool launch_row_norms_fast(const void *W, int dtype, int64_t ldw, int n_rows, co
 // ---------------------------------------------------------------------------------------------
 // Calibration of up to CAL_MAX_BATCH matrices in one pair of launches.
 // Step 1: one workgroup of 8 waves per chunk of CAL_ROWS consecutive rows of one matrix.  It first computes the norms of
-// its rows (slab sums in LDS, as the encoders do: the head rows are fetched from memory once), then wave w takes the slabs
-// w, w + CAL_WAVES, ... and sums |z_k| over the chunk's rows, row by row, in fp64, and writes one partial sum per pair.  A
-// small matrix is as long as one wave's chain, so rows of at most four slabs are split among the waves: 256 x 2048, the
-// only launch of 32 workgroups, 20.4 -> 12.2 us; 1024 head rows of 4096 columns 24.3 -> 16.1.  A layer's 1024 head rows of
-// seven matrices took 87.8 us, 69.1 with sqrt_magnitude(), the scales and signs once per slab and the next row on its way;
-// what is left is half issue (an instruction every 5.3 cycles, fp64 for the most part) and half waiting.
+// its rows (slab sums in LDS, to the bit those of the encoders: the head rows are fetched from memory once), then its waves sum
+// |z_k| over the chunk's rows, row by row, in fp64, and write one partial sum per pair; CalUnits deals out the slabs.  A
+// small matrix is as long as one wave's chain: 256 x 2048, the only launch of 32 workgroups, 20.4 us with a wave per slab, 12.2
+// with shared slabs; 1024 head rows of 4096 columns 24.3 -> 16.1.  What is left is some 30 of 51 us of issue for a 7B layer (fp64
+// for the most part) and waiting.
 // Step 2: per pair, the partial sums added up, then Eq. 1.
 // ---------------------------------------------------------------------------------------------
 struct CalMat {
@@ -70,20 +69,59 @@ struct CalBatch {
     float inv_sqrt_block;
 };
 
-// sqrt(a) of a >= 0 that is exact to a few fp64 roundings: the fp32 reciprocal square root (2^-23) and two Newton steps
-// (2^-46, then below 2^-53).  Outside the range of normal fp32, zero included, the library's square root; a wave takes that
-// for all its lanes.  8 fp64 operations instead of the 18 of sqrt(), whose scaling and special cases are not met here.
-__device__ __forceinline__ double sqrt_magnitude(double a) {
-    const float af = (float)a;
-    if (__ballot(!(af >= 1.0e-36f && af <= 1.0e36f)) != 0ull) return sqrt(a);
-    const float rf = __builtin_amdgcn_rsqf(af);
-    const double r = (double)rf, half = (double)(0.5f * rf);
-    double s = a * r;
-    s = __builtin_fma(__builtin_fma(-s, s, a), half, s);
-    return __builtin_fma(__builtin_fma(-s, s, a), half, s);
+// acc[k] += |(y[2k], y[2k + 1])|, the square root exact to a few fp64 roundings: the fp32 one (2^-22) and two Newton steps
+// (2^-44, then below 2^-53).  Where one of a wave's squares is outside the range of normal fp32, zero included, the library's
+// square root.  The squares of fp32 are exact in fp64, so the fused sum is rounded as a separate one.
+//   The eight chains are free of branches between them: with a test per pair they ran one after the other (4096 x 4096 bf16, this
+// launch 15.0 -> 14.4 us).
+__device__ __forceinline__ void add_magnitudes(double (&acc)[8], const float (&y)[16]) {
+    double a[8];
+    float af[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const double y0 = (double)y[2 * k], y1 = (double)y[2 * k + 1];
+        a[k] = __builtin_fma(y1, y1, y0 * y0);
+        af[k] = (float)a[k];
+    }
+    float least = af[0], most = af[0];
+#pragma unroll
+    for (int k = 1; k < 8; ++k) {
+        least = fminf(least, af[k]);
+        most = fmaxf(most, af[k]);
+    }
+    if (__ballot(!(least >= 1.0e-36f && most <= 1.0e36f)) != 0ull) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) acc[k] += sqrt(a[k]);
+        return;
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const float rf = __builtin_amdgcn_rsqf(af[k]);
+        const double half = (double)(0.5f * rf);
+        double s = (double)(af[k] * rf);
+        s = __builtin_fma(__builtin_fma(-s, s, a[k]), half, s);
+        acc[k] += __builtin_fma(__builtin_fma(-s, s, a[k]), half, s);
+    }
 }
 
-// Rows of few slabs: S waves share a slab's 8 rows, so that all 8 waves have one, and add their sums through LDS.
+// How the waves of a workgroup share its slabs: eight at a time a wave each, and of the rest S waves share a slab's 8 rows, so
+// that (nearly) all have some; their sums meet in LDS.  With 11 slabs a wave each, three waves did two slabs where the others
+// did one, and a launch is as long as its longest chain: seven matrices of a 7B layer 58.5 -> 51.2 us by the trace, of which these shares,
+// scales once per slab and rows requested together in the norms are a part (4096 x 4096 alone 14.4 -> 12.5).
+struct CalUnits {
+    int whole, rest, shift;                                     // slabs of a wave each, slabs that 1 << shift waves share
+    __device__ __forceinline__ explicit CalUnits(int n_slabs)
+        : whole(n_slabs & ~(CAL_WAVES - 1)), rest(n_slabs & (CAL_WAVES - 1)), shift(rest > 4 || rest == 0 ? 0 : rest > 2 ? 1 : rest > 1 ? 2 : 3) {}
+    __device__ __forceinline__ int count() const { return whole + (rest << shift); }
+    // unit u: its slab, and its rows of [row0, row1)
+    __device__ __forceinline__ int slab(int u) const { return u < whole ? u : whole + ((u - whole) >> shift); }
+    __device__ __forceinline__ void rows(int u, int row0, int row1, int &from, int &to) const {
+        const int s = u < whole ? 0 : shift;
+        from = row0 + (u & ((1 << s) - 1)) * (CAL_ROWS >> s);   // whole is a multiple of 8
+        to = min(row1, from + (CAL_ROWS >> s));
+    }
+};
+
 template <int DTYPE, int B>
 __global__ __launch_bounds__(CAL_THREADS) void k_calibrate_partial(CalBatch bt) {
     __shared__ double norm_part[CAL_ROWS * FUSED_NORM_MAX_SLABS];
@@ -104,22 +142,47 @@ __global__ __launch_bounds__(CAL_THREADS) void k_calibrate_partial(CalBatch bt) 
     double *__restrict__ partial = M.partial;
     const int chunk = (int)blockIdx.x - bt.chunk_begin[mi];
     const int row0 = chunk * CAL_ROWS, row1 = min(n_rows, row0 + CAL_ROWS);
-    const int tasks = (row1 - row0) * n_slabs;
-    for (int t = wid; t < tasks; t += CAL_WAVES) {
-        const int dr = t / n_slabs, slab = t - dr * n_slabs;
-        const double s2 = slab_sum_of_squares<DTYPE>(W, (int64_t)(row0 + dr) * ldw, slab, p, lane);
-        if (lane == 0) norm_part[t] = s2;
+    const CalUnits units(n_slabs);
+    constexpr int R = DTYPE == 0 ? 2 : 4;                       // rows requested together
+    for (int unit = wid; unit < units.count(); unit += CAL_WAVES) {
+        const int slab = units.slab(unit);
+        int from, to;
+        units.rows(unit, row0, row1, from, to);
+        const int c = slab * CSLAB + 16 * lane, at = c < p.d_in ? c : 0;
+        float sc[16];
+        Problem unsigned_scales = p;
+        unsigned_scales.signs = nullptr;
+        load_signed_scales(sc, unsigned_scales, at);
+#pragma unroll 1
+        for (int row = from; row < to; row += R) {
+            RawRow<DTYPE> raw[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) load_raw_row<DTYPE>(raw[r], W, (int64_t)min(row + r, to - 1) * ldw, at);
+#pragma unroll
+            for (int r = 0; r < R; ++r) {                       // the sums of slab_sum_of_squares(), to the bit
+                float w[16];
+                widen_raw_row<DTYPE>(w, raw[r]);
+                double s2 = 0.0;
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    w[e] *= sc[e];
+                    s2 = __builtin_fma((double)w[e], (double)w[e], s2);   // the product is exact: rounded once either way
+                }
+                s2 = wave_sum(c < p.d_in ? s2 : 0.0);
+                if (lane == 0 && row + r < to) norm_part[(row + r - row0) * n_slabs + slab] = s2;
+            }
+        }
     }
     __syncthreads();
     if ((int)threadIdx.x < row1 - row0) norm_row[threadIdx.x] = row_norm_from_slab_sums(norm_part, threadIdx.x, 0, n_slabs);
     __syncthreads();
-    const int shift = n_slabs > 4 ? 0 : n_slabs > 2 ? 1 : n_slabs > 1 ? 2 : 3, S = 1 << shift;   // S n_slabs <= 8 units, or S == 1
-    const int rows_per = CAL_ROWS >> shift;
     const LaneSigns<B> ls(lane);
     const float unit_factor = ls.parity * bt.inv_sqrt_block;
     double acc[8];
-    for (int unit = wid; unit < n_slabs << shift; unit += CAL_WAVES) {
-        const int slab = unit >> shift, from = row0 + (unit & (S - 1)) * rows_per, to = min(row1, from + rows_per);
+    for (int unit = wid; unit < units.count(); unit += CAL_WAVES) {
+        const int slab = units.slab(unit);
+        int from, to;
+        units.rows(unit, row0, row1, from, to);
         const int col0 = slab * CSLAB + 16 * slab_pos(lane);
         const bool active = col0 < p.d_in;
         const int c = active ? col0 : 0;
@@ -137,32 +200,31 @@ __global__ __launch_bounds__(CAL_THREADS) void k_calibrate_partial(CalBatch bt) 
             widen_raw_row<DTYPE>(y, raw);
 #pragma unroll
             for (int e = 0; e < 16; ++e) y[e] = y[e] * sc[e];
-            divide_by_norm(y, norm_row[row - row0]);
+            divide_by_norm(y, __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(norm_row[row - row0]))));
             fwht_wave<B>(y, ls);
 #pragma unroll
             for (int e = 0; e < 16; ++e) y[e] = y[e] * unit_factor;
-#pragma unroll
-            for (int k = 0; k < 8; ++k)
-                acc[k] += sqrt_magnitude((double)y[2 * k] * (double)y[2 * k] + (double)y[2 * k + 1] * (double)y[2 * k + 1]);
+            add_magnitudes(acc, y);
         }
-        if (S == 1 && active) {
+        if ((unit < units.whole || units.shift == 0) && active) {
             double *dst = partial + (int64_t)chunk * (p.d_in >> 1) + (c >> 1);
 #pragma unroll
             for (int k = 0; k < 8; ++k) dst[k] = acc[k];
         }
     }
-    if (S == 1) return;                                         // the same for the whole workgroup
-    if (wid < n_slabs << shift) {
+    if (units.shift == 0) return;                               // the same for the whole workgroup
+    if (wid < units.rest << units.shift) {                      // whose last unit was whole + wid
 #pragma unroll
         for (int k = 0; k < 8; ++k) shared_acc[wid][k][lane] = acc[k];
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < n_slabs * 8 * WAVE; i += CAL_THREADS) {
-        const int slab = i / (8 * WAVE), l = (i & (8 * WAVE - 1)) >> 3, k = i & 7;   // consecutive threads: consecutive pairs of a lane
-        const int col0 = slab * CSLAB + 16 * slab_pos(l);
+    for (int i = threadIdx.x; i < units.rest * 8 * WAVE; i += CAL_THREADS) {
+        const int sl = i / (8 * WAVE), l = (i & (8 * WAVE - 1)) >> 3, k = i & 7;     // consecutive threads: consecutive pairs of a lane
+        const int col0 = (units.whole + sl) * CSLAB + 16 * slab_pos(l);
         if (col0 >= p.d_in) continue;
-        double s = shared_acc[slab << shift][k][l];
-        for (int q = 1; q < S; ++q) s += shared_acc[(slab << shift) + q][k][l];
+        const int first = sl << units.shift;
+        double s = shared_acc[first][k][l];
+        for (int q = 1; q < 1 << units.shift; ++q) s += shared_acc[first + q][k][l];
         partial[(int64_t)chunk * (p.d_in >> 1) + (col0 >> 1) + k] = s;
     }
 }
