@@ -158,18 +158,28 @@ __global__ __launch_bounds__(CAL_THREADS) void k_calibrate_partial(CalBatch bt) 
             RawRow<DTYPE> raw[R];
 #pragma unroll
             for (int r = 0; r < R; ++r) load_raw_row<DTYPE>(raw[r], W, (int64_t)min(row + r, to - 1) * ldw, at);
+            double s2[R];
 #pragma unroll
             for (int r = 0; r < R; ++r) {                       // the sums of slab_sum_of_squares(), to the bit
                 float w[16];
                 widen_raw_row<DTYPE>(w, raw[r]);
-                double s2 = 0.0;
+                s2[r] = 0.0;
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    w[e] *= sc[e];
-                    s2 = __builtin_fma((double)w[e], (double)w[e], s2);   // the product is exact: rounded once either way
+                for (int e = 0; e < 16; ++e) s2[r] = add_square(s2[r], w[e] * sc[e]);
+                s2[r] = c < p.d_in ? s2[r] : 0.0;
+            }
+            auto put = [&](int r, double sum) {
+                if (row + r < to) norm_part[(row + r - row0) * n_slabs + slab] = sum;
+            };
+            if constexpr (R == 4) {
+                const double sum = wave_sum_4(s2);
+                if ((lane & 15) == 0) put(lane >> 4, sum);
+            } else {
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const double sum = wave_sum(s2[r]);
+                    if (lane == 0) put(r, sum);
                 }
-                s2 = wave_sum(c < p.d_in ? s2 : 0.0);
-                if (lane == 0 && row + r < to) norm_part[(row + r - row0) * n_slabs + slab] = s2;
             }
         }
     }

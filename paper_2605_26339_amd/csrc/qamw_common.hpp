@@ -67,7 +67,7 @@ constexpr int dpp_quad_lane(int q) { return q * 0x55; }
 
 // Sum over the 64 lanes of a wave in a fixed butterfly order (the same in every lane): lanes that differ in bit 0, then 1, ...
 // The mirrors serve for bits 2 and 3, since the lanes of a group of four, then eight, hold the same by then.
-__device__ __forceinline__ double wave_sum(double v) {
+__device__ __forceinline__ double wave_sum_of_16(double v) {     // each 16 lanes' sum
     auto step = [](double x, auto move) {
         return __hiloint2double(move(__double2hiint(x)), move(__double2loint(x)));
     };
@@ -75,12 +75,29 @@ __device__ __forceinline__ double wave_sum(double v) {
     v += step(v, [](int w) { return dpp_move<DPP_XOR2>(w); });
     v += step(v, [](int w) { return dpp_move<DPP_HALF_MIRROR>(w); });
     v += step(v, [](int w) { return dpp_move<DPP_MIRROR>(w); });
-    const auto h16 = __builtin_amdgcn_permlane16_swap((uint32_t)__double2hiint(v), (uint32_t)__double2hiint(v), false, false);
-    const auto l16 = __builtin_amdgcn_permlane16_swap((uint32_t)__double2loint(v), (uint32_t)__double2loint(v), false, false);
-    v = __hiloint2double((int)h16[0], (int)l16[0]) + __hiloint2double((int)h16[1], (int)l16[1]);
-    const auto h32 = __builtin_amdgcn_permlane32_swap((uint32_t)__double2hiint(v), (uint32_t)__double2hiint(v), false, false);
-    const auto l32 = __builtin_amdgcn_permlane32_swap((uint32_t)__double2loint(v), (uint32_t)__double2loint(v), false, false);
-    return __hiloint2double((int)h32[0], (int)l32[0]) + __hiloint2double((int)h32[1], (int)l32[1]);
+    return v;
+}
+// a in the lanes 0-15 and 32-47, b in the others: each the sum of its value in a pair of neighbouring 16 lanes
+__device__ __forceinline__ double wave_add_16(double a, double b) {
+    const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)__double2hiint(a), (uint32_t)__double2hiint(b), false, false);
+    const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)__double2loint(a), (uint32_t)__double2loint(b), false, false);
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+// a in the lower half of the lanes, b in the upper half: each the sum of its values 32 lanes apart
+__device__ __forceinline__ double wave_add_32(double a, double b) {
+    const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)__double2hiint(a), (uint32_t)__double2hiint(b), false, false);
+    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)__double2loint(a), (uint32_t)__double2loint(b), false, false);
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+__device__ __forceinline__ double wave_sum(double v) {
+    v = wave_sum_of_16(v);
+    v = wave_add_16(v, v);
+    return wave_add_32(v, v);
+}
+// wave_sum() of four values, to the bit: of v[r] in the lanes 16 r to 16 r + 15.
+__device__ __forceinline__ double wave_sum_4(const double (&v)[4]) {
+    const double a = wave_add_16(wave_sum_of_16(v[0]), wave_sum_of_16(v[1])), b = wave_add_16(wave_sum_of_16(v[2]), wave_sum_of_16(v[3]));
+    return wave_add_32(a, b);
 }
 
 // The smallest of the 64 lanes' values, in every lane; no NaN among them.

@@ -58,7 +58,8 @@ struct CellsBatch {
 // ------------------------------------------------------------------------------------------------ table and norms
 // Workgroups 0 .. (G/8)^2 - 1 make the table; the rest compute the row norms.
 // R rows per wave: large launches take four, which fetches the channel scales (twice the bytes of bf16 weights) a quarter as
-// often.  A 7B layer, 405 MB: 87 us with one row per wave, 77 so (84 with the sums slab by slab).
+// often.  A 7B layer, 405 MB: 87 us with one row per wave, 77 so (84 with the sums slab by slab;
+// by the trace 86 us, 79 since a square is added in one operation and four rows share the last steps of their butterflies).
 template <int DTYPE, int G, int R>
 __global__ __launch_bounds__(CP_THREADS) void k_cells_prepare(CellsBatch bt) {
     constexpr int REGIONS = (G / 8) * (G / 8);
@@ -75,9 +76,14 @@ __global__ __launch_bounds__(CP_THREADS) void k_cells_prepare(CellsBatch bt) {
     const int row = __builtin_amdgcn_readfirstlane(((b - bt.norm_begin[mi]) * CP_WAVES + (int)(threadIdx.x >> 6)) * R);
     if (row >= M.d_out) return;
     const int n_rows = min(R, M.d_out - row);
+    if (M.slab_sums) {
+        const double s2 = wave_rows_slab_sums<DTYPE, R>(M.W, row, n_rows, M.ldw, M.d_in, M.chan_scale, lane);
+        const int r = lane / (WAVE / R);
+        if (lane % (WAVE / R) == 0 && r < n_rows) M.norms[row + r] = (float)sqrt(s2);
+        return;
+    }
     double s2[R];
-    if (M.slab_sums) wave_rows_slab_sums<DTYPE, R>(s2, M.W, row, n_rows, M.ldw, M.d_in, M.chan_scale, lane);
-    else wave_rows_sum_of_squares<DTYPE, R>(s2, M.W, row, n_rows, M.ldw, M.d_in, M.chan_scale, lane);
+    wave_rows_sum_of_squares<DTYPE, R>(s2, M.W, row, n_rows, M.ldw, M.d_in, M.chan_scale, lane);
     if (lane == 0) {
 #pragma unroll
         for (int r = 0; r < R; ++r)

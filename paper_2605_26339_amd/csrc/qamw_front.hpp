@@ -140,6 +140,9 @@ inline int fused_norm_grid(int n_blocks) {                       // workgroups t
     return (n_blocks + FUSED_NORM_XCDS - 1) / FUSED_NORM_XCDS * FUSED_NORM_XCDS;
 }
 
+// acc + w^2: the square of an fp32 value is exact in fp64, so one rounding and the bits of a product and a sum.
+__device__ __forceinline__ double add_square(double acc, float w) { return __builtin_fma((double)w, (double)w, acc); }
+
 // Sum of squares of the scaled weights of columns [1024 slab, 1024 slab + 1024) of one row, the same in every lane.
 template <int DTYPE>
 __device__ __forceinline__ double slab_sum_of_squares(const void *__restrict__ W, int64_t row_base, int slab, const Problem &p,
@@ -169,7 +172,7 @@ __device__ __forceinline__ double slab_sum_of_squares(const void *__restrict__ W
             }
         }
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc += (double)w[e] * (double)w[e];
+        for (int e = 0; e < 16; ++e) acc = add_square(acc, w[e]);
     }
     return wave_sum(acc);
 }
@@ -253,7 +256,7 @@ __device__ __forceinline__ void wave_rows_sum_of_squares_as(double (&sum)[R], co
                     }
                 }
 #pragma unroll
-                for (int t = 0; t < V; ++t) sum[r] += (double)w[t] * (double)w[t];
+                for (int t = 0; t < V; ++t) sum[r] = add_square(sum[r], w[t]);
             }
         }
     }
@@ -269,13 +272,14 @@ __device__ __forceinline__ void wave_rows_sum_of_squares(double (&sum)[R], const
 }
 
 // The same sums in the order of slab_sum_of_squares() and row_norm_from_slab_sums(): to the bit what the kernels that compute
-// their own row norms get.
+// their own row norms get.  R is 1 or 4: row + r's sum in the lanes from 64 r / R on; four rows share the last two steps of
+// their butterflies.
 template <int DTYPE, int R>
-__device__ __forceinline__ void wave_rows_slab_sums(double (&sum)[R], const void *__restrict__ W, int row, int n_rows, int64_t ldw, int d_in,
-                                                    const float *__restrict__ s, int lane) {
+__device__ __forceinline__ double wave_rows_slab_sums(const void *__restrict__ W, int row, int n_rows, int64_t ldw, int d_in,
+                                                      const float *__restrict__ s, int lane) {
     constexpr int U = R == 1 ? 2 : 1;                           // slabs requested together
-#pragma unroll
-    for (int r = 0; r < R; ++r) sum[r] = 0.0;
+    static_assert(R == 1 || R == 4, "wave_sum or wave_sum_4");
+    double sum = 0.0;
     for (int slab = 0; slab * 1024 < d_in; slab += U) {
         RawRow<DTYPE> raw[U][R];
         float sc[U][16];
@@ -294,20 +298,21 @@ __device__ __forceinline__ void wave_rows_slab_sums(double (&sum)[R], const void
         for (int u = 0; u < U; ++u) {
             if ((slab + u) * 1024 >= d_in) break;
             const bool have = (slab + u) * 1024 + 16 * lane < d_in;
+            double acc[R];
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 float w[16];
                 widen_raw_row<DTYPE>(w, raw[u][r]);
-                double acc = 0.0;
+                acc[r] = 0.0;
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const float ws = w[e] * sc[u][e];
-                    acc += (double)ws * (double)ws;
-                }
-                sum[r] += wave_sum(have ? acc : 0.0);
+                for (int e = 0; e < 16; ++e) acc[r] = add_square(acc[r], w[e] * sc[u][e]);
+                acc[r] = have ? acc[r] : 0.0;
             }
+            if constexpr (R == 4) sum += wave_sum_4(acc);
+            else sum += wave_sum(acc[0]);
         }
     }
+    return sum;
 }
 
 // x = h + m + l exactly, each piece with at most 8 significant bits (a bf16 value held as fp32).
