@@ -14,6 +14,7 @@
 #include <cmath>
 
 #include "qamw_cells.hpp"
+#include "qamw_lloyd_stop.hpp"
 
 namespace qamw {
 
@@ -129,12 +130,7 @@ __global__ __launch_bounds__(LL_THREADS) void k_lloyd_init(int K, LloydAcc acc, 
 // next launch decides whether to stop; the kernels of later iterations then return at once.
 //   What bounds it: two launches that are each mostly latency.  2048 points, 2^20 samples (8 MB): 10.2 + 15.2 us an iteration.
 // A copy of the sums per workgroup (10.5 MB, more than the samples), added up by a launch of its own: 9.2 + 13.9 + 7.7; the
-// distances to all points took 401.  The kernels ask for what they work on before they look whether to stop.
-struct LloydState {
-    double D[2];                          // mean squared error of iteration t in D[t mod 2]
-    int stopped_at;                       // the last iteration, LC_RUNNING before it is known
-};
-constexpr int LC_RUNNING = 0x7fffffff;
+// distances to all points took 401.
 constexpr int LC_THREADS = 1024;
 constexpr int LC_MAX_BLOCKS = 256;                             // one workgroup per CU: a workgroup's sums are 20 bytes per point, each added to the one copy
 constexpr long long LC_HALF_UP_TO = 1 << 20;                   // samples up to which half as many workgroups cost less: see k_cells_lloyd_assign
@@ -190,7 +186,7 @@ __global__ __launch_bounds__(LL_THREADS) void k_cells_lloyd_init(int K, LloydCel
     }
     if (i == 0) {
         a.err[1] = 0;
-        *a.state = LloydState{{0.0, 0.0}, LC_RUNNING};
+        *a.state = lloyd_begin();
     }
 }
 
@@ -202,14 +198,14 @@ __device__ __forceinline__ bool lloyd_stops(const LloydCells &a, long long n, in
 }
 
 // Every workgroup computes all points, each writes its share of them and clears that share of this iteration's sums.  The
-// sums of iteration t - 1 are read by this launch alone.  One workgroup decides whether t - 1 was the last iteration; what
-// the others make meanwhile is then not looked at.
+// sums of iteration t - 1 are read by this launch alone.  One thread decides whether t - 1 was the last iteration; if so, what
+// this launch makes is not looked at.
 template <int G>
 __global__ __launch_bounds__(CP_THREADS) void k_cells_lloyd_table(int K, float half_per_sum, LloydCells a, long long n, int t, int max_iters, double tol) {
     __shared__ float2 points[2048 + 2048 / 8];                 // a place left out after eight: a thread reads a run of up to eight
     auto place = [](int i) { return i + (i >> 3); };
     const int from = (t + 1) & 1, to = t & 1;
-    const int stopped_at = a.state->stopped_at;
+    const int stopped_at = lloyd_seen_by_table(*a.state, t);
     float2 old[CP_PER_THREAD];
     long long sx[CP_PER_THREAD], sy[CP_PER_THREAD];
     unsigned c[CP_PER_THREAD];
@@ -221,7 +217,11 @@ __global__ __launch_bounds__(CP_THREADS) void k_cells_lloyd_table(int K, float h
         sy[j] = (long long)a.sy[from][k];
         old[j] = reinterpret_cast<const float2 *>(a.cb32[from])[k];
     }
-    if (stopped_at < t) return;
+    const bool decides = blockIdx.x == 0 && threadIdx.x == 0;
+    if (stopped_at != LC_RUNNING) {
+        if (decides) lloyd_table_decides(*a.state, t, false);
+        return;
+    }
     const int share = max(K / (int)gridDim.x, 1);
 #pragma unroll
     for (int j = 0; j < CP_PER_THREAD; ++j) {
@@ -239,14 +239,12 @@ __global__ __launch_bounds__(CP_THREADS) void k_cells_lloyd_table(int K, float h
             a.cnt[to][k] = 0;
         }
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (decides) {
         a.err[to] = 0;
-        if (t > 0) {
-            double D;
-            const bool stops = lloyd_stops(a, n, t - 1, max_iters, tol, D);
-            a.state->D[from] = D;
-            if (stops) a.state->stopped_at = t - 1;
-        }
+        double D = 0.0;
+        const bool stops = t > 0 && lloyd_stops(a, n, t - 1, max_iters, tol, D);
+        a.state->D[from] = D;
+        lloyd_table_decides(*a.state, t, stops);
     }
     __syncthreads();
     cells_build_region<G>(cells_points(K, [&](int i) { return points[place(i)]; }), K, half_per_sum, a.table, (int)blockIdx.x);
@@ -264,7 +262,7 @@ __global__ __launch_bounds__(LC_THREADS) void k_cells_lloyd_assign(const float2 
     extern __shared__ __align__(16) float2 lc_lds[];
     constexpr int U = 4;
     static_assert((G & (G - 1)) == 0, "the mask of the record's offset");
-    const int stopped_at = a.state->stopped_at;
+    const int stopped_at = lloyd_seen_by_assignment(*a.state, t);
     const float half = cells_half(a.table);
     const int lane = threadIdx.x & (WAVE - 1);
     const long long stride = (long long)gridDim.x * LC_THREADS;
@@ -286,7 +284,7 @@ __global__ __launch_bounds__(LC_THREADS) void k_cells_lloyd_assign(const float2 
         cnt[k] = 0;
     }
     if (threadIdx.x == 0) err_sum = 0;
-    if (stopped_at < t) return;
+    if (stopped_at != LC_RUNNING) return;
     const float inv_h = cells_inv_width<G>(half);
     __syncthreads();
 
@@ -354,21 +352,18 @@ __global__ __launch_bounds__(LC_THREADS) void k_cells_lloyd_assign(const float2 
     if (threadIdx.x == 0) atomicAdd(a.err + (t & 1), err_sum);
 }
 
-// After iteration t, the last that was launched: if it has stopped, the points of the last assignment.  stopped_at becomes t
-// here at most, and a workgroup that does not see it yet finds the same.
+// After iteration t, the last that was launched: if it or one before it was the last, the points of the last assignment.
 __global__ __launch_bounds__(LL_THREADS) void k_cells_lloyd_finish(long long n, int K, LloydCells a, int t, int max_iters, double tol, float *codebook) {
     const int i = blockIdx.x * LL_THREADS + threadIdx.x;
     const float points[2] = {i < 2 * K ? a.cb32[0][i] : 0.0f, i < 2 * K ? a.cb32[1][i] : 0.0f};   // on their way meanwhile
-    int at = a.state->stopped_at;
-    if (at >= t) {
+    int at = lloyd_seen_by_assignment(*a.state, t);
+    if (at == LC_RUNNING) {
         double D;
         if (!lloyd_stops(a, n, t, max_iters, tol, D)) return;
         at = t;
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-            a.state->D[t & 1] = D;
-            a.state->stopped_at = t;
-        }
+        if (i == 0) a.state->D[t & 1] = D;
     }
+    if (i == 0) a.state->last = at;
     if (i < 2 * K) codebook[i] = at & 1 ? points[1] : points[0];
 }
 
@@ -385,8 +380,8 @@ static hipError_t run_lloyd_cells(const float *samples, long long n, int K, floa
     const int most = n > LC_HALF_UP_TO ? LC_MAX_BLOCKS : LC_MAX_BLOCKS / 2;
     const unsigned blocks = (unsigned)(want < most ? want : most);
     hipLaunchKernelGGL(k_cells_lloyd_init, dim3(kb), dim3(LL_THREADS), 0, stream, K, a, codebook);
-    LloydState s{{0.0, 0.0}, LC_RUNNING};
-    for (int t = 0; s.stopped_at == LC_RUNNING;) {
+    LloydState s = lloyd_begin();
+    for (int t = 0; s.last == LC_RUNNING;) {
         const int until = max_iters - t < LC_AHEAD ? max_iters : t + LC_AHEAD;
         for (; t < until; ++t) {
             hipLaunchKernelGGL(k_cells_lloyd_table<G>, dim3((G / 8) * (G / 8)), dim3(CP_THREADS), 0, stream, K, half_per_sum, a, n, t, max_iters, tol);
@@ -401,8 +396,8 @@ static hipError_t run_lloyd_cells(const float *samples, long long n, int K, floa
         e = hipStreamSynchronize(stream);
         if (e != hipSuccess) return e;
     }
-    if (mse_out) *mse_out = s.D[s.stopped_at & 1];
-    if (iters_out) *iters_out = s.stopped_at + 1;
+    if (mse_out) *mse_out = s.D[s.last & 1];
+    if (iters_out) *iters_out = s.last + 1;
     return hipSuccess;
 }
 
