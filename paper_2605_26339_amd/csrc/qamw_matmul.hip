@@ -266,9 +266,12 @@ __global__ __launch_bounds__(GM_THREADS) void k_rotate_tile(GemvBatch bt) {
 
 // Field i of a lane's stream as a byte offset into the codebook, index times 8: one shift and one AND, with the mask in a register
 // (an AND of two registers issues at twice the rate of one with a literal).
+//   Never a plain shift to the left by one or two: the compiler then takes the offset for a multiple of two or four, the mask being
+// opaque, and reads the codeword as two halves, each with the bank conflicts of the whole (11 bits, one codeword in eight: 11008 x
+// 4096, one row, 14.8 us by the trace, 14.0 so; 13824 x 5120 19.9, 18.9).
 template <int BITS> __device__ __forceinline__ uint32_t gv_field_x8(const uint32_t (&w)[4], int i, uint32_t mask8) {
     const int bit = i * BITS, word = bit >> 5, off = bit & 31, s = off - 3;
-    const uint32_t v = s < 0 ? w[word] << -s : off + BITS <= 32 ? w[word] >> s : __builtin_amdgcn_alignbit(w[word + 1], w[word], s);
+    const uint32_t v = s == -3 ? w[word] << 3 : s < 0 ? __builtin_amdgcn_alignbit(w[word], w[word - 1], 32 + s) : off + BITS <= 32 ? w[word] >> s : __builtin_amdgcn_alignbit(w[word + 1], w[word], s);
     return v & mask8;
 }
 
