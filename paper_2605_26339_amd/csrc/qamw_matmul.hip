@@ -333,9 +333,11 @@ template <int N> __device__ __forceinline__ void gv_reduce_rows(float (&a)[N], i
 // before).  RB > 0 (the block size): every wave rotates the slabs it needs itself, with the same arithmetic, and moves
 // the result from the transform's lane order to the natural one -- the same z in the same lanes, so the same Y, bit for
 // bit, without the first launch; for launches so small that a second launch costs more than the repeated rotations.
-// AHEAD (self-rotating kernels only): the wave keeps two steps' packed words in registers; one activation row fits
+// AHEAD (self-rotating kernels only): the steps whose packed words the wave keeps in registers.  2: one activation row fits
 // three waves per SIMD (768 resident workgroups: a launch of up to 1024 finishes its last quarter in a second round),
-// two rows fit two (512 workgroups: the host picks the plain form for larger two-row launches).
+// two rows fit two (512 workgroups: the host picks the plain form for larger two-row launches).  1: no wave has a second step;
+// requests for steps that there are not are answered with zeros, but take the address unit's time (one row at 11 bits, by the trace,
+// with 2 / 1: 5632 x 2048 8.0 / 6.9 us, 1024 x 4096 6.7 / 5.6, 256 x 2048 6.4 / 5.5).
 #define QAMW_GV_WAVES_PER_EU (AHEAD ? (MT == 1 ? 3 : 2) : 1)
 template <int BITS, int MT, int RB, int AHEAD>
 __global__ __launch_bounds__(GV_THREADS) __attribute__((amdgpu_waves_per_eu(QAMW_GV_WAVES_PER_EU)))
@@ -560,9 +562,9 @@ void k_qgemv(GemvBatch bt) {
             work(std::false_type{}, at.slab, at.g, d);
         }
     } else {
-        // A launch that rotates the activations itself is a small one -- one to three waves per SIMD, two to four steps
+        // A launch that rotates the activations itself is a small one -- one to three waves per SIMD, one to four steps
         // per wave -- and lasts as long as one wave's chain of memory round trips.  So the chain is kept short: the
-        // rotation's inputs, the workgroup's share of the codebook, the packed words of the wave's first two steps and the norms
+        // rotation's inputs, the workgroup's share of the codebook, the packed words of the wave's first two steps (or its only one) and the norms
         // are requested before anything is waited for (the rotation's first: it has arithmetic to do while the rest
         // arrives), and from then on the next step's packed words are on their way while a step is worked on.  What stood in
         // the way: a branch on the element type or on the matrix's last row, at which the compiler waits for what either side
@@ -589,7 +591,7 @@ void k_qgemv(GemvBatch bt) {
             advance(ask);
         };
         fetch_next(step0, da);
-        fetch_next(step0 + 1, db);
+        if constexpr (AHEAD > 1) fetch_next(step0 + 1, db);
         load_norms();
         __builtin_amdgcn_sched_barrier(0);
         rot_finish(cur_slab, rin, z);
@@ -622,8 +624,13 @@ void k_qgemv(GemvBatch bt) {
                 fetch_next(step + 3, db);
             }
         };
-        if (last_slab > cur_slab) walk(std::true_type{});
-        else walk(std::false_type{});
+        if constexpr (AHEAD == 1) {
+            if (step0 < step1) work(std::true_type{}, at.slab, at.g, da);
+        } else if (last_slab > cur_slab) {
+            walk(std::true_type{});
+        } else {
+            walk(std::false_type{});
+        }
     }
     __syncthreads();
     // the 4 waves' sums in wave order, times the row norm
@@ -1173,8 +1180,11 @@ static hipError_t launch_qgemv_rb(const GemvBatch &bt, hipStream_t stream) {
     const unsigned blocks = (unsigned)bt.grp_begin[bt.n];
 #define QAMW_GV(MM, AH) hipLaunchKernelGGL((k_qgemv<BITS, MM, RB, AH>), dim3(blocks), dim3(GV_THREADS), 0, stream, bt)
     if constexpr (RB > 0) {                                     // the self-rotating kernels exist for one and two rows
-        if (bt.m == 1) QAMW_GV(1, 1);
-        else if (bt.m == 2 && blocks <= GV_AHEAD_MAX_WGS_2) QAMW_GV(2, 1);
+        bool one_step = true;                                   // in every wave
+        for (int i = 0; i < bt.n; ++i) one_step = one_step && bt.mat[i].n_slabs * (bt.mat[i].rows_per_wg / GV_RG) <= GV_WAVES;
+        if (bt.m == 1 && one_step) QAMW_GV(1, 1);
+        else if (bt.m == 1) QAMW_GV(1, 2);
+        else if (bt.m == 2 && blocks <= GV_AHEAD_MAX_WGS_2) QAMW_GV(2, 2);
         else if (bt.m == 2) QAMW_GV(2, 0);
         else return hipErrorNotSupported;
     } else {
