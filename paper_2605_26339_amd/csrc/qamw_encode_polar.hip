@@ -15,6 +15,7 @@
 #include <algorithm>
 
 #include "qamw_front.hpp"
+#include "qamw_polar_cells.hpp"
 
 namespace qamw {
 
@@ -27,14 +28,7 @@ constexpr int PF_MAX_ROWS = 32;        // rows of a workgroup
 constexpr int PF_ITEMS = 48;           // (row, slab) items of a workgroup in a large launch
 constexpr int PF_CUS = 256;
 constexpr int PF_MAX_ITEMS = 64;       // (row, slab) items of a workgroup, unless one row has more
-// Lookup tables in place of the two binary searches, for workgroups of at least PF_LUT_ITEMS items (making them takes a
-// workgroup 1 us).  Amplitude: by exponent and five mantissa bits of |x|^2, 16 octaves from 2^-10 on.  Phase: by x0 / (|x0| + |x1|),
-// which falls with the angle in [0, pi), in 256 cells; its slope is at least half of the angle's, so with up to 256 bins no cell
-// holds two boundaries.  An entry says where the cell begins; the one boundary that may lie in it is tested as the searches test it.
-constexpr int PF_LUT_ITEMS = 16;
-constexpr int PF_AMP_CELLS = 512, PF_PHASE_CELLS = 256, PF_LUT_MIN_BINS = 8, PF_LUT_MAX_BINS = 256;
 constexpr uint32_t PF_AMP_BASE = (127 - 10) << 5;
-constexpr float PF_LUT_MAX_A2 = 1e30f;  // beyond, 1 / (|x0| + |x1|) is on its way to the subnormals: the searches
 constexpr uint32_t PF_LUT_AT = 4 * (PF_MAX_LEVELS + 4) + 8 * PF_MAX_ITEMS + 4 * PF_MAX_ROWS;
 constexpr uint32_t PF_DIR_AT = PF_LUT_AT + PF_AMP_CELLS + PF_PHASE_CELLS + 8;   // LDS before the directions
 
@@ -78,7 +72,9 @@ __global__ __launch_bounds__(PF_THREADS) void k_encode_polar(const void *__restr
         sincospif(2.0f * (float)k / (float)Np, &sn, &cs);      // the angle 2 k h = pi * (2k / Np), argument exact
         lds_write<lds_f32x2_t>(DIR_AT + 8 * k, lds_f32x2_t{cs, sn});
     }
-    const bool want_lut = n_items >= PF_LUT_ITEMS && Np >= PF_LUT_MIN_BINS && Np <= PF_LUT_MAX_BINS;
+    // the workgroup's part of the items (all of them unless a long row is shared by several)
+    const PolarPart mine = polar_part(n_items, (int)blockIdx.y, (int)gridDim.y, Np);
+    const bool want_lut = mine.tables;
     if (threadIdx.x == 0) {
         lds_write<float>(THR_AT + 4 * Na, __builtin_inff());
         lds_write<lds_f32x2_t>(DIR_AT + 8 * Np, lds_f32x2_t{1.0f, 0.0f});
@@ -129,10 +125,8 @@ __global__ __launch_bounds__(PF_THREADS) void k_encode_polar(const void *__restr
     const LaneSigns<B> ls(lane);
     const int pos = slab_pos(lane);
     const float unit = ls.parity * p.inv_sqrt_block;
-    // the workgroup's part of the items (all of them unless a long row is shared by several)
-    const int parts = (int)gridDim.y, from = n_items * (int)blockIdx.y / parts, to = n_items * ((int)blockIdx.y + 1) / parts;
-    const int per = (to - from + PF_WAVES - 1) / PF_WAVES;
-    const int first = from + wid * per, last = min(to, first + per);
+    const int per = (mine.to - mine.from + PF_WAVES - 1) / PF_WAVES;
+    const int first = mine.from + wid * per, last = min(mine.to, first + per);
     int c = 0, cur_slab = -1;
     bool active = false;
     float sc[16], g[8];
@@ -176,9 +170,8 @@ __global__ __launch_bounds__(PF_THREADS) void k_encode_polar(const void *__restr
                 const int cell = (int)(__float_as_uint(a2[k]) >> 18) - (int)PF_AMP_BASE;
                 ia[k] = lds_read<uint8_t>(AMP_AT + (uint32_t)min(max(cell, 0), PF_AMP_CELLS - 1));
                 const float x0 = x[2 * k], x1 = x[2 * k + 1];
-                const float place = (upper[k] ? -x0 : x0) * __builtin_amdgcn_rcpf(fabsf(x0) + fabsf(x1));
-                const uint32_t at = (uint32_t)__builtin_fmaf(place, 0.5f * PF_PHASE_CELLS, 0.5f * PF_PHASE_CELLS);
-                ip[k] = 8u * lds_read<uint8_t>(PHASE_AT + min(at, (uint32_t)PF_PHASE_CELLS - 1u)) + (upper[k] ? 4u * (unsigned)Np : 0u);
+                const uint32_t at = polar_phase_cell(x0, x1, upper[k], [](float s) { return __builtin_amdgcn_rcpf(s); });
+                ip[k] = 8u * lds_read<uint8_t>(PHASE_AT + at) + (upper[k] ? 4u * (unsigned)Np : 0u);
             }
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
