@@ -233,7 +233,7 @@ static hipError_t launch_pdb(const void *W, int64_t ldw, const Problem &p, const
     while (rows > 1 && (p.d_out + rows - 1) / rows < 2 * PF_CUS && (rows + 1) / 2 * n_slabs >= PF_WAVES) rows = (rows + 1) / 2;
     const unsigned blocks = (unsigned)((p.d_out + rows - 1) / rows);
     // Few rows of many slabs: several workgroups share a row, down to an item per wave, each with all slab sums of its own
-    // (us at 5 + 6 bits, bf16, one workgroup a row / so: 16 x 40960 23.2 / 9.7, 64 x 65536 35.7 / 15.6).
+    // (us by the trace at 5 + 6 bits, bf16, all options, one workgroup a row / so: 16 x 40960 23.4 / 12.1, 64 x 65536 36.0 / 22.1).
     int parts = 1;
     if (rows == 1) parts = std::max(1, std::min((n_slabs + PF_WAVES - 1) / PF_WAVES, 2 * PF_CUS / p.d_out));
     const size_t lds = PF_DIR_AT + 8 * ((size_t)(1 << bits_p) + 1);

@@ -4,7 +4,7 @@
 
 namespace qamw {
 
-// Lookup tables in place of the two binary searches, for workgroups of at least PF_LUT_ITEMS (row, slab) items (making
+// Lookup tables in place of the two binary searches, for workgroups that encode at least PF_LUT_ITEMS (row, slab) items (making
 // them takes a workgroup 1 us).  Amplitude: by exponent and five mantissa bits of |x|^2, 16 octaves from 2^-10 on.  Phase: by
 // x0 / (|x0| + |x1|), which falls with the angle in [0, pi), in 256 cells; its slope is at least half of the angle's, so with up
 // to 256 bins no cell holds two boundaries.  An entry says where the cell begins; the one boundary that may lie in it is tested
@@ -20,7 +20,7 @@ struct PolarPart {
 };
 constexpr PolarPart polar_part(int n_items, int part, int parts, int Np) {
     const int from = n_items * part / parts, to = n_items * (part + 1) / parts;
-    return {from, to, n_items >= PF_LUT_ITEMS && Np >= PF_LUT_MIN_BINS && Np <= PF_LUT_MAX_BINS};
+    return {from, to, to - from >= PF_LUT_ITEMS && Np >= PF_LUT_MIN_BINS && Np <= PF_LUT_MAX_BINS};
 }
 
 // The phase cell of a pair with |x|^2 <= PF_LUT_MAX_A2, its angle in [pi, 2 pi) taken less pi; recip: 1 / s to some units.

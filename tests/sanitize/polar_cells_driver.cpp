@@ -33,13 +33,14 @@ int main() {
                 if (i) EXPECT((at == 0 || place > lo - 1e-5) && (at + 1 == PF_PHASE_CELLS || place < hi + 1e-5));
             }
     }
-    // the parts of a row's items are all of them, once
+    // the parts of a row's items are all of them, once; tables by what a workgroup encodes
     for (int n = 1; n <= 64; ++n)
         for (int parts = 1; parts <= (n + 7) / 8; ++parts) {
             int at = 0;
             for (int p = 0; p < parts; ++p) {
                 const PolarPart s = polar_part(n, p, parts, 64);
                 EXPECT(s.from == at && s.to >= s.from);
+                EXPECT(s.tables == (s.to - s.from >= PF_LUT_ITEMS));
                 EXPECT(!polar_part(n, p, parts, 4).tables && !polar_part(n, p, parts, 512).tables);
                 at = s.to;
             }

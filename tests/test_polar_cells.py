@@ -1,5 +1,5 @@
 """The polar encoder's phase cells and its workgroups' shares on the CPU: no conversion of what is no number in range (a pair of
-zeros is an ordinary input), and every item in one share."""
+zeros is an ordinary input), and lookup tables only where a workgroup encodes enough to pay for them."""
 import os
 import shutil
 import subprocess

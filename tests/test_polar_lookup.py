@@ -35,3 +35,18 @@ def test_tables_and_searches_agree(bits_a, bits_p, kind):
     for r in range(0, d_out, 500):                              # 8 rows per workgroup
         part, n = qamw.encode_polar(W[r:r + 500], levels, bits_a, bits_p, block, pair_sigma=sigma)
         assert torch.equal(full[r:r + 500], part) and torch.equal(norms[r:r + 500], n)
+
+
+@pytest.mark.parametrize("bits_a,bits_p,dtype", [(5, 6, torch.bfloat16), (3, 8, torch.float32)])
+def test_shared_rows_with_and_without_tables(bits_a, bits_p, dtype):
+    # 65 slabs: 128 rows are shared by four workgroups each, 16 or 17 items and tables; 100 rows by five, 13 and searches; 16 rows by
+    # nine, 7 or 8; 600 rows are not shared, 65 items and tables
+    print(f"[polar lookup] shared rows {bits_a}+{bits_p} {dtype}", flush=True)
+    levels = torch.from_numpy(qamw.polar_codebook(bits_a, bits_p)[0]).cuda()
+    W = torch.randn(600, 65 * 1024, device="cuda", generator=torch.Generator("cuda").manual_seed(bits_p)).to(dtype)
+    W[3, :2048] = 0
+    want, norms = qamw.encode_polar(W, levels, bits_a, bits_p, 1024)
+    for lo, n in ((0, 128), (0, 100), (1, 16), (472, 128)):
+        got, r = qamw.encode_polar(W[lo:lo + n], levels, bits_a, bits_p, 1024)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want[lo:lo + n]) and torch.equal(r, norms[lo:lo + n]), (lo, n)
