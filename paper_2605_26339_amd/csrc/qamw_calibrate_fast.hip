@@ -1,6 +1,7 @@
 // Vectorised row norms and the shape-specialised pair-scale calibration (Eq. 1).
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "qamw_front.hpp"
 
@@ -71,7 +72,8 @@ struct CalBatch {
 
 // acc[k] += |(y[2k], y[2k + 1])|, the square root exact to a few fp64 roundings: the fp32 one (2^-22) and two Newton steps
 // (2^-44, then below 2^-53).  Where one of a wave's squares is outside the range of normal fp32, zero included, the library's
-// square root.  The squares of fp32 are exact in fp64, so the fused sum is rounded as a separate one.
+// square root.  (So always in a slab that the row ends in, whose idle lanes hold zeros.  Left out of the test, or at work on other
+// columns, 48 x 13888 took 32.3 us in place of 33.0, but 4096 x 4096 12.6 in place of 12.4.)  The squares of fp32 are exact in fp64, so the fused sum is rounded as a separate one.
 //   The eight chains are free of branches between them: with a test per pair they ran one after the other (4096 x 4096 bf16, this
 // launch 15.0 -> 14.4 us).
 __device__ __forceinline__ void add_magnitudes(double (&acc)[8], const float (&y)[16]) {
@@ -143,7 +145,6 @@ __global__ __launch_bounds__(CAL_THREADS) void k_calibrate_partial(CalBatch bt) 
     const int chunk = (int)blockIdx.x - bt.chunk_begin[mi];
     const int row0 = chunk * CAL_ROWS, row1 = min(n_rows, row0 + CAL_ROWS);
     const CalUnits units(n_slabs);
-    constexpr int R = DTYPE == 0 ? 2 : 4;                       // rows requested together
     for (int unit = wid; unit < units.count(); unit += CAL_WAVES) {
         const int slab = units.slab(unit);
         int from, to;
@@ -153,35 +154,43 @@ __global__ __launch_bounds__(CAL_THREADS) void k_calibrate_partial(CalBatch bt) 
         Problem unsigned_scales = p;
         unsigned_scales.signs = nullptr;
         load_signed_scales(sc, unsigned_scales, at);
+        auto sums = [&](auto together) __attribute__((always_inline)) {
+            constexpr int R = decltype(together)::value;        // rows requested together
 #pragma unroll 1
-        for (int row = from; row < to; row += R) {
-            RawRow<DTYPE> raw[R];
+            for (int row = from; row < to; row += R) {
+                RawRow<DTYPE> raw[R];
 #pragma unroll
-            for (int r = 0; r < R; ++r) load_raw_row<DTYPE>(raw[r], W, (int64_t)min(row + r, to - 1) * ldw, at);
-            double s2[R];
+                for (int r = 0; r < R; ++r) load_raw_row<DTYPE>(raw[r], W, (int64_t)min(row + r, to - 1) * ldw, at);
+                double s2[R];
 #pragma unroll
-            for (int r = 0; r < R; ++r) {                       // the sums of slab_sum_of_squares(), to the bit
-                float w[16];
-                widen_raw_row<DTYPE>(w, raw[r]);
-                s2[r] = 0.0;
+                for (int r = 0; r < R; ++r) {                   // the sums of slab_sum_of_squares(), to the bit
+                    float w[16];
+                    widen_raw_row<DTYPE>(w, raw[r]);
+                    s2[r] = 0.0;
 #pragma unroll
-                for (int e = 0; e < 16; ++e) s2[r] = add_square(s2[r], w[e] * sc[e]);
-                s2[r] = c < p.d_in ? s2[r] : 0.0;
-            }
-            auto put = [&](int r, double sum) {
-                if (row + r < to) norm_part[(row + r - row0) * n_slabs + slab] = sum;
-            };
-            if constexpr (R == 4) {
-                const double sum = wave_sum_4(s2);
-                if ((lane & 15) == 0) put(lane >> 4, sum);
-            } else {
+                    for (int e = 0; e < 16; ++e) s2[r] = add_square(s2[r], w[e] * sc[e]);
+                    s2[r] = c < p.d_in ? s2[r] : 0.0;
+                }
+                auto put = [&](int r, double sum) {
+                    if (row + r < to) norm_part[(row + r - row0) * n_slabs + slab] = sum;
+                };
+                if constexpr (R == 4) {
+                    const double sum = wave_sum_4(s2);
+                    if ((lane & 15) == 0) put(lane >> 4, sum);
+                } else {
 #pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const double sum = wave_sum(s2[r]);
-                    if (lane == 0) put(r, sum);
+                    for (int r = 0; r < R; ++r) {
+                        const double sum = wave_sum(s2[r]);
+                        if (lane == 0) put(r, sum);
+                    }
                 }
             }
-        }
+        };
+        // No more than the unit has, one row of a slab that eight waves share, two of one that four do: with four bf16 rows whatever
+        // the unit, 100 x 512 took 7.4 us by the trace, 6.4 so; 1000 x 2048 10.4, 9.0.
+        if (to - from == 1) sums(std::integral_constant<int, 1>{});
+        else if (DTYPE == 0 || to - from == 2) sums(std::integral_constant<int, 2>{});
+        else sums(std::integral_constant<int, 4>{});
     }
     __syncthreads();
     if ((int)threadIdx.x < row1 - row0) norm_row[threadIdx.x] = row_norm_from_slab_sums(norm_part, threadIdx.x, 0, n_slabs);

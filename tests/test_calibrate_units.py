@@ -32,3 +32,10 @@ def test_alone_and_in_a_batch(dtype):
     torch.cuda.synchronize()
     for (_, _, _, got), want in zip(items, alone):
         assert torch.equal(got, want)
+
+
+# a unit of one, two, four and more rows of a chunk, and what a chunk at the matrix's end leaves of it
+@pytest.mark.parametrize("d_in,block", [(64, 64), (512, 512), (1024, 128), (1152, 128), (2048, 1024), (3072, 256), (5120, 64)])
+@pytest.mark.parametrize("d_out,dtype", [(1, "bf16"), (6, "bf16"), (11, "f32"), (27, "bf16")])
+def test_rows_of_a_unit(d_in, block, d_out, dtype):
+    check(d_in, block, d_out, dtype)
