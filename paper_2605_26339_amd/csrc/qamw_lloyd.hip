@@ -139,7 +139,6 @@ constexpr int LC_DENSE_ABOVE = 16;                             // of a wave's 64
 constexpr int lc_side(int K) { return K >= 1024 ? 128 : 64; }
 
 struct LloydCells {
-    double *cb64[2];
     unsigned long long *sx[2], *sy[2];                         // K fixed-point sums
     float *cb32[2];
     uint2 *table;
@@ -149,7 +148,7 @@ struct LloydCells {
 };
 static size_t lloyd_cells_bytes(int K) {
     const size_t G = lc_side(K);
-    return (size_t)K * 2 * (16 + 16 + 8 + 4) + G * G * 8 + 128;
+    return (size_t)K * 2 * (16 + 8 + 4) + G * G * 8 + 128;
 }
 static LloydCells lloyd_cells_layout(void *workspace, int K) {
     LloydCells a;
@@ -162,7 +161,6 @@ static LloydCells lloyd_cells_layout(void *workspace, int K) {
     a.state = reinterpret_cast<LloydState *>(take(64));
     a.err = reinterpret_cast<unsigned long long *>(take(64));
     for (int i = 0; i < 2; ++i) {
-        a.cb64[i] = reinterpret_cast<double *>(take((size_t)K * 16));
         a.sx[i] = reinterpret_cast<unsigned long long *>(take((size_t)K * 8));
         a.sy[i] = reinterpret_cast<unsigned long long *>(take((size_t)K * 8));
         a.cb32[i] = reinterpret_cast<float *>(take((size_t)K * 8));
@@ -175,10 +173,7 @@ static LloydCells lloyd_cells_layout(void *workspace, int K) {
 // The caller's points as the points of iteration -1, whose cells are all empty.
 __global__ __launch_bounds__(LL_THREADS) void k_cells_lloyd_init(int K, LloydCells a, const float *codebook) {
     const int i = blockIdx.x * LL_THREADS + threadIdx.x;
-    if (i < 2 * K) {
-        a.cb64[1][i] = (double)codebook[i];
-        a.cb32[1][i] = codebook[i];
-    }
+    if (i < 2 * K) a.cb32[1][i] = codebook[i];
     if (i < K) {
         a.sx[1][i] = 0;
         a.sy[1][i] = 0;
@@ -231,8 +226,6 @@ __global__ __launch_bounds__(CP_THREADS) void k_cells_lloyd_table(int K, float h
         const float2 p = c[j] > 0 ? make_float2((float)px, (float)py) : old[j];   // an empty cell keeps its point
         points[place(k)] = p;
         if (k / share == (int)blockIdx.x) {
-            a.cb64[to][2 * k] = c[j] > 0 ? px : a.cb64[from][2 * k];
-            a.cb64[to][2 * k + 1] = c[j] > 0 ? py : a.cb64[from][2 * k + 1];
             reinterpret_cast<float2 *>(a.cb32[to])[k] = p;
             a.sx[to][k] = 0;
             a.sy[to][k] = 0;
