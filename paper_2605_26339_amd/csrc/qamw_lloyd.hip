@@ -133,7 +133,7 @@ __global__ __launch_bounds__(LL_THREADS) void k_lloyd_init(int K, LloydAcc acc, 
 // distances to all points took 401.
 constexpr int LC_THREADS = 1024;
 constexpr int LC_MAX_BLOCKS = 256;                             // one workgroup per CU: a workgroup's sums are 20 bytes per point, each added to the one copy
-constexpr long long LC_HALF_UP_TO = 1 << 20;                   // samples up to which half as many workgroups cost less: see k_cells_lloyd_assign
+constexpr int LC_SAMPLES = 4;                                  // of a thread at once
 constexpr int LC_AHEAD = 16;                                   // iterations launched before the host looks whether it has stopped
 constexpr int LC_DENSE_ABOVE = 16;                             // of a wave's 64 samples
 constexpr int lc_side(int K) { return K >= 1024 ? 128 : 64; }
@@ -246,14 +246,12 @@ __global__ __launch_bounds__(CP_THREADS) void k_cells_lloyd_table(int K, float h
 // The records come from memory (L2), four samples' at a time: staging them took as long as the samples of a workgroup do, and
 // a table of 112 x 112 cells was all that fitted beside the sums, with 1.1 % of Gaussian samples in cells of six candidates --
 // a scan of the whole codebook in most waves, against 0.05 % with 128 x 128.  2048 points, 2^20 samples: 23.5 -> 11.5 us.
-//   The sums' atomics, three per point and workgroup, are what a workgroup costs whatever its share: 2048 points, 2^20 samples
-// 17.4 us with 256 workgroups, 16.8 with 192, 15.2 with 128, 16.0 with 96.  Beyond LC_HALF_UP_TO the samples weigh more: 16
-// iterations over 2^21 with all / half of the workgroups 570 / 564 us at 2048 points, 402 / 425 at 64.
+//   The sums' atomics, three per point and workgroup, are what a workgroup costs whatever its share; see lc_blocks().
 template <int G>
 __global__ __launch_bounds__(LC_THREADS) void k_cells_lloyd_assign(const float2 *__restrict__ samples, long long n, int K, LloydCells a, int t) {
     // points (at LDS address 0), then the sums: x, y (64 bits), count (32), error (64)
     extern __shared__ __align__(16) float2 lc_lds[];
-    constexpr int U = 4;
+    constexpr int U = LC_SAMPLES;
     static_assert((G & (G - 1)) == 0, "the mask of the record's offset");
     const int stopped_at = lloyd_seen_by_assignment(*a.state, t);
     const float half = cells_half(a.table);
@@ -360,6 +358,21 @@ __global__ __launch_bounds__(LL_THREADS) void k_cells_lloyd_finish(long long n, 
     if (i < 2 * K) codebook[i] = at & 1 ? points[1] : points[0];
 }
 
+// Workgroups of the assignment.  They work in passes of LC_SAMPLES samples a thread, and each adds its sums to the one copy at the
+// end.  So from half of the chip on as many as one pass needs; with 2048 points, whose atomics cost more than a pass, two.
+//   Us an iteration, both launches and the host's look, 128 / so / 256 workgroups, started from a codebook for such samples and
+// (in brackets) from points drawn at random, of which more samples are left to a scan of all points:
+//     64 points, 600 000 samples      18.7 / 18.9 / 20.6 (19.0 / 19.0 / 20.4),  2^20 20.7 / 20.9 / 20.9,  2^21 25.1 / 23.5 / 23.5
+//     1024 points, 700 000            23.5 / 22.7 / 23.9 (30.0 / 26.1 / 26.3),  2^20 24.4 / 24.6 / 24.6 (34.1 / 28.0 / 28.0)
+//     2048 points, 2^20               28.3 / 28.3 / 30.9 (51.9 / 51.9 / 41.1),  1 250 000 30.4 / 29.5 / 31.0 (58.5 / 53.3 / 45.1),
+//                  2^21               33.7 / 33.7 / 33.7 (79.8 / 55.3 / 55.3)
+// Below half of the chip: 64 points, 2^18 samples 16.9 with 64 workgroups, 17.3 with 128, but 2048 points at random 37.8, 31.0.
+static unsigned lc_blocks(int K, long long n) {
+    const long long pass = (long long)LC_THREADS * LC_SAMPLES * (K >= 2048 ? 2 : 1);
+    const long long want = std::min((n + pass - 1) / pass, (long long)LC_MAX_BLOCKS);
+    return (unsigned)std::min(std::max(want, (long long)LC_MAX_BLOCKS / 2), (n + LC_THREADS - 1) / LC_THREADS);
+}
+
 template <int G>
 static hipError_t run_lloyd_cells(const float *samples, long long n, int K, float *codebook, int max_iters, double tol,
                                   void *workspace, double *mse_out, int *iters_out, hipStream_t stream) {
@@ -369,9 +382,7 @@ static hipError_t run_lloyd_cells(const float *samples, long long n, int K, floa
     static_assert(2048 * 28 + 8 <= 64 * 1024, "what a workgroup may have without asking");
     const float half_per_sum = cells_half_per_sum(__builtin_ctz((unsigned)K));
     const unsigned kb = (unsigned)((2 * K + LL_THREADS - 1) / LL_THREADS);
-    const long long want = (n + LC_THREADS - 1) / LC_THREADS;
-    const int most = n > LC_HALF_UP_TO ? LC_MAX_BLOCKS : LC_MAX_BLOCKS / 2;
-    const unsigned blocks = (unsigned)(want < most ? want : most);
+    const unsigned blocks = lc_blocks(K, n);
     hipLaunchKernelGGL(k_cells_lloyd_init, dim3(kb), dim3(LL_THREADS), 0, stream, K, a, codebook);
     LloydState s = lloyd_begin();
     for (int t = 0; s.last == LC_RUNNING;) {

@@ -1,6 +1,6 @@
 """Device codebook training, where the sums of all workgroups meet in one copy per iteration: the same points as the call with
-the least workspace, bit for bit, with iterations that end just before, at and after the host looks (every 16), and on both
-sides of the sample count up to which half of the workgroups are used."""
+the least workspace, bit for bit, with iterations that end just before, at and after the host looks (every 16), and with
+any number of workgroups."""
 import ctypes as C
 import sys
 
@@ -29,3 +29,11 @@ def test_one_copy_of_the_sums(bits, n, iters):
         assert torch.equal(cb, want) and it == w_it.value
         # the error: fp64 sums of 32-bit distances, rounded to 2^-30 once per wave, of which there are n / 64 and one at most
         assert abs(mse - w_mse.value) <= 1e-12 * w_mse.value + 2.0 ** -30
+
+
+# workgroups of the assignment from half of the chip (128) on: as many as a pass of 4096 samples each needs, of 8192 with 2048
+# points; on either side of both ends, and between
+@pytest.mark.parametrize("bits,n", [(6, 128 * 4096 - 1), (6, 128 * 4096 + 1), (8, 700001), (10, 255 * 4096 + 1), (10, 256 * 4096 + 1),
+                                    (11, 128 * 8192 + 1), (11, 1500001), (11, 256 * 8192 + 1), (7, 127 * 1024 + 1), (7, 129 * 1024)])
+def test_any_number_of_workgroups(bits, n):
+    test_one_copy_of_the_sums(bits, n, 3)
