@@ -85,3 +85,24 @@ def test_either_kernel_around_four_tiles(d_out, d_in, m):
     kw = dict(chan_scale=s, signs=sg, pair_sigma=sigma)
     least = torch.empty(qamw.matmul_workspace_bytes(d_in, d_out, m), dtype=torch.uint8, device="cuda")
     assert torch.equal(qamw.matmul(X, packed, norms, cb, 7, 128, **kw), qamw.matmul(X, packed, norms, cb, 7, 128, workspace=least, **kw))
+
+
+# 256-row tiles over rows of several chunks a segment (the ring of three activation buffers goes round many times, and its requests
+# cross from one chunk and segment into the next): all three widths, a chunk count that eight does and does not divide, d_out and m
+# that end inside a tile; the second pair's last round goes into 128-row tiles of the same launch
+@pytest.mark.parametrize("bits,d_out,d_in,m", [(11, 8193, 2304, 1025), (7, 8193, 4096, 1025), (8, 8320, 2560, 1000),
+                                               (11, 11008, 4352, 1000), (7, 11008, 4352, 1000), (8, 11001, 4096, 993)])
+def test_deep_rows_of_the_larger_tiles(bits, d_out, d_in, m):
+    tiles256, tiles = (d_out + 127) // 128 * ((m + 255) // 256), (d_out + 127) // 128
+    assert tiles256 >= 256 and d_in > 8 * 256
+    first = tiles256 // 256 * 256 // ((m + 255) // 256)
+    say(f"[wide] larger tiles {d_out}x{d_in} m={m} B={bits}, {tiles - first} of {tiles} in a last round")
+    X, packed, norms, s, sg, sigma, cb = _product(d_out + m, d_out, d_in, m, bits, torch.bfloat16)
+    kw = dict(chan_scale=s, signs=sg, pair_sigma=sigma)
+    least = torch.empty(qamw.matmul_workspace_bytes(d_in, d_out, m), dtype=torch.uint8, device="cuda")
+    want = qamw.matmul(X, packed, norms, cb, bits, 128 if d_in % 1024 else 1024, workspace=least, **kw)
+    for _ in range(2):
+        got = qamw.matmul(X, packed, norms, cb, bits, 128 if d_in % 1024 else 1024, **kw)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want)
+
