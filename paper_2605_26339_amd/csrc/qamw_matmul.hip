@@ -1120,22 +1120,28 @@ bool matmul_supported(const Problem &p, int m) {
 }
 
 // Whether m activation rows are better taken whole, by the wide kernel, than 64 at a time.  A wide workgroup walks all columns,
-// 0.8 us per 64 of them, whatever the number of rows, so up to three tiles of 64 the smaller kernel is sooner done; with four it
-// still is where the columns are many and the wide tiles leave half of the chip idle.  In us, four tiles / wide, 256 rows at 11
-// bits: 4096 x 4096 61.9 / 64.2 (7 bits 55.2 / 60.2), 4096 x 11008 124.7 / 142.2 (104.4 / 131.6), 2048 x 5632 73.9 / 82.6; but
-// 1024 x 2048 46.0 / 39.3, 11008 x 4096 91.9 / 64.8; five tiles, 300 rows: 76.6 / 64.9, 154 / 142, 91.9 / 83.3.
+// 0.6 us per 64 of them, whatever the number of rows; the smaller kernel unpacks the matrix once per 64 rows, but spreads a row over
+// its waves.  So up to two tiles of 64 the smaller one is sooner done; with three where the rows are longer than WIDE_SHORT and the
+// wide tiles leave most of the chip idle, or fill a last round badly; with four where they are long and leave most of it idle.
+//   In us, tiles / wide, at 11 bits (7 and 8 alike).  129 rows: 256 x 2048 33.6 / 32.1, 4096 x 1024 31.5 / 22.2, 2048 x 2560 38.3 /
+// 36.3, 5120 x 5120 63.0 / 59.9, 8192 x 4096 60.5 / 51.9; but 2048 x 3072 39.1 / 41.3, 4096 x 4096 42.8 / 50.2, 4096 x 11008 80.8 /
+// 114, 11008 x 4096 twice (344 tiles of 128 x 128) 91.2 / 94.6.  256 rows: 4096 x 4096 57.1 / 51.8, 1024 x 5120 62.8 / 61.2, 5120 x
+// 13824 184 / 138; but 2048 x 5632 64.0 / 66.5, 4096 x 11008 107 / 114, 1024 x 14336 113 / 146.  128 rows: 4096 x 1024 21.9 / 22.2, others
+// 25 % to three times.  257 rows: 1024 x 14336 140 / 147, others wide.
 bool matmul_wide(const MatmulItem *items, int n, int m) {
-    if (m <= 3 * GM_MAX_M) return false;
-    for (int i = 0; i < n; ++i)
-        if (items[i].d_in >= 1 << 25) return false;             // a tile's activations: 64 bytes a column, 32-bit offsets
-    if (m > 4 * GM_MAX_M) return true;
-    int64_t groups = 0;
-    bool deep = true;
+    constexpr int WIDE_SHORT = 2560, WIDE_LONG = 5120;
+    if (m <= 2 * GM_MAX_M) return false;
+    int64_t groups = 0;                                         // of 128 x 128, one round of them on the chip
+    int longest = 0;
     for (int i = 0; i < n; ++i) {
+        if (items[i].d_in >= 1 << 25) return false;             // a tile's activations: 64 bytes a column, 32-bit offsets
         groups += (int64_t)((items[i].d_out + GW_ROWS - 1) / GW_ROWS) * ((m + 127) / 128);
-        deep = deep && items[i].d_in >= 4096;
+        longest = std::max(longest, items[i].d_in);
     }
-    return !(deep && 2 * groups <= GW_CUS);
+    if (m > 4 * GM_MAX_M) return true;
+    if (m > 3 * GM_MAX_M) return longest <= WIDE_LONG || 4 * groups > GW_CUS;
+    const int64_t rounds = (groups + GW_CUS - 1) / GW_CUS;
+    return longest <= WIDE_SHORT || (16 * groups >= 5 * GW_CUS && (rounds == 1 || 4 * groups >= 3 * GW_CUS * rounds));
 }
 
 size_t matmul_workspace_bytes(int d_in, int d_out, int m) {

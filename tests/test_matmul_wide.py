@@ -106,3 +106,15 @@ def test_deep_rows_of_the_larger_tiles(bits, d_out, d_in, m):
         torch.cuda.synchronize()
         assert torch.equal(got, want)
 
+
+# 129 to 256 rows: either side of each line of the choice between the wide kernel and tiles of 64 (the rows' length, how many of the
+# chip's CUs the wide tiles reach, how well they fill a last round)
+@pytest.mark.parametrize("d_out,d_in,m", [(200, 512, 128), (200, 512, 129), (300, 2560, 130), (300, 2816, 192), (4992, 2816, 129), (5000, 2816, 129),
+                                          (16385, 2816, 140), (24577, 2816, 140), (300, 5120, 193), (300, 5376, 256), (4096, 5376, 256),
+                                          (4097, 5376, 193)])
+def test_either_kernel_for_three_and_four_tiles(d_out, d_in, m):
+    say(f"[wide] three and four tiles {d_out}x{d_in} m={m}")
+    X, packed, norms, s, sg, sigma, cb = _product(m, d_out, d_in, m, 8, torch.float32)
+    kw = dict(chan_scale=s, signs=sg, pair_sigma=sigma)
+    least = torch.empty(qamw.matmul_workspace_bytes(d_in, d_out, m), dtype=torch.uint8, device="cuda")
+    assert torch.equal(qamw.matmul(X, packed, norms, cb, 8, 256, **kw), qamw.matmul(X, packed, norms, cb, 8, 256, workspace=least, **kw))
