@@ -569,8 +569,8 @@ void k_qgemv(GemvBatch bt) {
         // arrives), and from then on the next step's packed words are on their way while a step is worked on.  What stood in
         // the way: a branch on the element type or on the matrix's last row, at which the compiler waits for what either side
         // may have asked for, loads moved into the branch that uses them, a loop of scalar loads, the rotation inputs of a
-        // wave's second and third slab.  A 7B layer's four launches, one row: 67 us, so 61; then issue-bound, 8 instructions
-        // a codeword, where the launch has two waves and more per SIMD (11008 x 4096 twice: 20 us, 62 MB).
+        // wave's second and third slab.  A 7B layer's four launches, one row: 67 us, so 58; then issue-bound, 8 instructions
+        // a codeword, where the launch has two waves and more per SIMD (11008 x 4096 twice: 19 us, 62 MB).
         // bt.K == 2^BITS here.
         constexpr int KC = 1 << BITS, CB_PER_THREAD = (KC + GV_THREADS - 1) / GV_THREADS;
         GvRotIn<MT> rin;
