@@ -1,37 +1,50 @@
 // The cell table of the pruned nearest-codeword search (Sec. 3.1 / Sec. 3.5), made on the device: shared by the encoder
 // and the device's codebook training.
 //
-// A square [-R, R)^2 is cut into G x G cells; a cell's record lists, in ascending index order, every codeword that can be
+// A square [-R, R]^2 is cut into G x G cells; a cell's record lists, in ascending index order, every codeword that can be
 // nearest to a point of the cell, at most five, or says that the whole codebook has to be searched.
 //
-// R follows the codebook's scale: 4 where the codewords lie as those of a Lloyd codebook of the unit Gaussian (which holds
-// 99.99 % of the pairs such a codebook is for), in proportion to their mean |coordinate| otherwise, rounded to four
-// significant bits.  Every workgroup that makes a part of the table finds the same R, the first leaves it in the table
-// (cells_put_half).  A fixed square is of no use to a codebook of another scale: 4096 x 4096 bf16, 2048 points, codebook and
-// pairs / 16: 3960 us with [-4, 4)^2, where the search over the whole codebook takes 615; 36 so.
+// The cells are narrow in the middle, where a codebook of Gaussian pairs is dense, and wide at the edge: with s = x / 2R + 1/2,
+// kept between 0 and 1, a pair's cell is the integer nearest to (G - 1) s^2 (3 - 2s) in each coordinate, two more multiply-adds
+// than cells of one width.  In the middle that is as fine as 1.5 G cells of one width: for 2^11 points and G = 128 2.5 candidates
+// on average over the pairs, five for 0.14 % of them, more for 0.001 % (one width and R = 4: 3.1, 3.9 % and 0.05 %).  So four
+// candidates are read out of every record, and the fifth only where a wave holds one.
+//
+// The outermost cells reach to CELLS_FAR times R, and not only to R: strips that cross few codewords' neighbourhoods.  Pairs beyond
+// that, and the four corners, are searched for in the whole codebook.
+//
+// R is 17/16 of `half`, which follows the codebook's scale: 4 where the codewords lie as those of a Lloyd codebook of the unit
+// Gaussian, in proportion to their mean |coordinate| otherwise, rounded to four significant bits.  Every workgroup that makes a
+// part of the table finds the same, the first leaves it in the table (cells_put_half).  A fixed square is of no use to a codebook
+// of another scale: 4096 x 4096 bf16, 2048 points, codebook and pairs / 16: 3960 us with [-4, 4)^2, where the search over the whole
+// codebook takes 615; 36 so.
 //
 // Which codewords a cell lists.  For two codewords a and c the difference |x - c|^2 - |x - a|^2 is linear in x, so on a
-// box of half-width w around m it is at least |m - c|^2 - |m - a|^2 - 2 w (|c.x - a.x| + |c.y - a.y|).  c is left out
+// box of half-widths w, v around m it is at least |m - c|^2 - |m - a|^2 - 2 (w |c.x - a.x| + v |c.y - a.y|).  c is left out
 // when that exceeds a margin: then a is nearer at every point of the box, also after the roundings of the fp32 distances
-// (relative error below 2.4e-7 each; the margin is 4e-6 of the two squared distances and 1e-5 w^2).  As `a` serve the
+// (relative error below 2.4e-7 each; the margin is 4e-6 of the two squared distances and 1e-5 (w^2 + v^2)).  As `a` serve the
 // codewords nearest and second nearest to m: for a Lloyd codebook of the Gaussian that leaves the same lists as testing
-// all pairs (2^11 points, G = 128: 3.1 candidates on average over the pairs, six for 0.05 % of them, never more).  The lists are
-// found top down -- 8 x 8 cells, 4 x 4 cells, single cells -- and each level searches only its parent's list.
+// all pairs.  The lists are found top down -- 8 x 8 cells, 4 x 4 cells, single cells -- and each level searches only its parent's
+// list.
 #pragma once
 #include "qamw_front.hpp"
 
 namespace qamw {
 
 constexpr int CELLS_LIST = 5;                                  // candidates of a record
-constexpr uint32_t CELLS_SCAN = 0x80000000u;                   // in the record's upper word: decided by the whole codebook
-constexpr uint32_t CELLS_MORE = 1u;                            // in its lower word: more than three candidates
-
+// A record's two words: the first four candidates' byte offsets in the codebook, index times 8, in the bits 3 to 13 of the four
+// 16-bit halves, where one instruction takes them out; the fifth's index in what is left, see cells_fifth(); and
+constexpr uint32_t CELLS_FIFTH = 0x80000000u;                  // in the upper word: five candidates;
+constexpr uint32_t CELLS_SCAN = 0x40000000u;                   //   decided by the whole codebook;
+constexpr uint32_t CELLS_BORDER = 0x00004000u;                 //   a cell of the edge: of pairs within CELLS_FAR
+constexpr uint32_t CELLS_OFFSET = 0x3ff8u;
+constexpr float CELLS_REACH = 1.0625f, CELLS_FAR = 1.25f;      // R over half; how far the outermost cells reach, over R
 
 // Cells per side.  Four cells per codeword spacing at the centre of a Lloyd codebook keep the lists within a record;
 // the LDS holds 128 x 128 records beside 2048 codewords.
 constexpr int cells_side(int bits) { return bits >= 11 ? 128 : bits == 10 ? 96 : 64; }
 
-// R over the sum of the magnitudes of n = min(K, CP_SAMPLE) codewords' coordinates, so that a Lloyd codebook of the unit
+// half over the sum of the magnitudes of n = min(K, CP_SAMPLE) codewords' coordinates, so that a Lloyd codebook of the unit
 // Gaussian with K = 2^bits points gets 4 after the rounding, from 3.875 to 4.25: 4 over 2 n times 1 / 1.015 of the mean
 // |coordinate| of such a codebook's sample (qamw_train_codebook with 2^14 to 2^20 samples and 10 to 200 iterations: raw values
 // of 4.01 to 4.18 from 7 bits on).
@@ -41,29 +54,59 @@ inline float cells_half_per_sum(int bits) {
     const int n = 1 << bits < CP_SAMPLE ? 1 << bits : CP_SAMPLE;
     return 4.0f / (mean[bits - 1] * 2.0f * (float)n);
 }
-// R is kept in the first record, a border cell's, whose candidates do not matter: its upper 12 bits as the first index.
+// half is kept in the first record, a corner's, which has no candidates: its upper 12 bits from bit 3 on.
 __device__ __forceinline__ uint32_t cells_put_half(float half) { return (__float_as_uint(half) >> 20) << 3; }
 __device__ __forceinline__ float cells_half(const uint2 *table) { return __uint_as_float((table[0].x >> 3) << 20); }
-// Cells per unit length, G / 2R, one rounding or two off (the table's slack is 2^-19 of R).
-template <int G> __device__ __forceinline__ float cells_inv_width(float half) {
-    return 0.5f * G * __builtin_amdgcn_rcpf(__uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(half))));
+// 1 / 2R, one rounding or two off (the boxes' slack is 2^-16 of half).
+__device__ __forceinline__ float cells_inv_span(float half) {
+    return (0.5f / CELLS_REACH) * __builtin_amdgcn_rcpf(__uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(half))));
 }
+// Up to where a record of the edge holds.
+__device__ __forceinline__ float cells_far(float half) { return CELLS_REACH * CELLS_FAR * half; }
+
+// The cells' edges over half: of cell i from at[i] to at[i + 1].
+template <int G> struct CellsEdges {
+    float at[G + 1];
+    constexpr CellsEdges() : at() {
+        for (int i = 1; i < G; ++i) {
+            const double t = (i - 0.5) / (G - 1);
+            double lo = 0.0, hi = 1.0;                          // s^2 (3 - 2s) = t
+            for (int k = 0; k < 50; ++k) {
+                const double s = 0.5 * (lo + hi);
+                (s * s * (3.0 - 2.0 * s) < t ? lo : hi) = s;
+            }
+            at[i] = (float)((lo + hi - 1.0) * (double)CELLS_REACH);
+        }
+        at[0] = -CELLS_REACH * CELLS_FAR;
+        at[G] = CELLS_REACH * CELLS_FAR;
+    }
+};
+template <int G> static __constant__ const CellsEdges<G> cells_edges{};
 
 // ------------------------------------------------------------------------------------------------ the table
 constexpr int CP_THREADS = 256;
 constexpr int CP_WAVES = CP_THREADS / WAVE;
-constexpr int CP_REGION_LIST = 512;                            // candidates of 8 x 8 cells (200 at most for 2^11 Lloyd points)
-constexpr int CP_BLOCK_LIST = 128;                             // candidates of 4 x 4 cells (55)
+constexpr int CP_REGION_LIST = 512;                            // candidates of 8 x 8 cells (150 at most for 2^11 Lloyd points)
+constexpr int CP_BLOCK_LIST = 128;                             // candidates of 4 x 4 cells (70)
 constexpr int CP_PER_THREAD = 2048 / CP_THREADS;
 
-// Is codeword c farther than codeword a at every point of the box of half-width w around m?  dc2, da2: their squared
-// distances from m.
-__device__ __forceinline__ bool cells_dominated(float2 c, float dc2, float2 a, float da2, float w) {
-    const float reach = 2.00002f * w * (fabsf(c.x - a.x) + fabsf(c.y - a.y));
-    return dc2 - da2 > reach + 4e-6f * (dc2 + da2) + 1e-5f * w * w;
+struct CellsBox {
+    float mx, my, wx, wy;                                       // centre and half-widths
+};
+// n x n cells from (ix, iy) on
+template <int G> __device__ __forceinline__ CellsBox cells_box(int ix, int iy, int n, float half) {
+    const float slack = half * 0x1p-16f;                        // the fp32 roundings of the edges and of the cell lookup (2e-6)
+    const float x0 = cells_edges<G>.at[ix] * half, x1 = cells_edges<G>.at[ix + n] * half;
+    const float y0 = cells_edges<G>.at[iy] * half, y1 = cells_edges<G>.at[iy + n] * half;
+    return {0.5f * (x0 + x1), 0.5f * (y0 + y1), 0.5f * (x1 - x0) + slack, 0.5f * (y1 - y0) + slack};
 }
-__device__ __forceinline__ float cells_dist2(float mx, float my, float2 c) {
-    const float ex = mx - c.x, ey = my - c.y;
+// Is codeword c farther than codeword a at every point of the box?  dc2, da2: their squared distances from its centre.
+__device__ __forceinline__ bool cells_dominated(float2 c, float dc2, float2 a, float da2, const CellsBox &b) {
+    const float reach = 2.00002f * (b.wx * fabsf(c.x - a.x) + b.wy * fabsf(c.y - a.y));
+    return dc2 - da2 > reach + 4e-6f * (dc2 + da2) + 1e-5f * (b.wx * b.wx + b.wy * b.wy);
+}
+__device__ __forceinline__ float cells_dist2(const CellsBox &b, float2 c) {
+    const float ex = b.mx - c.x, ey = b.my - c.y;
     return ex * ex + ey * ey;
 }
 
@@ -119,14 +162,12 @@ __device__ __forceinline__ void cells_build_region(const CellsPoints &points, in
     s = wave_add(s) * half_per_sum;
     // squares of distances inside a cell stay normal numbers
     const float half = __uint_as_float((__float_as_uint(fminf(fmaxf(s, 0x1p-40f), 0x1p40f)) + 0x80000u) & 0xFFF00000u);
-    const float h = 2.0f * half / G;
-    const float slack = half * 0x1p-19f;                        // the fp32 roundings of the centres and of the cell lookup
-    float mx = ((float)x0 + 3.5f - 0.5f * G) * h, my = ((float)y0 + 3.5f - 0.5f * G) * h, w = 4.0f * h + slack;
+    CellsBox box = cells_box<G>(x0, y0, 8, half);
     float nd = 3.0e38f;
     float2 nc = make_float2(0.0f, 0.0f);
 #pragma unroll
     for (int j = 0; j < CP_PER_THREAD; ++j) {
-        d2[j] = cells_dist2(mx, my, c[j]);
+        d2[j] = cells_dist2(box, c[j]);
         if (d2[j] < nd) {
             nd = d2[j];
             nc = c[j];
@@ -150,7 +191,7 @@ __device__ __forceinline__ void cells_build_region(const CellsPoints &points, in
     unsigned keep = 0;
 #pragma unroll
     for (int j = 0; j < CP_PER_THREAD; ++j)
-        if (j < per && first + j < K && !cells_dominated(c[j], d2[j], nc, nd, w)) keep |= 1u << j;
+        if (j < per && first + j < K && !cells_dominated(c[j], d2[j], nc, nd, box)) keep |= 1u << j;
     int below = __popc(keep);                                   // inclusive sum over the lanes up to this one
 #pragma unroll
     for (int j = 0; j < CP_PER_THREAD; ++j) {
@@ -181,9 +222,7 @@ __device__ __forceinline__ void cells_build_region(const CellsPoints &points, in
 
     // ---- 4 x 4 cells: the wave's lanes share the region's candidates
     const int bx = x0 + 4 * (wid & 1), by = y0 + 4 * (wid >> 1);
-    mx = ((float)bx + 1.5f - 0.5f * G) * h;
-    my = ((float)by + 1.5f - 0.5f * G) * h;
-    w = 2.0f * h + slack;
+    box = cells_box<G>(bx, by, 4, half);
     nd = 3.0e38f;
     constexpr int RUNS = CP_REGION_LIST / WAVE;
     float2 ce[RUNS];
@@ -192,7 +231,7 @@ __device__ __forceinline__ void cells_build_region(const CellsPoints &points, in
     for (int u = 0; u < RUNS; ++u) ce[u] = reg_c[u * WAVE + lane < n_reg ? u * WAVE + lane : 0];
 #pragma unroll
     for (int u = 0; u < RUNS; ++u) {
-        de[u] = cells_dist2(mx, my, ce[u]);
+        de[u] = cells_dist2(box, ce[u]);
         if (u * WAVE + lane < n_reg && de[u] < nd) {
             nd = de[u];
             nc = ce[u];
@@ -203,7 +242,7 @@ __device__ __forceinline__ void cells_build_region(const CellsPoints &points, in
 #pragma unroll
     for (int u = 0; u < RUNS; ++u) {
         if (u * WAVE >= n_reg) break;
-        const bool k = u * WAVE + lane < n_reg && !cells_dominated(ce[u], de[u], nc, nd, w);
+        const bool k = u * WAVE + lane < n_reg && !cells_dominated(ce[u], de[u], nc, nd, box);
         const unsigned long long mask = __ballot(k);
         const int pos = n_blk + __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
         if (k && pos < CP_BLOCK_LIST) {
@@ -219,9 +258,7 @@ __device__ __forceinline__ void cells_build_region(const CellsPoints &points, in
     // ---- single cells: four lanes per cell, each a quarter of the block's candidates
     const int cell = lane >> 2, part = lane & 3;
     const int ix = bx + (cell & 3), iy = by + (cell >> 2);
-    mx = ((float)ix - 0.5f * G) * h;
-    my = ((float)iy - 0.5f * G) * h;
-    w = 0.5f * h + slack;
+    box = cells_box<G>(ix, iy, 1, half);
     const int quarter = (n_blk + 3) >> 2, e_begin = part * quarter, e_end = min(n_blk, e_begin + quarter);
     // The quarter's candidates in registers, in one round of LDS reads; those of a longer list are read again in both passes.
     constexpr int HELD = CP_BLOCK_LIST / 8;
@@ -242,10 +279,10 @@ __device__ __forceinline__ void cells_build_region(const CellsPoints &points, in
     };
 #pragma unroll
     for (int q = 0; q < HELD; ++q) {
-        dh[q] = e_begin + q < e_end ? cells_dist2(mx, my, held[q]) : 3.0e38f;
+        dh[q] = e_begin + q < e_end ? cells_dist2(box, held[q]) : 3.0e38f;
         rank(held[q], dh[q]);
     }
-    for (int e = e_begin + HELD; e < e_end; ++e) rank(blk_c[wid][e], cells_dist2(mx, my, blk_c[wid][e]));
+    for (int e = e_begin + HELD; e < e_end; ++e) rank(blk_c[wid][e], cells_dist2(box, blk_c[wid][e]));
     auto merge = [&](float oda, float odb, float2 oca, float2 ocb) {
         // each side's two, sorted: the first is the smaller head, the second the smaller of the other head and its own second
         const bool swap = oda < da;
@@ -265,13 +302,13 @@ __device__ __forceinline__ void cells_build_region(const CellsPoints &points, in
           make_float2(dpp_move<DPP_XOR2>(cb.x), dpp_move<DPP_XOR2>(cb.y)));
     unsigned kept = 0;                                          // bit e - e_begin (a quarter is at most 32 candidates)
     auto keeps = [&](float2 c, float d) {
-        return !(cells_dominated(c, d, ca, da, w) || (db < 3.0e38f && cells_dominated(c, d, cb, db, w)));
+        return !(cells_dominated(c, d, ca, da, box) || (db < 3.0e38f && cells_dominated(c, d, cb, db, box)));
     };
 #pragma unroll
     for (int q = 0; q < HELD; ++q)
         if (e_begin + q < e_end && keeps(held[q], dh[q])) kept |= 1u << q;
     for (int e = e_begin + HELD; e < e_end; ++e)
-        if (keeps(blk_c[wid][e], cells_dist2(mx, my, blk_c[wid][e]))) kept |= 1u << (e - e_begin);
+        if (keeps(blk_c[wid][e], cells_dist2(box, blk_c[wid][e]))) kept |= 1u << (e - e_begin);
     const int mine = __popc(kept);
     const int n0 = dpp_move<dpp_quad_lane(0)>(mine), n1 = dpp_move<dpp_quad_lane(1)>(mine), n2 = dpp_move<dpp_quad_lane(2)>(mine);
     int before = (part > 0 ? n0 : 0) + (part > 1 ? n1 : 0) + (part > 2 ? n2 : 0);
@@ -285,15 +322,14 @@ __device__ __forceinline__ void cells_build_region(const CellsPoints &points, in
     __syncthreads();
     if (part == 0) {
         uint2 r = make_uint2(0u, CELLS_SCAN);
-        // the border belongs to everything outside the square: the lookup clamps to it
-        const bool inside = ix > 0 && ix < G - 1 && iy > 0 && iy < G - 1;
-        if (inside && total >= 1 && total <= CELLS_LIST) {
-            unsigned i5[CELLS_LIST];
+        const bool edge_x = ix == 0 || ix == G - 1, edge_y = iy == 0 || iy == G - 1;
+        if (!(edge_x && edge_y) && total >= 1 && total <= CELLS_LIST) {
+            unsigned i5[CELLS_LIST];                            // ascending, padded with the first
 #pragma unroll
             for (int q = 0; q < CELLS_LIST; ++q) i5[q] = blk_i[wid][rec_i[wid][cell][q < total ? q : 0]];
-            // ascending; bits 3, 15, 27, 39, 51 onwards, padded with the first
-            r.x = (i5[0] << 3) | (i5[1] << 15) | (i5[2] << 27) | (total > 3 ? CELLS_MORE : 0u);
-            r.y = (i5[2] >> 5) | (i5[3] << 7) | (i5[4] << 19);
+            r.x = (i5[0] << 3) | (i5[1] << 19) | ((i5[4] & 31u) << 14);
+            r.y = (i5[2] << 3) | (i5[3] << 19) | (((i5[4] >> 5) & 15u) << 15) | (i5[4] >> 9) | (total > 4 ? CELLS_FIFTH : 0u) |
+                  (edge_x || edge_y ? CELLS_BORDER : 0u);
         }
         if (ix == 0 && iy == 0) r.x = cells_put_half(half);
         table[iy * G + ix] = r;
@@ -302,39 +338,65 @@ __device__ __forceinline__ void cells_build_region(const CellsPoints &points, in
 
 
 // ------------------------------------------------------------------------------------------------ the search
-// Byte offset from table_at of the record of the cell that holds (x0, x1); inv_h: cells per unit length, G / 2R.  The lookup
-// rounds x inv_h + G / 2 to the nearest integer and clamps it to the border, whose records say "whole codebook".
+// Byte offset from table_at of the record of the cell that holds (x0, x1); inv_span: 1 / 2R.
 constexpr uint32_t CELLS_MAGIC_BITS = 0x4B000000u;             // 2^23: adding it rounds to an integer, left in the low bits
-template <int G> __device__ __forceinline__ uint32_t cells_record_at(float x0, float x1, float inv_h, uint32_t table_at) {
+template <int G> __device__ __forceinline__ uint32_t cells_record_at(float x0, float x1, float inv_span, uint32_t table_at) {
     constexpr float magic = 8388608.0f;
-    const float vx = fminf(fmaxf(__builtin_fmaf(x0, inv_h, magic + G / 2), magic), magic + (G - 1));
-    const float vy = fminf(fmaxf(__builtin_fmaf(x1, inv_h, magic + G / 2), magic), magic + (G - 1));
-    // (iy G + ix) 8 + table_at mod 2^32, the two numbers' exponent bits taken out with the one constant
-    const uint32_t cell = __float_as_uint(vy) * G + __float_as_uint(vx);
+    auto place = [=](float x) {                                 // (G - 1) s^2 (3 - 2s); a NaN is 0
+        const float s = fminf(fmaxf(__builtin_fmaf(x, inv_span, 0.5f), 0.0f), 1.0f);
+        return __float_as_uint(__builtin_fmaf(s * s, __builtin_fmaf(s, -2.0f * (G - 1), 3.0f * (G - 1)), magic));
+    };
+    const uint32_t ix = place(x0), iy = place(x1);
+    // (iy G + ix) 8 + table_at mod 2^32, the two numbers' exponent bits taken out with the one constant.  Two instructions; three
+    // where the compiler multiplies out.
+    uint32_t cell;
+    if constexpr (G == 128) asm("v_lshl_add_u32 %0, %1, 7, %2" : "=v"(cell) : "v"(iy), "v"(ix));
+    else if constexpr (G == 64) asm("v_lshl_add_u32 %0, %1, 6, %2" : "=v"(cell) : "v"(iy), "v"(ix));
+    else cell = iy * G + ix;
     return (cell << 3) + (table_at - ((CELLS_MAGIC_BITS * G + CELLS_MAGIC_BITS) << 3));
 }
-__device__ __forceinline__ bool cells_scan(uint2 rec) { return rec.y >> 31; }
-// The nearest of the record's candidates, as its byte offset in the codebook (LDS, at byte address cb_at); m: its squared
-// distance.  All lanes of the wave call it together.  FIVE: nearly every wave holds a pair with more than three candidates.
-template <bool FIVE> __device__ __forceinline__ unsigned cells_nearest(uint2 rec, float x0, float x1, uint32_t cb_at, float &m) {
-    const unsigned lo = rec.x, hi = rec.y;
-    const unsigned o0 = lo & 0x7ff8u, o1 = (lo >> 12) & 0x7ff8u, o2 = __builtin_amdgcn_alignbit(hi, lo, 24) & 0x7ff8u;
-    auto dist = [&](unsigned o) {
-        const lds_f32x2_t c = lds_read<lds_f32x2_t>(cb_at + o);
-        return exact_dist2(x0, x1, make_float2(c[0], c[1]));
-    };
-    const float d0 = dist(o0), d1 = dist(o1), d2 = dist(o2);
-    m = fminf(fminf(d0, d1), d2);
-    unsigned o = o2;
-    if (FIVE || __ballot(lo & CELLS_MORE)) {
-        const unsigned o3 = (hi >> 4) & 0x7ff8u, o4 = (hi >> 16) & 0x7ff8u;
-        const float d3 = dist(o3), d4 = dist(o4);
-        m = fminf(fminf(m, d3), d4);
-        o = (d3 == m) ? o3 : o4;
-        o = (d2 == m) ? o2 : o;
-    }
-    o = (d1 == m) ? o1 : o;                                     // the lowest index among equals: the candidates ascend
-    return (d0 == m) ? o0 : o;
+// A candidate as one number: its squared distance's bits above its byte offset in the codebook.  As fp64 values (of finite
+// distances, infinity and NaN too) these are in the order of the distance and, of equal ones, of the index, so that the nearest is
+// the minimum, one instruction for a comparison and two selections.
+__device__ __forceinline__ double cells_candidate(float d, unsigned o) { return __hiloint2double(__float_as_int(d), (int)o); }
+__device__ __forceinline__ double cells_nearer(double a, double b) {
+    double m;
+    asm("v_min_f64 %0, %1, %2" : "=v"(m) : "v"(a), "v"(b));     // (as a function of the library it comes with two more that quiet a NaN)
+    return m;
+}
+__device__ __forceinline__ unsigned cells_offset(double candidate) { return (unsigned)__double2loint(candidate); }
+__device__ __forceinline__ float cells_distance(double candidate) { return __int_as_float(__double2hiint(candidate)); }
+
+// The record's first four candidates, requested from the codebook in LDS at byte address cb_at, ...
+struct CellsFour {
+    unsigned o[4];
+    lds_f32x2_t c[4];
+};
+__device__ __forceinline__ void cells_request(CellsFour &f, uint2 rec, uint32_t cb_at) {
+    f.o[0] = rec.x & CELLS_OFFSET;
+    f.o[1] = (rec.x >> 16) & CELLS_OFFSET;
+    f.o[2] = rec.y & CELLS_OFFSET;
+    f.o[3] = (rec.y >> 16) & CELLS_OFFSET;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) f.c[j] = lds_read<lds_f32x2_t>(cb_at + f.o[j]);
+}
+// ... and the nearest of them.
+__device__ __forceinline__ double cells_nearest(const CellsFour &f, float x0, float x1) {
+    double d[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) d[j] = cells_candidate(exact_dist2(x0, x1, make_float2(f.c[j][0], f.c[j][1])), f.o[j]);
+    return cells_nearer(cells_nearer(d[0], d[1]), cells_nearer(d[2], d[3]));
+}
+// `best` or the fifth candidate of a record that has one.
+__device__ __forceinline__ double cells_fifth(uint2 rec, float x0, float x1, uint32_t cb_at, double best) {
+    const unsigned o4 = (((rec.x >> 14) & 31u) | (((rec.y >> 15) & 15u) << 5) | ((rec.y & 3u) << 9)) << 3;
+    const lds_f32x2_t c = lds_read<lds_f32x2_t>(cb_at + o4);
+    const double nearer = cells_nearer(best, cells_candidate(exact_dist2(x0, x1, make_float2(c[0], c[1])), o4));
+    return rec.y & CELLS_FIFTH ? nearer : best;
+}
+// Whether the whole codebook decides the pair; far: cells_far().
+__device__ __forceinline__ bool cells_undecided(uint2 rec, float x0, float x1, float far) {
+    return (rec.y & CELLS_SCAN) || ((rec.y & CELLS_BORDER) && !(fmaxf(fabsf(x0), fabsf(x1)) <= far));
 }
 
 // ------------------------------------------------------------------------------------------------ without the table

@@ -1,20 +1,24 @@
 // QAM-W encoder with a cell table made on the device (Sec. 3.1 / Sec. 3.5; the index is the one the search over the
 // whole codebook returns, lowest index on ties).
 //
-// k_cells_prepare cuts a square that follows the codebook's scale -- 99.99 % of the pairs that a Lloyd codebook is for lie in
-// it -- into G x G cells and lists, per cell, every codeword that can be nearest to a point of the cell; the same launch
-// computes the row norms.  k_encode_cells keeps the codebook and the whole table in LDS and decides a pair by the exact fp32
-// squared distances to its cell's candidates, at most five.  A pair outside the table, or in a cell that lists more, is
-// decided by the exact scan of the whole codebook (64 lanes x K/64 codewords).
+// k_cells_prepare cuts a square that follows the codebook's scale into G x G cells and lists, per cell, every codeword that can
+// be nearest to a point of the cell; the same launch computes the row norms.  k_encode_cells keeps the codebook and the whole table
+// in LDS and decides a pair by the exact fp32 squared distances to its cell's first four candidates, and to the fifth where there
+// is one (0.14 % of the pairs that a Lloyd codebook of 2^11 points is for).  A pair outside the table (0.0002 % of them), or in a
+// cell that lists more (0.001 %), is decided by the exact scan of the whole codebook (64 lanes x K/64 codewords).
 //   Where that meets many of an item's pairs -- pairs much wider than the codebook, codewords that no Lloyd iteration has spread
 // -- the item is put off: once the wave has walked its rows it takes those without the table, all 512 pairs together
 // (nearest_of_all(); all distances up to 32 codewords).  That loop comes after the other and not inside it so that it costs
 // the other no registers.  After an item was put off the next is too, then the next 3, 7, 15, without a try.
 //
-// What bounds k_encode_cells: vector-ALU issue, with the LDS gathers (one record and five codewords per pair) close
-// behind.  Hence one workgroup of 16 waves per CU that stages its 144 KB once and walks the rows; a wave keeps to one
-// 1024-column slab of a matrix, so the slab's scales, signs and pair gains are loaded, divided and combined once per
-// wave instead of once per row.
+// What bounds k_encode_cells: the issue of its instructions (606 of the vector ALU, 140 scalar and 42 of LDS for a wave's 512
+// pairs), with four waves per SIMD to hide the LDS gathers behind.  A SIMD issues a vector instruction in 2.1 cycles, but one in
+// four of the kind that min, max, compare, shift and DPP are (adds, multiplies, ANDs and moves go in between), so what helps is
+// fewer instructions, and waves that do not wait at the same time.  Hence one workgroup of 16 waves per CU that stages its 144 KB
+// once and walks the rows; a wave keeps to one 1024-column slab of a matrix, so the slab's scales, signs and pair gains are
+// loaded, divided and combined once per wave instead of once per row; records of all eight pairs requested at once, and a pair's
+// candidates before the pair ahead of it is decided.  13824 x 5120 at 11 bits, the whole call: 134 us with five candidates in cells
+// of one width, a comparison and two selections each, so 107 (a 7B layer with its pair scales 411, so 333).
 #include <atomic>
 #include <cmath>
 
@@ -96,6 +100,7 @@ constexpr int CELLS_DIRECT_THREADS = 256;
 constexpr int cells_threads(int G) { return G == 128 ? 1024 : 512; }
 constexpr int cells_codewords(int G) { return G == 128 ? 2048 : G == 96 ? 1024 : 512; }
 constexpr int cells_least_k(int G) { return G == 128 ? 2048 : G == 96 ? 1024 : 2; }
+constexpr int cells_bits(int G) { return G == 128 ? 11 : G == 96 ? 10 : 0; }   // 0: 1 to 9
 constexpr size_t cells_lds_bytes(int G) { return (size_t)cells_codewords(G) * 8 + (size_t)G * G * 8; }
 
 // 1/sqrt(B) is a power of two: its product with the gain is exact, and so one multiplication gives the bits of two (what that
@@ -158,31 +163,77 @@ __global__ __launch_bounds__(STAGED ? cells_threads(G) : CELLS_DIRECT_THREADS) _
 void k_encode_cells(CellsBatch bt) {
     static_assert(STAGED || (G & (G - 1)) == 0, "the mask of the record's offset");
     constexpr int THREADS = STAGED ? cells_threads(G) : CELLS_DIRECT_THREADS, WAVES = THREADS / WAVE;
-    constexpr uint32_t TABLE_AT = cells_codewords(G) * 8;      // LDS: the codebook at 0, then the table
-    const int K = bt.K, bits = bt.bits;
-    const float half = cells_half(bt.table);                    // on its way while the LDS is filled
-    {
-        const lds_f32x2_t *cbk = reinterpret_cast<const lds_f32x2_t *>(bt.codebook);
-#pragma unroll 8
-        for (int i = threadIdx.x; i < K; i += THREADS) lds_write(8 * i, cbk[i]);
-        if (STAGED) {
-            const lds_u32x4_t *src = reinterpret_cast<const lds_u32x4_t *>(bt.table);
-#pragma unroll 8
-            for (int i = threadIdx.x; i < G * G / 2; i += THREADS) lds_write(TABLE_AT + 16 * i, src[i]);
-        }
-    }
-    __syncthreads();
-
+    constexpr int CODEWORDS = cells_codewords(G);
+    constexpr uint32_t TABLE_AT = CODEWORDS * 8;               // LDS: the codebook at 0, then the table
+    const int K = cells_bits(G) ? CODEWORDS : bt.K, bits = cells_bits(G) ? cells_bits(G) : bt.bits;
     const int lane = threadIdx.x & (WAVE - 1);
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const LaneSigns<B> ls(lane);
     const int pos = slab_pos(lane);
     const float unit = ls.parity * bt.inv_sqrt_block;
-
-    const float inv_h = cells_inv_width<G>(half);
-
     const int n_waves = (int)gridDim.x * WAVES;
     const int gw = (int)blockIdx.x * WAVES + wid;
+
+    // The wave's items, matrix by matrix, one slab of each.  The next row -- the next matrix's first after the last one of this --
+    // is on its way while one is searched: a wave meets a matrix every four to eleven rows of a 7B layer, and waited there for memory
+    // as all others did.
+    int mi = -1, turn = 0;                                      // the matrix that the next row is of
+    CellsShare share;
+    const char *w_next = nullptr;                               // the wave's next row
+    const float *norm_at = nullptr;
+    int64_t w_step = 0;
+    int left = 0;                                               // rows of it that the wave has yet to ask for
+    auto next_matrix = [&]() __attribute__((always_inline)) {
+        while (++mi < bt.n) {
+            const CellsMat &M = bt.m[mi];
+            if (!cells_share(share, M, gw, n_waves, turn)) continue;
+            const int64_t pitch = M.ldw * (DTYPE == 0 ? 4 : 2);
+            w_next = static_cast<const char *>(M.W) + share.row * pitch;
+            w_step = share.rows_step * pitch;
+            norm_at = M.norms + share.row;
+            left = (M.d_out - share.row + share.rows_step - 1) / share.rows_step;
+            return;
+        }
+    };
+    RawRow<DTYPE> next;
+    float norm_next = 0.0f;
+    auto first_column = [&](int slab, int d_in) __attribute__((always_inline)) {
+        const int col0 = slab * 1024 + 16 * pos;
+        return col0 < d_in ? col0 : 0;
+    };
+    auto request = [&]() __attribute__((always_inline)) {       // the next row
+        if (left == 0) next_matrix();
+        if (mi >= bt.n) return;
+        load_raw_row<DTYPE>(next, w_next, 0, first_column(share.slab, bt.m[mi].d_in));
+        norm_next = *norm_at;
+        w_next += w_step;
+        norm_at += share.rows_step;
+        --left;
+    };
+    request();
+
+    // the codebook and the table, requested in one go
+    const float half = cells_half(bt.table);
+    {
+        constexpr int CB = (CODEWORDS + THREADS - 1) / THREADS, RECS = STAGED ? G * G / 2 / THREADS : 0;
+        static_assert(!STAGED || G * G / 2 % THREADS == 0, "whole rounds");
+        const lds_f32x2_t *cbk = reinterpret_cast<const lds_f32x2_t *>(bt.codebook);
+        const lds_u32x4_t *src = reinterpret_cast<const lds_u32x4_t *>(bt.table);
+        lds_f32x2_t c[CB];
+        lds_u32x4_t r[RECS + 1];
+#pragma unroll
+        for (int i = 0; i < CB; ++i) c[i] = cbk[min((int)threadIdx.x + i * THREADS, K - 1)];
+#pragma unroll
+        for (int i = 0; i < RECS; ++i) r[i] = src[threadIdx.x + i * THREADS];
+#pragma unroll
+        for (int i = 0; i < CB; ++i)
+            if (cells_bits(G) || (int)threadIdx.x + i * THREADS < K) lds_write(8 * (threadIdx.x + i * THREADS), c[i]);
+#pragma unroll
+        for (int i = 0; i < RECS; ++i) lds_write(TABLE_AT + 16 * (threadIdx.x + i * THREADS), r[i]);
+    }
+    __syncthreads();
+
+    const float inv_span = cells_inv_span(half), far = cells_far(half);
     unsigned long long put_off[CELLS_PUT_OFF / 64] = {};        // items that the table does not help
     auto put = [&](int n) {
 #pragma unroll
@@ -191,47 +242,43 @@ void k_encode_cells(CellsBatch bt) {
     bool any_put_off = false;
     int skip = 0, streak = 0;                                   // items still to be put off untried; how many at a time
     int n = 0;                                                  // the wave's items so far
-    int turn = 0;
 #pragma unroll 1
-    for (int mi = 0; mi < bt.n; ++mi) {
+    while (mi < bt.n) {
         const CellsMat &M = bt.m[mi];
-        CellsShare share;
-        if (!cells_share(share, M, gw, n_waves, turn)) continue;
-        const int rows_step = share.rows_step;
         const int col0 = share.slab * 1024 + 16 * pos;
         const bool active = col0 < M.d_in;
         const int c = active ? col0 : 0;
-        const void *__restrict__ W = M.W;
-        const int64_t ldw = M.ldw;
-        const float *__restrict__ norms = M.norms;
-        const int d_out = M.d_out;
+        const unsigned long long lanes = __ballot(active);
+        const int64_t row_bytes = M.row_bytes;
+        const int d_in = M.d_in;
+        uint8_t *out = M.packed + share.row * row_bytes;
+        const int64_t out_step = share.rows_step * row_bytes;
         float sc[16], g[8];
         cells_constants<B>(sc, g, M, c, unit);
 
-        int row = share.row;
-        RawRow<DTYPE> next;
-        load_raw_row<DTYPE>(next, W, (int64_t)row * ldw, c);
-        float norm_next = norms[row];
-        for (; row < d_out; row += rows_step, ++n) {
+        for (int rows = left + 1; rows > 0; --rows, ++n, out += out_step) {
             const RawRow<DTYPE> raw = next;
             const float norm = norm_next;
-            if (row + rows_step < d_out) {                      // the wave's next row is on its way while this one is searched
-                load_raw_row<DTYPE>(next, W, (int64_t)(row + rows_step) * ldw, c);
-                norm_next = norms[row + rows_step];
-            }
+            request();
             if (skip > 0 && n < CELLS_PUT_OFF) {
                 --skip;
                 put(n);
                 continue;
             }
             float x[16];
-            cells_pairs<DTYPE, B>(x, raw, norm, sc, g, ls, unit);
+            if constexpr (STAGED && G == 128 && DTYPE == 0) {   // no registers for the lane's signs: made again
+                int p = pos;
+                asm volatile("" : "+v"(p));
+                cells_pairs<DTYPE, B>(x, raw, norm, sc, g, LaneSigns<B>(lane, p), unit);
+            } else {
+                cells_pairs<DTYPE, B>(x, raw, norm, sc, g, ls, unit);
+            }
 
             // ---------------- the cells' records
             uint2 rec[8];
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
-                const uint32_t at = cells_record_at<G>(x[2 * k], x[2 * k + 1], inv_h, STAGED ? TABLE_AT : 0u);
+                const uint32_t at = cells_record_at<G>(x[2 * k], x[2 * k + 1], inv_span, STAGED ? TABLE_AT : 0u);
                 if (STAGED) {
                     const lds_u32x2_t r = lds_read<lds_u32x2_t>(at);
                     rec[k] = make_uint2(r[0], r[1]);
@@ -239,47 +286,62 @@ void k_encode_cells(CellsBatch bt) {
                     rec[k] = *reinterpret_cast<const uint2 *>(reinterpret_cast<const char *>(bt.table) + (at & (G * G * 8u - 1u)));   // in range whatever x is
                 }
             }
+            // A pair's candidates are requested before the pair ahead of it is decided; otherwise a wave waits for LDS sixteen times.
+            __builtin_amdgcn_sched_barrier(0);
             unsigned idx8[8];                                   // 8 times the index: the codeword's byte offset
             unsigned any = 0;
+            CellsFour four[2];
+            cells_request(four[0], rec[0], 0u);
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
+                if (k + 1 < 8) cells_request(four[(k + 1) & 1], rec[k + 1], 0u);
+                __builtin_amdgcn_sched_barrier(0);
                 any |= rec[k].y;
-                float m;
-                idx8[k] = cells_nearest<G == 128>(rec[k], x[2 * k], x[2 * k + 1], 0u, m);
+                idx8[k] = cells_offset(cells_nearest(four[k & 1], x[2 * k], x[2 * k + 1]));
+                __builtin_amdgcn_sched_barrier(0);
             }
 
-            // ---------------- the rest: a few by the exact scan, the whole wave on one pair at a time; many later
-            const unsigned long long flagged = __ballot(active && (any & CELLS_SCAN));
-            if (flagged) {
-                // many: without the table, later.  (A grid decides most of them; otherwise as many as dense_above.)
-                bool many = __popcll(flagged) > CELLS_FEW_LANES && n < CELLS_PUT_OFF;
-                if (many && !bt.grid) {
-                    int n_scan = 0;
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) n_scan += __popcll(__ballot(active && cells_scan(rec[k])));
-                    many = n_scan > bt.dense_above;
-                }
-                if (many) {
-                    put(n);
-                    any_put_off = true;
-                    skip = streak = min(2 * streak + 1, 15);
-                    continue;
-                }
+            // ---------------- the rest: fifth candidates, ...
+            if (__ballot(any >= CELLS_SCAN || (any & CELLS_BORDER)) != 0ull) {
 #pragma unroll
                 for (int k = 0; k < 8; ++k) {
-                    unsigned long long mask = __ballot(active && cells_scan(rec[k]));
-                    while (mask) {
-                        const int src = __ffsll((long long)mask) - 1;
-                        mask &= mask - 1;
-                        const float x0 = __shfl(x[2 * k], src, WAVE), x1 = __shfl(x[2 * k + 1], src, WAVE);
-                        const int bi = wave_exact_scan<cells_least_k(G), cells_codewords(G)>(x0, x1, 0u, K, lane);
-                        if (lane == src) idx8[k] = 8u * (unsigned)bi;
+                    if (__ballot(rec[k].y & CELLS_FIFTH) == 0ull) continue;
+                    const lds_f32x2_t cw = lds_read<lds_f32x2_t>(idx8[k]);
+                    const double best = cells_candidate(exact_dist2(x[2 * k], x[2 * k + 1], make_float2(cw[0], cw[1])), idx8[k]);
+                    idx8[k] = cells_offset(cells_fifth(rec[k], x[2 * k], x[2 * k + 1], 0u, best));
+                }
+                // ... and pairs that no record decides, a few by the exact scan, the whole wave on one pair at a time; many later
+                if (__ballot(any & (CELLS_SCAN | CELLS_BORDER)) & lanes) {
+                    unsigned long long scan[8], flagged = 0;    // lanes whose k-th pair is scanned
+                    int n_scan = 0;
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) {
+                        scan[k] = __ballot(cells_undecided(rec[k], x[2 * k], x[2 * k + 1], far)) & lanes;
+                        flagged |= scan[k];
+                        n_scan += __popcll(scan[k]);
+                    }
+                    // many: without the table, later.  (A grid decides most of them; otherwise as many as dense_above.)
+                    if (__popcll(flagged) > CELLS_FEW_LANES && n < CELLS_PUT_OFF && (bt.grid || n_scan > bt.dense_above)) {
+                        put(n);
+                        any_put_off = true;
+                        skip = streak = min(2 * streak + 1, 15);
+                        continue;
+                    }
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) {
+                        unsigned long long mask = scan[k];
+                        while (mask) {
+                            const int src = __ffsll((long long)mask) - 1;
+                            mask &= mask - 1;
+                            const int bi = wave_exact_scan<cells_least_k(G), CODEWORDS>(lane_value(x[2 * k], src), lane_value(x[2 * k + 1], src), 0u, K, lane);
+                            if (lane == src) idx8[k] = 8u * (unsigned)bi;
+                        }
                     }
                 }
             }
             streak = 0;
 
-            if (active) store_fields<3>(M.packed + (int64_t)row * M.row_bytes, M.row_bytes, M.d_in, c, idx8, bits);
+            if (active) store_fields<3>(out, row_bytes, d_in, c, idx8, bits);
         }
     }
     if (!any_put_off) return;
@@ -295,7 +357,6 @@ void k_encode_cells(CellsBatch bt) {
 #pragma unroll 1
     for (int mi = 0; mi < bt.n; ++mi) {
         const CellsMat &M = bt.m[mi];
-        CellsShare share;
         if (!cells_share(share, M, gw, n_waves, turn)) continue;
         const int col0 = share.slab * 1024 + 16 * slab_pos(ln);
         const bool active = col0 < M.d_in;

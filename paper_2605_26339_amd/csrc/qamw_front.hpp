@@ -48,29 +48,33 @@ template <int DTYPE> __device__ __forceinline__ void widen_raw_row(float (&y)[16
     }
 }
 
-// The scaled weights divided by the row's norm; a zero norm gives zeros.
-__device__ __forceinline__ void divide_by_norm(float (&y)[16], float r) {
+// The scaled weights divided by the row's norm, which is the same in the whole wave; a zero norm gives zeros.
+__device__ __forceinline__ void divide_by_norm(float (&y)[16], float norm) {
     // u = ws / r, the correctly rounded quotient.  With q = fl(1/r) correctly rounded, q0 = fl(ws q) and the exact
     // remainder rem = ws - q0 r (one fused multiply-add), fl(q0 + rem q) IS the correctly rounded ws / r (Markstein's
     // division theorem) as long as nothing under- or overflows on the way: r within 2^+-60 and every |ws| at least
     // 2^-100.  A wave that holds anything else (an exact zero included) takes the plain division for all its lanes.
-    if (r > 0.0f) {
-        float amin = fminf(fabsf(y[0]), fabsf(y[1]));
+    // (No value is set before the branches: zeros for a norm of zero, set there, were 16 moves in every row.)
+    const uint32_t rb = __builtin_amdgcn_readfirstlane(__float_as_uint(norm));
+    const float r = __uint_as_float(rb);
+    float amin = fminf(fabsf(y[0]), fabsf(y[1]));
 #pragma unroll
-        for (int e = 2; e < 16; e += 2) amin = fminf(amin, fminf(fabsf(y[e]), fabsf(y[e + 1])));
-        const bool plain = !(amin >= 7.8886090522e-31f) || !(r >= 8.6736173799e-19f && r <= 1.1529215046e18f);
-        if (__ballot(plain) != 0ull) {
+    for (int e = 2; e < 16; e += 2) amin = fminf(amin, fminf(fabsf(y[e]), fabsf(y[e + 1])));
+    const bool usual = rb - 0x21800000u <= 0x5D800000u - 0x21800000u && __ballot(!(amin >= 0x1p-100f)) == 0ull;
+    if (__builtin_expect(usual, true)) {
+        // 1/r by the steps of the IEEE division; its scaling and its special cases do not arise
+        const float e0 = __builtin_amdgcn_rcpf(r), e1 = __builtin_fmaf(__builtin_fmaf(-r, e0, 1.0f), e0, e0);
+        const float e2 = __builtin_fmaf(__builtin_fmaf(-r, e1, 1.0f), e1, e1);
+        const float q = __builtin_fmaf(__builtin_fmaf(-r, e2, 1.0f), e1, e2);
 #pragma unroll
-            for (int e = 0; e < 16; ++e) y[e] = y[e] / r;                       // IEEE division
-        } else {
-            const float q = 1.0f / r;                                           // IEEE division, once
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const float q0 = y[e] * q;
-                const float rem = __builtin_fmaf(-q0, r, y[e]);
-                y[e] = __builtin_fmaf(rem, q, q0);
-            }
+        for (int e = 0; e < 16; ++e) {
+            const float q0 = y[e] * q;
+            const float rem = __builtin_fmaf(-q0, r, y[e]);
+            y[e] = __builtin_fmaf(rem, q, q0);
         }
+    } else if (r > 0.0f) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) y[e] = y[e] / r;                           // IEEE division
     } else {
 #pragma unroll
         for (int e = 0; e < 16; ++e) y[e] = 0.0f;
@@ -470,21 +474,23 @@ __device__ __forceinline__ void store_packed_fields(uint8_t *__restrict__ packed
     }
 }
 
-// The same with the bit count known to the compiler: the fields are shifted into dwords and stored as one or two unaligned
-// dword groups and the one to three bytes that remain.
+// The same with the bit count known to the compiler: the fields are put together two by two, these shifted into dwords, and the
+// dwords stored as one or two unaligned groups and the one to three bytes that remain.
 template <int BITS, int UP> __device__ __forceinline__ void store_fields_n(uint8_t *dst, const unsigned (&idx)[8]) {
     typedef uint32_t u32_a1_t __attribute__((aligned(1)));
     typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
     typedef u32x2_t u32x2_a1_t __attribute__((aligned(1)));
     typedef uint16_t u16_a1_t __attribute__((aligned(1)));
+    static_assert(2 * BITS + UP <= 32, "two fields in a dword");
     uint32_t w[(8 * BITS + 31) / 32 + 1];
 #pragma unroll
     for (int q = 0; q < (8 * BITS + 31) / 32 + 1; ++q) w[q] = 0u;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const int bit = k * BITS, word = bit >> 5, off = bit & 31;
-        w[word] |= off >= UP ? idx[k] << (off - UP) : idx[k] >> (UP - off);
-        if (off + BITS > 32) w[word + 1] |= idx[k] >> (32 - off + UP);
+    for (int k = 0; k < 4; ++k) {
+        const uint32_t two = idx[2 * k] | (idx[2 * k + 1] << BITS);
+        const int bit = 2 * k * BITS, word = bit >> 5, off = bit & 31;
+        w[word] |= off >= UP ? two << (off - UP) : two >> (UP - off);
+        if (off + 2 * BITS > 32) w[word + 1] |= two >> (32 - off + UP);
     }
     int at = 0;
     if (BITS >= 8) {

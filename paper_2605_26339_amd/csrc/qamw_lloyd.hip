@@ -276,7 +276,7 @@ __global__ __launch_bounds__(LC_THREADS) void k_cells_lloyd_assign(const float2 
     }
     if (threadIdx.x == 0) err_sum = 0;
     if (stopped_at != LC_RUNNING) return;
-    const float inv_h = cells_inv_width<G>(half);
+    const float inv_span = cells_inv_span(half), far = cells_far(half);
     __syncthreads();
 
     double err = 0.0;
@@ -287,15 +287,19 @@ __global__ __launch_bounds__(LC_THREADS) void k_cells_lloyd_assign(const float2 
         for (int u = 0; u < U; ++u) {
             x[u] = next[u];
             rec[u] = *reinterpret_cast<const uint2 *>(reinterpret_cast<const char *>(a.table) +
-                                                      (cells_record_at<G>(x[u].x, x[u].y, inv_h, 0u) & (G * G * 8u - 1u)));   // in range whatever x is
+                                                      (cells_record_at<G>(x[u].x, x[u].y, inv_span, 0u) & (G * G * 8u - 1u)));   // in range whatever x is
         }
         request(i + U * stride);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const bool active = i + u * stride < n;
-            float d;
-            int bi = (int)(cells_nearest<(G > 64)>(rec[u], x[u].x, x[u].y, 0u, d) >> 3);
-            unsigned long long mask = __ballot(active && cells_scan(rec[u]));
+            CellsFour four;
+            cells_request(four, rec[u], 0u);
+            double best = cells_nearest(four, x[u].x, x[u].y);
+            if (__ballot(rec[u].y & CELLS_FIFTH)) best = cells_fifth(rec[u], x[u].x, x[u].y, 0u, best);
+            int bi = (int)(cells_offset(best) >> 3);
+            float d = cells_distance(best);
+            unsigned long long mask = __ballot(active && cells_undecided(rec[u], x[u].x, x[u].y, far));
             // outside the table, or too many candidates: the whole codebook, for many samples at once or one after the other
             if (__popcll(mask) > LC_DENSE_ABOVE) {
                 const float x0[1] = {x[u].x}, x1[1] = {x[u].y};

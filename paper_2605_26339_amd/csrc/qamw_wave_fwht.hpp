@@ -93,8 +93,8 @@ template <bool HALVES> __device__ __forceinline__ void fwht_swap_stage(float (&x
 template <int B> struct LaneSigns {
     float s16, s32, s64, s128;     // -1 where the lane sits on the "minus" side of that stage
     float parity;                   // product of the above for the stages B uses
-    __device__ __forceinline__ explicit LaneSigns(int lane) {
-        int pos = slab_pos(lane);
+    __device__ __forceinline__ explicit LaneSigns(int lane) : LaneSigns(lane, slab_pos(lane)) {}
+    __device__ __forceinline__ LaneSigns(int, int pos) {       // pos: slab_pos(lane)
         s16 = (pos & 1) ? -1.f : 1.f;
         s32 = (pos & 2) ? -1.f : 1.f;
         s64 = (pos & 4) ? -1.f : 1.f;
