@@ -54,6 +54,9 @@ template <typename T> __device__ __forceinline__ T lds_read(uint32_t at) {
 template <typename T> __device__ __forceinline__ void lds_write(uint32_t at, T v) {
     *reinterpret_cast<__attribute__((address_space(3))) T *>(at) = v;
 }
+__device__ __forceinline__ uint32_t lds_add(uint32_t at, uint32_t v) {   // returns what was there
+    return __hip_atomic_fetch_add(reinterpret_cast<__attribute__((address_space(3))) uint32_t *>(at), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
 typedef float lds_f32x2_t __attribute__((ext_vector_type(2)));
 typedef uint32_t lds_u32x2_t __attribute__((ext_vector_type(2)));
 typedef uint32_t lds_u32x4_t __attribute__((ext_vector_type(4)));

@@ -18,7 +18,7 @@
 // once and walks the rows; a wave keeps to one 1024-column slab of a matrix, so the slab's scales, signs and pair gains are
 // loaded, divided and combined once per wave instead of once per row; records of all eight pairs requested at once, and a pair's
 // candidates before the pair ahead of it is decided.  13824 x 5120 at 11 bits, the whole call: 134 us with five candidates in cells
-// of one width, a comparison and two selections each, so 107 (a 7B layer with its pair scales 411, so 333).
+// of one width, a comparison and two selections each, so 97 (a 7B layer 381, so 305; of both 1.1 by the order of the waves, see below).
 #include <atomic>
 #include <cmath>
 
@@ -101,7 +101,8 @@ constexpr int cells_threads(int G) { return G == 128 ? 1024 : 512; }
 constexpr int cells_codewords(int G) { return G == 128 ? 2048 : G == 96 ? 1024 : 512; }
 constexpr int cells_least_k(int G) { return G == 128 ? 2048 : G == 96 ? 1024 : 2; }
 constexpr int cells_bits(int G) { return G == 128 ? 11 : G == 96 ? 10 : 0; }   // 0: 1 to 9
-constexpr size_t cells_lds_bytes(int G) { return (size_t)cells_codewords(G) * 8 + (size_t)G * G * 8; }
+constexpr uint32_t cells_count_at(int G) { return (uint32_t)(cells_codewords(G) * 8 + G * G * 8); }   // after codebook and table
+constexpr size_t cells_lds_bytes(int G) { return cells_count_at(G) + 16; }
 
 // 1/sqrt(B) is a power of two: its product with the gain is exact, and so one multiplication gives the bits of two (what that
 // could lose below the smallest normal number is nothing to a distance from a codeword).
@@ -231,6 +232,7 @@ void k_encode_cells(CellsBatch bt) {
 #pragma unroll
         for (int i = 0; i < RECS; ++i) lds_write(TABLE_AT + 16 * (threadIdx.x + i * THREADS), r[i]);
     }
+    if (STAGED && threadIdx.x == 0) lds_write<uint32_t>(cells_count_at(G), 0u);
     __syncthreads();
 
     const float inv_span = cells_inv_span(half), far = cells_far(half);
@@ -260,6 +262,10 @@ void k_encode_cells(CellsBatch bt) {
             const RawRow<DTYPE> raw = next;
             const float norm = norm_next;
             request();
+            // Four waves share a SIMD, and the oldest goes first: the others finished up to half as late again, alone on their SIMD
+            // by then.  So a wave that is behind the workgroup's average goes before one that is not.
+            unsigned done = 0;                                  // by the workgroup
+            if (STAGED && lane == 0) done = lds_add(cells_count_at(G), 1u);
             if (skip > 0 && n < CELLS_PUT_OFF) {
                 --skip;
                 put(n);
@@ -340,6 +346,10 @@ void k_encode_cells(CellsBatch bt) {
                 }
             }
             streak = 0;
+            if (STAGED) {
+                if (__builtin_amdgcn_readfirstlane(done) < (unsigned)(n * WAVES)) __builtin_amdgcn_s_setprio(0);
+                else __builtin_amdgcn_s_setprio(2);
+            }
 
             if (active) store_fields<3>(out, row_bytes, d_in, c, idx8, bits);
         }
