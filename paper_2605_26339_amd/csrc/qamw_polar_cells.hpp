@@ -7,8 +7,8 @@ namespace qamw {
 // Lookup tables in place of the two binary searches, for workgroups that encode at least PF_LUT_ITEMS (row, slab) items (making
 // them takes a workgroup 1 us).  Amplitude: by exponent and five mantissa bits of |x|^2, 16 octaves from 2^-10 on.  Phase: by
 // x0 / (|x0| + |x1|), which falls with the angle in [0, pi), in 256 cells; its slope is at least half of the angle's, so with up
-// to 256 bins no cell holds two boundaries.  An entry says where the cell begins; the one boundary that may lie in it is tested
-// as the searches test it.
+// to 256 bins no cell holds two boundaries.  An entry holds the code at the cell's beginning and the one boundary that may lie in it,
+// which is tested as the searches test it.
 constexpr int PF_LUT_ITEMS = 16;
 constexpr int PF_AMP_CELLS = 512, PF_PHASE_CELLS = 256, PF_LUT_MIN_BINS = 8, PF_LUT_MAX_BINS = 256;
 constexpr float PF_LUT_MAX_A2 = 1e30f;  // beyond, 1 / (|x0| + |x1|) is on its way to the subnormals: the searches
