@@ -19,6 +19,10 @@
 // loaded, divided and combined once per wave instead of once per row; records of all eight pairs requested at once, and a pair's
 // candidates before the pair ahead of it is decided.  13824 x 5120 at 11 bits, the whole call: 134 us with five candidates in cells
 // of one width, a comparison and two selections each, so 97 (a 7B layer 381, so 305; of both 1.1 by the order of the waves, see below).
+//   Row norms.  Of large matrices whose rows have 1, 2, 4, 8 or 16 slabs they are computed here (OWN): a row's waves are neighbours in
+// a workgroup, and each sums the slab of its next row, which is in its registers anyway, while the present one is searched, so that
+// the matrix is read from memory once.  The launch ahead of this then makes the table and the other norms: a 7B layer's 82 -> 22 us by
+// the trace, this one 187 -> 220 (7 of them the sums, 12 the waits for a row's other waves).
 #include <atomic>
 #include <cmath>
 
@@ -32,6 +36,12 @@ namespace qamw {
 // second L2 round trip takes: 1024 x 2048 at 10 bits 20.3 / 19.6, at 7 bits 18.7 / 25.1.
 constexpr int CELLS_DIRECT_MAX_ITEMS = 3072;
 constexpr int CELLS_ROWS_TOGETHER = 8192;                      // rows of a launch from which a wave sums four
+// Bytes of the matrices whose rows a workgroup's waves can share, from which the encoder computes those rows' norms itself: they cost
+// its waves more instructions than what a second reading from memory does beside the making of the table.  In us a call with the pair
+// scales, norms in the first launch / in the encoder: 4096 x 4096 bf16 (34 MB) 50 / 53, 16384 x 1024 42 / 46, 40000 x 512 57 / 63;
+// 11008 x 4096 (90 MB) 78 / 77, 22016 x 2048 75 / 71, 8192 x 8192 113 / 108, a 7B layer (405 MB, of which 90 in rows of 11 slabs) 310
+// / 280; fp32 8192 x 4096 (134 MB) 88 / 72, 14336 x 4096 133 / 111.
+constexpr int64_t CELLS_OWN_MIN_BYTES = 64 << 20;
 constexpr int CELLS_MIN_ITEMS = 4096;                          // (row, slab) items of a launch from which small codebooks use the table,
 constexpr int CELLS_GRID_MIN_ITEMS = 1024;                     // and from which the pruned search does
 
@@ -45,6 +55,7 @@ struct CellsMat {
     uint8_t *packed;
     int64_t row_bytes;
     int d_in, d_out, n_slabs, slab_sums;
+    int own_norms, log_slabs;                    // the encoder computes the norms: 2^log_slabs waves of a workgroup share a row
     float g_default;
 };
 struct CellsBatch {
@@ -60,7 +71,7 @@ struct CellsBatch {
 };
 
 // ------------------------------------------------------------------------------------------------ table and norms
-// Workgroups 0 .. (G/8)^2 - 1 make the table; the rest compute the row norms.
+// Workgroups 0 .. (G/8)^2 - 1 make the table; the rest compute the row norms that the encoder does not.
 // R rows per wave: large launches take four, which fetches the channel scales (twice the bytes of bf16 weights) a quarter as
 // often.  A 7B layer, 405 MB: 87 us with one row per wave, 77 so (84 with the sums slab by slab;
 // by the trace 86 us, 79 since a square is added in one operation and four rows share the last steps of their butterflies).
@@ -102,7 +113,13 @@ constexpr int cells_codewords(int G) { return G == 128 ? 2048 : G == 96 ? 1024 :
 constexpr int cells_least_k(int G) { return G == 128 ? 2048 : G == 96 ? 1024 : 2; }
 constexpr int cells_bits(int G) { return G == 128 ? 11 : G == 96 ? 10 : 0; }   // 0: 1 to 9
 constexpr uint32_t cells_count_at(int G) { return (uint32_t)(cells_codewords(G) * 8 + G * G * 8); }   // after codebook and table
-constexpr size_t cells_lds_bytes(int G) { return cells_count_at(G) + 16; }
+// Norms that the encoder computes: the slab sums of the waves' next rows, then per group of waves that share rows (groups of 16 / n
+// from number n on) how many are there, then the norm and of which row it is.
+constexpr int CELLS_GROUPS = 32;
+constexpr uint32_t cells_part_at(int G) { return cells_count_at(G) + 16; }
+constexpr uint32_t cells_arrived_at(int G) { return cells_part_at(G) + 16 * 8; }
+constexpr uint32_t cells_norm_at(int G) { return cells_arrived_at(G) + CELLS_GROUPS * 4; }
+constexpr size_t cells_lds_bytes(int G) { return cells_norm_at(G) + CELLS_GROUPS * 8; }
 
 // 1/sqrt(B) is a power of two: its product with the gain is exact, and so one multiplication gives the bits of two (what that
 // could lose below the smallest normal number is nothing to a distance from a codeword).
@@ -141,6 +158,10 @@ struct CellsShare {
 __device__ __forceinline__ bool cells_share(CellsShare &out, const CellsMat &M, int gw, int n_waves, int &turn) {
     const int n_slabs = M.n_slabs, n_items = M.d_out * n_slabs;
     const int rows_step = n_waves / n_slabs, step = rows_step * n_slabs;
+    if (M.own_norms) {                                         // a row's waves in one workgroup
+        turn = (turn + n_slabs - 1) & -n_slabs;                // a power of two
+        if (turn >= n_waves) turn -= n_waves;
+    }
     int local = gw - turn;
     if (local < 0) local += n_waves;
     turn += n_items % step;
@@ -159,10 +180,11 @@ constexpr int CELLS_PUT_OFF = 256;                             // items of a wav
 #define QAMW_CELLS_WAVES_PER_EU ((STAGED && (G == 128 || DTYPE == 1)) ? 4 : 2)
 // STAGED: the table in LDS beside the codebook.  Otherwise its records are read from memory (L2): in a launch of few items a
 // workgroup would stage 128 KB for an item or two per wave, and small workgroups reach more CUs.
-template <int DTYPE, int B, int G, bool STAGED>
+template <int DTYPE, int B, int G, bool STAGED, bool OWN>
 __global__ __launch_bounds__(STAGED ? cells_threads(G) : CELLS_DIRECT_THREADS) __attribute__((amdgpu_waves_per_eu(QAMW_CELLS_WAVES_PER_EU)))
 void k_encode_cells(CellsBatch bt) {
     static_assert(STAGED || (G & (G - 1)) == 0, "the mask of the record's offset");
+    static_assert(STAGED || !OWN, "the sums' place in LDS is after the table's");
     constexpr int THREADS = STAGED ? cells_threads(G) : CELLS_DIRECT_THREADS, WAVES = THREADS / WAVE;
     constexpr int CODEWORDS = cells_codewords(G);
     constexpr uint32_t TABLE_AT = CODEWORDS * 8;               // LDS: the codebook at 0, then the table
@@ -181,7 +203,7 @@ void k_encode_cells(CellsBatch bt) {
     int mi = -1, turn = 0;                                      // the matrix that the next row is of
     CellsShare share;
     const char *w_next = nullptr;                               // the wave's next row
-    const float *norm_at = nullptr;
+    float *norm_at = nullptr;
     int64_t w_step = 0;
     int left = 0;                                               // rows of it that the wave has yet to ask for
     auto next_matrix = [&]() __attribute__((always_inline)) {
@@ -198,18 +220,26 @@ void k_encode_cells(CellsBatch bt) {
     };
     RawRow<DTYPE> next;
     float norm_next = 0.0f;
+    uint32_t tag_next = 0;                                      // not 0: the next row's norm is this launch's, the row's mark
+    float *norm_out = nullptr;
     auto first_column = [&](int slab, int d_in) __attribute__((always_inline)) {
         const int col0 = slab * 1024 + 16 * pos;
         return col0 < d_in ? col0 : 0;
     };
     auto request = [&]() __attribute__((always_inline)) {       // the next row
         if (left == 0) next_matrix();
+        tag_next = 0;
         if (mi >= bt.n) return;
         load_raw_row<DTYPE>(next, w_next, 0, first_column(share.slab, bt.m[mi].d_in));
-        norm_next = *norm_at;
         w_next += w_step;
-        norm_at += share.rows_step;
         --left;
+        if (OWN && bt.m[mi].own_norms) {
+            tag_next = (uint32_t)(mi + 1) << 24 | (uint32_t)left;   // fewer than 2^24: see the launch
+            norm_out = norm_at;
+        } else {
+            norm_next = *norm_at;
+        }
+        norm_at += share.rows_step;
     };
     request();
 
@@ -233,7 +263,59 @@ void k_encode_cells(CellsBatch bt) {
         for (int i = 0; i < RECS; ++i) lds_write(TABLE_AT + 16 * (threadIdx.x + i * THREADS), r[i]);
     }
     if (STAGED && threadIdx.x == 0) lds_write<uint32_t>(cells_count_at(G), 0u);
+    if (OWN && threadIdx.x < 3 * CELLS_GROUPS) lds_write<uint32_t>(cells_arrived_at(G) + 4 * threadIdx.x, 0u);
     __syncthreads();
+
+    float sc[16], g[8];
+    // The sum of squares of the wave's slab of its next row, and the row's norm if the row's other waves have left theirs.  In the order
+    // of the kernels without scratch (a sign is nothing to a square, and wave_sum() meets the same pairs in slab_pos()'s order).
+    //   A wave's place for its sum, and its group's for the norm, are free by then: the wave has had the norm of the row that it works
+    // on, so that row's sums are read, and a norm follows only when all waves of the group have come as far.
+    auto sum_next = [&](int now) __attribute__((always_inline)) {
+        const CellsMat &M = bt.m[mi];
+        const int col0 = share.slab * 1024 + 16 * pos;
+        if (mi != now) {                                        // the row is another matrix's: this one's scales are done with
+            Problem p;
+            p.chan_scale = M.chan_scale;
+            p.signs = nullptr;
+            load_signed_scales(sc, p, col0 < M.d_in ? col0 : 0);
+        }
+        float w[16];
+        widen_raw_row<DTYPE>(w, next);
+        double s2 = 0.0;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) s2 = add_square(s2, w[e] * sc[e]);
+        s2 = wave_sum(col0 < M.d_in ? s2 : 0.0);
+        const int log = M.log_slabs, first = wid >> log << log, id = (16 + wid) >> log;
+        uint32_t before = 0;
+        if (lane == 0) {
+            lds_write<double>(cells_part_at(G) + 8 * wid, s2);
+            asm volatile("" ::: "memory");                      // before the arrival (LDS takes a wave's accesses in order)
+            before = lds_add(cells_arrived_at(G) + 4 * id, 1u);
+        }
+        if ((int)__builtin_amdgcn_readfirstlane(before) != (1 << log) - 1) return;
+        asm volatile("" ::: "memory");
+        double sum = 0.0;                                       // in slab order
+        for (int i = 0; i < 1 << log; ++i) sum += lds_read<double>(cells_part_at(G) + 8 * (first + i));
+        const float norm = (float)sqrt(sum);
+        if (lane == 0) {
+            lds_write<uint32_t>(cells_arrived_at(G) + 4 * id, 0u);
+            asm volatile("" ::: "memory");                      // before the norm, after which the next arrivals come
+            lds_write<lds_u32x2_t>(cells_norm_at(G) + 8 * id, lds_u32x2_t{__float_as_uint(norm), tag_next});
+            *norm_out = norm;
+        }
+    };
+    // The norm of the row marked `tag`.  The wait ends: the row's other waves, all of this workgroup, leave their sums with the row
+    // before it, for which they wait only for sums left with the row before that, and so on to the first, which they wait for none with.
+    auto wait_for_norm = [&](int log, uint32_t tag) __attribute__((always_inline)) {
+        const auto *at = reinterpret_cast<const volatile __attribute__((address_space(3))) uint64_t *>(cells_norm_at(G) + 8 * ((16 + wid) >> log));
+        for (;;) {
+            const uint64_t v = *at;
+            if ((uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32)) == tag) return __uint_as_float((uint32_t)v);
+            __builtin_amdgcn_s_sleep(1);
+        }
+    };
+    if (OWN && tag_next) sum_next(-1);
 
     const float inv_span = cells_inv_span(half), far = cells_far(half);
     unsigned long long put_off[CELLS_PUT_OFF / 64] = {};        // items that the table does not help
@@ -255,29 +337,35 @@ void k_encode_cells(CellsBatch bt) {
         const int d_in = M.d_in;
         uint8_t *out = M.packed + share.row * row_bytes;
         const int64_t out_step = share.rows_step * row_bytes;
-        float sc[16], g[8];
+        const int now = mi;
         cells_constants<B>(sc, g, M, c, unit);
 
         for (int rows = left + 1; rows > 0; --rows, ++n, out += out_step) {
             const RawRow<DTYPE> raw = next;
-            const float norm = norm_next;
+            float norm = norm_next;
+            const uint32_t tag = tag_next;
             request();
+            if (OWN && tag) norm = wait_for_norm(M.log_slabs, tag);
             // Four waves share a SIMD, and the oldest goes first: the others finished up to half as late again, alone on their SIMD
             // by then.  So a wave that is behind the workgroup's average goes before one that is not.
             unsigned done = 0;                                  // by the workgroup
             if (STAGED && lane == 0) done = lds_add(cells_count_at(G), 1u);
-            if (skip > 0 && n < CELLS_PUT_OFF) {
+            const bool try_table = skip == 0 || n >= CELLS_PUT_OFF;
+            float x[16];
+            if (try_table) {
+                if constexpr (STAGED && G == 128 && DTYPE == 0) {   // no registers for the lane's signs: made again
+                    int p = pos;
+                    asm volatile("" : "+v"(p));
+                    cells_pairs<DTYPE, B>(x, raw, norm, sc, g, LaneSigns<B>(lane, p), unit);
+                } else {
+                    cells_pairs<DTYPE, B>(x, raw, norm, sc, g, ls, unit);
+                }
+            }
+            if (OWN && tag_next) sum_next(now);              // by now the next row has come
+            if (!try_table) {
                 --skip;
                 put(n);
                 continue;
-            }
-            float x[16];
-            if constexpr (STAGED && G == 128 && DTYPE == 0) {   // no registers for the lane's signs: made again
-                int p = pos;
-                asm volatile("" : "+v"(p));
-                cells_pairs<DTYPE, B>(x, raw, norm, sc, g, LaneSigns<B>(lane, p), unit);
-            } else {
-                cells_pairs<DTYPE, B>(x, raw, norm, sc, g, ls, unit);
             }
 
             // ---------------- the cells' records
@@ -351,9 +439,12 @@ void k_encode_cells(CellsBatch bt) {
                 else __builtin_amdgcn_s_setprio(2);
             }
 
-            if (active) store_fields<3>(out, row_bytes, d_in, c, idx8, bits);
+            int at = c;                                         // (the lane's place in a row is not worth registers during the search)
+            asm volatile("" : "+v"(at));
+            if (active) store_fields<3>(out, row_bytes, d_in, at, idx8, bits);
         }
     }
+    if (OWN) __syncthreads();                                   // the norms are in memory
     if (!any_put_off) return;
 
     // ---------------- the items put off: all their pairs against the whole codebook.  All that follows from the lane is made
@@ -465,11 +556,11 @@ void k_encode_cells(CellsBatch bt) {
 
 // More than the default 64 KB of LDS per workgroup has to be asked for: a host-side setting per kernel and device, made
 // once per kernel instantiation and device (the devices' bits of `done`).
-template <int DTYPE, int B, int G> static bool cells_allow_large_lds(int dev) {
+template <int DTYPE, int B, int G, bool OWN> static bool cells_allow_large_lds(int dev) {
     static std::atomic<uint64_t> done{0};
     if (dev < 0 || dev >= 64) return false;
     if (done.load(std::memory_order_acquire) & (1ull << dev)) return true;
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_encode_cells<DTYPE, B, G, true>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_encode_cells<DTYPE, B, G, true, OWN>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)cells_lds_bytes(G));
     if (e != hipSuccess) {
         (void)hipGetLastError();
@@ -490,13 +581,22 @@ static hipError_t launch_cells_dbg(CellsBatch &bt, hipStream_t stream) {
     constexpr int WAVES = cells_threads(G) / WAVE;
     int64_t items = 0, rows = 0;
     int norm_blocks = 0, most_slabs = 1;
-    for (int i = 0; i < bt.n; ++i) rows += bt.m[i].d_out;
+    int64_t own_bytes = 0;
+    for (int i = 0; i < bt.n; ++i) {
+        CellsMat &M = bt.m[i];
+        rows += M.d_out;
+        items += (int64_t)M.d_out * M.n_slabs;
+        M.log_slabs = __builtin_ctz((unsigned)M.n_slabs);
+        M.own_norms = M.slab_sums && WAVES % M.n_slabs == 0;
+        if (M.own_norms) own_bytes += (int64_t)M.d_out * M.d_in * (DTYPE == 0 ? 4 : 2);
+    }
+    const bool direct_launch = G == 128 && items <= CELLS_DIRECT_MAX_ITEMS, own = !direct_launch && own_bytes >= CELLS_OWN_MIN_BYTES;
+    for (int i = 0; i < bt.n && !own; ++i) bt.m[i].own_norms = 0;
     const int per_wave = rows >= CELLS_ROWS_TOGETHER ? 4 : 1;
     for (int i = 0; i < bt.n; ++i) {
         const CellsMat &M = bt.m[i];
-        items += (int64_t)M.d_out * M.n_slabs;
         bt.norm_begin[i] = norm_blocks;
-        norm_blocks += (M.d_out + CP_WAVES * per_wave - 1) / (CP_WAVES * per_wave);
+        if (!M.own_norms) norm_blocks += (M.d_out + CP_WAVES * per_wave - 1) / (CP_WAVES * per_wave);
         if (M.n_slabs > most_slabs) most_slabs = M.n_slabs;
     }
     for (int i = bt.n; i <= QAMW_ENCODE_MAX_BATCH; ++i) bt.norm_begin[i] = norm_blocks;
@@ -507,24 +607,26 @@ static hipError_t launch_cells_dbg(CellsBatch &bt, hipStream_t stream) {
         return hipGetLastError();
     };
     if constexpr (G == 128) {
-        if (items <= CELLS_DIRECT_MAX_ITEMS) {
+        if (direct_launch) {
             constexpr int DIRECT_WAVES = CELLS_DIRECT_THREADS / WAVE;
             const unsigned direct = (unsigned)((items + most_slabs + DIRECT_WAVES - 1) / DIRECT_WAVES);   // an item per wave, whole rows
             const hipError_t e = prepare();
             if (e != hipSuccess) return e;
-            hipLaunchKernelGGL((k_encode_cells<DTYPE, B, G, false>), dim3(direct), dim3(CELLS_DIRECT_THREADS),
+            hipLaunchKernelGGL((k_encode_cells<DTYPE, B, G, false, false>), dim3(direct), dim3(CELLS_DIRECT_THREADS),
                                (size_t)cells_codewords(G) * sizeof(float2), stream, bt);
             return hipGetLastError();
         }
     }
-    if (cells_lds_bytes(G) > 64 * 1024 && !cells_allow_large_lds<DTYPE, B, G>(dev)) return hipErrorNotSupported;
+    if (cells_lds_bytes(G) > 64 * 1024 && !(own ? cells_allow_large_lds<DTYPE, B, G, true>(dev) : cells_allow_large_lds<DTYPE, B, G, false>(dev)))
+        return hipErrorNotSupported;
     const int per_cu = G == 128 ? 1 : 2;          // workgroups that fit a CU's LDS and registers
     int64_t blocks = (items + WAVES - 1) / WAVES;
     if (blocks > (int64_t)cus * per_cu) blocks = (int64_t)cus * per_cu;
     if (blocks * WAVES < most_slabs) return hipErrorNotSupported;   // every wave keeps to one slab: at least a row's worth of waves
     const hipError_t e = prepare();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_encode_cells<DTYPE, B, G, true>), dim3((unsigned)blocks), dim3(cells_threads(G)), cells_lds_bytes(G), stream, bt);
+    if (own) hipLaunchKernelGGL((k_encode_cells<DTYPE, B, G, true, true>), dim3((unsigned)blocks), dim3(cells_threads(G)), cells_lds_bytes(G), stream, bt);
+    else hipLaunchKernelGGL((k_encode_cells<DTYPE, B, G, true, false>), dim3((unsigned)blocks), dim3(cells_threads(G)), cells_lds_bytes(G), stream, bt);
     return hipGetLastError();
 }
 
