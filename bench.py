@@ -43,8 +43,9 @@ PEAK_FP32_TFLOPS = 157.3          # MI355X vector fp32 (published)
 PEAK_HBM_GBS = 8000.0             # MI355X HBM3E (published)
 PEAK_BF16_TFLOPS = 2500.0         # MI355X dense bf16 matrix cores (published)
 FLOPS_PER_EVAL = 4.0              # one distance evaluation = 2 FMA
-ENCODE_LIMIT = ("vector-ALU issue in the search (about 720 vector instructions and 51 LDS instructions per 512 pairs: butterflies, "
-                "correctly rounded division, up to five exact fp32 distances per pair), then the second read of W after the row norms")
+ENCODE_LIMIT = ("vector-ALU issue in the search (about 610 vector instructions and 42 LDS instructions per 512 pairs: butterflies, "
+                "correctly rounded division, four exact fp32 distances per pair; some 100 more for the row norms of large matrices with 1, 2, 4, 8 or "
+                "16 slabs of 1024 columns), then a second read of the other matrices for their norms")
 
 
 def build_workload(wl, layers, device):
@@ -247,7 +248,7 @@ def measure_workload(wl, layers, steps, warmup, decode_passes, dev, cb, valu_pat
         # What the call cannot do without is to read W and write the packed rows: priced against HBM.  The distances that the
         # cell table makes unnecessary are not work done; their count over the time is given for comparison with an encoder
         # that evaluates all K of them, and is not a fraction of any peak.
-        "roofline": {"kernel": "qamw_encode_batch_ws (two launches per layer of %d matrices: cell table + row norms, then the search)" % per_layer,
+        "roofline": {"kernel": "qamw_encode_batch_ws (two launches per layer of %d matrices: cell table and row norms that the search does not make, then the search)" % per_layer,
                      "bound": "hbm", "limited_by": ENCODE_LIMIT,
                      "achieved": enc_in_bytes / (enc_ms * 1e-3) / 1e9, "peak": PEAK_HBM_GBS, "unit": "GB/s",
                      "frac": enc_in_bytes / (enc_ms * 1e-3) / 1e9 / PEAK_HBM_GBS,
