@@ -433,6 +433,25 @@ __device__ __forceinline__ void load_pair_gains(float (&g)[8], const Problem &p,
     }
 }
 
+// 1/sqrt(B) is a power of two: its product with a gain is exact, and one multiplication by that gives the bits of the definition's
+// two, y = t / sqrt(B) and x = y g, unless y is below the smallest normal number, where it is rounded.
+constexpr bool unit_exact(int B) { return B == 64 || B == 256 || B == 1024; }
+// Up to this gain that is nothing to a pair: such a y times the gain is below 2^-102, so that its square is 0, and so are those of its
+// differences from codewords that it could still change (below 2^-76).  Usual gains are sqrt(d_in) and some powers of two around.
+constexpr float UNIT_EXACT_MAX_GAIN = 0x1p24f;
+// A lane's gains times its sign (the butterflies' parity) and 1/sqrt(B); or, where a lane of the wave has a larger gain, times the
+// sign alone and true: the wave multiplies by 1/sqrt(B) first.
+__device__ __forceinline__ bool combine_gains(float (&g)[8], float parity, float inv_sqrt_block) {
+    float most = g[0];
+#pragma unroll
+    for (int k = 1; k < 8; ++k) most = fmaxf(most, g[k]);
+    const bool two = __ballot(!(most <= UNIT_EXACT_MAX_GAIN)) != 0ull;
+    const float unit = two ? parity : parity * inv_sqrt_block;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) g[k] = unit * g[k];
+    return two;
+}
+
 // The lane's 16 channel scales with the sign mask in the sign bit: what a kernel that stays on one slab of a matrix keeps
 // instead of both.  Scaling by it is exact as regards the sign: rounding commutes with negation, and a quotient, a sum of
 // squares or a smallest magnitude does not see it.

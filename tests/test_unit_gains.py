@@ -1,0 +1,43 @@
+"""Pairs whose y = t / sqrt(block) is below the smallest normal number and is rounded there before the gain multiplies it: where
+1 / sqrt(block) is a power of two, one multiplication by its product with the gain would leave that rounding out.  Weights so small
+beside their row's norm, and pair scales that make up for it."""
+import pytest
+import torch
+
+from paper_2605_26339_amd import qamw
+
+pytestmark = pytest.mark.gpu
+
+
+def _row(block, d_in, a, b):
+    """A row of norm 1 whose second block's pairs rotate to (a + b, a - b) and (-(a + b), b - a)."""
+    W = torch.zeros((1, d_in), dtype=torch.float64)
+    W[0, 0] = 1.0
+    W[0, block + 2], W[0, block + 3] = a, b
+    return W.float().cuda()
+
+
+def _fields(packed, bits, n):
+    stream = (packed[..., None] >> torch.arange(8, device="cuda", dtype=torch.uint8)) & 1
+    return (stream.reshape(packed.shape[0], -1)[:, : n * bits].view(packed.shape[0], n, bits).long() << torch.arange(bits, device="cuda")).sum(-1)
+
+
+# workgroups of one row (binary searches) and of twelve (lookup tables)
+@pytest.mark.parametrize("block", [64, 256, 1024])
+@pytest.mark.parametrize("rows", [1, 6000])
+def test_polar_phase_of_a_rounded_pair(block, rows):
+    print(f"[unit gains] polar {block} rows {rows}", flush=True)
+    d_in, bits_a, bits_p = 4096, 3, 6
+    # t = +-(sqrt(block) 2^-130, -2 units in the last place): the y of the latter rounds to 0, the pair lies on the axis
+    W = _row(block, d_in, block ** 0.5 * 2.0 ** -131 - 2.0 ** -149, block ** 0.5 * 2.0 ** -131 + 2.0 ** -149)
+    sigma = torch.full((d_in // 2,), 2.0 ** -126, device="cuda")
+    levels = torch.from_numpy(qamw.polar_codebook(bits_a, bits_p)[0]).cuda()
+    pairs, _ = qamw.normalised_pairs(W, block, pair_sigma=sigma)
+    packed, _ = qamw.encode_polar(W.repeat(rows, 1), levels, bits_a, bits_p, block, pair_sigma=sigma)
+    torch.cuda.synchronize()
+    own = slice(block // 2, block)
+    x = pairs[:, own]
+    assert bool((x[..., 0].abs() == 2.0 ** -4).all()) and bool((x[..., 1] == 0).all())
+    assert bool((x[..., 0] < 0).any()) and bool((x[..., 0] > 0).any())
+    want = torch.where(x[..., 0] > 0, 0, 1 << (bits_p - 1)).expand(rows, -1)
+    assert torch.equal(_fields(packed, bits_a + bits_p, d_in // 2)[:, own] & ((1 << bits_p) - 1), want)
