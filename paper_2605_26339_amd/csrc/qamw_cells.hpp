@@ -396,7 +396,7 @@ __device__ __forceinline__ double cells_fifth(uint2 rec, float x0, float x1, uin
 }
 // Whether the whole codebook decides the pair; far: cells_far().
 __device__ __forceinline__ bool cells_undecided(uint2 rec, float x0, float x1, float far) {
-    return (rec.y & CELLS_SCAN) || ((rec.y & CELLS_BORDER) && !(fmaxf(fabsf(x0), fabsf(x1)) <= far));
+    return (rec.y & CELLS_SCAN) || ((rec.y & CELLS_BORDER) && !(fabsf(x0) <= far && fabsf(x1) <= far));   // nor a NaN beside a number
 }
 
 // ------------------------------------------------------------------------------------------------ without the table

@@ -35,8 +35,27 @@ def test_samples_on_the_edges_of_cells(bits, cells, scale):
     strips = (rng.uniform(-6.0, 6.0, (20000, 2)) * scale).astype(np.float32)
     x = np.concatenate([x, x[:, ::-1], corners, strips]).astype(np.float32)
     samples = torch.from_numpy(np.ascontiguousarray(x)).cuda()
+    _same_points(samples, init, bits)
+
+
+def _same_points(samples, init, bits):
+    """Two iterations with the table and with the least scratch, which computes all distances."""
     got, _, it = qamw.lloyd_device(samples, init, bits, max_iters=2, tol=0.0)
     want, least = init.clone(), torch.empty((1 << bits) * 40 + 64, dtype=torch.uint8, device="cuda")
     assert qamw.lib().qamw_lloyd_device(C.c_void_p(samples.data_ptr()), samples.shape[0], bits, C.c_void_p(want.data_ptr()), 2, 0.0,
                                         C.c_void_p(least.data_ptr()), least.numel(), None, None, None) == qamw.OK
     assert it == 2 and torch.equal(got, want)
+
+
+@pytest.mark.parametrize("bits", [6, 11])
+def test_samples_that_are_no_points(bits):
+    """One coordinate infinite or a NaN, the other anywhere in the table's range or on its edge."""
+    print(f"[cells edges] not finite, B={bits}", flush=True)
+    init = torch.from_numpy(qamw.train_codebook(bits, 1 << 16, max_iters=20)[0]).cuda()
+    good = torch.randn(20000, 2, generator=torch.Generator().manual_seed(bits))
+    good[::7] *= 1.6
+    for bad in (float("nan"), -float("nan"), float("inf"), -float("inf")):
+        for coordinate in (0, 1):
+            samples = good.clone()
+            samples[::5, coordinate] = bad
+            _same_points(samples.cuda(), init, bits)
