@@ -19,12 +19,14 @@
 // loaded, divided and combined once per wave instead of once per row; records of all eight pairs requested at once, and a pair's
 // candidates before the pair ahead of it is decided.  13824 x 5120 at 11 bits, the whole call: 134 us with five candidates in cells
 // of one width, a comparison and two selections each, so 97 (a 7B layer 381, so 305; of both 1.1 by the order of the waves, see below).
-//   Row norms.  Of large matrices whose rows have 1, 2, 4, 8 or 16 slabs they are computed here (OWN): a row's waves are neighbours in
+//   Row norms.  Of large matrices whose rows have 1, 2, 4 or 8 slabs, at 11 bits 16 too, they are computed here (OWN): a row's waves are neighbours in
 // a workgroup, and each sums the slab of its next row, which is in its registers anyway, while the present one is searched, so that
 // the matrix is read from memory once.  The launch ahead of this then makes the table and the other norms: a 7B layer's 82 -> 22 us by
 // the trace, this one 187 -> 220 (7 of them the sums, 12 the waits for a row's other waves).
+#include <algorithm>
 #include <atomic>
 #include <cmath>
+#include <type_traits>
 
 #include "qamw_cells.hpp"
 
@@ -108,18 +110,28 @@ __global__ __launch_bounds__(CP_THREADS) void k_cells_prepare(CellsBatch bt) {
 
 // ------------------------------------------------------------------------------------------------ the encoder
 constexpr int CELLS_DIRECT_THREADS = 256;
-constexpr int cells_threads(int G) { return G == 128 ? 1024 : 512; }
+constexpr int cells_threads(int G, bool own) { return G == 128 || (G == 96 && own) ? 1024 : 512; }
+// Slabs of a row up to which the encoder computes its norm.  (At 10 bits 16 waves could share a row too: 5000 x 16384 bf16 123 us so, 120 without.)
+constexpr int cells_most_shared(int G) { return G == 128 ? 16 : 8; }
 constexpr int cells_codewords(int G) { return G == 128 ? 2048 : G == 96 ? 1024 : 512; }
 constexpr int cells_least_k(int G) { return G == 128 ? 2048 : G == 96 ? 1024 : 2; }
 constexpr int cells_bits(int G) { return G == 128 ? 11 : G == 96 ? 10 : 0; }   // 0: 1 to 9
-constexpr uint32_t cells_count_at(int G) { return (uint32_t)(cells_codewords(G) * 8 + G * G * 8); }   // after codebook and table
-// Norms that the encoder computes: the slab sums of the waves' next rows, then per group of waves that share rows (groups of 16 / n
-// from number n on) how many are there, then the norm and of which row it is.
+// How many rows the workgroup's waves have taken: in the lower word of a corner's record, which has no candidates (whatever is there,
+// the reads that it makes end below 16 KB and are not looked at).
+constexpr uint32_t cells_count_at(int G) { return (uint32_t)(cells_codewords(G) * 8 + (G - 1) * 8); }
+// Norms that the encoder computes: after codebook and table the slab sums of the waves' next rows, then per group of waves that share
+// rows (groups of 16 / n from number n on) how many are there, then the norm and of which row it is.
 constexpr int CELLS_GROUPS = 32;
-constexpr uint32_t cells_part_at(int G) { return cells_count_at(G) + 16; }
+constexpr uint32_t cells_part_at(int G) { return (uint32_t)(cells_codewords(G) * 8 + G * G * 8); }
 constexpr uint32_t cells_arrived_at(int G) { return cells_part_at(G) + 16 * 8; }
 constexpr uint32_t cells_norm_at(int G) { return cells_arrived_at(G) + CELLS_GROUPS * 4; }
-constexpr size_t cells_lds_bytes(int G) { return cells_norm_at(G) + CELLS_GROUPS * 8; }
+constexpr size_t cells_lds_bytes(int G, bool own) { return own ? cells_norm_at(G) + CELLS_GROUPS * 8 : cells_part_at(G); }
+// Workgroups that a CU holds.  Codebook and table of 10 bits are half of its LDS to the byte, so with norms there is one of 16 waves
+// (with one of 8, and the launch's others after it, 11008 x 4096 bf16 took 82 us, 13824 x 5120 without norms 102; so 64 and 87; two
+// of 8 and the norms from the launch ahead 65, but a 7B layer 263 instead of 225, in fp32 402 instead of 290.  Small launches have
+// more workgroups of 8 waves: 512 x 4096 16.2, with those of 16 17.5).
+constexpr int cells_per_cu(int G, bool own) { return cells_threads(G, own) == 1024 ? 1 : 2; }
+template <int G, bool OWN> constexpr bool cells_resident() { return cells_per_cu(G, OWN) * cells_lds_bytes(G, OWN) <= 160 * 1024; }
 
 // 1/sqrt(B) is a power of two: its product with the gain is exact, and so one multiplication gives the bits of two (what that
 // could lose below the smallest normal number is nothing to a distance from a codeword).
@@ -177,15 +189,16 @@ constexpr int CELLS_FEW_LANES = 12;                            // lanes with an 
 constexpr int CELLS_PUT_OFF = 256;                             // items of a wave that can be put off, a bit each (in scalar registers)
 
 // Registers: two workgroups of 8 waves per CU for the smaller tables.  With fp32 weights that would cost spills, and one is left.
-#define QAMW_CELLS_WAVES_PER_EU ((STAGED && (G == 128 || DTYPE == 1)) ? 4 : 2)
+#define QAMW_CELLS_WAVES_PER_EU ((STAGED && (cells_threads(G, OWN) == 1024 || DTYPE == 1)) ? 4 : 2)
 // STAGED: the table in LDS beside the codebook.  Otherwise its records are read from memory (L2): in a launch of few items a
 // workgroup would stage 128 KB for an item or two per wave, and small workgroups reach more CUs.
 template <int DTYPE, int B, int G, bool STAGED, bool OWN>
-__global__ __launch_bounds__(STAGED ? cells_threads(G) : CELLS_DIRECT_THREADS) __attribute__((amdgpu_waves_per_eu(QAMW_CELLS_WAVES_PER_EU)))
+__global__ __launch_bounds__(STAGED ? cells_threads(G, OWN) : CELLS_DIRECT_THREADS) __attribute__((amdgpu_waves_per_eu(QAMW_CELLS_WAVES_PER_EU)))
 void k_encode_cells(CellsBatch bt) {
     static_assert(STAGED || (G & (G - 1)) == 0, "the mask of the record's offset");
     static_assert(STAGED || !OWN, "the sums' place in LDS is after the table's");
-    constexpr int THREADS = STAGED ? cells_threads(G) : CELLS_DIRECT_THREADS, WAVES = THREADS / WAVE;
+    static_assert(!STAGED || cells_resident<G, OWN>(), "the launch's workgroups are resident together");
+    constexpr int THREADS = STAGED ? cells_threads(G, OWN) : CELLS_DIRECT_THREADS, WAVES = THREADS / WAVE;
     constexpr int CODEWORDS = cells_codewords(G);
     constexpr uint32_t TABLE_AT = CODEWORDS * 8;               // LDS: the codebook at 0, then the table
     const int K = cells_bits(G) ? CODEWORDS : bt.K, bits = cells_bits(G) ? cells_bits(G) : bt.bits;
@@ -246,8 +259,8 @@ void k_encode_cells(CellsBatch bt) {
     // the codebook and the table, requested in one go
     const float half = cells_half(bt.table);
     {
-        constexpr int CB = (CODEWORDS + THREADS - 1) / THREADS, RECS = STAGED ? G * G / 2 / THREADS : 0;
-        static_assert(!STAGED || G * G / 2 % THREADS == 0, "whole rounds");
+        constexpr int CB = (CODEWORDS + THREADS - 1) / THREADS, RECS = STAGED ? (G * G / 2 + THREADS - 1) / THREADS : 0;
+        constexpr bool WHOLE = G * G / 2 % THREADS == 0;
         const lds_f32x2_t *cbk = reinterpret_cast<const lds_f32x2_t *>(bt.codebook);
         const lds_u32x4_t *src = reinterpret_cast<const lds_u32x4_t *>(bt.table);
         lds_f32x2_t c[CB];
@@ -255,14 +268,18 @@ void k_encode_cells(CellsBatch bt) {
 #pragma unroll
         for (int i = 0; i < CB; ++i) c[i] = cbk[min((int)threadIdx.x + i * THREADS, K - 1)];
 #pragma unroll
-        for (int i = 0; i < RECS; ++i) r[i] = src[threadIdx.x + i * THREADS];
+        for (int i = 0; i < RECS; ++i) r[i] = src[WHOLE ? (int)threadIdx.x + i * THREADS : min((int)threadIdx.x + i * THREADS, G * G / 2 - 1)];
 #pragma unroll
         for (int i = 0; i < CB; ++i)
             if (cells_bits(G) || (int)threadIdx.x + i * THREADS < K) lds_write(8 * (threadIdx.x + i * THREADS), c[i]);
 #pragma unroll
-        for (int i = 0; i < RECS; ++i) lds_write(TABLE_AT + 16 * (threadIdx.x + i * THREADS), r[i]);
+        for (int i = 0; i < RECS; ++i)
+            if (WHOLE || (int)threadIdx.x + i * THREADS < G * G / 2) lds_write(TABLE_AT + 16 * (threadIdx.x + i * THREADS), r[i]);
     }
-    if (STAGED && threadIdx.x == 0) lds_write<uint32_t>(cells_count_at(G), 0u);
+    if (STAGED && threadIdx.x == (G - 1) / 2) {                 // the thread that has written that record
+        asm volatile("" ::: "memory");
+        lds_write<uint32_t>(cells_count_at(G), 0u);
+    }
     if (OWN && threadIdx.x < 3 * CELLS_GROUPS) lds_write<uint32_t>(cells_arrived_at(G) + 4 * threadIdx.x, 0u);
     __syncthreads();
 
@@ -561,7 +578,7 @@ template <int DTYPE, int B, int G, bool OWN> static bool cells_allow_large_lds(i
     if (dev < 0 || dev >= 64) return false;
     if (done.load(std::memory_order_acquire) & (1ull << dev)) return true;
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_encode_cells<DTYPE, B, G, true, OWN>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)cells_lds_bytes(G));
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)cells_lds_bytes(G, OWN));
     if (e != hipSuccess) {
         (void)hipGetLastError();
         return false;
@@ -578,7 +595,6 @@ static hipError_t launch_cells_dbg(CellsBatch &bt, hipStream_t stream) {
         (void)hipGetLastError();
         return hipErrorNotSupported;
     }
-    constexpr int WAVES = cells_threads(G) / WAVE;
     int64_t items = 0, rows = 0;
     int norm_blocks = 0, most_slabs = 1;
     int64_t own_bytes = 0;
@@ -587,7 +603,7 @@ static hipError_t launch_cells_dbg(CellsBatch &bt, hipStream_t stream) {
         rows += M.d_out;
         items += (int64_t)M.d_out * M.n_slabs;
         M.log_slabs = __builtin_ctz((unsigned)M.n_slabs);
-        M.own_norms = M.slab_sums && WAVES % M.n_slabs == 0;
+        M.own_norms = M.slab_sums && cells_most_shared(G) % M.n_slabs == 0;
         if (M.own_norms) own_bytes += (int64_t)M.d_out * M.d_in * (DTYPE == 0 ? 4 : 2);
     }
     const bool direct_launch = G == 128 && items <= CELLS_DIRECT_MAX_ITEMS, own = !direct_launch && own_bytes >= CELLS_OWN_MIN_BYTES;
@@ -617,17 +633,19 @@ static hipError_t launch_cells_dbg(CellsBatch &bt, hipStream_t stream) {
             return hipGetLastError();
         }
     }
-    if (cells_lds_bytes(G) > 64 * 1024 && !(own ? cells_allow_large_lds<DTYPE, B, G, true>(dev) : cells_allow_large_lds<DTYPE, B, G, false>(dev)))
-        return hipErrorNotSupported;
-    const int per_cu = G == 128 ? 1 : 2;          // workgroups that fit a CU's LDS and registers
-    int64_t blocks = (items + WAVES - 1) / WAVES;
-    if (blocks > (int64_t)cus * per_cu) blocks = (int64_t)cus * per_cu;
-    if (blocks * WAVES < most_slabs) return hipErrorNotSupported;   // every wave keeps to one slab: at least a row's worth of waves
-    const hipError_t e = prepare();
-    if (e != hipSuccess) return e;
-    if (own) hipLaunchKernelGGL((k_encode_cells<DTYPE, B, G, true, true>), dim3((unsigned)blocks), dim3(cells_threads(G)), cells_lds_bytes(G), stream, bt);
-    else hipLaunchKernelGGL((k_encode_cells<DTYPE, B, G, true, false>), dim3((unsigned)blocks), dim3(cells_threads(G)), cells_lds_bytes(G), stream, bt);
-    return hipGetLastError();
+    auto search = [&](auto own_norms) {
+        constexpr bool OWN = decltype(own_norms)::value;
+        constexpr int WAVES = cells_threads(G, OWN) / WAVE;
+        constexpr size_t lds = cells_lds_bytes(G, OWN);
+        if (lds > 64 * 1024 && !cells_allow_large_lds<DTYPE, B, G, OWN>(dev)) return hipErrorNotSupported;
+        const int64_t blocks = std::min((items + WAVES - 1) / WAVES, (int64_t)cus * cells_per_cu(G, OWN));
+        if (blocks * WAVES < most_slabs) return hipErrorNotSupported;   // every wave keeps to one slab: at least a row's worth of waves
+        const hipError_t e = prepare();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((k_encode_cells<DTYPE, B, G, true, OWN>), dim3((unsigned)blocks), dim3(cells_threads(G, OWN)), lds, stream, bt);
+        return hipGetLastError();
+    };
+    return own ? search(std::true_type{}) : search(std::false_type{});
 }
 
 template <int DTYPE, int B>
