@@ -394,9 +394,11 @@ __device__ __forceinline__ double cells_fifth(uint2 rec, float x0, float x1, uin
     const double nearer = cells_nearer(best, cells_candidate(exact_dist2(x0, x1, make_float2(c[0], c[1])), o4));
     return rec.y & CELLS_FIFTH ? nearer : best;
 }
-// Whether the whole codebook decides the pair; far: cells_far().
-__device__ __forceinline__ bool cells_undecided(uint2 rec, float x0, float x1, float far) {
-    return (rec.y & CELLS_SCAN) || ((rec.y & CELLS_BORDER) && !(fabsf(x0) <= far && fabsf(x1) <= far));   // nor a NaN beside a number
+// Whether the whole codebook decides the pair; far: cells_far().  NANS: one coordinate may be a NaN and the other not (the larger of the
+// two is the number then).
+template <bool NANS> __device__ __forceinline__ bool cells_undecided(uint2 rec, float x0, float x1, float far) {
+    const bool near = NANS ? fabsf(x0) <= far && fabsf(x1) <= far : fmaxf(fabsf(x0), fabsf(x1)) <= far;
+    return (rec.y & CELLS_SCAN) || ((rec.y & CELLS_BORDER) && !near);
 }
 
 // ------------------------------------------------------------------------------------------------ without the table

@@ -427,7 +427,7 @@ void k_encode_cells(CellsBatch bt) {
                     int n_scan = 0;
 #pragma unroll
                     for (int k = 0; k < 8; ++k) {
-                        scan[k] = __ballot(cells_undecided(rec[k], x[2 * k], x[2 * k + 1], far)) & lanes;
+                        scan[k] = __ballot(cells_undecided<false>(rec[k], x[2 * k], x[2 * k + 1], far)) & lanes;
                         flagged |= scan[k];
                         n_scan += __popcll(scan[k]);
                     }

@@ -299,7 +299,7 @@ __global__ __launch_bounds__(LC_THREADS) void k_cells_lloyd_assign(const float2 
             if (__ballot(rec[u].y & CELLS_FIFTH)) best = cells_fifth(rec[u], x[u].x, x[u].y, 0u, best);
             int bi = (int)(cells_offset(best) >> 3);
             float d = cells_distance(best);
-            unsigned long long mask = __ballot(active && cells_undecided(rec[u], x[u].x, x[u].y, far));
+            unsigned long long mask = __ballot(active && cells_undecided<true>(rec[u], x[u].x, x[u].y, far));
             // outside the table, or too many candidates: the whole codebook, for many samples at once or one after the other
             if (__popcll(mask) > LC_DENSE_ABOVE) {
                 const float x0[1] = {x[u].x}, x1[1] = {x[u].y};
