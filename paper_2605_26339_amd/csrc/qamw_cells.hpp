@@ -545,11 +545,13 @@ __device__ __forceinline__ void nearest_of_all(const float (&x0)[P], const float
         }
     }
 }
-// Above this many of a wave's 512 pairs a search of all of them without the table is sooner done than one scan of the codebook
-// after the other: by the listing 60 + K / 11 vector instructions a scan, 2000 + 9 K for nearest_of_all() and 512 pairs, 41 K for
-// the distances to up to 32 codewords.  Measured where the pairs are 2.8 times as wide as a Lloyd codebook of 2^11 points, some 58 of
-// them undecided: 12288 x 4096 2010 us with all scanned one by one, 2085 with none (2300 with half the rows either way, whose waves
-// wait for each other, so 32 + K / 48 = 74, which is what three times as wide gives, cost more than either).
-constexpr int cells_dense_above(int K) { return K > 32 ? 32 + K / 80 : 16; }
+// Above this many undecided ones of a wave's 512 pairs a search of all of them without the table is sooner done than one scan of the
+// codebook after the other.  From pairs 2.2, 2.5, 2.8 and 3.2 times as wide as the codebook (24, 42, 67 and 105 undecided), us with all
+// scanned / none, 12288 x 4096 bf16: 6 bits 174 257 369 545 / 290; 8 bits 230 359 542 815 / 438; 9 bits 236 371 558 846 / 640;
+// 10 bits 305 475 733 1115 / 1140; 11 bits 488 818 1295 2004 / 2010.  The two meet at 50, 53, 78, 106 and 105; in 4096 x 4096 at 50, 52, 72, 95
+// and 92; with fp32 weights at 38 to 41 (6 to 8 bits), 62 (9) and 96 to 105 (11).  From 512 codewords on a scan requests eight a lane at once.
+constexpr int cells_dense_above(int K, bool bf16) {
+    return K >= 1024 ? 98 : K >= 512 ? (bf16 ? 72 : 62) : K > 32 ? (bf16 ? 50 : 39) : 16;
+}
 
 }  // namespace qamw

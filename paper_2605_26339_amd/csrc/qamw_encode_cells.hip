@@ -119,6 +119,10 @@ constexpr int cells_bits(int G) { return G == 128 ? 11 : G == 96 ? 10 : 0; }   /
 // How many rows the workgroup's waves have taken: in the lower word of a corner's record, which has no candidates (whatever is there,
 // the reads that it makes end below 16 KB and are not looked at).
 constexpr uint32_t cells_count_at(int G) { return (uint32_t)(cells_codewords(G) * 8 + (G - 1) * 8); }
+// In the two others that hold nothing else, where the encoder computes norms: the undecided pairs of the workgroup's recent items, and
+// whether items are put off; see cells_many().
+constexpr uint32_t cells_level_at(int G) { return (uint32_t)(cells_codewords(G) * 8 + (G * G - 1) * 8); }
+constexpr uint32_t cells_puts_at(int G) { return (uint32_t)(cells_codewords(G) * 8 + (G * G - G) * 8); }
 // Norms that the encoder computes: after codebook and table the slab sums of the waves' next rows, then per group of waves that share
 // rows (groups of 16 / n from number n on) how many are there, then the norm and of which row it is.
 constexpr int CELLS_GROUPS = 32;
@@ -187,6 +191,29 @@ __device__ __forceinline__ bool cells_share(CellsShare &out, const CellsMat &M, 
 constexpr int cells_together(int G, int B) { return G == 64 && B <= 256 ? 4 : 2; }   // pairs of a lane that nearest_of_all() takes: what the registers hold
 constexpr int CELLS_FEW_LANES = 12;                            // lanes with an undecided pair: up to here their pairs are scanned one by one
 constexpr int CELLS_PUT_OFF = 256;                             // items of a wave that can be put off, a bit each (in scalar registers)
+
+// Whether an item with n_scan undecided pairs, in more than a few lanes, is put off.  A little before the line, since waves finish late
+// that have some items of either kind by chance.  Where a row's waves wait for each other to have its norm they go one way: with some items
+// put off and some scanned all waited for those that scan, and the others gained nothing (12288 x 4096 bf16, 2048 points, pairs 2.8
+// times as wide as the codebook, the line at 57: 2320 us; all scanned 1295, none 2010).  So there a wave's first such item is put off
+// sooner, and then the mean over the workgroup's recent ones counts: the workgroup keeps its way until that is an eighth beyond the
+// line, and only an item far from it goes its own.  (Of waves that come here together each counts as if it were alone, which is near enough.)
+constexpr int CELLS_LEVEL_UNIT = 64, CELLS_LEVEL_FIRST = 16, CELLS_LEVEL_ITEMS = 32;
+constexpr uint32_t CELLS_NO_WAY = 2;                            // so far
+template <int G, bool OWN> __device__ __forceinline__ bool cells_many(int n_scan, int dense_above, bool first, int lane) {
+    if (!OWN) return 16 * n_scan > 13 * dense_above;
+    const int line = CELLS_LEVEL_UNIT * 15 / 16 * dense_above;
+    const uint32_t puts = __builtin_amdgcn_readfirstlane(lds_read<uint32_t>(cells_puts_at(G)));
+    int level = __builtin_amdgcn_readfirstlane((int)lds_read<uint32_t>(cells_level_at(G)));
+    const int step = (CELLS_LEVEL_UNIT * n_scan - level) / (puts == CELLS_NO_WAY ? CELLS_LEVEL_FIRST : CELLS_LEVEL_ITEMS);
+    if (lane == 0) lds_add(cells_level_at(G), (uint32_t)step);
+    level += step;
+    uint32_t now = puts;
+    if (puts == CELLS_NO_WAY ? !first : level > line + line / 8 || level < line - line / 8) now = level > line ? 1u : 0u;
+    if (now != puts && lane == 0) lds_write<uint32_t>(cells_puts_at(G), now);
+    if (first && puts == CELLS_NO_WAY) return 16 * n_scan > 11 * dense_above;
+    return n_scan > 2 * dense_above || (2 * n_scan > dense_above && now);
+}
 
 // Registers: two workgroups of 8 waves per CU for the smaller tables.  With fp32 weights that would cost spills, and one is left.
 #define QAMW_CELLS_WAVES_PER_EU ((STAGED && (cells_threads(G, OWN) == 1024 || DTYPE == 1)) ? 4 : 2)
@@ -276,10 +303,10 @@ void k_encode_cells(CellsBatch bt) {
         for (int i = 0; i < RECS; ++i)
             if (WHOLE || (int)threadIdx.x + i * THREADS < G * G / 2) lds_write(TABLE_AT + 16 * (threadIdx.x + i * THREADS), r[i]);
     }
-    if (STAGED && threadIdx.x == (G - 1) / 2) {                 // the thread that has written that record
-        asm volatile("" ::: "memory");
-        lds_write<uint32_t>(cells_count_at(G), 0u);
-    }
+    asm volatile("" ::: "memory");                             // (the threads that have written those records)
+    if (STAGED && threadIdx.x == (G - 1) / 2) lds_write<uint32_t>(cells_count_at(G), 0u);
+    if (OWN && threadIdx.x == (G * G / 2 - G / 2) % THREADS) lds_write<uint32_t>(cells_puts_at(G), CELLS_NO_WAY);
+    if (OWN && threadIdx.x == (G * G / 2 - 1) % THREADS) lds_write<uint32_t>(cells_level_at(G), (uint32_t)(CELLS_LEVEL_UNIT * bt.dense_above));
     if (OWN && threadIdx.x < 3 * CELLS_GROUPS) lds_write<uint32_t>(cells_arrived_at(G) + 4 * threadIdx.x, 0u);
     __syncthreads();
 
@@ -432,10 +459,10 @@ void k_encode_cells(CellsBatch bt) {
                         n_scan += __popcll(scan[k]);
                     }
                     // many: without the table, later.  (A grid decides most of them; otherwise as many as dense_above.)
-                    if (__popcll(flagged) > CELLS_FEW_LANES && n < CELLS_PUT_OFF && (bt.grid || n_scan > bt.dense_above)) {
+                    if (__popcll(flagged) > CELLS_FEW_LANES && n < CELLS_PUT_OFF && (bt.grid || cells_many<G, OWN>(n_scan, bt.dense_above, !any_put_off, lane))) {
                         put(n);
+                        if (!OWN || any_put_off || n_scan > 2 * bt.dense_above) skip = streak = min(2 * streak + 1, 15);
                         any_put_off = true;
-                        skip = streak = min(2 * streak + 1, 15);
                         continue;
                     }
 #pragma unroll
@@ -719,7 +746,7 @@ hipError_t launch_encode_cells(const EncodeItem *items, int n, int dtype, const 
     bt.K = p.K;
     bt.inv_sqrt_block = p.inv_sqrt_block;
     bt.half_per_sum = cells_half_per_sum(p.bits);
-    bt.dense_above = cells_dense_above(p.K);
+    bt.dense_above = cells_dense_above(p.K, dtype == 1);
     bt.grid = nullptr;
     bt.grid_side = 0;
     if (grid && p.K > 32) {                                     // (up to 32 codewords all distances are as soon computed)
