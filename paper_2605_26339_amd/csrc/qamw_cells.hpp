@@ -57,12 +57,14 @@ inline float cells_half_per_sum(int bits) {
 // half is kept in the first record, a corner's, which has no candidates: its upper 12 bits from bit 3 on.
 __device__ __forceinline__ uint32_t cells_put_half(float half) { return (__float_as_uint(half) >> 20) << 3; }
 __device__ __forceinline__ float cells_half(const uint2 *table) { return __uint_as_float((table[0].x >> 3) << 20); }
-// 1 / 2R, one rounding or two off (the boxes' slack is 2^-16 of half).
-__device__ __forceinline__ float cells_inv_span(float half) {
-    return (0.5f / CELLS_REACH) * __builtin_amdgcn_rcpf(__uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(half))));
+// 1 / 2R, one rounding or two off (the boxes' slack is 2^-16 of half), in a scalar register.
+__device__ __forceinline__ float wave_uniform(float v) {
+    asm volatile("" : "+v"(v));                                 // (left in a vector register where the compiler knows that it is uniform)
+    return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v)));
 }
+__device__ __forceinline__ float cells_inv_span(float half) { return wave_uniform((0.5f / CELLS_REACH) * __builtin_amdgcn_rcpf(wave_uniform(half))); }
 // Up to where a record of the edge holds.
-__device__ __forceinline__ float cells_far(float half) { return CELLS_REACH * CELLS_FAR * half; }
+__device__ __forceinline__ float cells_far(float half) { return wave_uniform(CELLS_REACH * CELLS_FAR * half); }
 
 // The cells' edges over half: of cell i from at[i] to at[i + 1].
 template <int G> struct CellsEdges {

@@ -232,7 +232,9 @@ void k_encode_cells(CellsBatch bt) {
     const int lane = threadIdx.x & (WAVE - 1);
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const LaneSigns<B> ls(lane);
-    const int pos = slab_pos(lane);
+    // The lane's first column in a slab.  (Of fp32 kernels with 128 x 128 cells every register counts: with the position kept too, 2 or 3
+    // were spilled, and scratch memory is what short launches pay for.  1024 x 4096 22.4 us, 18.4 so; 4096 x 2048 29.9, 25.4.)
+    const int lane_col = 16 * slab_pos(lane);
     const float unit = ls.parity * bt.inv_sqrt_block;
     const int n_waves = (int)gridDim.x * WAVES;
     const int gw = (int)blockIdx.x * WAVES + wid;
@@ -263,7 +265,7 @@ void k_encode_cells(CellsBatch bt) {
     uint32_t tag_next = 0;                                      // not 0: the next row's norm is this launch's, the row's mark
     float *norm_out = nullptr;
     auto first_column = [&](int slab, int d_in) __attribute__((always_inline)) {
-        const int col0 = slab * 1024 + 16 * pos;
+        const int col0 = slab * 1024 + lane_col;
         return col0 < d_in ? col0 : 0;
     };
     auto request = [&]() __attribute__((always_inline)) {       // the next row
@@ -317,7 +319,7 @@ void k_encode_cells(CellsBatch bt) {
     // on, so that row's sums are read, and a norm follows only when all waves of the group have come as far.
     auto sum_next = [&](int now) __attribute__((always_inline)) {
         const CellsMat &M = bt.m[mi];
-        const int col0 = share.slab * 1024 + 16 * pos;
+        const int col0 = share.slab * 1024 + lane_col;
         if (mi != now) {                                        // the row is another matrix's: this one's scales are done with
             Problem p;
             p.chan_scale = M.chan_scale;
@@ -373,7 +375,7 @@ void k_encode_cells(CellsBatch bt) {
 #pragma unroll 1
     while (mi < bt.n) {
         const CellsMat &M = bt.m[mi];
-        const int col0 = share.slab * 1024 + 16 * pos;
+        const int col0 = share.slab * 1024 + lane_col;
         const bool active = col0 < M.d_in;
         const int c = active ? col0 : 0;
         const unsigned long long lanes = __ballot(active);
@@ -398,9 +400,9 @@ void k_encode_cells(CellsBatch bt) {
             float x[16];
             if (try_table) {
                 if constexpr (STAGED && G == 128 && DTYPE == 0) {   // no registers for the lane's signs: made again
-                    int p = pos;
-                    asm volatile("" : "+v"(p));
-                    cells_pairs<DTYPE, B>(x, raw, norm, sc, g, LaneSigns<B>(lane, p), unit);
+                    int col = lane_col;
+                    asm volatile("" : "+v"(col));
+                    cells_pairs<DTYPE, B>(x, raw, norm, sc, g, LaneSigns<B>(lane, col >> 4), unit);
                 } else {
                     cells_pairs<DTYPE, B>(x, raw, norm, sc, g, ls, unit);
                 }
