@@ -134,8 +134,10 @@ constexpr size_t cells_lds_bytes(int G, bool own) { return own ? cells_norm_at(G
 // (with one of 8, and the launch's others after it, 11008 x 4096 bf16 took 82 us, 13824 x 5120 without norms 102; so 64 and 87; two
 // of 8 and the norms from the launch ahead 65, but a 7B layer 263 instead of 225, in fp32 402 instead of 290.  Small launches have
 // more workgroups of 8 waves: 512 x 4096 16.2, with those of 16 17.5).
-constexpr int cells_per_cu(int G, bool own) { return cells_threads(G, own) == 1024 ? 1 : 2; }
-template <int G, bool OWN> constexpr bool cells_resident() { return cells_per_cu(G, OWN) * cells_lds_bytes(G, OWN) <= 160 * 1024; }
+//   With fp32 weights 8 waves' registers (130 to 171 a lane) leave no room for 8 more.  Twice as many workgroups, the second half
+// after the first, each with a table to stage: 1024 x 4096 at 7 bits 18.7 us, 15.6 so, at 10 bits 20.9, 17.2; 4096 x 4096 at 7 bits 38.9, 35.7.
+constexpr int cells_per_cu(int G, bool own, int dtype) { return cells_threads(G, own) == 1024 || dtype == 0 ? 1 : 2; }
+template <int G, bool OWN> constexpr bool cells_resident(int dtype) { return cells_per_cu(G, OWN, dtype) * cells_lds_bytes(G, OWN) <= 160 * 1024; }
 
 // 1/sqrt(B) is a power of two: its product with the gain is exact, and so one multiplication gives the bits of two (what that
 // could lose below the smallest normal number is nothing to a distance from a codeword).
@@ -215,7 +217,7 @@ template <int G, bool OWN> __device__ __forceinline__ bool cells_many(int n_scan
     return n_scan > 2 * dense_above || (2 * n_scan > dense_above && now);
 }
 
-// Registers: two workgroups of 8 waves per CU for the smaller tables.  With fp32 weights that would cost spills, and one is left.
+// Registers: 16 waves per CU, of one workgroup or two; with fp32 weights and tables below 128 x 128 that would cost spills, and there are 8.
 #define QAMW_CELLS_WAVES_PER_EU ((STAGED && (cells_threads(G, OWN) == 1024 || DTYPE == 1)) ? 4 : 2)
 // STAGED: the table in LDS beside the codebook.  Otherwise its records are read from memory (L2): in a launch of few items a
 // workgroup would stage 128 KB for an item or two per wave, and small workgroups reach more CUs.
@@ -224,7 +226,7 @@ __global__ __launch_bounds__(STAGED ? cells_threads(G, OWN) : CELLS_DIRECT_THREA
 void k_encode_cells(CellsBatch bt) {
     static_assert(STAGED || (G & (G - 1)) == 0, "the mask of the record's offset");
     static_assert(STAGED || !OWN, "the sums' place in LDS is after the table's");
-    static_assert(!STAGED || cells_resident<G, OWN>(), "the launch's workgroups are resident together");
+    static_assert(!STAGED || cells_resident<G, OWN>(DTYPE), "the launch's workgroups are resident together");
     constexpr int THREADS = STAGED ? cells_threads(G, OWN) : CELLS_DIRECT_THREADS, WAVES = THREADS / WAVE;
     constexpr int CODEWORDS = cells_codewords(G);
     constexpr uint32_t TABLE_AT = CODEWORDS * 8;               // LDS: the codebook at 0, then the table
@@ -667,7 +669,7 @@ static hipError_t launch_cells_dbg(CellsBatch &bt, hipStream_t stream) {
         constexpr int WAVES = cells_threads(G, OWN) / WAVE;
         constexpr size_t lds = cells_lds_bytes(G, OWN);
         if (lds > 64 * 1024 && !cells_allow_large_lds<DTYPE, B, G, OWN>(dev)) return hipErrorNotSupported;
-        const int64_t blocks = std::min((items + WAVES - 1) / WAVES, (int64_t)cus * cells_per_cu(G, OWN));
+        const int64_t blocks = std::min((items + WAVES - 1) / WAVES, (int64_t)cus * cells_per_cu(G, OWN, DTYPE));
         if (blocks * WAVES < most_slabs) return hipErrorNotSupported;   // every wave keeps to one slab: at least a row's worth of waves
         const hipError_t e = prepare();
         if (e != hipSuccess) return e;
