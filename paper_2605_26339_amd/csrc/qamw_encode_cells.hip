@@ -19,7 +19,7 @@
 // loaded, divided and combined once per wave instead of once per row; records of all eight pairs requested at once, and a pair's
 // candidates before the pair ahead of it is decided.  13824 x 5120 at 11 bits, the whole call: 134 us with five candidates in cells
 // of one width, a comparison and two selections each, so 97 (a 7B layer 381, so 305; of both 1.1 by the order of the waves, see below).
-//   Row norms.  Of large matrices whose rows have 1, 2, 4 or 8 slabs, at 11 bits 16 too, they are computed here (OWN): a row's waves are neighbours in
+//   Row norms.  Of large matrices whose rows have 2, 4 or 8 slabs (see cells_shares_rows()) they are computed here (OWN): a row's waves are neighbours in
 // a workgroup, and each sums the slab of its next row, which is in its registers anyway, while the present one is searched, so that
 // the matrix is read from memory once.  The launch ahead of this then makes the table and the other norms: a 7B layer's 82 -> 22 us by
 // the trace, this one 187 -> 220 (7 of them the sums, 12 the waits for a row's other waves).
@@ -38,12 +38,23 @@ namespace qamw {
 // second L2 round trip takes: 1024 x 2048 at 10 bits 20.3 / 19.6, at 7 bits 18.7 / 25.1.
 constexpr int CELLS_DIRECT_MAX_ITEMS = 3072;
 constexpr int CELLS_ROWS_TOGETHER = 8192;                      // rows of a launch from which a wave sums four
-// Bytes of the matrices whose rows a workgroup's waves can share, from which the encoder computes those rows' norms itself: they cost
-// its waves more instructions than what a second reading from memory does beside the making of the table.  In us a call with the pair
-// scales, norms in the first launch / in the encoder: 4096 x 4096 bf16 (34 MB) 50 / 53, 16384 x 1024 42 / 46, 40000 x 512 57 / 63;
-// 11008 x 4096 (90 MB) 78 / 77, 22016 x 2048 75 / 71, 8192 x 8192 113 / 108, a 7B layer (405 MB, of which 90 in rows of 11 slabs) 310
-// / 280; fp32 8192 x 4096 (134 MB) 88 / 72, 14336 x 4096 133 / 111.
-constexpr int64_t CELLS_OWN_MIN_BYTES = 64 << 20;
+// Where the encoder computes row norms itself: matrices whose rows a workgroup's waves share without many idle lanes, and enough of
+// them, for that costs its waves more instructions, and waits for a row's other waves, than a second reading from memory does beside
+// the making of the table.  us a call, norms in the first launch / in the encoder, bf16: 4 slabs 8192 x 4096 (64 MiB) 50 / 51, 10240 55.6 /
+// 56.1, 12288 65.3 / 63.8, 14336 73.4 / 72.1, at 10 bits 74 / 68.5; 2 slabs 16384 x 2048 51.6 / 49.2, 22016 65.7 / 61.5; 8 slabs 4096 x 8192 46.9 / 50.2,
+// 7168 72.1 / 75.2, 8192 (128 MiB) 88 / 84, 28672 289 / 257; one slab 32768 x 1024 46.4 / 49.4, 65536 78.7 / 79.1; 16 slabs 4096 x 16384 80 / 102;
+// last slabs not full 17387 x 3136 76.6 / 80, 19660 x 3840 90.3 / 91.3, 9830 x 7680 90.8 / 95.4, 49152 x 1536 100 / 105.  fp32, whose norms in the
+// first launch read twice as much: 4096 x 4096 (64 MiB) 36.3 / 36.7, 6144 46.0 / 43.5, 8192 64.6 / 51.3; 20480 x 1024 41.7 / 39.9; 4096 x 8192 56.1 / 51.8;
+// 12288 x 1536 40.8 / 40.7.  Last slabs that are not full are out in fp32 too: their waves have fewer undecided pairs than the others that they
+// wait for, and which way the workgroup goes suits only some (12288 x 1536 at 7 bits, pairs 2.5 times as wide as the codebook: 205 / 326).
+//   A 7B layer (315 MB in rows of 4 slabs, 90 in rows of 11) 310 / 280.
+constexpr int CELLS_OWN_MOST_SLABS = 8;
+constexpr bool cells_shares_rows(int dtype, int n_slabs, int d_in) {
+    return CELLS_OWN_MOST_SLABS % n_slabs == 0 && d_in == 1024 * n_slabs && (n_slabs > 1 || dtype == 0);
+}
+// 64 MiB of matrices of one or two slabs, 96 of four, 128 of eight, or parts of each.
+constexpr int64_t CELLS_OWN_MIN_BYTES = 32 << 20;
+constexpr int cells_own_parts(int log_slabs) { return log_slabs < 1 ? 2 : 1 + log_slabs; }
 constexpr int CELLS_MIN_ITEMS = 4096;                          // (row, slab) items of a launch from which small codebooks use the table,
 constexpr int CELLS_GRID_MIN_ITEMS = 1024;                     // and from which the pruned search does
 
@@ -111,8 +122,6 @@ __global__ __launch_bounds__(CP_THREADS) void k_cells_prepare(CellsBatch bt) {
 // ------------------------------------------------------------------------------------------------ the encoder
 constexpr int CELLS_DIRECT_THREADS = 256;
 constexpr int cells_threads(int G, bool own) { return G == 128 || (G == 96 && own) ? 1024 : 512; }
-// Slabs of a row up to which the encoder computes its norm.  (At 10 bits 16 waves could share a row too: 5000 x 16384 bf16 123 us so, 120 without.)
-constexpr int cells_most_shared(int G) { return G == 128 ? 16 : 8; }
 constexpr int cells_codewords(int G) { return G == 128 ? 2048 : G == 96 ? 1024 : 512; }
 constexpr int cells_least_k(int G) { return G == 128 ? 2048 : G == 96 ? 1024 : 2; }
 constexpr int cells_bits(int G) { return G == 128 ? 11 : G == 96 ? 10 : 0; }   // 0: 1 to 9
@@ -634,8 +643,8 @@ static hipError_t launch_cells_dbg(CellsBatch &bt, hipStream_t stream) {
         rows += M.d_out;
         items += (int64_t)M.d_out * M.n_slabs;
         M.log_slabs = __builtin_ctz((unsigned)M.n_slabs);
-        M.own_norms = M.slab_sums && cells_most_shared(G) % M.n_slabs == 0;
-        if (M.own_norms) own_bytes += (int64_t)M.d_out * M.d_in * (DTYPE == 0 ? 4 : 2);
+        M.own_norms = M.slab_sums && cells_shares_rows(DTYPE, M.n_slabs, M.d_in);
+        if (M.own_norms) own_bytes += (int64_t)M.d_out * M.d_in * (DTYPE == 0 ? 4 : 2) / cells_own_parts(M.log_slabs);
     }
     const bool direct_launch = G == 128 && items <= CELLS_DIRECT_MAX_ITEMS, own = !direct_launch && own_bytes >= CELLS_OWN_MIN_BYTES;
     for (int i = 0; i < bt.n && !own; ++i) bt.m[i].own_norms = 0;
