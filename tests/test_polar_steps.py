@@ -17,7 +17,8 @@ pytestmark = pytest.mark.gpu
     (18433, 1024, 3, 8, 64, "bf16"),   # 37 rows of one slab, 256 bins, the last workgroup seven
     (9000, 2112, 5, 5, 64, "f32"),          # three slabs, the last of one block
     (20000, 2048, 0, 9, 1024, "bf16"),      # more bins than have tables
-    (20000, 2048, 6, 0, 512, "bf16")])      # no bins
+    (20000, 2048, 6, 0, 512, "bf16"),       # no bins
+    (1001, 66560, 5, 6, 1024, "bf16")])     # norms from a launch ahead; steps of one row, the last workgroup one step
 def test_a_row_in_any_step(d_out, d_in, bits_a, bits_p, block, dtype):
     print(f"[polar steps] {d_out}x{d_in} {bits_a}+{bits_p} b={block} {dtype}", flush=True)
     levels = torch.from_numpy(qamw.polar_codebook(bits_a, bits_p)[0]).cuda()
