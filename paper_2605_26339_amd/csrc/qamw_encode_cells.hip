@@ -148,11 +148,9 @@ constexpr size_t cells_lds_bytes(int G, bool own) { return own ? cells_norm_at(G
 constexpr int cells_per_cu(int G, bool own, int dtype) { return cells_threads(G, own) == 1024 || dtype == 0 ? 1 : 2; }
 template <int G, bool OWN> constexpr bool cells_resident(int dtype) { return cells_per_cu(G, OWN, dtype) * cells_lds_bytes(G, OWN) <= 160 * 1024; }
 
-// 1/sqrt(B) is a power of two: its product with the gain is exact, and so one multiplication gives the bits of two (what that
-// could lose below the smallest normal number is nothing to a distance from a codeword).
-constexpr bool cells_unit_exact(int B) { return B == 64 || B == 256 || B == 1024; }
-// The constants of a lane's 16 columns from c on: scale x sign per column, gain per pair.
-template <int B> __device__ __forceinline__ void cells_constants(float (&sc)[16], float (&g)[8], const CellsMat &M, int c, float unit) {
+// The constants of a lane's 16 columns from c on: scale x sign per column, gain per pair.  True: see combine_gains().
+template <int B>
+__device__ __forceinline__ bool cells_constants(float (&sc)[16], float (&g)[8], const CellsMat &M, int c, float parity, float inv_sqrt_block) {
     Problem p;
     p.chan_scale = M.chan_scale;
     p.signs = M.signs;
@@ -160,20 +158,23 @@ template <int B> __device__ __forceinline__ void cells_constants(float (&sc)[16]
     p.g_default = M.g_default;
     load_signed_scales(sc, p, c);
     load_pair_gains(g, p, c);
-#pragma unroll
-    for (int k = 0; k < 8; ++k) g[k] = cells_unit_exact(B) ? unit * g[k] : g[k];
+    return unit_exact(B) && combine_gains(g, parity, inv_sqrt_block);
 }
 // A lane's pairs from its raw words: rotated_unit_row with the sign folded into the scale (exact).
 template <int DTYPE, int B>
 __device__ __forceinline__ void cells_pairs(float (&x)[16], const RawRow<DTYPE> &raw, float norm, const float (&sc)[16], const float (&g)[8],
-                                            const LaneSigns<B> &ls, float unit) {
+                                            const LaneSigns<B> &ls, float unit, bool two, float inv_sqrt_block) {
     widen_raw_row<DTYPE>(x, raw);
 #pragma unroll
     for (int e = 0; e < 16; ++e) x[e] = x[e] * sc[e];
     divide_by_norm(x, norm);
     fwht_wave<B>(x, ls);
+    if (unit_exact(B) && __builtin_expect(two, false)) {
 #pragma unroll
-    for (int e = 0; e < 16; ++e) x[e] = (cells_unit_exact(B) ? x[e] : x[e] * unit) * g[e >> 1];
+        for (int e = 0; e < 16; ++e) x[e] = x[e] * inv_sqrt_block;
+    }
+#pragma unroll
+    for (int e = 0; e < 16; ++e) x[e] = (unit_exact(B) ? x[e] : x[e] * unit) * g[e >> 1];
 }
 
 // The waves of the launch take the (row, slab) items of a matrix in turn, `step` at a time, a multiple of the slab count: a
@@ -395,7 +396,7 @@ void k_encode_cells(CellsBatch bt) {
         uint8_t *out = M.packed + share.row * row_bytes;
         const int64_t out_step = share.rows_step * row_bytes;
         const int now = mi;
-        cells_constants<B>(sc, g, M, c, unit);
+        const bool two = cells_constants<B>(sc, g, M, c, ls.parity, bt.inv_sqrt_block);
 
         for (int rows = left + 1; rows > 0; --rows, ++n, out += out_step) {
             const RawRow<DTYPE> raw = next;
@@ -413,9 +414,9 @@ void k_encode_cells(CellsBatch bt) {
                 if constexpr (STAGED && G == 128 && DTYPE == 0) {   // no registers for the lane's signs: made again
                     int col = lane_col;
                     asm volatile("" : "+v"(col));
-                    cells_pairs<DTYPE, B>(x, raw, norm, sc, g, LaneSigns<B>(lane, col >> 4), unit);
+                    cells_pairs<DTYPE, B>(x, raw, norm, sc, g, LaneSigns<B>(lane, col >> 4), unit, two, bt.inv_sqrt_block);
                 } else {
-                    cells_pairs<DTYPE, B>(x, raw, norm, sc, g, ls, unit);
+                    cells_pairs<DTYPE, B>(x, raw, norm, sc, g, ls, unit, two, bt.inv_sqrt_block);
                 }
             }
             if (OWN && tag_next) sum_next(now);              // by now the next row has come
@@ -527,10 +528,10 @@ void k_encode_cells(CellsBatch bt) {
             float x[16];
             {
                 float sc[16], g[8];
-                cells_constants<B>(sc, g, M, c, unit2);
+                const bool two = cells_constants<B>(sc, g, M, c, ls2.parity, bt.inv_sqrt_block);
                 RawRow<DTYPE> raw;
                 load_raw_row<DTYPE>(raw, M.W, (int64_t)row * M.ldw, c);
-                cells_pairs<DTYPE, B>(x, raw, M.norms[row], sc, g, ls2, unit2);
+                cells_pairs<DTYPE, B>(x, raw, M.norms[row], sc, g, ls2, unit2, two, bt.inv_sqrt_block);
             }
             unsigned idx8[8];
             bool decided = false;

@@ -41,3 +41,24 @@ def test_polar_phase_of_a_rounded_pair(block, rows):
     assert bool((x[..., 0] < 0).any()) and bool((x[..., 0] > 0).any())
     want = torch.where(x[..., 0] > 0, 0, 1 << (bits_p - 1)).expand(rows, -1)
     assert torch.equal(_fields(packed, bits_a + bits_p, d_in // 2)[:, own] & ((1 << bits_p) - 1), want)
+
+
+# records from memory and from LDS, norms from a launch ahead and inside the search
+@pytest.mark.parametrize("block", [64, 256, 1024])
+@pytest.mark.parametrize("bits", [7, 10, 11])
+@pytest.mark.parametrize("rows", [300, 6000, 13000])
+def test_nearest_codeword_of_a_rounded_pair(block, bits, rows):
+    """The pairs lie half way between a codeword and its mirror image, where the lower index counts, or beside that by what is rounded."""
+    print(f"[unit gains] cells {block} bits {bits} rows {rows}", flush=True)
+    d_in = 4096
+    W = _row(block, d_in, block ** 0.5 * 2.0 ** -131 - 2.0 ** -149, block ** 0.5 * 2.0 ** -131 + 2.0 ** -149).repeat(rows, 1)
+    sigma = torch.full((d_in // 2,), 2.0 ** -126, device="cuda")
+    cb = torch.from_numpy(qamw.train_codebook(bits, 1 << 15, max_iters=20)[0]).cuda()
+    cb[::2, 1] = cb[::2, 1].abs()
+    cb[1::2] = cb[::2] * torch.tensor([1.0, -1.0], device="cuda")
+    scans = torch.zeros(1, dtype=torch.int64, device="cuda")
+    want, _ = qamw.encode(W, cb, bits, block, pair_sigma=sigma, full_scans=scans)
+    got, _ = qamw.encode(W, cb, bits, block, pair_sigma=sigma)
+    torch.cuda.synchronize()
+    assert not bool((_fields(want, bits, d_in // 2)[:, block // 2:block] & 1).any())
+    assert torch.equal(got, want)
