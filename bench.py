@@ -44,8 +44,8 @@ PEAK_HBM_GBS = 8000.0             # MI355X HBM3E (published)
 PEAK_BF16_TFLOPS = 2500.0         # MI355X dense bf16 matrix cores (published)
 FLOPS_PER_EVAL = 4.0              # one distance evaluation = 2 FMA
 ENCODE_LIMIT = ("vector-ALU issue in the search (about 610 vector instructions and 42 LDS instructions per 512 pairs: butterflies, "
-                "correctly rounded division, four exact fp32 distances per pair; some 100 more for the row norms of large matrices with 1, 2, 4, 8 or "
-                "16 slabs of 1024 columns), then a second read of the other matrices for their norms")
+                "correctly rounded division, four exact fp32 distances per pair; some 100 more for the row norms of large matrices with 2, 4 or 8 "
+                "slabs of 1024 columns), then a second read of the other matrices for their norms")
 
 
 def build_workload(wl, layers, device):

@@ -2,7 +2,7 @@
 // whole codebook returns, lowest index on ties).
 //
 // k_cells_prepare cuts a square that follows the codebook's scale into G x G cells and lists, per cell, every codeword that can
-// be nearest to a point of the cell; the same launch computes the row norms.  k_encode_cells keeps the codebook and the whole table
+// be nearest to a point of the cell; the same launch computes the row norms that the search does not.  k_encode_cells keeps the codebook and the whole table
 // in LDS and decides a pair by the exact fp32 squared distances to its cell's first four candidates, and to the fifth where there
 // is one (0.14 % of the pairs that a Lloyd codebook of 2^11 points is for).  A pair outside the table (0.0002 % of them), or in a
 // cell that lists more (0.001 %), is decided by the exact scan of the whole codebook (64 lanes x K/64 codewords).
@@ -18,11 +18,12 @@
 // once and walks the rows; a wave keeps to one 1024-column slab of a matrix, so the slab's scales, signs and pair gains are
 // loaded, divided and combined once per wave instead of once per row; records of all eight pairs requested at once, and a pair's
 // candidates before the pair ahead of it is decided.  13824 x 5120 at 11 bits, the whole call: 134 us with five candidates in cells
-// of one width, a comparison and two selections each, so 97 (a 7B layer 381, so 305; of both 1.1 by the order of the waves, see below).
-//   Row norms.  Of large matrices whose rows have 2, 4 or 8 slabs (see cells_shares_rows()) they are computed here (OWN): a row's waves are neighbours in
-// a workgroup, and each sums the slab of its next row, which is in its registers anyway, while the present one is searched, so that
+// of one width, a comparison and two selections each, so 98 (a 7B layer with the pair scales 398, so 313; of both 1.1 by the order of the
+// waves, see below).
+//   Row norms.  Of large matrices whose rows have 2, 4 or 8 slabs (see cells_shares_rows()) they are computed here (OWN): a row's waves are
+// neighbours in a workgroup, and each sums the slab of its next row, which is in its registers anyway, while the present one is searched, so that
 // the matrix is read from memory once.  The launch ahead of this then makes the table and the other norms: a 7B layer's 82 -> 22 us by
-// the trace, this one 187 -> 220 (7 of them the sums, 12 the waits for a row's other waves).
+// the trace, this one 187 -> 220 (7 of them the sums, 12 the waits for a row's other waves); the call 313 -> 290.
 #include <algorithm>
 #include <atomic>
 #include <cmath>
@@ -47,7 +48,7 @@ constexpr int CELLS_ROWS_TOGETHER = 8192;                      // rows of a laun
 // first launch read twice as much: 4096 x 4096 (64 MiB) 36.3 / 36.7, 6144 46.0 / 43.5, 8192 64.6 / 51.3; 20480 x 1024 41.7 / 39.9; 4096 x 8192 56.1 / 51.8;
 // 12288 x 1536 40.8 / 40.7.  Last slabs that are not full are out in fp32 too: their waves have fewer undecided pairs than the others that they
 // wait for, and which way the workgroup goes suits only some (12288 x 1536 at 7 bits, pairs 2.5 times as wide as the codebook: 205 / 326).
-//   A 7B layer (315 MB in rows of 4 slabs, 90 in rows of 11) 310 / 280.
+//   A 7B layer (315 MB in rows of 4 slabs, 90 in rows of 11) 313 / 290 with the pair scales.
 constexpr int CELLS_OWN_MOST_SLABS = 8;
 constexpr bool cells_shares_rows(int dtype, int n_slabs, int d_in) {
     return CELLS_OWN_MOST_SLABS % n_slabs == 0 && d_in == 1024 * n_slabs && (n_slabs > 1 || dtype == 0);
@@ -143,7 +144,7 @@ constexpr size_t cells_lds_bytes(int G, bool own) { return own ? cells_norm_at(G
 // (with one of 8, and the launch's others after it, 11008 x 4096 bf16 took 82 us, 13824 x 5120 without norms 102; so 64 and 87; two
 // of 8 and the norms from the launch ahead 65, but a 7B layer 263 instead of 225, in fp32 402 instead of 290.  Small launches have
 // more workgroups of 8 waves: 512 x 4096 16.2, with those of 16 17.5).
-//   With fp32 weights 8 waves' registers (130 to 171 a lane) leave no room for 8 more.  Twice as many workgroups, the second half
+//   With fp32 weights 8 waves' registers (130 to 177 a lane) leave no room for 8 more.  Twice as many workgroups, the second half
 // after the first, each with a table to stage: 1024 x 4096 at 7 bits 18.7 us, 15.6 so, at 10 bits 20.9, 17.2; 4096 x 4096 at 7 bits 38.9, 35.7.
 constexpr int cells_per_cu(int G, bool own, int dtype) { return cells_threads(G, own) == 1024 || dtype == 0 ? 1 : 2; }
 template <int G, bool OWN> constexpr bool cells_resident(int dtype) { return cells_per_cu(G, OWN, dtype) * cells_lds_bytes(G, OWN) <= 160 * 1024; }
@@ -244,7 +245,7 @@ void k_encode_cells(CellsBatch bt) {
     const int lane = threadIdx.x & (WAVE - 1);
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const LaneSigns<B> ls(lane);
-    // The lane's first column in a slab.  (Of fp32 kernels with 128 x 128 cells every register counts: with the position kept too, 2 or 3
+    // The lane's first column in a slab.  (Of fp32 kernels with 128 x 128 cells every register counts: with the position kept too, 18 to 20
     // were spilled, and scratch memory is what short launches pay for.  1024 x 4096 22.4 us, 18.4 so; 4096 x 2048 29.9, 25.4.)
     const int lane_col = 16 * slab_pos(lane);
     const float unit = ls.parity * bt.inv_sqrt_block;

@@ -42,8 +42,8 @@ constexpr uint32_t PF_DIR_AT = PF_LUT_AT + 8 * PF_AMP_CELLS + 2 * 16 * PF_PHASE_
 // some 50 of the two binary searches or 27 with the lookup tables), so the lane's pairs go side by side.  4096 x 11008 bf16 at 5 + 6
 // bits, 90 MB read, us a call: 115 -> 84 with the slabs summed once, 74 with byte tables that say where the searches would be one
 // step before their end, 72 with workgroups that stay for two steps (the second one's norms cost no memory round trips, and the
-// tables are made half as often), 69 with entries that hold what is tested and the code (without any norms of the second step it
-// would be 63).  11008 x 4096 at 4 + 4 66.5 -> 60, 14336 x 4096 fp32 95 -> 86, 4096 x 4096 fp32 at 3 + 4 36 -> 31 of late.
+// tables are made half as often), 66 with entries that hold what is tested and the code (the norms of the second step are 6 of
+// that).  11008 x 4096 at 4 + 4 66.5 -> 60, 14336 x 4096 fp32 95 -> 86, 4096 x 4096 fp32 at 3 + 4 36 -> 31 of late.
 // (The next item's weights requested ahead: the same.)
 template <int DTYPE, int B>
 __global__ __launch_bounds__(PF_THREADS) __attribute__((amdgpu_waves_per_eu(4)))   // two workgroups per CU

@@ -370,8 +370,9 @@ __device__ __forceinline__ unsigned grid_nearest(const uint4 &rec, float x0, flo
 // wins a tie.  Every lane returns the index (0 if every distance is NaN).  codeword(k): from wherever the caller keeps them.
 // K_FROM, K_TO: what the caller knows of K; the loops that it rules out are left out.
 template <int K_FROM, int K_TO, typename F> __device__ __forceinline__ int wave_exact_scan_of(float x0, float x1, F codeword, int K, int lane) {
-    // Codewords requested together: the scan is a chain of LDS latencies otherwise.  0.065 % of Gaussian pairs come here at 2^11
-    // points, one in three of a wave's 512-pair items: 13824 x 5120, the whole encode call, 156 us one at a time, 137 so.
+    // Codewords requested together: the scan is a chain of LDS latencies otherwise.  Where 0.065 % of the pairs came here, one in three
+    // of a wave's 512-pair items (2^11 points, cells of one width; with the cells of now 0.001 %), 13824 x 5120, the whole encode call,
+    // took 156 us one at a time, 137 so.
     constexpr int AHEAD = 8;
     float bd = 3.0e38f;
     int bi = 0x7fffffff;

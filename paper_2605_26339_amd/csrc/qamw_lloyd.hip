@@ -244,8 +244,9 @@ __global__ __launch_bounds__(CP_THREADS) void k_cells_lloyd_table(int K, float h
 }
 
 // The records come from memory (L2), four samples' at a time: staging them took as long as the samples of a workgroup do, and
-// a table of 112 x 112 cells was all that fitted beside the sums, with 1.1 % of Gaussian samples in cells of six candidates --
-// a scan of the whole codebook in most waves, against 0.05 % with 128 x 128.  2048 points, 2^20 samples: 23.5 -> 11.5 us.
+// a table of 112 x 112 cells was all that fitted beside the sums, with 1.1 % of Gaussian samples in cells of six candidates
+// while cells were of one width -- a scan of the whole codebook in most waves, against 0.05 % with 128 x 128 (0.001 % with the cells of
+// now).  2048 points, 2^20 samples: 23.5 -> 11.5 us.
 //   The sums' atomics, three per point and workgroup, are what a workgroup costs whatever its share; see lc_blocks().
 template <int G>
 __global__ __launch_bounds__(LC_THREADS) void k_cells_lloyd_assign(const float2 *__restrict__ samples, long long n, int K, LloydCells a, int t) {
