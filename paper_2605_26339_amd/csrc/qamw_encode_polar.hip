@@ -157,7 +157,6 @@ void k_encode_polar(const void *__restrict__ W, int64_t ldw, Problem p, const fl
     const bool lut = lds_read<uint32_t>(NO_LUT_AT) == 0u;
     const LaneSigns<B> ls(lane);
     const float unit = ls.parity * p.inv_sqrt_block;
-    bool two = false;                                           // two multiplications by 1/sqrt(B) and the gains, see combine_gains()
     int odd = 0;
 #pragma unroll 1
     for (int row0 = wg_row0; row0 < wg_end; row0 += rows, odd ^= 1) {
@@ -179,7 +178,6 @@ void k_encode_polar(const void *__restrict__ W, int64_t ldw, Problem p, const fl
             if (slab != cur_slab) {
                 at_slab(slab);
                 load_pair_gains(g, p, c);
-                if (unit_exact(B)) two = combine_gains(g, ls.parity, p.inv_sqrt_block);
             }
             // the same slab of a row of the next step, for its norm
             RawRow<DTYPE> ahead;
@@ -195,12 +193,10 @@ void k_encode_polar(const void *__restrict__ W, int64_t ldw, Problem p, const fl
             for (int e = 0; e < 16; ++e) x[e] = x[e] * sc[e];       // sign included: a sign commutes with every rounding below
             divide_by_norm(x, lds_read<float>(NORM_AT + 4 * (row - row0)));
             fwht_wave<B>(x, ls);
-            if (two) {
+            // Two multiplications also where 1/sqrt(B) is a power of two: y = t / sqrt(B) may be rounded to 0 below the smallest normal
+            // number, and the phase of a pair on an axis is not that of one beside it, whatever the gain.
 #pragma unroll
-                for (int e = 0; e < 16; ++e) x[e] = x[e] * p.inv_sqrt_block;
-            }
-#pragma unroll
-            for (int e = 0; e < 16; ++e) x[e] = (unit_exact(B) ? x[e] : x[e] * unit) * g[e >> 1];
+            for (int e = 0; e < 16; ++e) x[e] = x[e] * unit * g[e >> 1];
 
             // ---------------- amplitude level and phase bin of the lane's 8 pairs
             float a2[8];

@@ -437,8 +437,8 @@ __device__ __forceinline__ void load_pair_gains(float (&g)[8], const Problem &p,
 // 1/sqrt(B) is a power of two: its product with a gain is exact, and one multiplication by that gives the bits of the definition's
 // two, y = t / sqrt(B) and x = y g, unless y is below the smallest normal number, where it is rounded.
 constexpr bool unit_exact(int B) { return B == 64 || B == 256 || B == 1024; }
-// Up to this gain that is nothing to a pair: such a y times the gain is below 2^-102, so that its square is 0, and so are those of its
-// differences from codewords that it could still change (below 2^-76).  Usual gains are sqrt(d_in) and some powers of two around.
+// Up to this gain that is nothing to a pair's distances: such a y times the gain is below 2^-102, so that its square is 0, and so are
+// those of its differences from codewords that it could still change (below 2^-76).  (A phase can depend on whether y is 0.)  Usual gains are sqrt(d_in) and some powers of two around.
 constexpr float UNIT_EXACT_MAX_GAIN = 0x1p24f;
 // A lane's gains times its sign (the butterflies' parity) and 1/sqrt(B); or, where a lane of the wave has a larger gain, times the
 // sign alone and true: the wave multiplies by 1/sqrt(B) first.

@@ -43,6 +43,27 @@ def test_polar_phase_of_a_rounded_pair(block, rows):
     assert torch.equal(_fields(packed, bits_a + bits_p, d_in // 2)[:, own] & ((1 << bits_p) - 1), want)
 
 
+@pytest.mark.parametrize("block", [64, 256, 1024])
+@pytest.mark.parametrize("rows", [1, 6000])
+def test_polar_phase_of_a_pair_rounded_to_an_axis(block, rows):
+    """One coordinate far above the smallest normal number, the y of the other rounded to 0: with gains as usual, the pair is on the axis."""
+    print(f"[unit gains] polar axis {block} rows {rows}", flush=True)
+    d_in, bits_a, bits_p = 4096, 3, 6
+    levels = torch.from_numpy(qamw.polar_codebook(bits_a, bits_p)[0]).cuda()
+    own = slice(block // 2, block)
+    for tiny in (2.0 ** -149, -2.0 ** -149):
+        W = _row(block, d_in, tiny, -tiny)                      # (0, 2 tiny) after the first butterfly, y at most 2^-151
+        W[0, block + 4:block + 6] = 2.0 ** -30                  # (2^-29, 0)
+        pairs, _ = qamw.normalised_pairs(W, block)
+        packed, _ = qamw.encode_polar(W.repeat(rows, 1), levels, bits_a, bits_p, block)
+        torch.cuda.synchronize()
+        x = pairs[:, own]
+        assert bool((x[..., 0].abs() == 2.0 ** -29 * (d_in / block) ** 0.5).all()) and bool((x[..., 1] == 0).all())
+        assert bool((x[..., 0] < 0).any()) and bool((x[..., 0] > 0).any())
+        want = torch.where(x[..., 0] > 0, 0, 1 << (bits_p - 1)).expand(rows, -1)
+        assert torch.equal(_fields(packed, bits_a + bits_p, d_in // 2)[:, own] & ((1 << bits_p) - 1), want)
+
+
 # records from memory and from LDS, norms from a launch ahead and inside the search
 @pytest.mark.parametrize("block", [64, 256, 1024])
 @pytest.mark.parametrize("bits", [7, 10, 11])
